@@ -34,13 +34,40 @@ struct DevBuf {
     ~DevBuf() {
         if (p) (void)hipFree(p);
     }
-    hipError_t upload(const void *src, size_t bytes) {
-        hipError_t e = hipMalloc(&p, bytes ? bytes : 16);
+    hipError_t alloc(size_t bytes) { return hipMalloc(&p, bytes ? bytes : 16); }
+};
+
+// Arrays that live and die together share one device allocation; small ones also one copy.
+struct Arena {
+    struct Item {
+        const void *src;
+        size_t bytes, at;
+        void **dst;
+    };
+    std::vector<Item> items;
+    size_t total = 0;
+    template <typename V, typename A> void add(const std::vector<V, A> &v, void *&dst) {
+        add(v.data(), v.size() * sizeof(V), dst);
+    }
+    void add(const void *src, size_t bytes, void *&dst) {
+        items.push_back(Item{src, bytes, total, &dst});
+        total += (bytes + 271) / 256 * 256;            // (never empty, 256-byte aligned)
+    }
+    hipError_t upload(DevBuf &buf) {
+        hipError_t e = buf.alloc(total);
         if (e != hipSuccess) return e;
-        if (bytes) e = hipMemcpy(p, src, bytes, hipMemcpyHostToDevice);
+        char *base = static_cast<char *>(buf.p);
+        const bool together = total <= ((size_t)4 << 20);
+        std::vector<char> host(together ? total : 0);
+        for (const Item &i : items) {
+            *i.dst = base + i.at;
+            if (!i.bytes) continue;
+            if (together) std::memcpy(host.data() + i.at, i.src, i.bytes);
+            else if (e == hipSuccess) e = hipMemcpy(base + i.at, i.src, i.bytes, hipMemcpyHostToDevice);
+        }
+        if (together && total) e = hipMemcpy(base, host.data(), total, hipMemcpyHostToDevice);
         return e;
     }
-    hipError_t alloc(size_t bytes) { return hipMalloc(&p, bytes ? bytes : 16); }
 };
 
 }  // namespace
@@ -55,20 +82,25 @@ struct tf_plan {
     tf::Schedule s;
     double plan_seconds = 0.0;
     struct PackBufs {
-        DevBuf units, rows, idx, vals;
+        void *units = nullptr, *rows = nullptr, *idx = nullptr, *vals = nullptr;
         int64_t n_units = 0;
         bool sorted = false;
         tf::PackDev dev() const {
             tf::PackDev d;
-            d.units = static_cast<const tf::UnitDesc *>(units.p);
-            d.rows = static_cast<const int32_t *>(rows.p);
-            d.idx = idx.p;
-            d.vals = vals.p;
+            d.units = static_cast<const tf::UnitDesc *>(units);
+            d.rows = static_cast<const int32_t *>(rows);
+            d.idx = idx;
+            d.vals = vals;
             return d;
         }
     };
-    DevBuf tile_desc, tile_meta, tile_first, tile_info, tile_scale, row_info, row_scale;
+    DevBuf arrays;                         // everything below that the plan uploads
+    void *tile_desc = nullptr, *tile_meta = nullptr, *tile_first = nullptr, *tile_info = nullptr,
+         *tile_scale = nullptr, *row_info = nullptr, *row_scale = nullptr;
     PackBufs wf1, all;
+    void *chain_blocks = nullptr, *chain_rows = nullptr, *chain_idx = nullptr, *chain_vals = nullptr;
+    int32_t n_chain_blocks = 0;            // 0: the fused calls run the two wavefronts, else the chain in one pass
+    bool chain_contiguous = true;
     DevBuf d1;                             // fused path: one slot per spilled D1 row
     bool has_baseline = false;             // the packed copy of all rows of A exists
     int n_cu = 256;
@@ -96,21 +128,18 @@ tf_status check_csr_host(int64_t n_rows, int64_t n_cols, int64_t nnz, const int3
     return TF_OK;
 }
 
-template <typename V, typename A> hipError_t up(DevBuf &b, const std::vector<V, A> &v) {
-    return b.upload(v.data(), v.size() * sizeof(V));
-}
-
-hipError_t upload_pack(tf_plan::PackBufs &b, tf::RowPack &pk) {
-    hipError_t e = up(b.units, pk.units);
-    if (e == hipSuccess) e = up(b.rows, pk.rows);
-    if (e == hipSuccess) e = up(b.idx, pk.idx32);
-    if (e == hipSuccess) e = up(b.vals, pk.vals);
+void add_pack(Arena &arena, tf_plan::PackBufs &b, const tf::RowPack &pk) {
+    arena.add(pk.units, b.units);
+    arena.add(pk.rows, b.rows);
+    arena.add(pk.idx32, b.idx);
+    arena.add(pk.vals, b.vals);
     b.n_units = (int64_t)pk.units.size();
     b.sorted = pk.sorted;
-    // the packed entries live on the device from here on; the row lists stay for the schedule view
+}
+// the packed entries live on the device from here on; the row lists stay for the schedule view
+void drop_entries(tf::RowPack &pk) {
     tf::RawVec<int32_t>().swap(pk.idx32);
     tf::RawVec<unsigned char>().swap(pk.vals);
-    return e;
 }
 
 // column -> (slice, offset inside the slice) of a workspace: a shift and a mask; with one slice the
@@ -138,11 +167,11 @@ tf::FusedLaunch fused_args(const tf_plan *p, const void *C, void *D) {
     a.need_tile = p->s.n_lds_rows > 0 ? 1 : 0;
     a.lds_bytes = tf::fused_lds_bytes(p->dtype, p->b_is_sparse, a.bcol, a.ccol, a.cs,
                                       (int)p->s.max_tile_rows, a.s_in_lds ? a.s_cap : 0, a.need_tile);
-    a.tile_desc = static_cast<const tf::TileDesc *>(p->tile_desc.p);
-    a.tile_meta = static_cast<const unsigned char *>(p->tile_meta.p);
-    a.tile_first = static_cast<const int32_t *>(p->tile_first.p);
-    a.tile_info = static_cast<const uint32_t *>(p->tile_info.p);
-    a.tile_scale = p->s.n_direct_rows > 0 ? p->tile_scale.p : nullptr;
+    a.tile_desc = static_cast<const tf::TileDesc *>(p->tile_desc);
+    a.tile_meta = static_cast<const unsigned char *>(p->tile_meta);
+    a.tile_first = static_cast<const int32_t *>(p->tile_first);
+    a.tile_info = static_cast<const uint32_t *>(p->tile_info);
+    a.tile_scale = p->s.n_direct_rows > 0 ? p->tile_scale : nullptr;
     a.first_stride = p->s.first_stride;
     a.n_cu = p->n_cu;
     a.C = C;
@@ -267,8 +296,8 @@ tf_status first_wavefront_dense(const tf_plan *p, const void *B, const void *C, 
         g.B = B;
         g.C = C;
         gemm_workspace(g, ws, p->s.d1);
-        g.row_info = static_cast<const uint32_t *>(p->row_info.p);
-        g.row_scale = p->s.n_direct_rows > 0 ? p->row_scale.p : nullptr;
+        g.row_info = static_cast<const uint32_t *>(p->row_info);
+        g.row_scale = p->s.n_direct_rows > 0 ? p->row_scale : nullptr;
         g.D = D;
         const int e = tf::launch_gemm(g, stream);
         if (e) return hip_fail((hipError_t)e, "launching the first wavefront");
@@ -286,8 +315,8 @@ tf_status first_wavefront_sparse(const tf_plan *p, const tf_csr *B, const void *
     int e;
     if (p->s.streaming) {
         tf::CsrSpmmLaunch f = csr_spmm_args(p, B, C, ws, p->s.d1);
-        f.row_info = static_cast<const uint32_t *>(p->row_info.p);
-        f.row_scale = p->s.n_direct_rows > 0 ? p->row_scale.p : nullptr;
+        f.row_info = static_cast<const uint32_t *>(p->row_info);
+        f.row_scale = p->s.n_direct_rows > 0 ? p->row_scale : nullptr;
         f.D = D;
         e = tf::launch_csr_spmm(f, stream);
     } else {
@@ -299,6 +328,28 @@ tf_status first_wavefront_sparse(const tf_plan *p, const tf_csr *B, const void *
         e = tf::launch_fused_spmm_spmm(a, stream);
     }
     if (e) return hip_fail((hipError_t)e, "launching the first wavefront");
+    return TF_OK;
+}
+// The chain in one pass (dense B).
+tf_status run_chain(const tf_plan *p, const void *B, const void *C, void *D, void *stream) {
+    tf::ChainLaunch a{};
+    a.dtype = p->dtype;
+    a.n_blocks = p->n_chain_blocks;
+    a.n = p->n;
+    a.bcol = (int32_t)p->bcol;
+    a.ccol = (int32_t)p->ccol;
+    a.contiguous = p->chain_contiguous ? 1 : 0;
+    a.n_cu = p->n_cu;
+    a.blocks = static_cast<const tf::ChainBlock *>(p->chain_blocks);
+    a.rows = static_cast<const int32_t *>(p->chain_rows);
+    a.idx = static_cast<const int32_t *>(p->chain_idx);
+    a.vals = p->chain_vals;
+    a.B = B;
+    a.C = C;
+    a.c_transposed = p->c_transposed ? 1 : 0;
+    a.D = D;
+    const int e = tf::launch_chain(a, stream);
+    if (e) return hip_fail((hipError_t)e, "launching the chain");
     return TF_OK;
 }
 tf_status second_wavefront(const tf_plan *p, void *D, void *ws, void *stream) {
@@ -446,6 +497,7 @@ tf_status tf_plan_create(const tf_csr *A, int64_t bCol, int64_t cCol, int32_t b_
         const int64_t lds_limit = schedule_only ? 160 * 1024 : device_lds_limit();
         in.fast_mem_bytes = (tp && tp->fast_mem_bytes > 0) ? tp->fast_mem_bytes : lds_limit;
         if (!schedule_only && in.fast_mem_bytes > lds_limit) in.fast_mem_bytes = lds_limit;
+        in.whole_fast_mem = !(tp && tp->fast_mem_bytes > 0);
         std::string err;
         st = tf::build_schedule(in, p->s, err);
         if (st != TF_OK) return fail(st, err);
@@ -471,29 +523,40 @@ tf_status tf_plan_create(const tf_csr *A, int64_t bCol, int64_t cCol, int32_t b_
         if (launch_lds() > lds_limit) p->s.second_block_in_lds = false;
         if (launch_lds() > lds_limit)
             return fail(TF_EUNSUPPORTED, "a tile does not fit the LDS of this device");
-        hipError_t e = hipSuccess;
-        auto ok = [&](hipError_t r) {
-            if (e == hipSuccess) e = r;
-        };
-        ok(up(p->tile_desc, p->s.tile_desc));
-        if (e == hipSuccess) e = p->tile_meta.upload(p->s.tile_meta.get(), p->s.tile_meta_bytes);
-        p->s.tile_meta.reset();
-        ok(up(p->tile_first, p->s.tile_first));
-        std::vector<int32_t>().swap(p->s.tile_first);
-        ok(up(p->tile_info, p->s.tile_info));
-        std::vector<uint32_t>().swap(p->s.tile_info);
-        ok(up(p->tile_scale, p->s.tile_scale));
-        tf::RawVec<unsigned char>().swap(p->s.tile_scale);
-        if (p->s.streaming) {
-            ok(up(p->row_info, p->s.row_info));
-            std::vector<uint32_t>().swap(p->s.row_info);
-            ok(up(p->row_scale, p->s.row_scale));
-            tf::RawVec<unsigned char>().swap(p->s.row_scale);
+        tf::build_chain_pack(in, p->s);
+        tf::Schedule &sc = p->s;
+        Arena arena;
+        arena.add(sc.tile_desc, p->tile_desc);
+        arena.add(sc.tile_meta.get(), sc.tile_meta_bytes, p->tile_meta);
+        arena.add(sc.tile_first, p->tile_first);
+        arena.add(sc.tile_info, p->tile_info);
+        arena.add(sc.tile_scale, p->tile_scale);
+        if (sc.streaming) {
+            arena.add(sc.row_info, p->row_info);
+            arena.add(sc.row_scale, p->row_scale);
         }
-        ok(upload_pack(p->wf1, p->s.wf1));
-        if (p->has_baseline) ok(upload_pack(p->all, p->s.all));
-        ok(p->d1.alloc((size_t)p->s.d1.elements() * es));
+        add_pack(arena, p->wf1, sc.wf1);
+        if (p->has_baseline) add_pack(arena, p->all, sc.all);
+        if (!sc.chain.blocks.empty()) {
+            p->n_chain_blocks = (int32_t)sc.chain.blocks.size();
+            p->chain_contiguous = sc.chain.contiguous;
+            arena.add(sc.chain.blocks, p->chain_blocks);
+            arena.add(sc.chain.rows, p->chain_rows);
+            arena.add(sc.chain.idx, p->chain_idx);
+            arena.add(sc.chain.vals, p->chain_vals);
+        }
+        hipError_t e = arena.upload(p->arrays);
+        if (e == hipSuccess) e = p->d1.alloc((size_t)sc.d1.elements() * es);
         if (e != hipSuccess) return hip_fail(e, "allocating the plan's device memory");
+        sc.tile_meta.reset();
+        std::vector<int32_t>().swap(sc.tile_first);
+        std::vector<uint32_t>().swap(sc.tile_info);
+        tf::RawVec<unsigned char>().swap(sc.tile_scale);
+        std::vector<uint32_t>().swap(sc.row_info);
+        tf::RawVec<unsigned char>().swap(sc.row_scale);
+        drop_entries(sc.wf1);
+        drop_entries(sc.all);
+        sc.chain = tf::ChainPack();
         guard.p = nullptr;
         *out = p;
         return TF_OK;
@@ -619,6 +682,7 @@ tf_status tf_gemm_spmm(const tf_plan *p, const void *B, const void *C, void *D, 
     tf_status st = check_exec(p, 0, C, D);
     if (st != TF_OK) return st;
     if (!B || !aligned16(B)) return fail(TF_EINVAL, "B must be a 16-byte aligned device pointer");
+    if (p->n_chain_blocks > 0) return run_chain(p, B, C, D, stream);
     st = first_wavefront_dense(p, B, C, D, p->d1.p, stream);
     if (st != TF_OK) return st;
     return second_wavefront(p, D, p->d1.p, stream);
@@ -633,6 +697,7 @@ tf_status tf_gemm_spmm_static(const tf_plan *p, const void *B, const void *C, vo
         return fail(TF_EUNSUPPORTED, "the plan's D1 workspace (" + std::to_string(need) +
                                          " bytes) exceeds the static workspace of " +
                                          std::to_string(kStaticScratchBytes) + " bytes");
+    if (p->n_chain_blocks > 0) return run_chain(p, B, C, D, stream);
     void *ws = nullptr;
     st = static_scratch(&ws);
     if (st != TF_OK) return st;

@@ -958,6 +958,102 @@ tf_status build_schedule(const InspectorInput &in, Schedule &s, std::string &err
     return TF_OK;
 }
 
+// Estimated microseconds of the fused calls on a matrix whose rows stay near the diagonal, in one pass
+// and in two wavefronts.  The rates (bytes per microsecond) are fits to measured executions: the
+// one-pass kernel gathers rows of B out of the L2 at 18 TB/s and streams at 5 TB/s, the tiled kernels
+// move B and D at 3.2 TB/s; unaligned widths take the tiled kernels three times as long (scalar lanes).
+static bool chain_is_faster(const InspectorInput &in) {
+    const double es = elem_size(in.dtype), n = (double)in.n, nnz = (double)in.nnz;
+    const int v = vec_elems(in.dtype);
+    const double one = 5.0 + nnz * in.bcol * es / 18e6 + n * (in.bcol + in.ccol) * es / 5e6;
+    const double aligned = in.bcol % v || in.ccol % v ? 3.0 : 1.0;
+    const double two = 15.0 + aligned * (n * (in.bcol + 2.0 * in.ccol) * es / 3.2e6 + nnz * in.ccol * es / 25e6);
+    return one < two;
+}
+
+void build_chain_pack(const InspectorInput &in, Schedule &s) {
+    s.chain = ChainPack();
+    const int64_t n = in.n;
+    const int es = elem_size(in.dtype);
+    if (in.b_is_sparse || n == 0 || in.nnz == 0) return;
+    // only where the caller has left the whole choice to the library
+    if (!s.automatic || in.col_slice || in.gather_slices || !in.whole_fast_mem) return;
+    const int ks = chain_ksteps(in.dtype, in.bcol);
+    if (ks == 0 || chain_lds_bytes(in.dtype, in.bcol, in.ccol) > in.fast_mem_bytes) return;
+    // (the kernel stores D through 32-bit byte offsets, in whole 16-byte pieces)
+    if (in.ccol < vec_elems(in.dtype) || n * in.ccol * es >= ((int64_t)1 << 32) - 64) return;
+    if (s.far_rows || !chain_is_faster(in)) return;
+    auto len = [&](int64_t j) { return (int64_t)in.rowptr[j + 1] - in.rowptr[j]; };
+    int64_t longest = 0;
+    for (int64_t j = 0; j < n; ++j) longest = std::max(longest, len(j));
+    if (longest > kChainLongRow) return;
+    // few blocks: rows are cut into parts so that there are about two waves per compute unit
+    int slog = 0;
+    while (slog < 4 && ((n << slog) + 15) / 16 < 2 * (int64_t)in.n_cu && (in.nnz / n >> slog) >= 6) ++slog;
+    const int64_t per_block = 16 >> slog;
+    ChainPack &c = s.chain;
+    // rows in their own order while that pads little, else sorted by length inside windows
+    int64_t padded = 0;
+    for (int64_t j0 = 0; j0 < n; j0 += per_block) {
+        int64_t mx = 0;
+        for (int64_t j = j0; j < std::min(n, j0 + per_block); ++j) mx = std::max(mx, len(j));
+        padded += mx * per_block;
+    }
+    c.rows.resize((size_t)n);
+    std::iota(c.rows.begin(), c.rows.end(), 0);
+    if (padded > in.nnz + in.nnz / 4) {
+        const int64_t window = 2048;
+        for (int64_t j0 = 0; j0 < n; j0 += window)
+            std::stable_sort(c.rows.begin() + j0, c.rows.begin() + std::min(n, j0 + window),
+                             [&](int32_t x, int32_t y) { return len(x) > len(y); });
+    }
+    c.blocks.reserve((size_t)(n / per_block) + 16);
+    int64_t slot = 0;
+    for (int64_t q0 = 0; q0 < n;) {
+        // (empty rows share no block with others: nothing of B may be read for them)
+        int64_t mx = len(c.rows[(size_t)q0]), q1 = q0 + 1;
+        while (q1 < n && q1 < q0 + per_block && (len(c.rows[(size_t)q1]) == 0) == (mx == 0))
+            mx = std::max(mx, len(c.rows[(size_t)q1++]));
+        ChainBlock cb{};
+        cb.slot_base = (uint32_t)slot;
+        cb.slots = (int32_t)((mx + (1 << slog) - 1) >> slog);
+        cb.row_begin = (int32_t)q0;
+        const int em = chain_entries(ks), passes = (cb.slots + em - 1) / em;
+        cb.info = slog | (passes ? (cb.slots + passes - 1) / passes : 0) << 3 | (int32_t)((q1 - q0) << 7);
+        c.blocks.push_back(cb);
+        slot += cb.slots;
+        q0 = q1;
+    }
+    const int64_t nb = (int64_t)c.blocks.size();
+    const int64_t end = slot + kChainSpareSlots;
+    c.idx.resize((size_t)end * 16);
+    c.vals.resize((size_t)end * 16 * es);
+    std::memset(c.idx.data() + slot * 16, 0, (size_t)kChainSpareSlots * 16 * 4);
+    std::memset(c.vals.data() + (size_t)slot * 16 * es, 0, (size_t)kChainSpareSlots * 16 * es);
+    auto fill = [&](auto tag) {
+        typedef decltype(tag) T;
+        const T *vals = static_cast<const T *>(in.vals);
+        T *out = reinterpret_cast<T *>(c.vals.data());
+        for_each_item(nb, host_threads(in.nnz, nb, 64), [&](int64_t b) {
+            const ChainBlock &cb = c.blocks[(size_t)b];
+            const int sl_log = cb.info & 7, parts = 1 << sl_log, n_rows = cb.info >> 7;
+            for (int v = 0; v < 16; ++v) {
+                // (virtual rows past the block's end repeat its last row; they are not stored)
+                const int ri = std::min(v >> sl_log, n_rows - 1);
+                const int64_t j = c.rows[(size_t)(cb.row_begin + ri)], k0 = in.rowptr[j], ln = len(j);
+                const int64_t p0 = (int64_t)(v & (parts - 1)) * cb.slots;
+                for (int64_t sl = 0; sl < cb.slots; ++sl) {
+                    const int64_t at = ((int64_t)cb.slot_base + sl) * 16 + v, k = p0 + sl;
+                    c.idx[(size_t)at] = in.colidx[k0 + std::min(k, ln - 1)];
+                    out[at] = k < ln ? vals[k0 + k] : T(0);
+                }
+            }
+        });
+    };
+    if (in.dtype == TF_F64) fill(double());
+    else fill(float());
+}
+
 bool build_baseline_pack(const InspectorInput &in, Schedule &s) {
     std::vector<int32_t> all((size_t)in.n);
     std::iota(all.begin(), all.end(), 0);

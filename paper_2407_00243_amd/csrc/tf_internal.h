@@ -221,6 +221,84 @@ struct RowPack {
     int64_t entries() const { return (int64_t)idx32.size(); }
 };
 
+// ---- the chain in one pass, D = (A B) C (dense B) -----------------------------------------------
+// A is re-packed into blocks of sixteen virtual rows: a row, or one of the 2^k equal parts that the
+// rows of the block are cut into.  All virtual rows of a block have `slots` entries (padding repeats
+// a column of the row with value 0), stored slot after slot, sixteen entries each.
+struct ChainBlock {
+    uint32_t slot_base;    // first slot of the block: its entries start at 16 slot_base
+    int32_t slots;         // 0: the block's rows are empty
+    int32_t row_begin;     // position of the block's first row in the row list
+    int32_t info;          // log2 of the parts per row (3 bits) | slots per gather pass << 3 (4 bits) |
+                           // rows of the block << 7
+};
+struct ChainPack {
+    std::vector<ChainBlock> blocks;
+    std::vector<int32_t> rows;           // row ids in block order
+    RawVec<int32_t> idx;
+    RawVec<unsigned char> vals;
+    bool contiguous = true;              // neighbouring blocks read neighbouring rows of B
+};
+constexpr int kChainThreads = 512;       // largest workgroup of the kernel
+constexpr int kChainMaxEntries = 8;      // most entries per row in flight
+constexpr int kChainLongRow = 1024;      // longest row a block takes
+constexpr int kChainSpareSlots = 2 * kChainMaxEntries;   // zero slots behind the last block (entries are fetched ahead)
+// 16-byte pieces of a row of B per lane: ceil(bCol / (4 V)) rounded up to a depth the kernel is
+// instantiated for; 0 = none.
+constexpr int kChainDepths32[] = {1, 2, 3, 4, 6, 8}, kChainDepths64[] = {2, 4, 6, 8, 12, 16};
+inline int chain_ksteps(int dtype, int64_t bcol) {
+    const int v = vec_elems(dtype);
+    if (bcol < v) return 0;
+    for (int k = 0; k < 6; ++k) {
+        const int ks = dtype == TF_F64 ? kChainDepths64[k] : kChainDepths32[k];
+        if (bcol <= (int64_t)4 * v * ks) return ks;
+    }
+    return 0;
+}
+// The depth below `ks`: pieces up to there are whole in every row that takes depth ks.
+constexpr int chain_ksteps_below(int dtype, int ks) {
+    int below = 0;
+    for (int k = 0; k < 6; ++k) {
+        const int d = dtype == TF_F64 ? kChainDepths64[k] : kChainDepths32[k];
+        if (d < ks) below = d;
+    }
+    return below;
+}
+// Entries per row whose gathers are in flight at once (about 24 pieces of 16 bytes per lane).
+constexpr int chain_entries(int ks) { return ks <= 2 ? 8 : ks == 3 ? 6 : ks == 4 ? 5 : ks <= 8 ? 3 : 2; }
+// Waves per SIMD that the kernel is held to: where a third one costs no spilled registers.
+constexpr int chain_waves(int dtype, int ks) { return ks <= (dtype == TF_F64 ? 2 : 6) ? 3 : 2; }
+// Blocks of sixteen columns of D that are multiplied together: the count (3 or 4, or all of them)
+// that wastes the fewest blocks; two at the largest depth, where the registers end.
+inline int chain_col_blocks(int ks, int64_t ccol) {
+    const int64_t nb = (ccol + 15) / 16;
+    if (ks >= 16) return nb > 1 ? 2 : 1;
+    if (nb <= 4) return (int)nb;
+    return (nb + 2) / 3 * 3 < (nb + 3) / 4 * 4 ? 3 : 4;
+}
+// LDS per wave (see k_gather_gemm): loads of 64 entries per pass, k steps per change of lanes, blocks of
+// sixteen columns that leave together, and what that comes to in bytes.
+constexpr int chain_entry_loads(int ks) { return (chain_entries(ks) + 3) / 4; }
+constexpr int chain_exchange(int ks) { return ks < 4 ? ks : ks < 16 ? 4 : 2; }
+constexpr int chain_store_blocks(int dtype, int ks, int nbc) {
+    return dtype == TF_F32 ? nbc : ks < 16 && nbc % 2 == 0 ? 2 : 1;
+}
+constexpr int chain_exchange_bytes(int dtype, int ks, int nbc) {
+    const int in = chain_exchange(ks) * 1024;
+    const int out = 16 * (chain_store_blocks(dtype, ks, nbc) * 16 * (dtype == TF_F64 ? 8 : 4) + 16);
+    return in > out ? in : out;
+}
+constexpr int64_t chain_wave_lds(int dtype, int ks, int nbc) {
+    return chain_exchange_bytes(dtype, ks, nbc) + 64 + chain_entry_loads(ks) * 64 * (4 + (dtype == TF_F64 ? 8 : 4));
+}
+// LDS of the largest workgroup: C and the waves' own.
+inline int64_t chain_lds_bytes(int dtype, int64_t bcol, int64_t ccol) {
+    const int ks = chain_ksteps(dtype, bcol);
+    const int64_t nb = (ccol + 15) / 16, nbc = chain_col_blocks(ks, ccol);
+    return (nb + nbc - 1) / nbc * nbc * 16 * ks * 4 * vec_elems(dtype) * elem_size(dtype) +
+           kChainThreads / 64 * chain_wave_lds(dtype, ks, (int)nbc);
+}
+
 // Host-side schedule produced by the inspector.
 struct Schedule {
     int64_t n = 0, nnz = 0;
@@ -259,6 +337,7 @@ struct Schedule {
     int64_t lds_meta_bytes_per_row = 0;                   // part of lds_bytes_per_row: row ids + estimate of the second-phase block
     RowPack wf1;                   // wf1_rows re-packed
     RowPack all;                   // all rows re-packed (unfused baseline)
+    ChainPack chain;               // all rows re-packed for the one-pass chain; no blocks: not used
     int64_t n_fused_rows = 0, n_spill_rows = 0, fused_nnz = 0;
     int64_t max_tile_rows = 0;
     int64_t lds_fixed_bytes = 0, lds_bytes_per_row = 0, fast_mem_bytes = 0;
@@ -279,6 +358,7 @@ struct InspectorInput {
     uint32_t flags;
     int32_t gather_slices;            // column slices of the D1 workspace and of the gather kernel; 0 = chosen here
     int32_t n_cu;                     // compute units of the device the plan will run on
+    bool whole_fast_mem;              // fast_mem_bytes is the device's own, not the caller's
 };
 
 // Builds the schedule; returns TF_OK or an error with a message in `err`.
@@ -287,6 +367,8 @@ tf_status build_schedule(const InspectorInput &in, Schedule &out, std::string &e
 // (Schedule::all).  Not part of the fused schedule and not counted in its time.
 // (false: a unit exceeds the gather kernel's staging arrays; never expected)
 bool build_baseline_pack(const InspectorInput &in, Schedule &s);
+// Decides whether the fused calls of the plan run the chain in one pass, and packs A for it.
+void build_chain_pack(const InspectorInput &in, Schedule &s);
 
 
 // ---------------------------------------------------------------- device launch interface
@@ -378,11 +460,28 @@ struct GemmLaunch {
     void *D;
 };
 
+struct ChainLaunch {
+    int32_t dtype;
+    int32_t n_blocks, n_groups, groups_per_wg;   // (the column groups are set by the launcher)
+    int64_t n;
+    int32_t bcol, ccol;
+    int32_t contiguous;
+    int32_t n_cu;
+    const ChainBlock *blocks;
+    const int32_t *rows;
+    const int32_t *idx;
+    const void *vals;
+    const void *B, *C;
+    int32_t c_transposed;             // C is cCol x bCol
+    void *D;
+};
+
 // Each returns hipError_t as int (0 = success).  `stream` is a hipStream_t.
 int launch_fused_gemm_spmm(const FusedLaunch &a, void *stream);
 int launch_fused_spmm_spmm(const FusedLaunch &a, void *stream);
 int launch_packed_spmm(const PackedSpmmLaunch &a, void *stream);
 int launch_csr_spmm(const CsrSpmmLaunch &a, void *stream);
 int launch_gemm(const GemmLaunch &a, void *stream);
+int launch_chain(const ChainLaunch &a, void *stream);
 
 }  // namespace tf
