@@ -19,15 +19,6 @@
 namespace tf {
 namespace {
 
-// Sixteen bytes at any element-aligned address.
-template <typename T> struct Piece16;
-template <> struct Piece16<float> {
-    typedef float Vec __attribute__((ext_vector_type(4), aligned(4)));
-};
-template <> struct Piece16<double> {
-    typedef double Vec __attribute__((ext_vector_type(2), aligned(8)));
-};
-
 // Flags word of a buffer descriptor for plain 32-bit data (range-checked byte offsets).
 constexpr int kBufferRaw = 0x00020000;
 

@@ -52,6 +52,38 @@ template <typename T, int N> __device__ __forceinline__ void store_pack(T *p, co
     *reinterpret_cast<Pack<T, N> *>(p) = v;
 }
 
+// Sixteen bytes at any element-aligned address.
+template <typename T> struct Piece16;
+template <> struct Piece16<float> {
+    typedef float Vec __attribute__((ext_vector_type(4), aligned(4)));
+};
+template <> struct Piece16<double> {
+    typedef double Vec __attribute__((ext_vector_type(2), aligned(8)));
+};
+// The same for device memory: one 16-byte access (N = elements per 16 bytes) or one element (N = 1) at
+// any element-aligned address.
+template <typename T, int N> __device__ __forceinline__ void load_any(T (&dst)[N], const T *p) {
+    static_assert(N == 1 || N == Tr<T>::V, "one element or sixteen bytes");
+    if constexpr (N == 1) {
+        dst[0] = *p;
+    } else {
+        const typename Piece16<T>::Vec v = *reinterpret_cast<const typename Piece16<T>::Vec *>(p);
+#pragma unroll
+        for (int i = 0; i < N; ++i) dst[i] = v[i];
+    }
+}
+template <typename T, int N> __device__ __forceinline__ void store_any(T *p, const T (&src)[N]) {
+    static_assert(N == 1 || N == Tr<T>::V, "one element or sixteen bytes");
+    if constexpr (N == 1) {
+        *p = src[0];
+    } else {
+        typename Piece16<T>::Vec v;
+#pragma unroll
+        for (int i = 0; i < N; ++i) v[i] = src[i];
+        *reinterpret_cast<typename Piece16<T>::Vec *>(p) = v;
+    }
+}
+
 __device__ __forceinline__ int pow2_at_least(int x) {
     int g = 1;
     while (g < x) g <<= 1;

@@ -311,9 +311,7 @@ TileBlock pack_tile(const int32_t *rowptr, const int32_t *colidx, const unsigned
 // Units of a packed row list of `count` rows: a unit is one workgroup; short lists are cut into
 // smaller units (down to one row per lane group) so that they still spread over the machine.
 static PackRules pack_rules(const InspectorInput &in, int64_t count, int sw) {
-    const int v = vec_elems(in.dtype);
-    const int vv = in.ccol % v == 0 ? v : 1;
-    const int groups = kSpmmThreads / lane_group(sw, vv);
+    const int groups = kSpmmThreads / lane_group(sw, lane_elems(in.dtype, in.ccol, sw));
     const int64_t want = (count + 1023) / 1024;
     return PackRules{(int)std::min<int64_t>(kUnitRows, std::max<int64_t>(groups, want)), kUnitSlots,
                      groups};
@@ -341,7 +339,10 @@ tf_status build_schedule(const InspectorInput &in, Schedule &s, std::string &err
     // ---- column slice -------------------------------------------------------------------
     const int v = vec_elems(in.dtype);
     int64_t max_cs = in.b_is_sparse ? 64 * v : kMaxMfmaSliceCols;
-    if (in.ccol % v != 0) max_cs = 64;                 // scalar lanes: one column per lane
+    // scalar lanes, one column each: the dense kernels at an unaligned width, and the limit of a slice
+    // that the caller asks for
+    if (in.ccol % v != 0 && (!in.b_is_sparse || in.col_slice > 0 || (in.ccol > max_cs && in.ccol % max_cs < v)))
+        max_cs = 64;
     int64_t cs = in.col_slice > 0 ? in.col_slice : in.ccol;
     if (in.col_slice < 0) {
         err = "col_slice must be >= 0";
@@ -421,7 +422,8 @@ tf_status build_schedule(const InspectorInput &in, Schedule &s, std::string &err
         int64_t best_cs = cs, best_rows = capacity();
         for (int64_t k = 2; best_rows < want && cs > 16; k *= 2) {
             const int64_t c = round_up((widest + k - 1) / k, 16);
-            if (c >= cs) continue;
+            // (more than 64 scalar lanes are not covered)
+            if (c >= cs || (in.b_is_sparse && c > 64 && lane_elems(in.dtype, in.ccol, c) == 1)) continue;
             cs = c;
             model(cs);
             if (capacity() > best_rows) {
@@ -817,11 +819,10 @@ tf_status build_schedule(const InspectorInput &in, Schedule &s, std::string &err
     // reading the packed entries of A once per slice.  Matrices whose rows stay near the diagonal
     // (stencils, bands) keep one slice: their operands are in the L2 anyway.
     {
-        const int vv = in.ccol % v == 0 ? v : 1;
         int n_sl = 1;
         auto usable = [&](int k) {
             if (k == 1) return true;
-            if (vv == 1 || in.ccol % k) return false;
+            if (in.ccol % v || in.ccol % k) return false;
             // (the MFMA phase stores 16-column blocks that start at multiples of the fused column
             // slice: they must not straddle a slice of the workspace)
             if (s.n_slices > 1 && cs % 16 != 0) return false;
@@ -849,7 +850,7 @@ tf_status build_schedule(const InspectorInput &in, Schedule &s, std::string &err
         s.d1.n_sl = n_sl;
         s.d1.sw = (int32_t)(in.ccol / n_sl);
         s.d1.rows = std::max<int64_t>(1, s.n_spill_rows);
-        const int groups = kSpmmThreads / lane_group(s.d1.sw, vv);
+        const int groups = kSpmmThreads / lane_group(s.d1.sw, lane_elems(in.dtype, in.ccol, s.d1.sw));
         s.gather_r = groups >= 64 ? 1 : groups >= 32 ? 2 : 4;
     }
     TF_TICK("spill set, slots, layout");

@@ -124,24 +124,34 @@ __device__ __forceinline__ void mfma_row_block(typename Tr<T>::Acc (&acc)[NB], c
 }
 
 // Stores the four columns a lane holds of accumulator block nb to `dst` (which points at the
-// lane's first column), keeping to columns below w.
-template <typename T, bool FAST>
-__device__ __forceinline__ void store_acc4(T *dst, const typename Tr<T>::Acc &a, int col, int w) {
+// lane's first column, 16 nb + 4 g), keeping to columns below w: 16-byte pieces, at whatever element
+// they begin, and the columns of a block that w cuts one by one.
+template <typename T>
+__device__ __forceinline__ void store_acc4(T *dst, const typename Tr<T>::Acc &a, int nb, int g, int w) {
     constexpr int V = Tr<T>::V;
-    if (FAST) {
+    if (16 * nb + 16 <= w) {
 #pragma unroll
         for (int h = 0; h < 4 / V; ++h) {
-            if (col + V * h < w) {
-                T tmp[V];
+            T tmp[V];
 #pragma unroll
-                for (int i = 0; i < V; ++i) tmp[i] = a[V * h + i];
-                store_pack<T, V>(dst + V * h, tmp);
-            }
+            for (int i = 0; i < V; ++i) tmp[i] = a[V * h + i];
+            store_any<T, V>(dst + V * h, tmp);
         }
     } else {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-            if (col + i < w) dst[i] = a[i];
+        for (int h = 0; h < 4 / V; ++h) {
+            const int col = 16 * nb + 4 * g + V * h;
+            if (col + V <= w) {
+                T tmp[V];
+#pragma unroll
+                for (int i = 0; i < V; ++i) tmp[i] = a[V * h + i];
+                store_any<T, V>(dst + V * h, tmp);
+            } else {
+#pragma unroll
+                for (int i = 0; i + 1 < V; ++i)
+                    if (col + i < w) dst[V * h + i] = a[V * h + i];
+            }
+        }
     }
 }
 
@@ -183,7 +193,7 @@ __device__ __forceinline__ void rows_dot(T (&acc)[R][N], const IdxT *__restrict_
 #pragma unroll
         for (int r = 0; r < R; ++r)
 #pragma unroll
-            for (int e = 0; e < E; ++e) load_pack<T, N>(x[r][e], X + c[r][e] * ldx);
+            for (int e = 0; e < E; ++e) load_any<T, N>(x[r][e], X + c[r][e] * ldx);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
 #pragma unroll
@@ -210,81 +220,10 @@ template <typename T, int N, bool WIDE>
 __device__ __forceinline__ void load_x(T (&x)[N], const T *X, uint32_t c, uint32_t ldx,
                                        uint32_t lane_off) {
     if (WIDE) {
-        load_pack<T, N>(x, X + ((uint64_t)c * ldx + lane_off));
+        load_any<T, N>(x, X + ((uint64_t)c * ldx + lane_off));
     } else {
         const uint32_t off = (c * ldx + lane_off) * (uint32_t)sizeof(T);
-        load_pack<T, N>(x, reinterpret_cast<const T *>(reinterpret_cast<const char *>(X) + off));
-    }
-}
-
-// One unit, rows not split: lane group `grp` of `ngrp` takes rows grp, grp + ngrp, ..., R at a
-// time, E slots of each per pass (R * E gathers in flight per lane).  out(row id, acc).
-template <typename T, int N, typename IdxT, int R, int E, bool WIDE, typename OutFn>
-__device__ __forceinline__ void unit_rows(const UnitDesc d, const int32_t *__restrict__ rows,
-                                          const IdxT *__restrict__ idx,
-                                          const T *__restrict__ val, const T *X, uint32_t ldx,
-                                          uint32_t lane_off, int grp, int ngrp, OutFn out) {
-    const int L = d.slots;
-    for (int i0 = grp; i0 < d.n_rows; i0 += ngrp * R) {
-        const IdxT *ip[R];
-        const T *vp[R];
-        int32_t rid[R];
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int i = i0 + r * ngrp;
-            const int ic = i < d.n_rows ? i : i0;
-            const int64_t at = d.entry_base + (int64_t)ic * L;
-            ip[r] = idx + at;
-            vp[r] = val + at;
-            rid[r] = rows[d.row_begin + ic];
-        }
-        T acc[R][N];
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-#pragma unroll
-            for (int i = 0; i < N; ++i) acc[r][i] = T(0);
-        int s = 0;
-        for (; s + E <= L; s += E) {
-            uint32_t c[R][E];
-            T v[R][E];
-            T x[R][E][N];
-#pragma unroll
-            for (int r = 0; r < R; ++r)
-#pragma unroll
-                for (int e = 0; e < E; ++e) {
-                    c[r][e] = (uint32_t)ip[r][s + e];
-                    v[r][e] = vp[r][s + e];
-                }
-#pragma unroll
-            for (int r = 0; r < R; ++r)
-#pragma unroll
-                for (int e = 0; e < E; ++e) load_x<T, N, WIDE>(x[r][e], X, c[r][e], ldx, lane_off);
-#pragma unroll
-            for (int r = 0; r < R; ++r)
-#pragma unroll
-                for (int e = 0; e < E; ++e)
-#pragma unroll
-                    for (int i = 0; i < N; ++i) acc[r][i] += v[r][e] * x[r][e][i];
-        }
-        for (; s < L; ++s) {
-            uint32_t c[R];
-            T v[R];
-            T x[R][N];
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                c[r] = (uint32_t)ip[r][s];
-                v[r] = vp[r][s];
-            }
-#pragma unroll
-            for (int r = 0; r < R; ++r) load_x<T, N, WIDE>(x[r], X, c[r], ldx, lane_off);
-#pragma unroll
-            for (int r = 0; r < R; ++r)
-#pragma unroll
-                for (int i = 0; i < N; ++i) acc[r][i] += v[r] * x[r][i];
-        }
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-            if (i0 + r * ngrp < d.n_rows) out(rid[r], acc[r]);
+        load_any<T, N>(x, reinterpret_cast<const T *>(reinterpret_cast<const char *>(X) + off));
     }
 }
 
@@ -300,6 +239,55 @@ __device__ __forceinline__ void load_b_frag(BFrag<T, KS> &f, const T *__restrict
     constexpr int V = Tr<T>::V, KC = 4 * V;
 #pragma unroll
     for (int s = 0; s < KS; ++s) load_pack<T, V>(f.v[s], brow + KC * s + V * g);
+}
+
+// The same for rows of B of any length up to 4 V KS and at any element: pieces that would reach past the
+// row are moved back so that they end with it, and put right when they have arrived (elements past
+// bCol are zeros then).  Pieces below kWholeSteps are whole in every row that takes this depth.
+template <int KS> constexpr int kWholeSteps = KS == 2 ? 0 : KS / 2;
+template <typename T, int KS>
+__device__ __forceinline__ void load_b_frag_any(BFrag<T, KS> &f, const T *__restrict__ brow, int g, int bcol) {
+    constexpr int V = Tr<T>::V, KC = 4 * V;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+        const int kb = KC * s + V * g;
+        load_any<T, V>(f.v[s], brow + (s < kWholeSteps<KS> ? kb : min(kb, bcol - V)));
+    }
+}
+template <typename T, int KS>
+__device__ __forceinline__ void set_right(BFrag<T, KS> &f, int g, int bcol) {
+    constexpr int V = Tr<T>::V, KC = 4 * V;
+#pragma unroll
+    for (int s = kWholeSteps<KS>; s < KS; ++s) {
+        const int back = max(0, KC * s + V * g - (bcol - V));
+        T t[V];
+#pragma unroll
+        for (int q = 0; q < V; ++q) {
+            t[q] = T(0);
+#pragma unroll
+            for (int j = q; j < V; ++j)
+                if (back == j - q) t[q] = f.v[s][j];
+        }
+#pragma unroll
+        for (int q = 0; q < V; ++q) f.v[s][q] = t[q];
+    }
+}
+// (steps that bCol does not reach are left out; C is staged up to there only)
+template <typename T, int NB, int KS>
+__device__ __forceinline__ void mfma_frag_any(typename Tr<T>::Acc (&acc)[NB], const T *Cl,
+                                              const BFrag<T, KS> &f, int lane, int bcol) {
+    constexpr int V = Tr<T>::V, KC = 4 * V;
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) acc[nb] = typename Tr<T>::Acc{0, 0, 0, 0};
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+        if (s >= kWholeSteps<KS> && KC * s >= bcol) break;
+#pragma unroll
+        for (int q = 0; q < V; ++q)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+                acc[nb] = mfma16(Cl[((s * V + q) * NB + nb) * 64 + lane], f.v[s][q], acc[nb]);
+    }
 }
 
 template <typename T, int NB, int KS>
@@ -457,7 +445,7 @@ __device__ __forceinline__ SecondBlock<T> second_block(const unsigned char *sb, 
 template <typename T, int VV, int R, int W = 1>
 __device__ __forceinline__ void fused_tail(const FusedLaunch &a, const TileDesc &d,
                                            const unsigned char *sb,
-                                           const T *tileD1, int ldl, int c0, int gl, int grp,
+                                           const T *tileD1, int ldl, int c0, int w, int gl, int grp,
                                            int ngrp) {
     const int ccol = a.ccol;
     const uint32_t lane_off = (uint32_t)(W * VV * gl);      // W packs of VV columns per lane
@@ -569,7 +557,8 @@ __device__ __forceinline__ void fused_tail(const FusedLaunch &a, const TileDesc 
                 if (grp + (kb * R + r) * ngrp < un.n_rows) {
 #pragma unroll
                     for (int wq = 0; wq < W; ++wq)
-                        store_pack<T, VV>(D + (int64_t)rid[r] * ccol + c0 + lane_off + wq * VV, acc[r][wq]);
+                        store_any<T, VV>(D + (int64_t)rid[r] * ccol + c0 +
+                                             min((int)lane_off + wq * VV, w - VV), acc[r][wq]);
                 }
         }
     }
@@ -828,10 +817,10 @@ __global__ __launch_bounds__(kFusedThreads) void k_fused_gemm_spmm(const FusedLa
             const int G2 = G / 2;
             const int gl2 = (int)threadIdx.x % G2;
             if (2 * VV * gl2 < w)
-                fused_tail<T, VV, 2, 2>(a, d, SLDS ? sm.second : blk, tileD1, ldl, c0, gl2,
+                fused_tail<T, VV, 2, 2>(a, d, SLDS ? sm.second : blk, tileD1, ldl, c0, w, gl2,
                                         (int)threadIdx.x / G2, (int)blockDim.x / G2);
         } else if (VV * gl < w) {
-            fused_tail<T, VV, 3>(a, d, SLDS ? sm.second : blk, tileD1, ldl, c0, gl, grp, ngrp);
+            fused_tail<T, VV, 3>(a, d, SLDS ? sm.second : blk, tileD1, ldl, c0, w, gl, grp, ngrp);
         }
         if (!has_next) break;
         // (the next tile rewrites the LDS tile and the staged block; its row ids are in the other buffer)
@@ -952,12 +941,12 @@ __device__ __forceinline__ void gather_staged_rows(int rows, const int32_t *ext,
 #pragma unroll
         for (int e = 0; e < CAP / 2; ++e)
 #pragma unroll
-            for (int r = 0; r < RP; ++r) load_pack<T, VV>(x[r][e], Xl + (int64_t)ci[r][e] * ldx);
+            for (int r = 0; r < RP; ++r) load_any<T, VV>(x[r][e], Xl + (int64_t)ci[r][e] * ldx);
         if (second_half) {
 #pragma unroll
             for (int e = CAP / 2; e < CAP; ++e)
 #pragma unroll
-                for (int r = 0; r < RP; ++r) load_pack<T, VV>(x[r][e], Xl + (int64_t)ci[r][e] * ldx);
+                for (int r = 0; r < RP; ++r) load_any<T, VV>(x[r][e], Xl + (int64_t)ci[r][e] * ldx);
         }
         auto sum_slots = [&](int r, const T(&v)[CAP], int e0) {
 #pragma unroll
@@ -1011,6 +1000,7 @@ __global__ __launch_bounds__(kFusedSparseThreads) void k_fused_spmm_spmm(const F
     const FusedSmem sm = fused_smem(a, true, 0, (int)sizeof(T));
     T *tileD1 = reinterpret_cast<T *>(sm.tile);
     const int G = pow2_at_least((a.cs + VV - 1) / VV);
+    const int pieces = (w + VV - 1) / VV;              // of a row of this slice
     const int gl = threadIdx.x % G, grp = threadIdx.x / G, ngrp = (int)blockDim.x / G;
     const T *__restrict__ bvals = static_cast<const T *>(a.Bs.vals);
     const T *__restrict__ C = static_cast<const T *>(a.C);
@@ -1052,7 +1042,7 @@ __global__ __launch_bounds__(kFusedSparseThreads) void k_fused_spmm_spmm(const F
             stage_entries<T>(rows, ext_cur, sm.bidx, eval, a.Bs.colidx, bvals);
             T *tile_lane = tileD1 + VV * gl;
             // the lane's columns of a workspace row (slices of d1_sw columns) and of a row of D
-            const int colg = c0 + VV * gl;
+            const int colg = c0 + min(VV * gl, w - VV);
             T *D1l = static_cast<T *>(a.D1) + (int64_t)(colg >> a.d1_sw_shift) * a.d1_slice_stride +
                      (colg & a.d1_sw_mask);
             T *Dl = static_cast<T *>(a.D) + colg;
@@ -1065,18 +1055,17 @@ __global__ __launch_bounds__(kFusedSparseThreads) void k_fused_spmm_spmm(const F
                 T sc;
             };
             gather_staged_rows<T, VV, 1>(
-                rows, ext_cur, sm.bidx, eval, a.Bs.colidx, bvals, C + c0 + VV * gl, ccol,
-                VV * gl < w, grp, ngrp,
+                rows, ext_cur, sm.bidx, eval, a.Bs.colidx, bvals, C + colg, ccol, gl < pieces, grp, ngrp,
                 [&](int pos) { return RowInfo{info_t[pos], scale_t ? scale_t[pos] : T(0)}; },
                 [&](int pos, const RowInfo &ri, const T(&acc)[VV]) {
                     if (has2) store_pack<T, VV>(tile_lane + (int64_t)pos * ldl, acc);
                     if (ri.info & kInfoSpill)
-                        store_pack<T, VV>(D1l + (int64_t)(ri.info & kInfoSlotMask) * a.d1_sw, acc);
+                        store_any<T, VV>(D1l + (int64_t)(ri.info & kInfoSlotMask) * a.d1_sw, acc);
                     if (ri.info & (kInfoDirect | kInfoZero)) {
                         T x[VV];
 #pragma unroll
                         for (int i = 0; i < VV; ++i) x[i] = (ri.info & kInfoZero) ? T(0) : ri.sc * acc[i];
-                        store_pack<T, VV>(Dl + (int64_t)first[pos] * ccol, x);
+                        store_any<T, VV>(Dl + (int64_t)first[pos] * ccol, x);
                     }
                 });
         }
@@ -1107,14 +1096,14 @@ __global__ __launch_bounds__(kFusedSparseThreads) void k_fused_spmm_spmm(const F
         // registers, half the index and address work per column)
         if (!has2) {
             // nothing reads the LDS tile
-        } else if (FAST && G >= 2 && w % (2 * VV) == 0) {
+        } else if (FAST && G >= 2 && pieces % 2 == 0) {
             const int G2 = G / 2;
             const int gl2 = (int)threadIdx.x % G2;
-            if (2 * VV * gl2 < w)
-                fused_tail<T, VV, 1, 2>(a, d, SLDS ? sm.second : blk, tileD1, ldl, c0, gl2,
+            if (2 * gl2 < pieces)
+                fused_tail<T, VV, 1, 2>(a, d, SLDS ? sm.second : blk, tileD1, ldl, c0, w, gl2,
                                         (int)threadIdx.x / G2, (int)blockDim.x / G2);
-        } else if (VV * gl < w) {
-            fused_tail<T, VV, 2>(a, d, SLDS ? sm.second : blk, tileD1, ldl, c0, gl, grp, ngrp);
+        } else if (gl < pieces) {
+            fused_tail<T, VV, 2>(a, d, SLDS ? sm.second : blk, tileD1, ldl, c0, w, gl, grp, ngrp);
         }
         if (!has_next) break;
         {
@@ -1210,8 +1199,8 @@ __global__ __launch_bounds__(kSpmmThreads) void k_packed_spmm(const PackedSpmmLa
         __syncthreads();
         const int L = d.slots;
         for (int cb = 0; cb < w; cb += G * VV) {
-            const int col = cb + VV * gl;
-            const bool active = col < w;
+            const bool active = cb + VV * gl < w;
+            const int col = min(cb + VV * gl, w - VV);
             const uint32_t lane_off = active ? (uint32_t)col : 0u;      // idle lanes read column 0
             for (int i0 = grp; i0 < d.n_rows; i0 += ngrp * R) {
                 int at[R];
@@ -1271,15 +1260,15 @@ __global__ __launch_bounds__(kSpmmThreads) void k_packed_spmm(const PackedSpmmLa
 #pragma unroll
                     for (int r = 0; r < R; ++r)
                         if (i0 + r * ngrp < d.n_rows)
-                            store_pack<T, VV>(Y + (int64_t)rid[r] * ccol + col, acc[r]);
+                            store_any<T, VV>(Y + (int64_t)rid[r] * ccol + col, acc[r]);
                 }
             }
         }
         return;
     }
     for (int cb = 0; cb < w; cb += G * VV) {
-        const int col = cb + VV * gl;
-        const bool active = col < w;
+        const bool active = cb + VV * gl < w;
+        const int col = min(cb + VV * gl, w - VV);
         const uint32_t lane_off = active ? (uint32_t)col : 0u;      // idle lanes read column 0
         {
             // group -> (row, part); `split` groups share a row, each takes a range of the slots
@@ -1363,7 +1352,7 @@ __global__ __launch_bounds__(kSpmmThreads) void k_packed_spmm(const PackedSpmmLa
                 for (int pp = 0; pp < d.split; ++pp)
 #pragma unroll
                     for (int i = 0; i < VV; ++i) sum[i] += red[((grp + pp) * G + gl) * VV + i];
-                store_pack<T, VV>(Y + (int64_t)rows[d.row_begin + row_i] * ccol + col, sum);
+                store_any<T, VV>(Y + (int64_t)rows[d.row_begin + row_i] * ccol + col, sum);
             }
             __syncthreads();
         }
@@ -1408,14 +1397,15 @@ __global__ __launch_bounds__(kSpmmThreads) void k_csr_spmm(const CsrSpmmLaunch a
     __syncthreads();
     stage_entries<T>(rows, ext_s, idx_s, val_s, a.S.colidx, vals);
     for (int cb = 0; cb < ccol; cb += G * VV) {
-        const int col = cb + VV * gl;
+        const bool active = cb + VV * gl < ccol;
+        const int col = min(cb + VV * gl, ccol - VV);
         // the lane's columns of a row of the workspace (slices of y_sw columns)
         T *Yl = Y + (int64_t)(col >> a.y_sw_shift) * a.y_slice_stride + (col & a.y_sw_mask);
         if (!a.row_info) {
             gather_staged_rows<T, VV, 2>(rows, ext_s, idx_s, val_s, a.S.colidx, vals, X + col, ccol,
-                                         col < ccol, grp, ngrp, [](int) { return 0; },
+                                         active, grp, ngrp, [](int) { return 0; },
                                          [&](int pos, int, const T(&acc)[VV]) {
-                                             store_pack<T, VV>(Yl + (r0 + pos) * a.y_sw, acc);
+                                             store_any<T, VV>(Yl + (r0 + pos) * a.y_sw, acc);
                                          });
         } else {
             // first wavefront of a plan without an LDS tile: what happens to a finished D1 row is
@@ -1427,16 +1417,16 @@ __global__ __launch_bounds__(kSpmmThreads) void k_csr_spmm(const CsrSpmmLaunch a
             const T *scale = static_cast<const T *>(a.row_scale);
             T *Dl = static_cast<T *>(a.D) + col;
             gather_staged_rows<T, VV, 2>(
-                rows, ext_s, idx_s, val_s, a.S.colidx, vals, X + col, ccol, col < ccol, grp, ngrp,
+                rows, ext_s, idx_s, val_s, a.S.colidx, vals, X + col, ccol, active, grp, ngrp,
                 [&](int pos) { return RowInfo{a.row_info[r0 + pos], scale ? scale[r0 + pos] : T(0)}; },
                 [&](int pos, const RowInfo &ri, const T(&acc)[VV]) {
                     if (ri.info & kInfoSpill)
-                        store_pack<T, VV>(Yl + (int64_t)(ri.info & kInfoSlotMask) * a.y_sw, acc);
+                        store_any<T, VV>(Yl + (int64_t)(ri.info & kInfoSlotMask) * a.y_sw, acc);
                     if (ri.info & (kInfoDirect | kInfoZero)) {
                         T x[VV];
 #pragma unroll
                         for (int i = 0; i < VV; ++i) x[i] = (ri.info & kInfoZero) ? T(0) : ri.sc * acc[i];
-                        store_pack<T, VV>(Dl + (r0 + pos) * ccol, x);
+                        store_any<T, VV>(Dl + (r0 + pos) * ccol, x);
                     }
                 });
         }
@@ -1445,6 +1435,10 @@ __global__ __launch_bounds__(kSpmmThreads) void k_csr_spmm(const CsrSpmmLaunch a
 
 // D1 = B C for all rows, one 16-row block per wave at a time, the next block's rows of B in
 // flight while the current one is multiplied (KS > 0, as above).
+// KS > 0, FAST: bCol = 4 V KS exactly; not FAST: any bCol from V up to there, rows of B at any element.
+// KS = 0: any bCol, nothing in flight ahead; FAST: bCol is a multiple of V.  cCol is any.
+// (Graph of 150000 rows, fp32 128 -> 41, product and gather: 229 us while an unaligned cCol took the loop
+// over k with single elements stored and gathered, 117 us with this depth and 16-byte pieces.)
 // INFO = false: the GeMM of the unfused baseline; every row goes to the workspace, slot = row.
 // INFO = true: the first wavefront of a plan none of whose fused rows reads the LDS tile (a graph:
 // the only rows that fuse hold just a diagonal entry, or nothing).  Then no tile has to sit in LDS
@@ -1490,22 +1484,20 @@ __global__ __launch_bounds__(kFusedThreads) void k_gemm(const GemmLaunch a) {
         if constexpr (!INFO) {
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) {
-                const int col = 16 * nb + 4 * g;
                 const int cb = c0 + 16 * nb;        // the workspace is cut into slices of d1_sw columns
-                store_acc4<T, FAST>(D1 + (int64_t)(cb >> a.d1_sw_shift) * a.d1_slice_stride +
+                store_acc4<T>(D1 + (int64_t)(cb >> a.d1_sw_shift) * a.d1_slice_stride +
                                         row * a.d1_sw + (cb & a.d1_sw_mask) + 4 * g,
-                                    acc[nb], col, w);
+                                    acc[nb], nb, g, w);
             }
         } else {
             if (ri.info & kInfoSpill) {
                 const int64_t slot = (int64_t)(ri.info & kInfoSlotMask);
 #pragma unroll
                 for (int nb = 0; nb < NB; ++nb) {
-                    const int col = 16 * nb + 4 * g;
                     const int cb = c0 + 16 * nb;
-                    store_acc4<T, FAST>(D1 + (int64_t)(cb >> a.d1_sw_shift) * a.d1_slice_stride +
+                    store_acc4<T>(D1 + (int64_t)(cb >> a.d1_sw_shift) * a.d1_slice_stride +
                                             slot * a.d1_sw + (cb & a.d1_sw_mask) + 4 * g,
-                                        acc[nb], col, w);
+                                        acc[nb], nb, g, w);
                 }
             }
             if (ri.info & (kInfoDirect | kInfoZero)) {
@@ -1515,7 +1507,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_gemm(const GemmLaunch a) {
                     typename Tr<T>::Acc x;
 #pragma unroll
                     for (int i = 0; i < 4; ++i) x[i] = (ri.info & kInfoZero) ? T(0) : ri.sc * acc[nb][i];
-                    store_acc4<T, FAST>(dst + 16 * nb, x, 16 * nb + 4 * g, w);
+                    store_acc4<T>(dst + 16 * nb, x, nb, g, w);
                 }
             }
         }
@@ -1523,21 +1515,27 @@ __global__ __launch_bounds__(kFusedThreads) void k_gemm(const GemmLaunch a) {
     if constexpr (KS > 0) {
         constexpr int KSF = KS;
         BFrag<T, KSF> cur, nxt;
+        auto load = [&](BFrag<T, KSF> &f, int64_t row) __attribute__((always_inline)) {
+            const T *brow = B + (row < a.n ? row : a.n - 1) * a.bcol;
+            if constexpr (FAST) load_b_frag<T, KSF>(f, brow, g);
+            else load_b_frag_any<T, KSF>(f, brow, g, a.bcol);
+        };
         int64_t lb = lb0 + wave;
-        {
-            const int64_t row = lb * 16 + r;
-            load_b_frag<T, KSF>(cur, B + (row < a.n ? row : a.n - 1) * a.bcol, g);
-        }
+        load(cur, lb * 16 + r);
         for (; lb < lb1; lb += nwaves) {
             // The C slice is loop invariant; keeping all of it in registers only pays while it
             // is small, so for larger slices the LDS reads are pinned inside the loop.
             if constexpr (KSF * Tr<T>::V * NB * (sizeof(T) / 4) > 64) asm volatile("" ::: "memory");
-            const int64_t nrow = (lb + nwaves) * 16 + r;
-            load_b_frag<T, KSF>(nxt, B + (nrow < a.n ? nrow : a.n - 1) * a.bcol, g);
+            load(nxt, (lb + nwaves) * 16 + r);
             const RowInfo ri = row_info(lb);
             __builtin_amdgcn_sched_barrier(0);      // keep the prefetch ahead of the MFMAs
             typename Tr<T>::Acc acc[NB];
-            mfma_frag<T, NB, KSF>(acc, Cl, cur, lane);
+            if constexpr (FAST) {
+                mfma_frag<T, NB, KSF>(acc, Cl, cur, lane);
+            } else {
+                set_right<T, KSF>(cur, g, a.bcol);
+                mfma_frag_any<T, NB, KSF>(acc, Cl, cur, lane, a.bcol);
+            }
             write_block(lb, ri, acc);
             cur = nxt;
         }
@@ -1702,10 +1700,6 @@ bool gemm_fast(int dtype, int bcol, int ccol, int cs) {
     const int v = vec_elems(dtype);
     return bcol % v == 0 && ccol % v == 0 && (cs % v == 0);
 }
-bool spmm_fast(int dtype, int ccol, int cs) {
-    const int v = vec_elems(dtype);
-    return ccol % v == 0 && cs % v == 0;
-}
 
 }  // namespace
 
@@ -1730,7 +1724,7 @@ int launch_fused_gemm_spmm(const FusedLaunch &a, void *stream) {
 int launch_fused_spmm_spmm(const FusedLaunch &a, void *stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (a.n_tiles == 0) return 0;
-    const bool fast = spmm_fast(a.dtype, a.ccol, a.cs);
+    const bool fast = lane_elems(a.dtype, a.ccol, a.cs) > 1;
     if (a.dtype == TF_F32)
         return fast ? run_fused_spmm<float, true>(a, st) : run_fused_spmm<float, false>(a, st);
     return fast ? run_fused_spmm<double, true>(a, st) : run_fused_spmm<double, false>(a, st);
@@ -1740,7 +1734,7 @@ int launch_packed_spmm(const PackedSpmmLaunch &a, void *stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (a.n_units == 0) return 0;
     if (a.n_xs != 1 && a.n_xs != 2 && a.n_xs != 4 && a.n_xs != 8) return (int)hipErrorInvalidValue;
-    const bool fast = spmm_fast(a.dtype, a.ccol, a.sw);
+    const bool fast = lane_elems(a.dtype, a.ccol, a.sw) > 1;
     // one workgroup per unit and slice; with slices, 8 / n_xs units per round of eight workgroups
     const int64_t rounds = (a.n_units * a.n_xs + kXcds - 1) / kXcds;
     const dim3 grid((unsigned)(rounds * kXcds)), block(kSpmmThreads);
@@ -1767,7 +1761,7 @@ int launch_csr_spmm(const CsrSpmmLaunch &a, void *stream) {
     if (a.n_rows == 0) return 0;
     // the kernel stages the rows of a workgroup in LDS arrays of this many rows
     if (a.rows_per_wg < 1 || a.rows_per_wg > kCsrRowsPerWg) return (int)hipErrorInvalidValue;
-    const bool fast = spmm_fast(a.dtype, a.ccol, a.ccol);
+    const bool fast = lane_elems(a.dtype, a.ccol, a.ccol) > 1;
     const int64_t n_wg = (a.n_rows + a.rows_per_wg - 1) / a.rows_per_wg;
     const dim3 grid((unsigned)((n_wg + kXcds - 1) / kXcds * kXcds)), block(kSpmmThreads);
     (void)hipGetLastError();
@@ -1784,18 +1778,21 @@ int launch_csr_spmm(const CsrSpmmLaunch &a, void *stream) {
 int launch_gemm(const GemmLaunch &a, void *stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (a.n == 0) return 0;
-    const bool fast = gemm_fast(a.dtype, a.bcol, a.ccol, a.cs);
-    if (!fast) {
-        return dispatch_nb(a.cs, [&](auto nb) {
-            constexpr int NB = decltype(nb)::value;
-            return a.dtype == TF_F32 ? run_gemm<float, NB, 0, false>(a, st)
-                                     : run_gemm<double, NB, 0, false>(a, st);
-        });
-    }
-    return dispatch_shape(a.dtype, a.cs, a.bcol, fast, [&](auto nb, auto ks) {
+    // The depth: the smallest one that covers bCol where bCol is all of it, or where rows of B are not
+    // aligned.  Aligned rows of other lengths take the loop over k, whose few registers leave room for
+    // more waves (graph of 119367 rows, fp32 36 -> 128, whole chain: 146 us, 150 us with the covering
+    // depth; 194822 rows, fp64 78 -> 16: 92 us, 97 us).
+    const int v = vec_elems(a.dtype), kc = 4 * v;
+    int depth = 2;
+    while (depth < 16 && depth * kc < a.bcol) depth *= 2;
+    const bool exact = a.bcol == depth * kc;
+    const bool covered = exact || (a.bcol % v && a.bcol >= v && a.bcol <= depth * kc);
+    const bool fast = exact || (!covered && a.bcol % v == 0);
+    return dispatch_shape(a.dtype, a.cs, covered ? depth * kc : 1, true, [&](auto nb, auto ks) {
         constexpr int NB = decltype(nb)::value, KS = decltype(ks)::value;
-        return a.dtype == TF_F32 ? run_gemm<float, NB, KS, true>(a, st)
-                                 : run_gemm<double, NB, KS, true>(a, st);
+        if (a.dtype == TF_F32)
+            return fast ? run_gemm<float, NB, KS, true>(a, st) : run_gemm<float, NB, KS, false>(a, st);
+        return fast ? run_gemm<double, NB, KS, true>(a, st) : run_gemm<double, NB, KS, false>(a, st);
     });
 }
 

@@ -1,0 +1,73 @@
+"""Widths that are no whole number of 16-byte pieces in the kernels of the two wavefronts: rows gathered
+and stored in pieces of which the last is moved back, rows of B of the dense product the same way.
+Small-integer entries: the result must equal the oracle bit for bit."""
+import numpy as np
+import pytest
+
+import oracle
+import tf_inputs as ti
+
+pytestmark = pytest.mark.gpu
+
+
+def _far(n, dtype, seed):
+    """Rows of 0 to 11 entries, all of them half of the matrix away (no tile fuses one), a few rows with the
+    diagonal entry only, and one row long enough to be split."""
+    rng = np.random.default_rng(seed)
+    lens = rng.integers(0, 12, n)
+    lens[5] = 300
+    diag = rng.random(n) < 0.1
+    lens[diag] = 1
+    rows = np.repeat(np.arange(n), lens)
+    cols = (rows + n // 2 + rng.integers(-n // 8, n // 8, rows.size)) % n
+    cols[np.isin(rows, np.flatnonzero(diag))] = rows[np.isin(rows, np.flatnonzero(diag))]
+    order = np.lexsort((cols, rows))
+    rowptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    return ti.Csr(n, n, rowptr, cols[order].astype(np.int32), rng.integers(-2, 3, rows.size).astype(dtype))
+
+
+def _check(A, B, C, kind, streams=None, **params):
+    from gpu_util import Case
+    D_ref, _ = oracle.chain(A, B, C)
+    c = Case(ti.Problem("ragged", kind, C.dtype, A, B, C), **params)
+    try:
+        if streams is not None:
+            assert c.plan.schedule()["first_wavefront_streams"] == streams
+        for fused in (True, False):
+            assert np.array_equal(c.run(fused).astype(np.float64), D_ref)
+    finally:
+        c.close()
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("ccol", [1, 2, 3, 4, 5, 7, 9, 30, 31, 41, 63, 65, 67, 127, 130, 257, 258, 259, 385, 515])
+@pytest.mark.parametrize("far", [0, 1])
+def test_gathered_rows_of_every_width(dtype, ccol, far):
+    """Tiles in LDS (rows near the diagonal) and the streaming first wavefront (far rows); widths around
+    one piece, one wave of pieces and the column slices of the tiles."""
+    n = 611
+    A = _far(n, dtype, 7) if far else ti.random_local_csr(n, 9, 6, 0.0, dtype, 21, int_values=True, empty_row_prob=0.1)
+    B = ti.random_local_csr(n, n - 1, 9, 0.0, dtype, 22, int_values=True, empty_row_prob=0.1)
+    _check(A, B, ti.dense_small_int(n, ccol, dtype, 5), "spmm_spmm", **(dict(streams=1, ct_size=64) if far else {}))
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("ccol,col_slice", [(30, 16), (33, 16), (35, 5), (70, 64), (66, 16), (9, 2)])
+def test_ragged_column_slices_of_tiles(dtype, ccol, col_slice):
+    if (col_slice * np.dtype(dtype).itemsize) % 16 and (ccol * np.dtype(dtype).itemsize) % 16 == 0:
+        pytest.skip("slices of an aligned width are whole pieces")
+    n = 611
+    A = ti.random_local_csr(n, 9, 6, 0.0, dtype, 21, int_values=True, empty_row_prob=0.1)
+    _check(A, A, ti.dense_small_int(n, ccol, dtype, 5), "spmm_spmm", col_slice=col_slice, ct_size=64)
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("bcol", [1, 2, 3, 4, 5, 15, 17, 31, 33, 48, 63, 65, 96, 127, 129, 250, 257, 260])
+def test_streaming_product_with_every_depth(dtype, bcol):
+    """One size below and above every depth the product is instantiated for, aligned or not, into D1 rows
+    and rows of D of any alignment."""
+    n = 611
+    A = _far(n, dtype, 8)
+    ccol = (41, 64, 23, 130)[bcol % 4]
+    B, C = ti.dense_small_int(n, bcol, dtype, 5), ti.dense_small_int(bcol, ccol, dtype, 6)
+    _check(A, B, C, "gemm_spmm", streams=1, ct_size=64)
