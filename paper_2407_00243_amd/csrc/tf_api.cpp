@@ -249,6 +249,7 @@ tf_status check_sparse_b(const tf_plan *p, const tf_csr *B) {
 bool gemm_shape(const tf_plan *p, tf::GemmLaunch &g) {
     g.dtype = p->dtype;
     g.n = p->n;
+    g.n_cu = p->n_cu;
     g.bcol = (int32_t)p->bcol;
     g.ccol = (int32_t)p->ccol;
     g.cs = p->ccol > tf::kMaxMfmaSliceCols ? tf::kMaxMfmaSliceCols : (int32_t)p->ccol;

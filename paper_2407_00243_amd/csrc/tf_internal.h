@@ -461,6 +461,7 @@ struct GemmLaunch {
     int32_t dtype;
     int64_t n;
     int32_t bcol, ccol, cs, n_slices;
+    int32_t n_cu;                     // compute units of the device
     const void *B, *C;
     int32_t c_ldk, c_ldc;             // element (k, c) of the multiplier is C[k c_ldk + c c_ldc]
     void *D1;                         // workspace layout: slices of d1_sw columns

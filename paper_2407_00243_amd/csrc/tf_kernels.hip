@@ -45,7 +45,7 @@ __device__ __forceinline__ void stage_c_slice(T *Cl, const T *__restrict__ C, in
     constexpr int V = Tr<T>::V, KC = 4 * V;
     const int ksteps = (bcol + KC - 1) / KC;
     const int total = ksteps * V * NB * 64;
-    constexpr int U = 8;                                  // loads in flight per thread
+    constexpr int U = 16;                                 // loads in flight per thread
     for (int e0 = threadIdx.x; e0 < total; e0 += U * (int)blockDim.x) {
         T tmp[U];
 #pragma unroll
@@ -1453,16 +1453,15 @@ __global__ __launch_bounds__(kFusedThreads) void k_gemm(const GemmLaunch a) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
     const int g = lane >> 4, r = lane & 15;
     T *Cl = reinterpret_cast<T *>(tf_smem);
-    stage_c_slice<T, NB>(Cl, static_cast<const T *>(a.C), a.bcol, a.c_ldk, a.c_ldc, c0,
-                         w);
-    __syncthreads();
     const int64_t nblk = (a.n + 15) >> 4;
     const T *__restrict__ B = static_cast<const T *>(a.B);
     T *__restrict__ D1 = static_cast<T *>(a.D1);
     // contiguous range of row blocks per workgroup, waves interleaved inside it
-    const int64_t per_wg = (nblk + gridDim.x - 1) / gridDim.x;
-    const int64_t lb0 = (int64_t)blockIdx.x * per_wg;
-    const int64_t lb1 = lb0 + per_wg < nblk ? lb0 + per_wg : nblk;
+    const int64_t lb0 = nblk * blockIdx.x / gridDim.x, lb1 = nblk * (blockIdx.x + 1) / gridDim.x;
+    auto stage_c = [&]() __attribute__((always_inline)) {
+        stage_c_slice<T, NB>(Cl, static_cast<const T *>(a.C), a.bcol, a.c_ldk, a.c_ldc, c0, w);
+        __syncthreads();
+    };
     struct RowInfo {
         uint32_t info;
         T sc;
@@ -1521,7 +1520,8 @@ __global__ __launch_bounds__(kFusedThreads) void k_gemm(const GemmLaunch a) {
             else load_b_frag_any<T, KSF>(f, brow, g, a.bcol);
         };
         int64_t lb = lb0 + wave;
-        load(cur, lb * 16 + r);
+        load(cur, lb * 16 + r);            // on its way while C is staged
+        stage_c();
         for (; lb < lb1; lb += nwaves) {
             // The C slice is loop invariant; keeping all of it in registers only pays while it
             // is small, so for larger slices the LDS reads are pinned inside the loop.
@@ -1540,6 +1540,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_gemm(const GemmLaunch a) {
             cur = nxt;
         }
     } else {
+        stage_c();
         for (int64_t lb = lb0 + wave; lb < lb1; lb += nwaves) {
             const int64_t row = lb * 16 + r;
             const bool valid = row < a.n;
@@ -1639,8 +1640,18 @@ template <typename T, bool FAST> int run_fused_spmm(const FusedLaunch &a, hipStr
 template <typename T, int NB, int KS, bool FAST, bool INFO>
 int run_gemm2(const GemmLaunch &a, hipStream_t st) {
     const int64_t lds = lds_fixed_bytes(a.dtype, 0, a.bcol, a.cs);
+    const int64_t nblk = (a.n + 15) / 16;
+    // As many workgroups as the machine holds at once, so that each stages C only once, the first rows of
+    // B on their way meanwhile (with up to 1024 of them most waves multiplied one block each: fp32 n =
+    // 131072, 64 -> 128, 48.5 us, now 38; n = 150000, 128 -> 41, 47 us, now 36; n = 2^20, 128 -> 128, where
+    // the matrix cores are 60 % busy, 399 us, now 374); few blocks are spread thin, as far as a wave
+    // does not have to stage more than 4 KiB of C.
+    int nwaves = kFusedThreads / 64;
+    while (nwaves > 1 && nblk * a.n_slices < (int64_t)a.n_cu * nwaves && nwaves * 2048 >= lds) nwaves /= 2;
     static std::mutex m;
-    static int64_t raised = -1;
+    static int64_t raised = -1, occ_lds = -1;
+    static int occ_waves = 0, occ = 1;
+    int wg_per_cu;
     {
         std::lock_guard<std::mutex> lock(m);
         if (lds > raised) {
@@ -1648,14 +1659,18 @@ int run_gemm2(const GemmLaunch &a, hipStream_t st) {
             if (e) return e;
             raised = lds;
         }
+        if (lds != occ_lds || nwaves != occ_waves) {
+            occ = resident_per_cu(k_gemm<T, NB, KS, FAST, INFO>, 64 * nwaves, lds, 16);
+            occ_lds = lds;
+            occ_waves = nwaves;
+        }
+        wg_per_cu = occ;
     }
-    const int nwaves = kFusedThreads / 64;
-    const int64_t nblk = (a.n + 15) / 16;
-    int64_t gx = (nblk + nwaves - 1) / nwaves;
-    gx = gx < 1 ? 1 : (gx > 1024 ? 1024 : gx);
+    const int64_t most = std::max<int64_t>(1, (int64_t)a.n_cu * wg_per_cu / a.n_slices);
+    const int64_t gx = std::min(most, (nblk + nwaves - 1) / nwaves);
     (void)hipGetLastError();
     k_gemm<T, NB, KS, FAST, INFO>
-        <<<dim3((unsigned)gx, (unsigned)a.n_slices), dim3(kFusedThreads), lds, st>>>(a);
+        <<<dim3((unsigned)gx, (unsigned)a.n_slices), dim3(64 * nwaves), lds, st>>>(a);
     return (int)hipGetLastError();
 }
 template <typename T, int NB, int KS, bool FAST> int run_gemm(const GemmLaunch &a, hipStream_t st) {
