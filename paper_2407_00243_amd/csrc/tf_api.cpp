@@ -108,7 +108,9 @@ struct tf_plan {
     std::vector<std::unique_ptr<DevBuf>> arrays;   // everything below that the plan uploads
     void *tile_desc = nullptr, *tile_meta = nullptr, *tile_first = nullptr, *tile_info = nullptr,
          *tile_scale = nullptr, *row_info = nullptr, *row_scale = nullptr;
-    PackBufs wf1, all;
+    PackBufs wf1, all, gf;
+    void *gf_info = nullptr;
+    bool gather_first = false;             // the fused calls run Y = A B, D = Y C
     void *chain_blocks = nullptr, *chain_rows = nullptr, *chain_idx = nullptr, *chain_vals = nullptr;
     int32_t n_chain_blocks = 0;            // 0: the fused calls run the two wavefronts, else the chain in one pass
     bool chain_contiguous = true;
@@ -209,6 +211,7 @@ tf::PackedSpmmLaunch packed_args(const tf_plan *p, const tf_plan::PackBufs &b, c
     w.X = X;
     w.n_xs = lay.n_sl;
     w.sw = lay.sw;
+    w.ldx = lay.sw;
     w.x_slice_stride = lay.slice_stride();
     w.rows_per_pass = p->s.gather_r;
     w.Y = D;
@@ -340,6 +343,30 @@ tf_status first_wavefront_sparse(const tf_plan *p, const tf_csr *B, const void *
         e = tf::launch_fused_spmm_spmm(a, stream);
     }
     if (e) return hip_fail((hipError_t)e, "launching the first wavefront");
+    return TF_OK;
+}
+// Y = A B into the workspace, D = Y C (dense B).
+tf_status run_gather_first(const tf_plan *p, const void *B, const void *C, void *D, void *ws, void *stream) {
+    tf::D1Layout y;
+    y.sw = (int32_t)p->bcol;
+    y.rows = p->n;
+    tf::PackedSpmmLaunch w = packed_args(p, p->s.gather_first_shares ? p->all : p->gf, B, y, ws);
+    w.rows_per_pass = p->s.gather_first_r;
+    w.ccol = (int32_t)p->bcol;
+    int e = tf::launch_packed_spmm(w, stream);
+    if (e) return hip_fail((hipError_t)e, "launching the SpMM");
+    tf::GemmLaunch g{};
+    if (!gemm_shape(p, g)) return fail(TF_EUNSUPPORTED, "internal: no shape for the product");
+    g.B = ws;
+    g.C = C;
+    tf::D1Layout d;                        // every row of Y has its row of D for a slot
+    d.sw = (int32_t)p->ccol;
+    d.rows = p->n;
+    gemm_workspace(g, D, d);
+    g.row_info = static_cast<const uint32_t *>(p->gf_info);
+    g.D = D;
+    e = tf::launch_gemm(g, stream);
+    if (e) return hip_fail((hipError_t)e, "launching the GeMM");
     return TF_OK;
 }
 // The chain in one pass (dense B).
@@ -536,6 +563,9 @@ tf_status tf_plan_create(const tf_csr *A, int64_t bCol, int64_t cCol, int32_t b_
         if (launch_lds() > lds_limit)
             return fail(TF_EUNSUPPORTED, "a tile does not fit the LDS of this device");
         tf::build_chain_pack(in, p->s);
+        tf::GemmLaunch shape{};
+        if (gemm_shape(p, shape) && !tf::build_gather_first(in, p->s, p->has_baseline))
+            return fail(TF_EUNSUPPORTED, "internal: a unit exceeds the staging arrays of the gather kernel");
         tf::Schedule &sc = p->s;
         Arena arena;
         arena.add(sc.tile_desc, p->tile_desc);
@@ -549,6 +579,11 @@ tf_status tf_plan_create(const tf_csr *A, int64_t bCol, int64_t cCol, int32_t b_
         }
         add_pack(arena, p->wf1, sc.wf1);
         if (p->has_baseline) add_pack(arena, p->all, sc.all);
+        if (sc.gather_first) {
+            p->gather_first = true;
+            if (!sc.gather_first_shares) add_pack(arena, p->gf, sc.gf);
+            arena.add(sc.gf_info, p->gf_info);
+        }
         if (!sc.chain.blocks.empty()) {
             p->n_chain_blocks = (int32_t)sc.chain.blocks.size();
             p->chain_contiguous = sc.chain.contiguous;
@@ -569,6 +604,8 @@ tf_status tf_plan_create(const tf_csr *A, int64_t bCol, int64_t cCol, int32_t b_
         drop_entries(sc.wf1);
         drop_entries(sc.all);
         sc.chain = tf::ChainPack();
+        sc.gf = tf::RowPack();
+        std::vector<uint32_t>().swap(sc.gf_info);
         guard.p = nullptr;
         *out = p;
         return TF_OK;
@@ -695,6 +732,7 @@ tf_status tf_gemm_spmm(const tf_plan *p, const void *B, const void *C, void *D, 
     if (st != TF_OK) return st;
     if (!B || !aligned16(B)) return fail(TF_EINVAL, "B must be a 16-byte aligned device pointer");
     if (p->n_chain_blocks > 0) return run_chain(p, B, C, D, stream);
+    if (p->gather_first) return run_gather_first(p, B, C, D, p->d1.p, stream);
     st = first_wavefront_dense(p, B, C, D, p->d1.p, stream);
     if (st != TF_OK) return st;
     return second_wavefront(p, D, p->d1.p, stream);
@@ -713,6 +751,7 @@ tf_status tf_gemm_spmm_static(const tf_plan *p, const void *B, const void *C, vo
     void *ws = nullptr;
     st = static_scratch(&ws);
     if (st != TF_OK) return st;
+    if (p->gather_first) return run_gather_first(p, B, C, D, ws, stream);
     // every spilled row is written by the first wavefront before the second one reads it: nothing
     // in the array has to start at zero
     st = first_wavefront_dense(p, B, C, D, ws, stream);

@@ -351,6 +351,12 @@ struct Schedule {
     RowPack wf1;                   // wf1_rows re-packed
     RowPack all;                   // all rows re-packed (unfused baseline)
     ChainPack chain;               // all rows re-packed for the one-pass chain; no blocks: not used
+    // The chain as Y = A B, D = Y C (see build_gather_first).
+    bool gather_first = false;
+    bool gather_first_shares = false;      // Y is gathered with `all`, else with `gf`
+    int32_t gather_first_r = 4;            // rows per lane group and pass of that gather
+    RowPack gf;
+    std::vector<uint32_t> gf_info;         // info word per row of Y: its row of D, or zeros
     int64_t n_fused_rows = 0, n_spill_rows = 0, fused_nnz = 0;
     int64_t max_tile_rows = 0;
     int64_t lds_fixed_bytes = 0, lds_bytes_per_row = 0, fast_mem_bytes = 0;
@@ -382,6 +388,8 @@ tf_status build_schedule(const InspectorInput &in, Schedule &out, std::string &e
 bool build_baseline_pack(const InspectorInput &in, Schedule &s);
 // Decides whether the fused calls of the plan run the chain in one pass, and packs A for it.
 void build_chain_pack(const InspectorInput &in, Schedule &s);
+// Decides whether they run it as Y = A B, D = Y C, and packs A for that (have_all: `all` is packed).
+bool build_gather_first(const InspectorInput &in, Schedule &s, bool have_all);
 
 
 // ---------------------------------------------------------------- device launch interface
@@ -433,9 +441,10 @@ struct PackedSpmmLaunch {
     int32_t contiguous;               // 1: neighbouring units share an XCD; 0: round robin (one slice only)
     int32_t wide;                     // 1: X spans 4 GiB or more (64-bit operand offsets)
     PackDev pack;                     // int32 indices: rows (slots) of X
-    const void *X;                    // D1 workspace in the layout below
+    const void *X;                    // D1 workspace in the layout below, or a dense B
     int32_t n_xs, sw;                 // column slices (1, 2, 4 or 8; each handled by 8 / n_xs XCDs) of sw columns
     int64_t x_slice_stride;           // elements between the slices of X
+    int32_t ldx;                      // elements between the rows of a slice
     int32_t rows_per_pass;            // R of the kernel instantiation: 1, 2 or 4
     void *Y;                          // row-major, ccol columns
     int32_t ccol;

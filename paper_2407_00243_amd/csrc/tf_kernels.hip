@@ -1173,7 +1173,7 @@ __global__ __launch_bounds__(kSpmmThreads) void k_packed_spmm(const PackedSpmmLa
     const int32_t *__restrict__ idx = static_cast<const int32_t *>(a.pack.idx);
     const T *__restrict__ val = static_cast<const T *>(a.pack.vals);
     const T *__restrict__ X = static_cast<const T *>(a.X) + (int64_t)slice * a.x_slice_stride;
-    const uint32_t ldx = (uint32_t)a.sw;
+    const uint32_t ldx = (uint32_t)a.ldx;
     T *__restrict__ Y = static_cast<T *>(a.Y) + c0;
     if (d.split <= 1) {
         const int n_ent = d.n_rows * d.slots;

@@ -71,3 +71,43 @@ def test_streaming_product_with_every_depth(dtype, bcol):
     ccol = (41, 64, 23, 130)[bcol % 4]
     B, C = ti.dense_small_int(n, bcol, dtype, 5), ti.dense_small_int(bcol, ccol, dtype, 6)
     _check(A, B, C, "gemm_spmm", streams=1, ct_size=64)
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("bcol,ccol", [(32, 92), (36, 128), (5, 128), (1, 120), (64, 130), (17, 127)])
+@pytest.mark.parametrize("transposed", [0, 1])
+def test_graph_with_narrow_rows_of_b_multiplies_a_by_b_first(dtype, bcol, ccol, transposed):
+    """Far rows and bCol well below cCol: Y = A B, which the workspace then holds, D = Y C; rows split over
+    lane groups, and empty rows, which are zeros even where C holds no finite number."""
+    import ctypes
+    import torch
+    import paper_2407_00243_amd as tf
+    from gpu_util import dev, dev_csr
+    n = 40000
+    rng = np.random.default_rng(4)
+    lens = rng.integers(0, 9, n)
+    lens[rng.integers(0, n, 20)] = rng.integers(100, 2000, 20)
+    lens[:50] = 0
+    rowptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    colidx = rng.integers(0, n, rowptr[-1]).astype(np.int32)
+    A = ti.Csr(n, n, rowptr, colidx, rng.integers(-2, 3, colidx.size).astype(dtype))
+    B = ti.dense_small_int(n, bcol, dtype, 5)
+    C = ti.dense_small_int(*((ccol, bcol) if transposed else (bcol, ccol)), dtype, 6)
+    D_ref, _ = (oracle.chain_ct if transposed else oracle.chain)(A, B, C)
+    Y_ref = oracle.chain(A, B, np.eye(bcol, dtype=dtype))[0]
+    D = torch.full((n, ccol), float("nan"), dtype=dev(B).dtype, device="cuda")
+    stream = torch.cuda.current_stream().cuda_stream
+    with tf.Plan(dev_csr(A), bcol, ccol, False, flags=tf.TF_FLAG_C_TRANSPOSED if transposed else 0) as plan:
+        Bd, Cd = dev(B), dev(C)
+        plan.run(Bd, Cd, D, stream)
+        torch.cuda.synchronize()
+        assert np.array_equal(D.cpu().numpy().astype(np.float64), D_ref)
+        Y = np.empty((n, bcol), dtype=dtype)
+        hip = ctypes.CDLL("libamdhip64.so")
+        hip.hipMemcpy.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_int]
+        assert hip.hipMemcpy(Y.ctypes.data, plan.workspace(), Y.nbytes, 2) == 0
+        assert np.array_equal(Y.astype(np.float64), Y_ref)
+        Cd.fill_(float("inf"))
+        plan.run(Bd, Cd, D, stream)
+        torch.cuda.synchronize()
+        assert not D[:50].cpu().numpy().any()
