@@ -340,6 +340,7 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS)) void
         // wait for the next block's gathers, which were sent out before, does not include them.
         if (g == 0)
             er[r] = (r >> slog) < n_rows && (r & ((1 << slog) - 1)) == 0 ? (uint32_t)row * (uint32_t)a.ccol : ~0u;
+        const bool empty = d.slots == 0;      // (empty rows are zeros whatever C holds)
         __builtin_amdgcn_s_setprio(0);
         int grp = 0;
         do {
@@ -360,7 +361,7 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS)) void
                     for (int h = 0; h < 4 / V; ++h) {
                         Vec16 y;
 #pragma unroll
-                        for (int q = 0; q < V; ++q) y[q] = o[nb][V * h + q];
+                        for (int q = 0; q < V; ++q) y[q] = empty ? T(0) : o[nb][V * h + q];
                         *reinterpret_cast<Vec16 *>(ex + r * PITCH + ((nb - nb0) * 16 / V + 4 * h + g) * 16) = y;
                     }
                 __builtin_amdgcn_wave_barrier();

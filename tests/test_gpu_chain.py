@@ -69,4 +69,8 @@ def test_rows_of_many_lengths_and_empty_rows(empty):
     with tf.Plan(A, w, w, False) as plan:
         plan.run(B, dev(np.eye(w, dtype=np.float32)), D, torch.cuda.current_stream().cuda_stream)
         torch.cuda.synchronize()
-    assert not D.cpu().numpy().any()
+        assert not D.cpu().numpy().any()
+        C = torch.full((w, w), float("inf"), device="cuda")
+        plan.run(B, C, D, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+    assert not D.cpu().numpy()[lens == 0].any()
