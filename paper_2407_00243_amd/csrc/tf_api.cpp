@@ -96,6 +96,7 @@ struct tf_plan {
         void *units = nullptr, *rows = nullptr, *idx = nullptr, *vals = nullptr;
         int64_t n_units = 0;
         bool sorted = false;
+        int32_t rows_per_pass = 1;
         tf::PackDev dev() const {
             tf::PackDev d;
             d.units = static_cast<const tf::UnitDesc *>(units);
@@ -148,6 +149,7 @@ void add_pack(Arena &arena, tf_plan::PackBufs &b, const tf::RowPack &pk) {
     arena.add(pk.vals, b.vals);
     b.n_units = (int64_t)pk.units.size();
     b.sorted = pk.sorted;
+    b.rows_per_pass = pk.rows_per_pass;
 }
 // the packed entries live on the device from here on; the row lists stay for the schedule view
 void drop_entries(tf::RowPack &pk) {
@@ -213,7 +215,7 @@ tf::PackedSpmmLaunch packed_args(const tf_plan *p, const tf_plan::PackBufs &b, c
     w.sw = lay.sw;
     w.ldx = lay.sw;
     w.x_slice_stride = lay.slice_stride();
-    w.rows_per_pass = p->s.gather_r;
+    w.rows_per_pass = b.rows_per_pass;
     w.Y = D;
     w.ccol = (int32_t)p->ccol;
     return w;
@@ -351,7 +353,6 @@ tf_status run_gather_first(const tf_plan *p, const void *B, const void *C, void 
     y.sw = (int32_t)p->bcol;
     y.rows = p->n;
     tf::PackedSpmmLaunch w = packed_args(p, p->s.gather_first_shares ? p->all : p->gf, B, y, ws);
-    w.rows_per_pass = p->s.gather_first_r;
     w.ccol = (int32_t)p->bcol;
     int e = tf::launch_packed_spmm(w, stream);
     if (e) return hip_fail((hipError_t)e, "launching the SpMM");

@@ -147,6 +147,11 @@ void pack_rows(const int32_t *rowptr, const int32_t *colidx, const unsigned char
             out.sorted = true;
         }
     }
+    // A lane group works on as many rows at a time as a full unit holds for it, four at most: more would
+    // fetch rows again that it has (short lists, whose time is the longest unit's chain of passes: graph
+    // of 12504 rows, fp64, 24 columns, second wavefront 30 us with four rows per pass, now 12).
+    if (rules.split_groups > 0)
+        out.rows_per_pass = std::min(4, std::max(1, rules.max_rows / rules.split_groups));
     const int64_t list_base = (int64_t)out.rows.size();
     out.rows.insert(out.rows.end(), list.begin(), list.end());
     const size_t first_unit = out.units.size();
@@ -312,9 +317,11 @@ TileBlock pack_tile(const int32_t *rowptr, const int32_t *colidx, const unsigned
 // smaller units (down to one row per lane group) so that they still spread over the machine.
 static PackRules pack_rules(const InspectorInput &in, int64_t count, int sw) {
     const int groups = kSpmmThreads / lane_group(sw, lane_elems(in.dtype, in.ccol, sw));
-    const int64_t want = (count + 1023) / 1024;
-    return PackRules{(int)std::min<int64_t>(kUnitRows, std::max<int64_t>(groups, want)), kUnitSlots,
-                     groups};
+    const int64_t want = std::min<int64_t>(kUnitRows, (count + 1023) / 1024);
+    // whole passes of the lane groups: a power of two of rows for each
+    int rows = groups;
+    while (2 * rows <= want) rows *= 2;
+    return PackRules{std::min(rows, kUnitRows), kUnitSlots, groups};
 }
 
 // The gather kernel stages the entries of a unit whose rows are not split in LDS arrays of
@@ -850,8 +857,6 @@ tf_status build_schedule(const InspectorInput &in, Schedule &s, std::string &err
         s.d1.n_sl = n_sl;
         s.d1.sw = (int32_t)(in.ccol / n_sl);
         s.d1.rows = std::max<int64_t>(1, s.n_spill_rows);
-        const int groups = kSpmmThreads / lane_group(s.d1.sw, lane_elems(in.dtype, in.ccol, s.d1.sw));
-        s.gather_r = groups >= 64 ? 1 : groups >= 32 ? 2 : 4;
     }
     TF_TICK("spill set, slots, layout");
     // ---- per-tile blocks (see TileDesc) ---------------------------------------------------
@@ -1073,8 +1078,6 @@ bool build_gather_first(const InspectorInput &in, Schedule &s, bool have_all) {
     if (5 * touched(in.bcol) > 4 * touched(in.ccol)) return true;
     const int group = lane_group((int)in.bcol, lane_elems(in.dtype, in.bcol, in.bcol));
     const int group_all = lane_group(s.d1.sw, lane_elems(in.dtype, in.ccol, s.d1.sw));
-    const int groups = kSpmmThreads / group;
-    s.gather_first_r = groups >= 64 ? 1 : groups >= 32 ? 2 : 4;
     s.gather_first_shares = have_all && group == group_all;
     if (!s.gather_first_shares) {
         std::vector<int32_t> all((size_t)n);

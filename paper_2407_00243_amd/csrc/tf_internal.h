@@ -231,6 +231,7 @@ struct RowPack {
     RawVec<int32_t> idx32;               // column indices
     RawVec<unsigned char> vals;          // packed values, element size of the plan's dtype
     bool sorted = false;                 // rows were re-ordered by length
+    int32_t rows_per_pass = 1;           // rows that a lane group of the gather kernel works on at a time
     int64_t entries() const { return (int64_t)idx32.size(); }
 };
 
@@ -334,7 +335,6 @@ struct Schedule {
     D1Layout d1;                                          // workspace of the fused path (rows = spilled rows)
     int64_t n_direct_rows = 0;                            // fused rows that leave from registers (diagonal-only or empty)
     int64_t n_lds_rows = 0;                               // fused rows computed out of the LDS tile
-    int32_t gather_r = 4;                                 // rows per lane group and pass of the gather kernel
     // When no fused row reads the LDS tile the first wavefront streams through the rows without
     // tiles: the info words and diagonal entries again, indexed by row (empty otherwise).
     std::vector<uint32_t> row_info;
@@ -354,7 +354,6 @@ struct Schedule {
     // The chain as Y = A B, D = Y C (see build_gather_first).
     bool gather_first = false;
     bool gather_first_shares = false;      // Y is gathered with `all`, else with `gf`
-    int32_t gather_first_r = 4;            // rows per lane group and pass of that gather
     RowPack gf;
     std::vector<uint32_t> gf_info;         // info word per row of Y: its row of D, or zeros
     int64_t n_fused_rows = 0, n_spill_rows = 0, fused_nnz = 0;
