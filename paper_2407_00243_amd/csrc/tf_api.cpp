@@ -116,6 +116,7 @@ struct tf_plan {
     int32_t n_chain_blocks = 0;            // 0: the fused calls run the two wavefronts, else the chain in one pass
     bool chain_contiguous = true;
     DevBuf d1;                             // fused path: one slot per spilled D1 row
+    DevBuf d1_pair;                        // plain pair of operations: all rows of D1
     bool has_baseline = false;             // the packed copy of all rows of A exists
     int n_cu = 256;
     // unfused baseline: all n rows of D1, allocated by the first unfused call (or tf_plan_prepare_unfused)
@@ -347,6 +348,14 @@ tf_status first_wavefront_sparse(const tf_plan *p, const tf_csr *B, const void *
     if (e) return hip_fail((hipError_t)e, "launching the first wavefront");
     return TF_OK;
 }
+// D1 = B C and D = A D1 over all rows (CSR B).
+tf_status run_plain_pair(const tf_plan *p, const tf_csr *B, const void *C, void *D, void *ws, void *stream) {
+    int e = tf::launch_csr_spmm(csr_spmm_args(p, B, C, ws, p->unf_layout()), stream);
+    if (e) return hip_fail((hipError_t)e, "launching the first SpMM");
+    e = tf::launch_packed_spmm(packed_args(p, p->all, ws, p->unf_layout(), D), stream);
+    if (e) return hip_fail((hipError_t)e, "launching the second SpMM");
+    return TF_OK;
+}
 // Y = A B into the workspace, D = Y C (dense B).
 tf_status run_gather_first(const tf_plan *p, const void *B, const void *C, void *D, void *ws, void *stream) {
     tf::D1Layout y;
@@ -550,7 +559,8 @@ tf_status tf_plan_create(const tf_csr *A, int64_t bCol, int64_t cCol, int32_t b_
             return TF_OK;
         }
         p->has_baseline = !(tp && (tp->flags & TF_FLAG_NO_BASELINE));
-        if (p->has_baseline && !tf::build_baseline_pack(in, p->s))
+        p->s.plain_pair = tf::plain_pair_is_faster(in, p->s);
+        if ((p->has_baseline || p->s.plain_pair) && !tf::build_baseline_pack(in, p->s))
             return fail(TF_EUNSUPPORTED, "internal: a unit of the baseline exceeds the staging arrays of the gather kernel");
         p->lds_per_cu = lds_limit;
         // the launch must fit the device whatever the schedule's own estimate said
@@ -579,7 +589,7 @@ tf_status tf_plan_create(const tf_csr *A, int64_t bCol, int64_t cCol, int32_t b_
             arena.add(sc.row_scale, p->row_scale);
         }
         add_pack(arena, p->wf1, sc.wf1);
-        if (p->has_baseline) add_pack(arena, p->all, sc.all);
+        if (p->has_baseline || sc.plain_pair) add_pack(arena, p->all, sc.all);
         if (sc.gather_first) {
             p->gather_first = true;
             if (!sc.gather_first_shares) add_pack(arena, p->gf, sc.gf);
@@ -595,6 +605,7 @@ tf_status tf_plan_create(const tf_csr *A, int64_t bCol, int64_t cCol, int32_t b_
         }
         hipError_t e = arena.upload(p->arrays);
         if (e == hipSuccess) e = p->d1.alloc((size_t)sc.d1.elements() * es);
+        if (e == hipSuccess && sc.plain_pair) e = p->d1_pair.alloc((size_t)p->unf_layout().elements() * es);
         if (e != hipSuccess) return hip_fail(e, "allocating the plan's device memory");
         sc.tile_meta.reset();
         std::vector<int32_t>().swap(sc.tile_first);
@@ -765,6 +776,7 @@ tf_status tf_spmm_spmm(const tf_plan *p, const tf_csr *B, const void *C, void *D
     if (st != TF_OK) return st;
     st = check_sparse_b(p, B);
     if (st != TF_OK) return st;
+    if (p->s.plain_pair) return run_plain_pair(p, B, C, D, p->d1_pair.p, stream);
     st = first_wavefront_sparse(p, B, C, D, p->d1.p, stream);
     if (st != TF_OK) return st;
     return second_wavefront(p, D, p->d1.p, stream);
@@ -815,12 +827,7 @@ tf_status tf_unfused_spmm_spmm(const tf_plan *p, const tf_csr *B, const void *C,
     if (st != TF_OK) return st;
     st = prepare_unfused(p);
     if (st != TF_OK) return st;
-    tf::CsrSpmmLaunch f = csr_spmm_args(p, B, C, p->d1_unf.p, p->unf_layout());
-    int e = tf::launch_csr_spmm(f, stream);
-    if (e) return hip_fail((hipError_t)e, "launching the first SpMM");
-    e = tf::launch_packed_spmm(all_rows_args(p, D), stream);
-    if (e) return hip_fail((hipError_t)e, "launching the second SpMM");
-    return TF_OK;
+    return run_plain_pair(p, B, C, D, p->d1_unf.p, stream);
 }
 
 }  // extern "C"

@@ -1095,6 +1095,20 @@ bool build_gather_first(const InspectorInput &in, Schedule &s, bool have_all) {
     return true;
 }
 
+// A CSR B and a D1 that the caches hold whole: tiles save no memory traffic then, and what is left of them
+// is their chain of barriers and dependent loads.  The two operations over all rows, D1 = B C and
+// D = A D1, are the faster pair up to about 12 MB of D1 (us per execution, tiles / plain pair: 3D stencil
+// fp32 20^3 x 32, 1 MB, 18.9 / 8.9; 32^3 x 80, 10.5 MB, 32.7 / 19.3; 2D stencil fp32 150^2 x 100, 9 MB, 27.6
+// / 18.1; band of 30000 rows fp64 x 32, 7.7 MB, 40.6 / 28.5; beyond: 2D fp64 150^2 x 100, 18 MB, 26.8 /
+// 31.6; 2D fp32 400^2 x 32, 20.5 MB, 24.5 / 28.5).
+bool plain_pair_is_faster(const InspectorInput &in, const Schedule &s) {
+    if (!in.b_is_sparse || in.n == 0 || in.nnz == 0 || s.streaming) return false;
+    // only where the caller has left the whole choice to the library
+    if (!s.automatic || in.col_slice || in.gather_slices || !in.whole_fast_mem || (in.flags & TF_FLAG_SKIP_UNREAD))
+        return false;
+    return in.n * in.ccol * elem_size(in.dtype) <= 12000000;
+}
+
 bool build_baseline_pack(const InspectorInput &in, Schedule &s) {
     std::vector<int32_t> all((size_t)in.n);
     std::iota(all.begin(), all.end(), 0);

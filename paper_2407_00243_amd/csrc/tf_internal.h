@@ -350,6 +350,7 @@ struct Schedule {
     int64_t lds_meta_bytes_per_row = 0;                   // part of lds_bytes_per_row: row ids + estimate of the second-phase block
     RowPack wf1;                   // wf1_rows re-packed
     RowPack all;                   // all rows re-packed (unfused baseline)
+    bool plain_pair = false;       // CSR B: the fused calls run the two operations over all rows, see plain_pair_is_faster
     ChainPack chain;               // all rows re-packed for the one-pass chain; no blocks: not used
     // The chain as Y = A B, D = Y C (see build_gather_first).
     bool gather_first = false;
@@ -387,6 +388,8 @@ tf_status build_schedule(const InspectorInput &in, Schedule &out, std::string &e
 bool build_baseline_pack(const InspectorInput &in, Schedule &s);
 // Decides whether the fused calls of the plan run the chain in one pass, and packs A for it.
 void build_chain_pack(const InspectorInput &in, Schedule &s);
+// Whether the fused calls of a CSR-B plan run the plain pair of operations.
+bool plain_pair_is_faster(const InspectorInput &in, const Schedule &s);
 // Decides whether they run it as Y = A B, D = Y C, and packs A for that (have_all: `all` is packed).
 bool build_gather_first(const InspectorInput &in, Schedule &s, bool have_all);
 

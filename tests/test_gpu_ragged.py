@@ -48,7 +48,9 @@ def test_gathered_rows_of_every_width(dtype, ccol, far):
     n = 611
     A = _far(n, dtype, 7) if far else ti.random_local_csr(n, 9, 6, 0.0, dtype, 21, int_values=True, empty_row_prob=0.1)
     B = ti.random_local_csr(n, n - 1, 9, 0.0, dtype, 22, int_values=True, empty_row_prob=0.1)
-    _check(A, B, ti.dense_small_int(n, ccol, dtype, 5), "spmm_spmm", **(dict(streams=1, ct_size=64) if far else {}))
+    C = ti.dense_small_int(n, ccol, dtype, 5)
+    _check(A, B, C, "spmm_spmm", ct_size=64, **(dict(streams=1) if far else {}))
+    _check(A, B, C, "spmm_spmm")               # (the library's choice: the plain pair of operations)
 
 
 @pytest.mark.parametrize("dtype", [np.float32, np.float64])
@@ -111,3 +113,19 @@ def test_graph_with_narrow_rows_of_b_multiplies_a_by_b_first(dtype, bcol, ccol, 
         plan.run(Bd, Cd, D, stream)
         torch.cuda.synchronize()
         assert not D[:50].cpu().numpy().any()
+
+
+def test_small_plan_without_baseline_still_runs_the_plain_pair():
+    """The pack of all rows exists for the fused calls, the baseline calls stay refused."""
+    import paper_2407_00243_amd as tf
+    from gpu_util import Case
+    n = 3000
+    A = ti.random_local_csr(n, 9, 6, 0.0, np.float32, 21, int_values=True, empty_row_prob=0.1)
+    C = ti.dense_small_int(n, 20, np.float32, 5)
+    c = Case(ti.Problem("pair", "spmm_spmm", C.dtype, A, A, C), flags=tf.TF_FLAG_NO_BASELINE)
+    try:
+        assert np.array_equal(c.run().astype(np.float64), oracle.chain(A, A, C)[0])
+        with pytest.raises(Exception):
+            c.run(False)
+    finally:
+        c.close()
