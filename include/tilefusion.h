@@ -17,8 +17,13 @@
  *     summed in an unspecified order.
  *   - D is overwritten (the listings of Section 3.2 accumulate into zeroed outputs).
  *   - The caller owns A, B, C and D.  The plan owns a device copy of A (pattern and values), the
- *     schedule and a workspace with one slot for every D1 row that crosses tiles (no other D1
- *     row ever reaches device memory: Section 3.1, one synchronisation between two wavefronts).
+ *     schedule and a workspace with one slot for every D1 row that crosses tiles (in the two
+ *     wavefronts no other D1 row ever reaches device memory: Section 3.1, one synchronisation).
+ *   - Where the tiling was left to the library (see tf_tile_params) the fused calls may run the
+ *     chain in another way than the two wavefronts, whichever is expected to be the fastest:
+ *     tf_schedule_view.execution tells which.  D agrees to rounding; rows of A without entries
+ *     give rows of zeros in every case.  With finite operands the ways differ in nothing else;
+ *     D = (A B) C and D = A (B C) may disagree on where infinities and NaN arise.
  *   - Errors are reported by return code; tf_last_error() gives a message for the calling
  *     thread's most recent failure.  No call throws or aborts.
  */
@@ -110,8 +115,16 @@ typedef struct tf_tile_params {
 #define TF_FLAG_SKIP_UNREAD 16u
 /* The plan serves the fused calls only: the packed copy of all rows of A that the unfused
  * baseline runs on is not built (saves its time and device memory); tf_unfused_* then fail with
- * TF_EINVAL. */
+ * TF_EINVAL.  (A plan whose fused calls themselves run the two operations over all rows,
+ * TF_EXECUTE_PLAIN_PAIR, holds that copy all the same; its tf_unfused_* fail likewise.) */
 #define TF_FLAG_NO_BASELINE 32u
+
+/* How the fused calls of a plan run the chain (tf_schedule_view.execution).  All but the first are
+ * chosen only where no tile parameter, column slice, slice count or fast memory is given. */
+#define TF_EXECUTE_WAVEFRONTS 0    /* the schedule: fused tiles, then the leftover rows               */
+#define TF_EXECUTE_ONE_PASS 1      /* dense B, rows near the diagonal: D = (A B) C in one launch      */
+#define TF_EXECUTE_GATHER_FIRST 2  /* dense B, graph, narrow B: Y = A B for all rows, then D = Y C    */
+#define TF_EXECUTE_PLAIN_PAIR 3    /* CSR B, small D1: D1 = B C and D = A D1 over all rows            */
 
 typedef struct tf_plan tf_plan; /* opaque, library-owned */
 
@@ -123,7 +136,8 @@ typedef struct tf_plan tf_plan; /* opaque, library-owned */
  *   second_rows[tile_second_ptr[v] .. tile_second_ptr[v+1])   (the tile's "second" list);
  * unit u of the second wavefront computes the rows wf1_rows[wf1_unit_ptr[u] .. wf1_unit_ptr[u+1]).
  * spill[i] != 0 marks D1 rows that are also stored to device memory because a row of the
- * second wavefront reads them. */
+ * second wavefront reads them.  Every figure is that of the two wavefronts, whatever `execution`
+ * says. */
 typedef struct tf_schedule_view {
     int64_t n;
     int64_t nnz;
@@ -132,7 +146,7 @@ typedef struct tf_schedule_view {
     int32_t n_slices;
     int32_t dtype;
     int32_t b_is_sparse;
-    int32_t reserved0;
+    int32_t execution;          /* TF_EXECUTE_*: what the fused calls of the plan run          */
     int64_t n_coarse_tiles;     /* tiles after step 1                                          */
     int64_t n_tiles;            /* tiles after step 2                                          */
     const int32_t *tile_first_ptr;
@@ -160,7 +174,7 @@ typedef struct tf_schedule_view {
     double eq2_cost_max;        /* largest Eq. 2 data-movement cost over the tiles (elements)  */
     double plan_seconds;        /* host time spent building the schedule (without the packed
                                    copy of A that only the unfused baseline uses)              */
-    int64_t alg_bytes;          /* algorithmic HBM bytes of one fused execution: A, B, C and D once,
+    int64_t alg_bytes;          /* algorithmic HBM bytes of the two wavefronts: A, B, C and D once,
                                    every spilled D1 row written once and read once.  A CSR B is
                                    not known to the plan and is NOT included: the caller adds
                                    4 (n + 1) + nnz(B) (4 + element size)                         */
@@ -211,7 +225,9 @@ tf_status tf_plan_schedule(const tf_plan *plan, tf_schedule_view *out);
 
 /* Fused execution of D = A (B C) with dense B (Section 3.2, fused GeMM-SpMM listing): first
  * wavefront = one launch over the fused tiles, second wavefront = one launch over the leftover
- * rows; stream order is the single barrier between them.  B, C, D are device pointers.
+ * rows; stream order is the single barrier between them.  A plan with another `execution` runs one
+ * launch (TF_EXECUTE_ONE_PASS: no workspace) or two (TF_EXECUTE_GATHER_FIRST: the plan's workspace
+ * holds Y = A B, n x bCol), unless tf_plan_workspace was called.  B, C, D are device pointers.
  * Asynchronous on `hip_stream` (a hipStream_t, NULL = the default stream); allocates nothing,
  * never synchronises.  Two executions of one plan must not overlap (they share the plan's
  * workspace). */
@@ -220,9 +236,10 @@ tf_status tf_gemm_spmm(const tf_plan *plan, const void *B, const void *C, void *
 
 /* tf_gemm_spmm for callers that cannot allocate device memory and do not want a plan-owned
  * workspace to be touched: code under HIP graph capture, tight serving loops, harnesses that
- * forbid hipMalloc.  Same arguments and result as tf_gemm_spmm, but the D1 rows that cross tiles
- * go to a fixed array of 64 MiB that is part of the library's code object (one copy per GPU,
- * held until the process ends) instead of the plan's workspace.  The call allocates nothing.
+ * forbid hipMalloc.  Same arguments and result as tf_gemm_spmm, but what that call keeps in the
+ * plan's workspace (the D1 rows that cross tiles; Y = A B of a TF_EXECUTE_GATHER_FIRST plan; nothing
+ * of a TF_EXECUTE_ONE_PASS plan) goes to a fixed array of 64 MiB that is part of the library's code
+ * object (one copy per GPU, held until the process ends).  The call allocates nothing.
  * A plan whose workspace (tf_schedule_view: d1_slices x d1_rows x d1_slice_cols elements) exceeds
  * 64 MiB is rejected with TF_EUNSUPPORTED.  All calls on one GPU share that GPU's array, whatever
  * the plan: calls that overlap in time on one GPU race (serialise them on one stream).  The array
@@ -232,7 +249,9 @@ tf_status tf_gemm_spmm_static(const tf_plan *plan, const void *B, const void *C,
                               void *hip_stream);
 
 /* Fused execution with CSR B (Section 3.2, fused SpMM-SpMM listing).  B must be on the device,
- * n x bCol with the plan's bCol and dtype; C is bCol x cCol.  B may alias A's arrays.
+ * n x bCol with the plan's bCol and dtype; C is bCol x cCol.  B may alias A's arrays.  A
+ * TF_EXECUTE_PLAIN_PAIR plan runs the two operations over all rows instead, with all of D1 in an array
+ * of its own (12 MB at most), unless tf_plan_workspace was called.
  * B's arrays live on the device and are NOT validated by the execution calls (only its shape
  * and element type are): a well-formed CSR (monotone rowptr with rowptr[0] = 0, 0 <= column <
  * bCol) is the caller's precondition; tf_csr_validate checks it where that is in doubt. */
@@ -252,7 +271,8 @@ tf_status tf_unfused_spmm_spmm(const tf_plan *plan, const tf_csr *B, const void 
 /* One wavefront of the fused execution on its own (wavefront 0 = fused tiles, 1 = leftover
  * rows), for per-kernel timing and tests.  Pass the dense B in B_dense or the CSR B in B_csr
  * according to the plan (the other NULL; both may be NULL for wavefront 1, which reads only the
- * plan's workspace).  Wavefront 1 is only meaningful after wavefront 0 of the same inputs. */
+ * plan's workspace).  Wavefront 1 is only meaningful after wavefront 0 of the same inputs.
+ * Available whatever the plan's `execution` is. */
 tf_status tf_run_wavefront(const tf_plan *plan, int32_t wavefront, const void *B_dense,
                            const tf_csr *B_csr, const void *C, void *D, void *hip_stream);
 
@@ -260,7 +280,10 @@ tf_status tf_run_wavefront(const tf_plan *plan, int32_t wavefront, const void *B
 tf_status tf_plan_prepare_unfused(const tf_plan *plan);
 
 /* Device pointer of the plan's D1 workspace: after a fused execution slot spill_slot[i] holds D1
- * row i, in the layout that tf_schedule_view describes (d1_slices, d1_slice_cols, d1_rows).
+ * row i, in the layout that tf_schedule_view describes (d1_slices, d1_slice_cols, d1_rows).  Only the
+ * two wavefronts leave D1 rows there: on a plan with another `execution`, tf_gemm_spmm[_static] and
+ * tf_spmm_spmm run the two wavefronts from the first call of this function on (executions before it,
+ * and graphs captured before it, leave the workspace untouched or hold Y = A B there).
  * tf_plan_workspace_unfused: the baseline's workspace, same layout with n rows and slot = row
  * (NULL before the first unfused call or tf_plan_prepare_unfused).  For tests. */
 tf_status tf_plan_workspace(const tf_plan *plan, void **d1_device);

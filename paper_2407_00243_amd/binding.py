@@ -18,6 +18,7 @@ TF_FLAG_REORDER = 4
 TF_FLAG_C_TRANSPOSED = 8
 TF_FLAG_SKIP_UNREAD = 16
 TF_FLAG_NO_BASELINE = 32
+TF_EXECUTE_WAVEFRONTS, TF_EXECUTE_ONE_PASS, TF_EXECUTE_GATHER_FIRST, TF_EXECUTE_PLAIN_PAIR = 0, 1, 2, 3
 
 _STATUS = {0: "TF_OK", 1: "TF_EINVAL", 2: "TF_EBADCSR", 3: "TF_ENOMEM", 4: "TF_EHIP",
            5: "TF_EUNSUPPORTED", 6: "TF_EMISMATCH"}
@@ -52,7 +53,7 @@ class tf_schedule_view(ctypes.Structure):
     _fields_ = [("n", ctypes.c_int64), ("nnz", ctypes.c_int64), ("t", ctypes.c_int32),
                 ("col_slice", ctypes.c_int32), ("n_slices", ctypes.c_int32),
                 ("dtype", ctypes.c_int32), ("b_is_sparse", ctypes.c_int32),
-                ("reserved0", ctypes.c_int32),
+                ("execution", ctypes.c_int32),
                 ("n_coarse_tiles", ctypes.c_int64), ("n_tiles", ctypes.c_int64),
                 ("tile_first_ptr", ctypes.POINTER(ctypes.c_int32)),
                 ("first_rows", ctypes.POINTER(ctypes.c_int32)),

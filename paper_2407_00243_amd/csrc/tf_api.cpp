@@ -2,6 +2,7 @@
 // two-launch execution (first wavefront, then second wavefront, in stream order).
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <chrono>
 #include <cstdio>
 #include <cstring>
@@ -91,6 +92,12 @@ struct tf_plan {
     bool schedule_only = false;
     bool c_transposed = false;             // dense-B calls take C as cCol x bCol (D = A (B C^T))
     tf::Schedule s;
+    int32_t execution = TF_EXECUTE_WAVEFRONTS;      // what the fused calls run
+    // set by tf_plan_workspace: its caller reads the D1 rows that only the two wavefronts leave there
+    mutable std::atomic<bool> workspace_read{false};
+    int32_t fused_execution() const {
+        return workspace_read.load(std::memory_order_relaxed) ? TF_EXECUTE_WAVEFRONTS : execution;
+    }
     double plan_seconds = 0.0;
     struct PackBufs {
         void *units = nullptr, *rows = nullptr, *idx = nullptr, *vals = nullptr;
@@ -111,9 +118,8 @@ struct tf_plan {
          *tile_scale = nullptr, *row_info = nullptr, *row_scale = nullptr;
     PackBufs wf1, all, gf;
     void *gf_info = nullptr;
-    bool gather_first = false;             // the fused calls run Y = A B, D = Y C
     void *chain_blocks = nullptr, *chain_rows = nullptr, *chain_idx = nullptr, *chain_vals = nullptr;
-    int32_t n_chain_blocks = 0;            // 0: the fused calls run the two wavefronts, else the chain in one pass
+    int32_t n_chain_blocks = 0;
     bool chain_contiguous = true;
     DevBuf d1;                             // fused path: one slot per spilled D1 row
     DevBuf d1_pair;                        // plain pair of operations: all rows of D1
@@ -553,16 +559,25 @@ tf_status tf_plan_create(const tf_csr *A, int64_t bCol, int64_t cCol, int32_t b_
         p->plan_seconds =
             std::chrono::duration<double>(std::chrono::steady_clock::now() - t_start).count();
 
+        p->lds_per_cu = lds_limit;
+        p->has_baseline = !(tp && (tp->flags & TF_FLAG_NO_BASELINE));
+        tf::Schedule &sc = p->s;
+        tf::GemmLaunch shape{};
+        sc.plain_pair = tf::plain_pair_is_faster(in, sc);
+        tf::build_chain_pack(in, sc, !schedule_only);
+        if (gemm_shape(p, shape)) tf::choose_gather_first(in, sc);
+        p->execution = !sc.chain.blocks.empty() ? TF_EXECUTE_ONE_PASS
+                       : sc.gather_first        ? TF_EXECUTE_GATHER_FIRST
+                       : sc.plain_pair          ? TF_EXECUTE_PLAIN_PAIR
+                                                : TF_EXECUTE_WAVEFRONTS;
         if (schedule_only) {
+            sc.chain = tf::ChainPack();
             guard.p = nullptr;
             *out = p;
             return TF_OK;
         }
-        p->has_baseline = !(tp && (tp->flags & TF_FLAG_NO_BASELINE));
-        p->s.plain_pair = tf::plain_pair_is_faster(in, p->s);
-        if ((p->has_baseline || p->s.plain_pair) && !tf::build_baseline_pack(in, p->s))
+        if ((p->has_baseline || sc.plain_pair) && !tf::build_baseline_pack(in, sc))
             return fail(TF_EUNSUPPORTED, "internal: a unit of the baseline exceeds the staging arrays of the gather kernel");
-        p->lds_per_cu = lds_limit;
         // the launch must fit the device whatever the schedule's own estimate said
         auto launch_lds = [&]() {
             return tf::fused_lds_bytes(p->dtype, p->b_is_sparse, (int)bCol, (int)cCol, p->s.col_slice,
@@ -573,11 +588,8 @@ tf_status tf_plan_create(const tf_csr *A, int64_t bCol, int64_t cCol, int32_t b_
         if (launch_lds() > lds_limit) p->s.second_block_in_lds = false;
         if (launch_lds() > lds_limit)
             return fail(TF_EUNSUPPORTED, "a tile does not fit the LDS of this device");
-        tf::build_chain_pack(in, p->s);
-        tf::GemmLaunch shape{};
-        if (gemm_shape(p, shape) && !tf::build_gather_first(in, p->s, p->has_baseline))
+        if (sc.gather_first && !tf::build_gather_first(in, sc, p->has_baseline))
             return fail(TF_EUNSUPPORTED, "internal: a unit exceeds the staging arrays of the gather kernel");
-        tf::Schedule &sc = p->s;
         Arena arena;
         arena.add(sc.tile_desc, p->tile_desc);
         arena.add(sc.tile_meta.get(), sc.tile_meta_bytes, p->tile_meta);
@@ -591,7 +603,6 @@ tf_status tf_plan_create(const tf_csr *A, int64_t bCol, int64_t cCol, int32_t b_
         add_pack(arena, p->wf1, sc.wf1);
         if (p->has_baseline || sc.plain_pair) add_pack(arena, p->all, sc.all);
         if (sc.gather_first) {
-            p->gather_first = true;
             if (!sc.gather_first_shares) add_pack(arena, p->gf, sc.gf);
             arena.add(sc.gf_info, p->gf_info);
         }
@@ -667,6 +678,7 @@ tf_status tf_plan_schedule(const tf_plan *p, tf_schedule_view *v) {
     v->n_slices = s.n_slices;
     v->dtype = p->dtype;
     v->b_is_sparse = p->b_is_sparse;
+    v->execution = p->execution;
     v->n_coarse_tiles = s.n_coarse_tiles;
     v->n_tiles = (int64_t)s.tile_first_ptr.size() - 1;
     v->tile_first_ptr = s.tile_first_ptr.data();
@@ -723,6 +735,7 @@ tf_status tf_plan_schedule(const tf_plan *p, tf_schedule_view *v) {
 
 tf_status tf_plan_workspace(const tf_plan *p, void **d1_device) {
     if (!p || !d1_device) return fail(TF_EINVAL, "null argument");
+    p->workspace_read.store(true, std::memory_order_relaxed);
     *d1_device = p->d1.p;
     return TF_OK;
 }
@@ -743,8 +756,9 @@ tf_status tf_gemm_spmm(const tf_plan *p, const void *B, const void *C, void *D, 
     tf_status st = check_exec(p, 0, C, D);
     if (st != TF_OK) return st;
     if (!B || !aligned16(B)) return fail(TF_EINVAL, "B must be a 16-byte aligned device pointer");
-    if (p->n_chain_blocks > 0) return run_chain(p, B, C, D, stream);
-    if (p->gather_first) return run_gather_first(p, B, C, D, p->d1.p, stream);
+    const int32_t execution = p->fused_execution();
+    if (execution == TF_EXECUTE_ONE_PASS) return run_chain(p, B, C, D, stream);
+    if (execution == TF_EXECUTE_GATHER_FIRST) return run_gather_first(p, B, C, D, p->d1.p, stream);
     st = first_wavefront_dense(p, B, C, D, p->d1.p, stream);
     if (st != TF_OK) return st;
     return second_wavefront(p, D, p->d1.p, stream);
@@ -759,11 +773,12 @@ tf_status tf_gemm_spmm_static(const tf_plan *p, const void *B, const void *C, vo
         return fail(TF_EUNSUPPORTED, "the plan's D1 workspace (" + std::to_string(need) +
                                          " bytes) exceeds the static workspace of " +
                                          std::to_string(kStaticScratchBytes) + " bytes");
-    if (p->n_chain_blocks > 0) return run_chain(p, B, C, D, stream);
+    const int32_t execution = p->fused_execution();      // (as tf_gemm_spmm: the same sums in the same order)
+    if (execution == TF_EXECUTE_ONE_PASS) return run_chain(p, B, C, D, stream);
     void *ws = nullptr;
     st = static_scratch(&ws);
     if (st != TF_OK) return st;
-    if (p->gather_first) return run_gather_first(p, B, C, D, ws, stream);
+    if (execution == TF_EXECUTE_GATHER_FIRST) return run_gather_first(p, B, C, D, ws, stream);
     // every spilled row is written by the first wavefront before the second one reads it: nothing
     // in the array has to start at zero
     st = first_wavefront_dense(p, B, C, D, ws, stream);
@@ -776,7 +791,7 @@ tf_status tf_spmm_spmm(const tf_plan *p, const tf_csr *B, const void *C, void *D
     if (st != TF_OK) return st;
     st = check_sparse_b(p, B);
     if (st != TF_OK) return st;
-    if (p->s.plain_pair) return run_plain_pair(p, B, C, D, p->d1_pair.p, stream);
+    if (p->fused_execution() == TF_EXECUTE_PLAIN_PAIR) return run_plain_pair(p, B, C, D, p->d1_pair.p, stream);
     st = first_wavefront_sparse(p, B, C, D, p->d1.p, stream);
     if (st != TF_OK) return st;
     return second_wavefront(p, D, p->d1.p, stream);

@@ -977,7 +977,7 @@ static bool chain_is_faster(const InspectorInput &in) {
     return one < two;
 }
 
-void build_chain_pack(const InspectorInput &in, Schedule &s) {
+void build_chain_pack(const InspectorInput &in, Schedule &s, bool entries) {
     s.chain = ChainPack();
     const int64_t n = in.n;
     const int es = elem_size(in.dtype);
@@ -1030,6 +1030,7 @@ void build_chain_pack(const InspectorInput &in, Schedule &s) {
         slot += cb.slots;
         q0 = q1;
     }
+    if (!entries) return;
     const int64_t nb = (int64_t)c.blocks.size();
     const int64_t end = slot + kChainSpareSlots;
     c.idx.resize((size_t)end * 16);
@@ -1067,15 +1068,19 @@ void build_chain_pack(const InspectorInput &in, Schedule &s) {
 // Drawn at a fifth narrower; measured beyond (graphs, us per execution before -> after): fp32 131072
 // rows 64 -> 128 160 -> 104, 382143 rows 32 -> 92 385 -> 157, fp64 142709 rows 64 -> 128 231 -> 220.
 // Y takes the place of D1 in the plan's workspace.
+void choose_gather_first(const InspectorInput &in, Schedule &s) {
+    const int64_t n = in.n, es = elem_size(in.dtype);
+    if (in.b_is_sparse || n == 0 || in.nnz == 0) return;
+    // only where the caller has left the whole choice to the library
+    if (!s.automatic || in.col_slice || in.gather_slices || !in.whole_fast_mem) return;
+    if (!s.chain.blocks.empty() || !s.streaming) return;
+    if (n > (int64_t)kInfoSlotMask || n * in.bcol > s.d1.elements()) return;
+    auto touched = [&](int64_t cols) { return cols * es % 64 ? cols * es + 64 : cols * es; };
+    s.gather_first = 5 * touched(in.bcol) <= 4 * touched(in.ccol);
+}
+
 bool build_gather_first(const InspectorInput &in, Schedule &s, bool have_all) {
     const int64_t n = in.n, es = elem_size(in.dtype);
-    if (in.b_is_sparse || n == 0 || in.nnz == 0) return true;
-    // only where the caller has left the whole choice to the library
-    if (!s.automatic || in.col_slice || in.gather_slices || !in.whole_fast_mem) return true;
-    if (!s.chain.blocks.empty() || !s.streaming) return true;
-    if (n > (int64_t)kInfoSlotMask || n * in.bcol > s.d1.elements()) return true;
-    auto touched = [&](int64_t cols) { return cols * es % 64 ? cols * es + 64 : cols * es; };
-    if (5 * touched(in.bcol) > 4 * touched(in.ccol)) return true;
     const int group = lane_group((int)in.bcol, lane_elems(in.dtype, in.bcol, in.bcol));
     const int group_all = lane_group(s.d1.sw, lane_elems(in.dtype, in.ccol, s.d1.sw));
     s.gather_first_shares = have_all && group == group_all;
@@ -1091,7 +1096,6 @@ bool build_gather_first(const InspectorInput &in, Schedule &s, bool have_all) {
     s.gf_info.resize((size_t)n);
     for (int64_t j = 0; j < n; ++j)
         s.gf_info[(size_t)j] = in.rowptr[j + 1] > in.rowptr[j] ? kInfoSpill | (uint32_t)j : kInfoZero;
-    s.gather_first = true;
     return true;
 }
 

@@ -352,7 +352,7 @@ struct Schedule {
     RowPack all;                   // all rows re-packed (unfused baseline)
     bool plain_pair = false;       // CSR B: the fused calls run the two operations over all rows, see plain_pair_is_faster
     ChainPack chain;               // all rows re-packed for the one-pass chain; no blocks: not used
-    // The chain as Y = A B, D = Y C (see build_gather_first).
+    // The chain as Y = A B, D = Y C (see choose_gather_first).
     bool gather_first = false;
     bool gather_first_shares = false;      // Y is gathered with `all`, else with `gf`
     RowPack gf;
@@ -386,11 +386,14 @@ tf_status build_schedule(const InspectorInput &in, Schedule &out, std::string &e
 // (Schedule::all).  Not part of the fused schedule and not counted in its time.
 // (false: a unit exceeds the gather kernel's staging arrays; never expected)
 bool build_baseline_pack(const InspectorInput &in, Schedule &s);
-// Decides whether the fused calls of the plan run the chain in one pass, and packs A for it.
-void build_chain_pack(const InspectorInput &in, Schedule &s);
+// Decides whether the fused calls of the plan run the chain in one pass, and packs A for it (entries =
+// false: the blocks only).
+void build_chain_pack(const InspectorInput &in, Schedule &s, bool entries);
 // Whether the fused calls of a CSR-B plan run the plain pair of operations.
 bool plain_pair_is_faster(const InspectorInput &in, const Schedule &s);
-// Decides whether they run it as Y = A B, D = Y C, and packs A for that (have_all: `all` is packed).
+// Decides whether they run it as Y = A B, D = Y C (Schedule::gather_first).
+void choose_gather_first(const InspectorInput &in, Schedule &s);
+// Packs A for that (have_all: `all` is packed).
 bool build_gather_first(const InspectorInput &in, Schedule &s, bool have_all);
 
 

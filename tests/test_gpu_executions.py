@@ -1,0 +1,54 @@
+"""The ways in which the fused calls run the chain where the library chooses (tf_schedule_view.execution)."""
+import numpy as np
+import pytest
+
+import oracle
+import tf_inputs as ti
+
+pytestmark = pytest.mark.gpu
+
+
+def far_csr(n, dtype, seed):
+    """Rows of 0 to 8 entries anywhere in the matrix, a few long enough to be split over lane groups."""
+    rng = np.random.default_rng(seed)
+    lens = rng.integers(0, 9, n)
+    lens[rng.integers(0, n, 20)] = rng.integers(100, 2000, 20)
+    rowptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    colidx = rng.integers(0, n, rowptr[-1]).astype(np.int32)
+    return ti.Csr(n, n, rowptr, colidx, rng.integers(-2, 3, colidx.size).astype(dtype))
+
+
+def _problem(execution, dtype):
+    import paper_2407_00243_amd as tf
+    local = lambda n: ti.random_local_csr(n, 9, 6, 0.0, dtype, 21, int_values=True, empty_row_prob=0.1)
+    if execution == tf.TF_EXECUTE_PLAIN_PAIR:
+        A = local(3000)
+        return ti.Problem("pair", "spmm_spmm", np.dtype(dtype), A, A, ti.dense_small_int(3000, 20, dtype, 6))
+    A, bcol, ccol = (local(3000), 24, 40) if execution == tf.TF_EXECUTE_ONE_PASS else (far_csr(40000, dtype, 4), 32, 92)
+    return ti.Problem("chain", "gemm_spmm", np.dtype(dtype), A, ti.dense_small_int(A.n_rows, bcol, dtype, 5),
+                      ti.dense_small_int(bcol, ccol, dtype, 6))
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("execution", [1, 2, 3])
+def test_workspace_holds_the_d1_rows_for_whoever_asked_for_it(execution, dtype):
+    """After tf_plan_workspace a fused execution leaves D1 row i in slot spill_slot[i], whatever way the
+    library had chosen for the plan; small-integer entries, so D and D1 must be exact."""
+    from gpu_util import Case, read_workspace
+    prob = _problem(execution, dtype)
+    D_ref, _ = oracle.chain(prob.A, prob.B, prob.C)
+    eye = ti.Csr(prob.n, prob.n, np.arange(prob.n + 1, dtype=np.int32), np.arange(prob.n, dtype=np.int32),
+                 np.ones(prob.n, dtype))
+    D1_ref, _ = oracle.chain(eye, prob.B, prob.C)
+    c = Case(prob)
+    try:
+        s = c.plan.schedule()
+        assert s["execution"] == execution
+        assert np.array_equal(c.run().astype(np.float64), D_ref)
+        c.plan.workspace()
+        assert np.array_equal(c.run().astype(np.float64), D_ref)
+        ws = read_workspace(c.plan, s, c.ccol, dtype).astype(np.float64)
+        rows = np.flatnonzero(s["spill_slot"] >= 0)
+        assert rows.size and np.array_equal(ws[s["spill_slot"][rows]], D1_ref[rows])
+    finally:
+        c.close()

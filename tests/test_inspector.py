@@ -369,3 +369,18 @@ def test_csr_validate_checks_a_matrix_on_request():
     ci[5] = -1
     assert bad(B._replace(colidx=ci)) == "TF_EBADCSR"
     assert bad(B._replace(rowptr=B.rowptr[:-1].copy(), n_rows=49)) == "TF_EBADCSR"   # rowptr[n] != nnz
+
+
+def test_execution_that_the_fused_calls_run():
+    """tf_schedule_view.execution: chosen only where the whole choice is left to the library."""
+    A = ti.random_local_csr(3000, 9, 6, 0.0, np.float32, 21, empty_row_prob=0.1)
+    G = ti.random_pattern_csr(40000, 40000, 2e-4, np.float32, 3)
+    assert plan_schedule(A, 24, 40, False)["execution"] == tf.TF_EXECUTE_ONE_PASS
+    assert plan_schedule(G, 32, 92, False)["execution"] == tf.TF_EXECUTE_GATHER_FIRST
+    assert plan_schedule(G, 92, 92, False)["execution"] == tf.TF_EXECUTE_WAVEFRONTS
+    assert plan_schedule(A, 3000, 20, True)["execution"] == tf.TF_EXECUTE_PLAIN_PAIR
+    for given in (dict(ct_size=64), dict(p=4), dict(col_slice=16), dict(gather_slices=1),
+                  dict(fast_mem_bytes=64 * 1024), dict(flags=tf.TF_FLAG_REORDER)):
+        assert plan_schedule(A, 24, 40, False, **given)["execution"] == tf.TF_EXECUTE_WAVEFRONTS
+        assert plan_schedule(A, 3000, 20, True, **given)["execution"] == tf.TF_EXECUTE_WAVEFRONTS
+    assert plan_schedule(A, 3000, 20, True, flags=tf.TF_FLAG_SKIP_UNREAD)["execution"] == tf.TF_EXECUTE_WAVEFRONTS
