@@ -120,6 +120,7 @@ struct tf_plan {
     void *gf_info = nullptr;
     void *chain_blocks = nullptr, *chain_rows = nullptr, *chain_idx = nullptr, *chain_vals = nullptr;
     int32_t n_chain_blocks = 0;
+    size_t chain_zeros = 0;                // bytes into chain_vals
     bool chain_contiguous = true;
     DevBuf d1;                             // fused path: one slot per spilled D1 row
     DevBuf d1_pair;                        // plain pair of operations: all rows of D1
@@ -399,6 +400,7 @@ tf_status run_chain(const tf_plan *p, const void *B, const void *C, void *D, voi
     a.rows = static_cast<const int32_t *>(p->chain_rows);
     a.idx = static_cast<const int32_t *>(p->chain_idx);
     a.vals = p->chain_vals;
+    a.zeros = static_cast<const char *>(p->chain_vals) + p->chain_zeros;
     a.B = B;
     a.C = C;
     a.c_transposed = p->c_transposed ? 1 : 0;
@@ -613,6 +615,7 @@ tf_status tf_plan_create(const tf_csr *A, int64_t bCol, int64_t cCol, int32_t b_
             arena.add(sc.chain.rows, p->chain_rows);
             arena.add(sc.chain.idx, p->chain_idx);
             arena.add(sc.chain.vals, p->chain_vals);
+            p->chain_zeros = sc.chain.vals.size() - tf::kChainZeroRows * tf::kChainRowBytes;
         }
         hipError_t e = arena.upload(p->arrays);
         if (e == hipSuccess) e = p->d1.alloc((size_t)sc.d1.elements() * es);

@@ -108,6 +108,8 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS)) void
     constexpr int K0 = chain_ksteps_below(dtype_of<T>(), KS);      // pieces that are whole for certain
     typedef typename Piece16<T>::Vec Vec;
     typedef T Vec16 __attribute__((ext_vector_type(V)));
+    typedef const __attribute__((address_space(1))) char *GlobalBytes;
+    typedef const __attribute__((address_space(1))) Vec *GlobalVec;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nwaves = (int)blockDim.x >> 6;
     const int g = lane >> 4, r = lane & 15;              // as the matrix cores see the lane
@@ -122,14 +124,14 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS)) void
     // behind C, per wave: the place where pieces change lanes -- sums into operands (TS x 16 rows x 64
     // bytes; the pieces of a row are swizzled so that the sixteen rows' pieces g sit in different
     // banks), results into rows of D (16 rows of CB blocks and 16 bytes) -- then the offsets of the
-    // rows of D and the entries of a pass (NE x 64 values, then column indices)
+    // rows of D and the entries of a pass (NE x 64 values, then addresses of rows of B)
     constexpr int NE = chain_entry_loads(KS), TS = chain_exchange(KS), CB = chain_store_blocks(dtype_of<T>(), KS, NBC);
     constexpr int W = CB * 16 / V, PITCH = W * 16 + 16;
     unsigned char *ex = tf_smem + a.groups_per_wg * (NBC * KS * V * 64 * (int)sizeof(T)) +
                         wave * (int)chain_wave_lds(dtype_of<T>(), KS, NBC);
     uint32_t *er = reinterpret_cast<uint32_t *>(ex + chain_exchange_bytes(dtype_of<T>(), KS, NBC));
     T *ev = reinterpret_cast<T *>(er + 16);
-    int32_t *ei = reinterpret_cast<int32_t *>(ev + NE * 64);
+    uint64_t *ea = reinterpret_cast<uint64_t *>(ev + NE * 64);
     const unsigned char *ex_r = ex + r * 64 + (g ^ (r >> 2)) * 16;
 
     // blocks of this wave: near the diagonal every XCD has a contiguous range, through which its
@@ -149,7 +151,15 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS)) void
     }
 
     // The entries of a pass: fetched a pass ahead, 64 (four slots of sixteen rows) per load, put into
-    // LDS when their turn comes, read back by the lanes of their row
+    // LDS when their turn comes, read back by the lanes of their row.  A column becomes the address of its
+    // row of B on the way (once per entry, not once per lane and gather), padding that of zeros: whatever B
+    // holds, padding adds nothing.  The waves of an XCD use different copies of the zeros, and have theirs
+    // in the L1 before the first gather needs it (band of 4096 rows, fp64 32 -> 32: 6.24 us with one copy, 6.15
+    // with sixteen, 5.90 with sixteen fetched ahead; 5.98 when padding read the row's last column again).
+    const uint32_t row_bytes = (uint32_t)a.bcol * (uint32_t)sizeof(T);
+    const uint64_t zeros = reinterpret_cast<uint64_t>(a.zeros) +
+                           (blockIdx.x / kXcds * nwaves + wave) % kChainZeroRows * kChainRowBytes;
+    const float zeros_ahead = *(const __attribute__((address_space(1))) float *)(zeros + min((uint32_t)lane * 16, row_bytes - 4));
     int32_t ci[NE];
     T vi[NE];
     auto fetch = [&](uint32_t slot) __attribute__((always_inline)) {
@@ -161,7 +171,13 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS)) void
     };
     auto put = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int e = 0; e < NE; ++e) ei[e * 64 + lane] = ci[e];
+        for (int e = 0; e < NE; ++e) {
+            const uint64_t at = reinterpret_cast<uint64_t>(B) + (uint64_t)(uint32_t)ci[e] * row_bytes;
+            // (all ones for padding; kept from the compiler, which would make a branch of the choice)
+            int32_t pad = ci[e] >> 31;
+            asm("" : "+v"(pad));
+            ea[e * 64 + lane] = at ^ ((at ^ zeros) & (uint64_t)(int64_t)pad);
+        }
 #pragma unroll
         for (int e = 0; e < NE; ++e) ev[e * 64 + lane] = vi[e];
         __builtin_amdgcn_wave_barrier();
@@ -178,10 +194,8 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS)) void
         fetch(d.slot_base);
         dn = blocks[min(blk + step, end - 1)];
     }
-    // the lane's bytes inside a row of B; pieces that may reach past bCol are moved back so that
-    // they end with the row, and put right after the sums are complete
-    B += pp * 16;
-    const uint32_t row_bytes = (uint32_t)a.bcol * (uint32_t)sizeof(T);
+    // pieces of a row of B that may reach past bCol are moved back so that they end with the row, and put
+    // right after the sums are complete
     constexpr int T0 = K0 / RS;                          // pieces t below are whole
     int back[KP - T0];                                   // bytes
 #pragma unroll
@@ -201,11 +215,10 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS)) void
             if (e < n) {
 #pragma unroll
                 for (int h = 0; h < RS; ++h) {
-                    const uint32_t c = (uint32_t)ei[e * 16 + rr + h * (64 / LR)];
-                    const char *p = B + (uint64_t)c * row_bytes;
+                    const GlobalBytes p = (GlobalBytes)(ea[e * 16 + rr + h * (64 / LR)] + pp * 16);
 #pragma unroll
                     for (int t = 0; t < KP; ++t)
-                        x[e][h][t] = *reinterpret_cast<const Vec *>(
+                        x[e][h][t] = *(GlobalVec)(
                             t < T0 ? p + 16 * LR * t : p + (16 * LR * t - back[t < T0 ? 0 : t - T0]));
                 }
             }
@@ -257,6 +270,7 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS)) void
         __syncthreads();
         if (blk >= end) return;
         __builtin_amdgcn_s_waitcnt(0);
+        asm volatile("" : : "v"(zeros_ahead));
     }
 
     for (;;) {

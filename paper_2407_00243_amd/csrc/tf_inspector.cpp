@@ -1034,9 +1034,9 @@ void build_chain_pack(const InspectorInput &in, Schedule &s, bool entries) {
     const int64_t nb = (int64_t)c.blocks.size();
     const int64_t end = slot + kChainSpareSlots;
     c.idx.resize((size_t)end * 16);
-    c.vals.resize((size_t)end * 16 * es);
+    c.vals.resize((size_t)end * 16 * es + kChainZeroRows * kChainRowBytes);
     std::memset(c.idx.data() + slot * 16, 0, (size_t)kChainSpareSlots * 16 * 4);
-    std::memset(c.vals.data() + (size_t)slot * 16 * es, 0, (size_t)kChainSpareSlots * 16 * es);
+    std::memset(c.vals.data() + (size_t)slot * 16 * es, 0, (size_t)kChainSpareSlots * 16 * es + kChainZeroRows * kChainRowBytes);
     auto fill = [&](auto tag) {
         typedef decltype(tag) T;
         const T *vals = static_cast<const T *>(in.vals);
@@ -1051,7 +1051,7 @@ void build_chain_pack(const InspectorInput &in, Schedule &s, bool entries) {
                 const int64_t p0 = (int64_t)(v & (parts - 1)) * cb.slots;
                 for (int64_t sl = 0; sl < cb.slots; ++sl) {
                     const int64_t at = ((int64_t)cb.slot_base + sl) * 16 + v, k = p0 + sl;
-                    c.idx[(size_t)at] = in.colidx[k0 + std::min(k, ln - 1)];
+                    c.idx[(size_t)at] = k < ln ? in.colidx[k0 + k] : kChainPad;
                     out[at] = k < ln ? vals[k0 + k] : T(0);
                 }
             }

@@ -237,8 +237,8 @@ struct RowPack {
 
 // ---- the chain in one pass, D = (A B) C (dense B) -----------------------------------------------
 // A is re-packed into blocks of sixteen virtual rows: a row, or one of the 2^k equal parts that the
-// rows of the block are cut into.  All virtual rows of a block have `slots` entries (padding repeats
-// a column of the row with value 0), stored slot after slot, sixteen entries each.
+// rows of the block are cut into.  All virtual rows of a block have `slots` entries (padding: column
+// kChainPad, value 0), stored slot after slot, sixteen entries each.
 struct ChainBlock {
     uint32_t slot_base;    // first slot of the block: its entries start at 16 slot_base
     int32_t slots;         // 0: the block's rows are empty
@@ -256,7 +256,10 @@ struct ChainPack {
 constexpr int kChainThreads = 512;       // largest workgroup of the kernel
 constexpr int kChainMaxEntries = 8;      // most entries per row in flight
 constexpr int kChainLongRow = 1024;      // longest row a block takes
+constexpr int32_t kChainPad = -1;        // the column of a padding entry: zeros are read in the place of a row of B
 constexpr int kChainSpareSlots = 2 * kChainMaxEntries;   // zero slots behind the last block (entries are fetched ahead)
+constexpr int kChainZeroRows = 16;       // copies of a row of zeros, which padding reads, behind the values
+constexpr int kChainRowBytes = 1024;     // longest row of B
 // 16-byte pieces of a row of B per lane: ceil(bCol / (4 V)) rounded up to a depth the kernel is
 // instantiated for; 0 = none.
 constexpr int kChainDepths32[] = {1, 2, 3, 4, 6, 8}, kChainDepths64[] = {2, 4, 6, 8, 12, 16};
@@ -269,6 +272,8 @@ inline int chain_ksteps(int dtype, int64_t bcol) {
     }
     return 0;
 }
+static_assert(4 * 16 * kChainDepths32[5] <= kChainRowBytes && 4 * 16 * kChainDepths64[5] <= kChainRowBytes,
+              "a copy of the zeros is as long as the longest row of B");
 // The depth below `ks`: pieces up to there are whole in every row that takes depth ks.
 constexpr int chain_ksteps_below(int dtype, int ks) {
     int below = 0;
@@ -303,7 +308,7 @@ constexpr int chain_exchange_bytes(int dtype, int ks, int nbc) {
     return in > out ? in : out;
 }
 constexpr int64_t chain_wave_lds(int dtype, int ks, int nbc) {
-    return chain_exchange_bytes(dtype, ks, nbc) + 64 + chain_entry_loads(ks) * 64 * (4 + (dtype == TF_F64 ? 8 : 4));
+    return chain_exchange_bytes(dtype, ks, nbc) + 64 + chain_entry_loads(ks) * 64 * (8 + (dtype == TF_F64 ? 8 : 4));
 }
 // LDS of the largest workgroup: C and the waves' own.
 inline int64_t chain_lds_bytes(int dtype, int64_t bcol, int64_t ccol) {
@@ -499,6 +504,7 @@ struct ChainLaunch {
     const int32_t *rows;
     const int32_t *idx;
     const void *vals;
+    const void *zeros;                // kChainZeroRows x kChainRowBytes
     const void *B, *C;
     int32_t c_transposed;             // C is cCol x bCol
     void *D;

@@ -52,3 +52,31 @@ def test_workspace_holds_the_d1_rows_for_whoever_asked_for_it(execution, dtype):
         assert rows.size and np.array_equal(ws[s["spill_slot"][rows]], D1_ref[rows])
     finally:
         c.close()
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("bcol", [4, 30, 64, 127])
+@pytest.mark.parametrize("n,even", [(150, True), (5000, True), (20000, False)])
+def test_padding_of_the_one_pass_chain_adds_nothing(dtype, bcol, n, even):
+    """Rows cut into parts of unequal length (few rows) and blocks of unequal rows are padded: where B holds
+    infinities, a row of D is infinite if its row of A reads one of them, and its finite sum if not."""
+    import paper_2407_00243_amd as tf
+    from gpu_util import Case
+    rng = np.random.default_rng(8)
+    lens = np.full(n, 7) if even else rng.integers(1, 14, n)
+    rowptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    rows = np.repeat(np.arange(n), lens)
+    colidx = np.minimum(np.maximum(rows - 6, 0) + (np.arange(rows.size) - rowptr[rows]), n - 1).astype(np.int32)
+    A = ti.Csr(n, n, rowptr, colidx, rng.integers(1, 4, rows.size).astype(dtype))
+    B, C = rng.integers(1, 4, (n, bcol)).astype(dtype), rng.integers(1, 4, (bcol, 20)).astype(dtype)
+    hit = rng.random(n) < 0.05
+    D_ref, _ = oracle.chain(A, np.where(hit[:, None], dtype(0), B), C)
+    D_ref[np.unique(rows[hit[colidx]])] = np.inf
+    B[hit] = np.inf
+    c = Case(ti.Problem("chain", "gemm_spmm", np.dtype(dtype), A, B, C))
+    try:
+        assert c.plan.schedule()["execution"] == tf.TF_EXECUTE_ONE_PASS
+        assert np.isinf(D_ref).any() and np.isfinite(D_ref).any()
+        assert np.array_equal(c.run().astype(np.float64), D_ref)
+    finally:
+        c.close()
