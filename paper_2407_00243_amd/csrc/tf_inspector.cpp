@@ -964,17 +964,44 @@ tf_status build_schedule(const InspectorInput &in, Schedule &s, std::string &err
     return TF_OK;
 }
 
-// Estimated microseconds of the fused calls on a matrix whose rows stay near the diagonal, in one pass
-// and in two wavefronts.  The rates (bytes per microsecond) are fits to measured executions: the
-// one-pass kernel gathers rows of B out of the L2 at 18 TB/s and streams at 5 TB/s, the tiled kernels
-// move B and D at 3.2 TB/s; unaligned widths take the tiled kernels three times as long (scalar lanes).
-static bool chain_is_faster(const InspectorInput &in) {
+// Estimated microseconds of the fused calls on a matrix whose rows stay near the diagonal, in two
+// wavefronts and in one pass.  The rates (bytes per microsecond) are fits to measured executions: the
+// tiled kernels move B and D at 3.2 TB/s; unaligned widths take them three times as long (scalar lanes).
+static double two_wavefronts_us(const InspectorInput &in) {
     const double es = elem_size(in.dtype), n = (double)in.n, nnz = (double)in.nnz;
     const int v = vec_elems(in.dtype);
-    const double one = 5.0 + nnz * in.bcol * es / 18e6 + n * (in.bcol + in.ccol) * es / 5e6;
     const double aligned = in.bcol % v || in.ccol % v ? 3.0 : 1.0;
-    const double two = 15.0 + aligned * (n * (in.bcol + 2.0 * in.ccol) * es / 3.2e6 + nnz * in.ccol * es / 25e6);
-    return one < two;
+    return 15.0 + aligned * (n * (in.bcol + 2.0 * in.ccol) * es / 3.2e6 + nnz * in.ccol * es / 25e6);
+}
+// The one-pass kernel gathers rows of B out of the L2 at 18 TB/s and streams at 5 TB/s.  `entries`: with
+// padding, where that is known.
+static double one_pass_us(const InspectorInput &in, double entries) {
+    const double es = elem_size(in.dtype), n = (double)in.n;
+    return 5.0 + entries * in.bcol * es / 18e6 + n * (in.bcol + in.ccol) * es / 5e6;
+}
+// Matrix instructions of one block of the kernel, back to back.
+static double block_mfma_us(const InspectorInput &in, int ks) {
+    return ks * vec_elems(in.dtype) * ((in.ccol + 15) / 16) * (in.dtype == TF_F64 ? 64 : 32) / 2400.0;
+}
+// What rows of unequal length add to it: the multiplications of blocks that hold fewer than sixteen rows,
+// and what the wave with the most passes of gathers takes longer than the mean one.  A pass waits for its
+// gathers, 0.8 us (band of 20011 rows, eight of them of 400 and of 1024 entries, uncut: fp32 32 columns 48 and
+// 116 us, 64 columns 66 and 165, fp64 128 columns 135 and 374: 0.87, 0.79 and 0.77 us a pass).  Blocks are
+// dealt to the waves of an XCD as k_gather_gemm takes them.
+static double one_pass_tail_us(const InspectorInput &in, const ChainPack &c, int ks) {
+    const int em = chain_entries(ks);
+    const int64_t nb = (int64_t)c.blocks.size(), per = (nb + kXcds - 1) / kXcds;
+    const int64_t waves = std::max<int64_t>(1, std::min(per, (int64_t)in.n_cu / kXcds * 4 * chain_waves(in.dtype, ks)));
+    std::vector<int32_t> passes((size_t)(kXcds * waves), 0);
+    int64_t sum = 0, longest = 0;
+    for (int64_t b = 0; b < nb; ++b) {
+        int32_t &w = passes[(size_t)(b / per * waves + b % per % waves)];
+        const int32_t p = (c.blocks[(size_t)b].slots + em - 1) / em;
+        sum += p;
+        longest = std::max<int64_t>(longest, w += p);
+    }
+    return 0.8 * ((double)longest - (double)sum / (double)(kXcds * waves)) +
+           std::max(0.0, (double)nb - (double)in.n / 16) / (4.0 * in.n_cu) * block_mfma_us(in, ks);
 }
 
 void build_chain_pack(const InspectorInput &in, Schedule &s, bool entries) {
@@ -988,15 +1015,19 @@ void build_chain_pack(const InspectorInput &in, Schedule &s, bool entries) {
     if (ks == 0 || chain_lds_bytes(in.dtype, in.bcol, in.ccol) > in.fast_mem_bytes) return;
     // (the kernel stores D through 32-bit byte offsets, in whole 16-byte pieces)
     if (in.ccol < vec_elems(in.dtype) || n * in.ccol * es >= ((int64_t)1 << 32) - 64) return;
-    if (s.far_rows || !chain_is_faster(in)) return;
+    const double two = two_wavefronts_us(in);
+    if (s.far_rows || one_pass_us(in, (double)in.nnz) >= two) return;
     auto len = [&](int64_t j) { return (int64_t)in.rowptr[j + 1] - in.rowptr[j]; };
     int64_t longest = 0;
     for (int64_t j = 0; j < n; ++j) longest = std::max(longest, len(j));
     if (longest > kChainLongRow) return;
     // few blocks: rows are cut into parts so that there are about two waves per compute unit
     int slog = 0;
-    while (slog < 4 && ((n << slog) + 15) / 16 < 2 * (int64_t)in.n_cu && (in.nnz / n >> slog) >= 6) ++slog;
+    while (slog < kChainMaxCut && ((n << slog) + 15) / 16 < 2 * (int64_t)in.n_cu && (in.nnz / n >> slog) >= 6) ++slog;
     const int64_t per_block = 16 >> slog;
+    // A block far longer than the others holds one wave up while the rest of the machine is done: its
+    // rows are cut further, until it has at most twice as many slots as a pass or a row of mean length.
+    const int64_t most_slots = 2 * std::max<int64_t>(chain_entries(ks), in.nnz / n >> slog);
     ChainPack &c = s.chain;
     // rows in their own order while that pads little, else sorted by length inside windows
     int64_t padded = 0;
@@ -1016,22 +1047,32 @@ void build_chain_pack(const InspectorInput &in, Schedule &s, bool entries) {
     c.blocks.reserve((size_t)(n / per_block) + 16);
     int64_t slot = 0;
     for (int64_t q0 = 0; q0 < n;) {
-        // (empty rows share no block with others: nothing of B may be read for them)
-        int64_t mx = len(c.rows[(size_t)q0]), q1 = q0 + 1;
-        while (q1 < n && q1 < q0 + per_block && (len(c.rows[(size_t)q1]) == 0) == (mx == 0))
-            mx = std::max(mx, len(c.rows[(size_t)q1++]));
         ChainBlock cb{};
+        int64_t q1;
+        int cut = slog;
+        for (;; ++cut) {
+            // (empty rows share no block with others: nothing of B may be read for them)
+            int64_t mx = len(c.rows[(size_t)q0]);
+            q1 = q0 + 1;
+            while (q1 < n && q1 < q0 + (16 >> cut) && (len(c.rows[(size_t)q1]) == 0) == (mx == 0))
+                mx = std::max(mx, len(c.rows[(size_t)q1++]));
+            cb.slots = (int32_t)((mx + (1 << cut) - 1) >> cut);
+            if (cb.slots <= most_slots || cut == kChainMaxCut) break;
+        }
         cb.slot_base = (uint32_t)slot;
-        cb.slots = (int32_t)((mx + (1 << slog) - 1) >> slog);
         cb.row_begin = (int32_t)q0;
         const int em = chain_entries(ks), passes = (cb.slots + em - 1) / em;
-        cb.info = slog | (passes ? (cb.slots + passes - 1) / passes : 0) << 3 | (int32_t)((q1 - q0) << 7);
+        cb.info = cut | (passes ? (cb.slots + passes - 1) / passes : 0) << 3 | (int32_t)((q1 - q0) << 7);
         c.blocks.push_back(cb);
         slot += cb.slots;
         q0 = q1;
     }
-    if (!entries) return;
     const int64_t nb = (int64_t)c.blocks.size();
+    if (one_pass_us(in, 16.0 * (double)slot) + one_pass_tail_us(in, c, ks) >= two) {
+        c = ChainPack();
+        return;
+    }
+    if (!entries) return;
     const int64_t end = slot + kChainSpareSlots;
     c.idx.resize((size_t)end * 16);
     c.vals.resize((size_t)end * 16 * es + kChainZeroRows * kChainRowBytes);

@@ -256,6 +256,7 @@ struct ChainPack {
 constexpr int kChainThreads = 512;       // largest workgroup of the kernel
 constexpr int kChainMaxEntries = 8;      // most entries per row in flight
 constexpr int kChainLongRow = 1024;      // longest row a block takes
+constexpr int kChainMaxCut = 4;          // log2 of the most parts that a row is cut into
 constexpr int32_t kChainPad = -1;        // the column of a padding entry: zeros are read in the place of a row of B
 constexpr int kChainSpareSlots = 2 * kChainMaxEntries;   // zero slots behind the last block (entries are fetched ahead)
 constexpr int kChainZeroRows = 16;       // copies of a row of zeros, which padding reads, behind the values

@@ -80,3 +80,38 @@ def test_padding_of_the_one_pass_chain_adds_nothing(dtype, bcol, n, even):
         assert np.array_equal(c.run().astype(np.float64), D_ref)
     finally:
         c.close()
+
+
+def _rows_of(lens, dtype, rng):
+    """Rows of the given lengths whose columns lie around the diagonal, in no order, some twice."""
+    n = lens.size
+    rowptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    rows = np.repeat(np.arange(n), lens)
+    reach = np.repeat(np.maximum(lens, 8), lens)
+    colidx = np.clip(rows + rng.integers(-reach, reach + 1), 0, n - 1).astype(np.int32)
+    return ti.Csr(n, n, rowptr, colidx, rng.integers(-2, 3, rows.size).astype(dtype))
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("bcol,ccol", [(8, 8), (50, 23), (64, 64), (128, 128)])
+@pytest.mark.parametrize("kind", ["few", "many"])
+def test_long_rows_among_short_ones_are_cut(dtype, bcol, ccol, kind):
+    """Blocks of the one-pass chain that hold a row far longer than the others: rows of just below and above
+    every number of parts, next to each other, first and last, up to the longest row that a block takes."""
+    import paper_2407_00243_amd as tf
+    from gpu_util import Case
+    rng = np.random.default_rng(9)
+    if kind == "few":
+        lens = np.full(60011, 5)
+        lens[[0, 17, 18, 40, 41, 42, 43, 5000, 5016, 9999, 60009, 60010]] = [
+            33, 200, 1024, 16, 17, 31, 32, 0, 513, 80, 129, 640]
+    else:
+        lens = np.minimum(np.exp(rng.normal(1.3, 1.2, 50000)).astype(np.int64), 1024)
+    A = _rows_of(lens, dtype, rng)
+    B, C = ti.dense_small_int(A.n_rows, bcol, dtype, 5), ti.dense_small_int(bcol, ccol, dtype, 6)
+    c = Case(ti.Problem("chain", "gemm_spmm", np.dtype(dtype), A, B, C))
+    try:
+        assert c.plan.schedule()["execution"] == tf.TF_EXECUTE_ONE_PASS
+        assert np.array_equal(c.run().astype(np.float64), oracle.chain(A, B, C)[0])
+    finally:
+        c.close()

@@ -384,3 +384,20 @@ def test_execution_that_the_fused_calls_run():
         assert plan_schedule(A, 24, 40, False, **given)["execution"] == tf.TF_EXECUTE_WAVEFRONTS
         assert plan_schedule(A, 3000, 20, True, **given)["execution"] == tf.TF_EXECUTE_WAVEFRONTS
     assert plan_schedule(A, 3000, 20, True, flags=tf.TF_FLAG_SKIP_UNREAD)["execution"] == tf.TF_EXECUTE_WAVEFRONTS
+
+
+@pytest.mark.parametrize("longest,execution", [(17, tf.TF_EXECUTE_ONE_PASS), (300, tf.TF_EXECUTE_ONE_PASS),
+                                               (1024, tf.TF_EXECUTE_WAVEFRONTS), (1025, tf.TF_EXECUTE_WAVEFRONTS)])
+def test_rows_that_would_hold_one_wave_up_decide_the_execution(longest, execution):
+    """The one-pass chain cuts a row into sixteen parts at most: where the wave that gets a long row would
+    still run on alone for longer than the chain gains (fp64 128 -> 128: two entries a pass), the two
+    wavefronts, which split the row over lane groups, stay."""
+    n, h = 20011, 5
+    lens = np.full(n, 2 * h + 1)
+    lens[[3000, 9000]] = longest
+    rows = np.repeat(np.arange(n), lens)
+    rowptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    first = np.clip(np.arange(n) - lens // 2, 0, n - lens)
+    colidx = (first[rows] + np.arange(rows.size) - rowptr[rows]).astype(np.int32)
+    A = ti.Csr(n, n, rowptr, colidx, np.ones(rows.size))
+    assert plan_schedule(A, 128, 128, False)["execution"] == execution
