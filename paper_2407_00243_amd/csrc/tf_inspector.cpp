@@ -965,23 +965,33 @@ tf_status build_schedule(const InspectorInput &in, Schedule &s, std::string &err
 }
 
 // Estimated microseconds of the fused calls on a matrix whose rows stay near the diagonal, in two
-// wavefronts and in one pass.  The rates (bytes per microsecond) are fits to measured executions: the
-// tiled kernels move B and D at 3.2 TB/s; unaligned widths take them three times as long (scalar lanes).
+// wavefronts and in one pass.  The rates (bytes per microsecond) are fits to measured executions.
+// Tiles in LDS: the kernels move B and D at 3.2 TB/s; unaligned widths take them three times as long (scalar
+// lanes).
 static double two_wavefronts_us(const InspectorInput &in) {
     const double es = elem_size(in.dtype), n = (double)in.n, nnz = (double)in.nnz;
     const int v = vec_elems(in.dtype);
     const double aligned = in.bcol % v || in.ccol % v ? 3.0 : 1.0;
     return 15.0 + aligned * (n * (in.bcol + 2.0 * in.ccol) * es / 3.2e6 + nnz * in.ccol * es / 25e6);
 }
+// Matrix instructions of one block of the kernel, back to back.
+static double block_mfma_us(const InspectorInput &in, int ks) {
+    return ks * vec_elems(in.dtype) * ((in.ccol + 15) / 16) * (in.dtype == TF_F64 ? 64 : 32) / 2400.0;
+}
+// A first wavefront without tiles: both kernels take rows of any alignment in 16-byte pieces.  The
+// product's waves start and end with a block's multiplications, the gather gets 10 TB/s (lognormal rows of
+// mean length 10 and 18, and R-MAT graphs; estimate / measured: 200000 rows fp32 64 -> 64 114 / 99 and 159 /
+// 145 us, fp64 128 -> 128 427 / 442 and 600 / 642, 50000 rows fp32 32 -> 32 25 / 26, 50 -> 23 26 / 28, R-MAT of
+// 4000 rows fp32 50 -> 23 13 / 14, 128 -> 128 23 / 28, fp64 64 -> 64 19 / 23).
+static double streaming_wavefronts_us(const InspectorInput &in, int ks) {
+    const double es = elem_size(in.dtype), n = (double)in.n, nnz = (double)in.nnz;
+    return 11.0 + 2.0 * block_mfma_us(in, ks) + n * (in.bcol + 2.0 * in.ccol) * es / 3.2e6 + nnz * in.ccol * es / 10e6;
+}
 // The one-pass kernel gathers rows of B out of the L2 at 18 TB/s and streams at 5 TB/s.  `entries`: with
 // padding, where that is known.
 static double one_pass_us(const InspectorInput &in, double entries) {
     const double es = elem_size(in.dtype), n = (double)in.n;
     return 5.0 + entries * in.bcol * es / 18e6 + n * (in.bcol + in.ccol) * es / 5e6;
-}
-// Matrix instructions of one block of the kernel, back to back.
-static double block_mfma_us(const InspectorInput &in, int ks) {
-    return ks * vec_elems(in.dtype) * ((in.ccol + 15) / 16) * (in.dtype == TF_F64 ? 64 : 32) / 2400.0;
 }
 // What rows of unequal length add to it: the multiplications of blocks that hold fewer than sixteen rows,
 // and what the wave with the most passes of gathers takes longer than the mean one.  A pass waits for its
@@ -1015,8 +1025,7 @@ void build_chain_pack(const InspectorInput &in, Schedule &s, bool entries) {
     if (ks == 0 || chain_lds_bytes(in.dtype, in.bcol, in.ccol) > in.fast_mem_bytes) return;
     // (the kernel stores D through 32-bit byte offsets, in whole 16-byte pieces)
     if (in.ccol < vec_elems(in.dtype) || n * in.ccol * es >= ((int64_t)1 << 32) - 64) return;
-    const double two = two_wavefronts_us(in);
-    if (s.far_rows || one_pass_us(in, (double)in.nnz) >= two) return;
+    if (s.far_rows || one_pass_us(in, (double)in.nnz) >= two_wavefronts_us(in)) return;
     auto len = [&](int64_t j) { return (int64_t)in.rowptr[j + 1] - in.rowptr[j]; };
     int64_t longest = 0;
     for (int64_t j = 0; j < n; ++j) longest = std::max(longest, len(j));
@@ -1068,6 +1077,7 @@ void build_chain_pack(const InspectorInput &in, Schedule &s, bool entries) {
         q0 = q1;
     }
     const int64_t nb = (int64_t)c.blocks.size();
+    const double two = s.streaming ? streaming_wavefronts_us(in, ks) : two_wavefronts_us(in);
     if (one_pass_us(in, 16.0 * (double)slot) + one_pass_tail_us(in, c, ks) >= two) {
         c = ChainPack();
         return;

@@ -401,3 +401,18 @@ def test_rows_that_would_hold_one_wave_up_decide_the_execution(longest, executio
     colidx = (first[rows] + np.arange(rows.size) - rowptr[rows]).astype(np.int32)
     A = ti.Csr(n, n, rowptr, colidx, np.ones(rows.size))
     assert plan_schedule(A, 128, 128, False)["execution"] == execution
+
+
+@pytest.mark.parametrize("bcol,ccol,execution", [(32, 32, tf.TF_EXECUTE_ONE_PASS), (50, 23, tf.TF_EXECUTE_WAVEFRONTS)])
+def test_unaligned_widths_of_a_streaming_plan_decide_no_execution(bcol, ccol, execution):
+    """The kernels of a first wavefront without tiles take rows of any alignment in 16-byte pieces: an
+    unaligned width is no reason to leave the two wavefronts there (rows of 1 to 1000 entries, fp32: one pass
+    and two wavefronts 12.3 and 14.1 us at 32 -> 32, 16.0 and 13.8 us at 50 -> 23)."""
+    n = 5000
+    rng = np.random.default_rng(3)
+    lens = np.clip(np.round(np.exp(rng.normal(np.log(6), 1.5, n))), 1, 1000).astype(np.int64)
+    rows = np.repeat(np.arange(n), lens)
+    colidx = np.clip(rows + rng.integers(-400, 401, rows.size), 0, n - 1).astype(np.int32)
+    rowptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    s = plan_schedule(ti.Csr(n, n, rowptr, colidx, np.ones(rows.size, np.float32)), bcol, ccol, False)
+    assert s["first_wavefront_streams"] == 1 and s["execution"] == execution
