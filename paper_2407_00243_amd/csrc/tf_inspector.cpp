@@ -584,17 +584,21 @@ tf_status build_schedule(const InspectorInput &in, Schedule &s, std::string &err
         // the sample: 64 runs of up to 1024 consecutive rows, evenly spread (runs, not single rows:
         // their entries are read as a stream)
         const int64_t run = std::min<int64_t>(1024, std::max<int64_t>(1, n / 64));
+        const double far_b = 1048576.0 / ((double)in.bcol * es);       // rows of B in 1 MiB
         double dist = 0.0;
-        int64_t cnt = 0;
+        int64_t cnt = 0, far = 0;
         for (int64_t k = 0; k < 64; ++k) {
             const int64_t j0 = std::min(n - run, n * k / 64);
             for (int64_t j = j0; j < j0 + run; ++j)
                 for (int64_t q = in.rowptr[j]; q < in.rowptr[j + 1]; ++q) {
-                    dist += std::abs((double)in.colidx[q] - (double)j);
+                    const double d = std::abs((double)in.colidx[q] - (double)j);
+                    dist += d;
+                    far += d > far_b;
                     ++cnt;
                 }
         }
         far_rows = cnt > 0 && dist / (double)cnt * (double)in.ccol * es > 4.0 * 1048576.0;
+        s.far_b_share = cnt > 0 ? (double)far / (double)cnt : 0.0;
     }
     s.far_rows = far_rows;
     bool demote_lds_rows = false;
@@ -966,8 +970,11 @@ tf_status build_schedule(const InspectorInput &in, Schedule &s, std::string &err
 
 // Estimated microseconds of the fused calls on a matrix whose rows stay near the diagonal, in two
 // wavefronts and in one pass.  The rates (bytes per microsecond) are fits to measured executions.
-// Tiles in LDS: the kernels move B and D at 3.2 TB/s; unaligned widths take them three times as long (scalar
-// lanes).
+// Tiles in LDS: the kernels move B and D at 3.2 TB/s.  Unaligned widths take them 1.1 to 1.5 times as long
+// (the middle half of 2206 bands and 2D and 3D stencils of 3000 to 3 million rows, 4 to 128 columns: 0.9 to
+// 1.7 times); they are charged three times, with which the rule takes the slower way by more than 5 % on 33
+// of these plans, by 1.56 times at most.  (1.25 times and 25 us for fp64: 12 of them, but ten plans lose up
+// to a fifth that have the right way now.)
 static double two_wavefronts_us(const InspectorInput &in) {
     const double es = elem_size(in.dtype), n = (double)in.n, nnz = (double)in.nnz;
     const int v = vec_elems(in.dtype);
@@ -988,10 +995,10 @@ static double streaming_wavefronts_us(const InspectorInput &in, int ks) {
     return 11.0 + 2.0 * block_mfma_us(in, ks) + n * (in.bcol + 2.0 * in.ccol) * es / 3.2e6 + nnz * in.ccol * es / 10e6;
 }
 // The one-pass kernel gathers rows of B out of the L2 at 18 TB/s and streams at 5 TB/s.  `entries`: with
-// padding, where that is known.
-static double one_pass_us(const InspectorInput &in, double entries) {
+// padding, where that is known; `far`: the share of them whose row of B is not in the L2.
+static double one_pass_us(const InspectorInput &in, double entries, double far = 0.0) {
     const double es = elem_size(in.dtype), n = (double)in.n;
-    return 5.0 + entries * in.bcol * es / 18e6 + n * (in.bcol + in.ccol) * es / 5e6;
+    return 5.0 + entries * in.bcol * es * (1.0 / 18e6 + far / 32e6) + n * (in.bcol + in.ccol) * es / 5e6;
 }
 // What rows of unequal length add to it: the multiplications of blocks that hold fewer than sixteen rows,
 // and what the wave with the most passes of gathers takes longer than the mean one.  A pass waits for its
@@ -1078,7 +1085,15 @@ void build_chain_pack(const InspectorInput &in, Schedule &s, bool entries) {
     }
     const int64_t nb = (int64_t)c.blocks.size();
     const double two = s.streaming ? streaming_wavefronts_us(in, ks) : two_wavefronts_us(in);
-    if (one_pass_us(in, 16.0 * (double)slot) + one_pass_tail_us(in, c, ks) >= two) {
+    // Columns scattered around the diagonal (no tile fuses anything: the plan streams) find their row of B
+    // in the L2 while it lies within 1 MiB of the row's own; farther ones come at 11.5 TB/s.  Stencils find
+    // theirs at any distance: their columns move along with the rows.  (us, one pass / two wavefronts:
+    // 141435 rows of 6 columns up to 27624 rows away, fp32 128 -> 32, 56 / 41; 281094 rows of 16, up to
+    // 15680 away, fp64 103 -> 48, 475 / 249; 400000 rows of 8, fp32 128 -> 64, up to 2000 away 128 / 149, 25000
+    // 212 / 187.  Of 696 such matrices this moved 17 that were up to 1.9 times faster in two wavefronts, and
+    // none that was not.)
+    const double far = s.streaming ? s.far_b_share : 0.0;
+    if (one_pass_us(in, 16.0 * (double)slot, far) + one_pass_tail_us(in, c, ks) >= two) {
         c = ChainPack();
         return;
     }

@@ -348,6 +348,7 @@ struct Schedule {
     bool streaming = false;
     bool automatic = false;        // the caller left the tiling to the library
     bool far_rows = false;         // rows reach far from the diagonal (a graph), see build_schedule
+    double far_b_share = 0.0;      // share of the entries whose row of B is more than 1 MiB away from the row's own
     bool grown_tiles = false;      // tiles grown along the dependence graph
     int64_t n_demoted_rows = 0;    // rows that a tile could have fused but that were left to the second wavefront
     int32_t first_stride = 0;                             // largest tile, in rows, rounded up to 16

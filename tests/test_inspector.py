@@ -416,3 +416,17 @@ def test_unaligned_widths_of_a_streaming_plan_decide_no_execution(bcol, ccol, ex
     rowptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
     s = plan_schedule(ti.Csr(n, n, rowptr, colidx, np.ones(rows.size, np.float32)), bcol, ccol, False)
     assert s["first_wavefront_streams"] == 1 and s["execution"] == execution
+
+
+@pytest.mark.parametrize("reach,execution", [(400, tf.TF_EXECUTE_ONE_PASS), (27624, tf.TF_EXECUTE_WAVEFRONTS)])
+def test_distance_of_the_gathered_rows_of_b_decides_the_execution(reach, execution):
+    """The one pass gathers rows of B: whether they come out of the L2 is a matter of their own width, not of
+    that of the rows of D (fp32 128 -> 32, six columns per row up to 27624 rows away: one pass 56.2 us, two
+    wavefronts 41.4 us)."""
+    n, per_row = 141435, 6
+    rng = np.random.default_rng(4)
+    rows = np.repeat(np.arange(n), per_row)
+    colidx = np.clip(rows + rng.integers(-reach, reach + 1, rows.size), 0, n - 1).astype(np.int32)
+    A = ti.Csr(n, n, np.arange(0, n * per_row + 1, per_row, dtype=np.int32), colidx, np.ones(rows.size, np.float32))
+    s = plan_schedule(A, 128, 32, False)
+    assert s["far_rows"] == 0 and s["execution"] == execution
