@@ -121,7 +121,6 @@ struct tf_plan {
     void *chain_blocks = nullptr, *chain_rows = nullptr, *chain_idx = nullptr, *chain_vals = nullptr;
     int32_t n_chain_blocks = 0;
     size_t chain_zeros = 0;                // bytes into chain_vals
-    bool chain_contiguous = true;
     DevBuf d1;                             // fused path: one slot per spilled D1 row
     DevBuf d1_pair;                        // plain pair of operations: all rows of D1
     bool has_baseline = false;             // the packed copy of all rows of A exists
@@ -394,7 +393,6 @@ tf_status run_chain(const tf_plan *p, const void *B, const void *C, void *D, voi
     a.n = p->n;
     a.bcol = (int32_t)p->bcol;
     a.ccol = (int32_t)p->ccol;
-    a.contiguous = p->chain_contiguous ? 1 : 0;
     a.n_cu = p->n_cu;
     a.blocks = static_cast<const tf::ChainBlock *>(p->chain_blocks);
     a.rows = static_cast<const int32_t *>(p->chain_rows);
@@ -610,7 +608,6 @@ tf_status tf_plan_create(const tf_csr *A, int64_t bCol, int64_t cCol, int32_t b_
         }
         if (!sc.chain.blocks.empty()) {
             p->n_chain_blocks = (int32_t)sc.chain.blocks.size();
-            p->chain_contiguous = sc.chain.contiguous;
             arena.add(sc.chain.blocks, p->chain_blocks);
             arena.add(sc.chain.rows, p->chain_rows);
             arena.add(sc.chain.idx, p->chain_idx);

@@ -134,21 +134,11 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS)) void
     uint64_t *ea = reinterpret_cast<uint64_t *>(ev + NE * 64);
     const unsigned char *ex_r = ex + r * 64 + (g ^ (r >> 2)) * 16;
 
-    // blocks of this wave: near the diagonal every XCD has a contiguous range, through which its
-    // waves move side by side (rows of B that neighbouring blocks share stay in that XCD's L2);
-    // blocks sorted by length are dealt out over the whole machine
-    int blk, end, step;
-    if (a.contiguous) {
-        const int per = (a.n_blocks + kXcds - 1) / kXcds;
-        const int x = blockIdx.x % kXcds;
-        blk = x * per + (int)(blockIdx.x / kXcds) * nwaves + wave;
-        end = min(a.n_blocks, (x + 1) * per);
-        step = (int)(gridDim.x / kXcds) * nwaves;
-    } else {
-        blk = (int)blockIdx.x * nwaves + wave;
-        end = a.n_blocks;
-        step = (int)gridDim.x * nwaves;
-    }
+    // blocks of this wave: every XCD has a contiguous range, through which its waves move side by side
+    // (rows of B that neighbouring blocks share stay in that XCD's L2)
+    const int per = (a.n_blocks + kXcds - 1) / kXcds, xcd = blockIdx.x % kXcds;
+    const int end = min(a.n_blocks, (xcd + 1) * per), step = (int)(gridDim.x / kXcds) * nwaves;
+    int blk = xcd * per + (int)(blockIdx.x / kXcds) * nwaves + wave;
 
     // The entries of a pass: fetched a pass ahead, 64 (four slots of sixteen rows) per load, put into
     // LDS when their turn comes, read back by the lanes of their row.  A column becomes the address of its

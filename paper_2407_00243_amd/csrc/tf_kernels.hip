@@ -206,9 +206,6 @@ __device__ __forceinline__ void rows_dot(T (&acc)[R][N], const IdxT *__restrict_
     }
 }
 
-constexpr int kRowsPerPass = 4;     // R: rows a lane group works on at once
-constexpr int kEntriesPerPass = 4;  // E: entries of each of those rows fetched per pass
-
 // ------------------------------------------------------------------------------------------
 // Packed row lists (see RowPack): every row of a unit has `slots` entries, so the gather loop has
 // a wave-uniform trip count and needs neither row pointers nor bounds on individual entries.
