@@ -39,3 +39,33 @@ def test_full_size_config(cfg):
             assert err <= tol, f"cfg{cfg} fused={fused}: {err:.3e} > {tol:.0e}"
     finally:
         c.close()
+
+
+@pytest.mark.parametrize("cfg", [1, 2])
+def test_full_size_config_in_two_wavefronts(cfg):
+    """The configurations that the library runs in one pass, in the two wavefronts of its own tiling: every
+    row of D, and the D1 rows that the first one leaves for the second."""
+    import bench
+    import paper_2407_00243_amd as tf
+    from gpu_util import Case, TOL, read_workspace
+    prob = ti.config(cfg)
+    c = Case(prob, **bench.tile_params(cfg))
+    try:
+        s = c.plan.schedule()
+        assert s["automatic"] == 1 and s["execution"] == tf.TF_EXECUTE_ONE_PASS and not s["first_wavefront_streams"]
+        c.plan.workspace()
+        D_ref, W = oracle.chain(prob.A, prob.B, prob.C, parallel=True)
+        D = c.run()
+        assert np.all(np.isfinite(D)), "a row of D was not written"
+        tol = TOL[np.dtype(prob.dtype)]
+        err = oracle.rowwise_rel_err(D, D_ref, W)
+        assert err <= tol, f"cfg{cfg}: {err:.3e} > {tol:.0e}"
+        eye = ti.Csr(prob.n, prob.n, np.arange(prob.n + 1, dtype=np.int32), np.arange(prob.n, dtype=np.int32),
+                     np.ones(prob.n, prob.dtype))
+        D1_ref, W1 = oracle.chain(eye, prob.B, prob.C, parallel=True)
+        rows = np.flatnonzero(s["spill_slot"] >= 0)
+        ws = read_workspace(c.plan, s, c.ccol, prob.dtype)
+        err = oracle.rowwise_rel_err(ws[s["spill_slot"][rows]], D1_ref[rows], W1[rows])
+        assert rows.size and err <= tol, f"cfg{cfg} D1: {err:.3e} > {tol:.0e}"
+    finally:
+        c.close()

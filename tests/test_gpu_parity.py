@@ -745,6 +745,24 @@ def test_experiment_grid_with_default_plans(cfg, width, dtype):
     assert np.all(D[empty] == 0)
 
 
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("width", [23, 32, 64, 128])
+@pytest.mark.parametrize("cfg", [1, 2, 4])
+def test_experiment_grid_in_two_wavefronts(cfg, width, dtype):
+    """The same for the plans whose fused calls run the chain in another way (one pass, plain pair): the two
+    wavefronts of the library's own tiling, which they run once their workspace was asked for."""
+    from gpu_util import assert_parity
+    prob = ti.config(cfg, scale_down=GRID_SCALE[cfg], width=width, dtype=dtype)
+    c = _case(prob)
+    try:
+        s = c.plan.schedule()
+        assert s["automatic"] == 1 and s["execution"] != 0 and not s["first_wavefront_streams"]
+        c.plan.workspace()
+        assert_parity(prob, c.run())
+    finally:
+        c.close()
+
+
 # ---------------------------------------------------------------- workspaces of 4 GiB and more
 
 def test_workspace_slices_of_four_gib_and_more():
