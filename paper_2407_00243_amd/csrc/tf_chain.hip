@@ -99,7 +99,7 @@ __device__ __forceinline__ void write_c(T *Cl, const CPiece<T> (&tmp)[kStageC]) 
 // of a wave complete in order on this machine, so gathers that were sent out after the stores of D
 // would wait for these to reach memory.
 template <typename T, int KS, int NBC>
-__global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS)) void k_gather_gemm(
+__global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS, NBC)) void k_gather_gemm(
     const ChainLaunch a, const ChainBlock *__restrict__ blocks, const int32_t *__restrict__ rows,
     const int32_t *__restrict__ idx, const T *__restrict__ val, const char *__restrict__ B,
     void *D) {

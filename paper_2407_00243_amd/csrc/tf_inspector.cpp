@@ -1008,7 +1008,8 @@ static double one_pass_us(const InspectorInput &in, double entries, double far =
 static double one_pass_tail_us(const InspectorInput &in, const ChainPack &c, int ks) {
     const int em = chain_entries(ks);
     const int64_t nb = (int64_t)c.blocks.size(), per = (nb + kXcds - 1) / kXcds;
-    const int64_t waves = std::max<int64_t>(1, std::min(per, (int64_t)in.n_cu / kXcds * 4 * chain_waves(in.dtype, ks)));
+    const int per_simd = chain_waves(in.dtype, ks, chain_col_blocks(ks, in.ccol));
+    const int64_t waves = std::max<int64_t>(1, std::min(per, (int64_t)in.n_cu / kXcds * 4 * per_simd));
     std::vector<int32_t> passes((size_t)(kXcds * waves), 0);
     int64_t sum = 0, longest = 0;
     for (int64_t b = 0; b < nb; ++b) {

@@ -285,8 +285,12 @@ constexpr int chain_ksteps_below(int dtype, int ks) {
 }
 // Entries per row whose gathers are in flight at once (about 24 pieces of 16 bytes per lane).
 constexpr int chain_entries(int ks) { return ks <= 2 ? 8 : ks == 3 ? 6 : ks == 4 ? 5 : ks <= 8 ? 3 : 2; }
-// Waves per SIMD that the kernel is held to: where a third one costs no spilled registers.
-constexpr int chain_waves(int dtype, int ks) { return ks <= (dtype == TF_F64 ? 2 : 6) ? 3 : 2; }
+// Waves per SIMD that the kernel is held to: where a third one costs no spilled registers (fp64 at depth 2 with
+// four blocks of columns: held to three it spills 12 bytes a lane; bands and 3D stencils, 16 -> 64, us
+// with three and two: 264964 rows of 5 32.9 / 30.9, 60^3 29.9 / 27.5, 439631 rows of 12, 8 -> 64, 63.7 / 61.3).
+constexpr int chain_waves(int dtype, int ks, int nbc) {
+    return dtype == TF_F64 ? (ks == 2 && nbc < 4 ? 3 : 2) : ks <= 6 ? 3 : 2;
+}
 // Blocks of sixteen columns of D that are multiplied together: the count (3 or 4, or all of them)
 // that wastes the fewest blocks; two at the largest depth, where the registers end.
 inline int chain_col_blocks(int ks, int64_t ccol) {
