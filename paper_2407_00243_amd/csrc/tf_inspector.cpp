@@ -1000,26 +1000,28 @@ static double one_pass_us(const InspectorInput &in, double entries, double far =
     const double es = elem_size(in.dtype), n = (double)in.n;
     return 5.0 + entries * in.bcol * es * (1.0 / 18e6 + far / 32e6) + n * (in.bcol + in.ccol) * es / 5e6;
 }
-// What rows of unequal length add to it: the multiplications of blocks that hold fewer than sixteen rows,
-// and what the wave with the most passes of gathers takes longer than the mean one.  A pass waits for its
-// gathers, 0.8 us (band of 20011 rows, eight of them of 400 and of 1024 entries, uncut: fp32 32 columns 48 and
-// 116 us, 64 columns 66 and 165, fp64 128 columns 135 and 374: 0.87, 0.79 and 0.77 us a pass).  Blocks are
-// dealt to the waves of an XCD as k_gather_gemm takes them.
-static double one_pass_tail_us(const InspectorInput &in, const ChainPack &c, int ks) {
+// What rows of unequal length add to it: the multiplications of blocks that hold fewer rows than `per_block`,
+// and what the wave with the most passes of gathers takes longer than it would with blocks of mean length.  A
+// pass waits for its gathers, 0.8 us (band of 20011 rows, eight of them of 400 and of 1024 entries, uncut: fp32
+// 32 columns 48 and 116 us, 64 columns 66 and 165, fp64 128 columns 135 and 374: 0.87, 0.79 and 0.77 us a
+// pass).  Blocks are dealt to the waves of an XCD as k_gather_gemm takes them.  That some waves have a block
+// more than others is no matter of row lengths, and in the fits of one_pass_us already (band of 50000 rows of
+// 41, fp64 100 -> 100, where it was charged here too: 169 us in two wavefronts, 121 in one pass).
+static double one_pass_tail_us(const InspectorInput &in, const ChainPack &c, int ks, int64_t per_block) {
     const int em = chain_entries(ks);
     const int64_t nb = (int64_t)c.blocks.size(), per = (nb + kXcds - 1) / kXcds;
     const int per_simd = chain_waves(in.dtype, ks, chain_col_blocks(ks, in.ccol));
     const int64_t waves = std::max<int64_t>(1, std::min(per, (int64_t)in.n_cu / kXcds * 4 * per_simd));
     std::vector<int32_t> passes((size_t)(kXcds * waves), 0);
-    int64_t sum = 0, longest = 0;
+    int64_t slots = 0, longest = 0;
     for (int64_t b = 0; b < nb; ++b) {
         int32_t &w = passes[(size_t)(b / per * waves + b % per % waves)];
-        const int32_t p = (c.blocks[(size_t)b].slots + em - 1) / em;
-        sum += p;
-        longest = std::max<int64_t>(longest, w += p);
+        slots += c.blocks[(size_t)b].slots;
+        longest = std::max<int64_t>(longest, w += (c.blocks[(size_t)b].slots + em - 1) / em);
     }
-    return 0.8 * ((double)longest - (double)sum / (double)(kXcds * waves)) +
-           std::max(0.0, (double)nb - (double)in.n / 16) / (4.0 * in.n_cu) * block_mfma_us(in, ks);
+    const int64_t even = (per + waves - 1) / waves * ((slots + nb * em - 1) / (nb * em));
+    return 0.8 * (double)std::max<int64_t>(0, longest - even) +
+           std::max(0.0, (double)nb - (double)in.n / (double)per_block) / (4.0 * in.n_cu) * block_mfma_us(in, ks);
 }
 
 void build_chain_pack(const InspectorInput &in, Schedule &s, bool entries) {
@@ -1094,7 +1096,9 @@ void build_chain_pack(const InspectorInput &in, Schedule &s, bool entries) {
     // 212 / 187.  Of 696 such matrices this moved 17 that were up to 1.9 times faster in two wavefronts, and
     // none that was not.)
     const double far = s.streaming ? s.far_b_share : 0.0;
-    if (one_pass_us(in, 16.0 * (double)slot, far) + one_pass_tail_us(in, c, ks) >= two) {
+    // (the few per cent by which the ends of a stencil's rows pad are in the fits)
+    const double with_padding = 16.0 * (double)slot > 1.125 * (double)in.nnz ? 16.0 * (double)slot : (double)in.nnz;
+    if (one_pass_us(in, with_padding, far) + one_pass_tail_us(in, c, ks, per_block) >= two) {
         c = ChainPack();
         return;
     }

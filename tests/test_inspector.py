@@ -430,3 +430,16 @@ def test_distance_of_the_gathered_rows_of_b_decides_the_execution(reach, executi
     A = ti.Csr(n, n, np.arange(0, n * per_row + 1, per_row, dtype=np.int32), colidx, np.ones(rows.size, np.float32))
     s = plan_schedule(A, 128, 32, False)
     assert s["far_rows"] == 0 and s["execution"] == execution
+
+
+@pytest.mark.parametrize("n,h,dtype,bcol,ccol", [(50000, 20, np.float64, 100, 100), (62226, 20, np.float64, 64, 39),
+                                                 (20011, 5, np.float32, 64, 64)])
+def test_rows_of_equal_length_hold_no_wave_up(n, h, dtype, bcol, ccol):
+    """That some waves have one block more than others is no reason to leave the one pass (fp64 100 -> 100, n =
+    50000: one pass 121 us, two wavefronts 169 us)."""
+    rows = np.repeat(np.arange(n), 2 * h + 1)
+    cols = rows + np.tile(np.arange(-h, h + 1), n)
+    keep = (cols >= 0) & (cols < n)
+    rowptr = np.concatenate([[0], np.cumsum(np.bincount(rows[keep], minlength=n))]).astype(np.int32)
+    A = ti.Csr(n, n, rowptr, cols[keep].astype(np.int32), np.ones(keep.sum(), dtype))
+    assert plan_schedule(A, bcol, ccol, False)["execution"] == tf.TF_EXECUTE_ONE_PASS
