@@ -3,7 +3,8 @@
 
     python bench.py [--gpus 1] [--steps K] [--warmup W] [--config 1..5] [--no-cpu] [tile options]
 
-A step is one fused execution (first wavefront + second wavefront) of the workload; the
+A step is one fused execution of the workload, in the way that the library chose for the plan
+("execution": the two wavefronts, or the chain in one pass, or another, see tf_schedule_view); the
 schedule is built once before the timed region and its time is reported separately, as the
 paper does (Section 4.1: executor time only, scheduler overhead evaluated on its own).  All
 inputs are resident in device memory before timing starts.  Successive steps rotate over
@@ -39,6 +40,12 @@ HEADLINE_CONFIG = 3
 # Steps for the configurations under per_config: their steps take 15 to 600 us, so the driver's
 # 20 steps would make a timed region of a millisecond or less.
 PER_CONFIG_STEPS = {1: 400, 2: 300, 4: 200, 5: 100}
+
+
+# What the fused call of a plan launches (tf_schedule_view.execution), dense and CSR B
+EXECUTIONS = ["wavefronts", "one_pass", "gather_first", "plain_pair"]
+CALL_KERNELS = {"one_pass": "k_gather_gemm", "gather_first": "k_packed_spmm + k_gemm",
+                "plain_pair": "k_csr_spmm + k_packed_spmm"}
 
 
 def tile_params(cfg, width=None, dtype=None):
@@ -174,12 +181,18 @@ def measure(cfg, args, steps, warmup, headline):
         f"fused nnz={sched['fused_ratio_nnz']:.3f} direct={sched['n_direct_rows']} "
         f"demoted={sched['n_demoted_rows']} streams={sched['first_wavefront_streams']} "
         f"spill={sched['n_spill_rows'] / max(n, 1):.3f} d1 slices={sched['d1_slices']} "
+        f"execution={EXECUTIONS[sched['execution']]} "
         f"wf1 units={sched['n_wf1_units']} "
         f"plan {min(plan_seconds) * 1e3:.1f} ms ({sched['plan_seconds'] * 1e3:.1f} ms schedule)")
 
     flops = ti.useful_flops(prob)
-    q_alg = sched["alg_bytes"] + (b_bytes if sparse else 0)
+    execution = EXECUTIONS[sched["execution"]]
+    # algorithmic bytes of the two wavefronts, of the unfused pair and of what the fused call runs
+    q_two = sched["alg_bytes"] + (b_bytes if sparse else 0)
     q_unf = sched["alg_bytes_unfused"] + (b_bytes if sparse else 0)
+    q_once = q_two - 2 * sched["n_spill_rows"] * ccol * es           # A, B, C and D once
+    q_alg = {"wavefronts": q_two, "one_pass": q_once, "gather_first": q_once + 2 * n * bcol * es,
+             "plain_pair": q_unf}[execution]
 
     def timed(fn, k, w):
         for i in range(w):
@@ -246,7 +259,8 @@ def measure(cfg, args, steps, warmup, headline):
         graph_ms = {"fused": timed_graphs(graphs_of(fused)),
                     "unfused": timed_graphs(graphs_of(unfused))}
 
-    # ---- per-kernel durations over the same rotation, HIP events on the launch stream
+    # ---- durations of the two wavefronts over the same rotation, HIP events on the launch stream (by
+    # themselves, also where the fused call runs the chain in another way)
     def avg_kernel_ms(fn, before=None):
         reps = max(steps, 2 * n_sets)
         e0 = [torch.cuda.Event(enable_timing=True) for _ in range(reps)]
@@ -264,14 +278,17 @@ def measure(cfg, args, steps, warmup, headline):
     ms_wf0 = avg_kernel_ms(wf0)
     ms_wf1 = avg_kernel_ms(wf1, before=wf0) if sched["n_wf1_units"] else 0.0
 
-    # algorithmic bytes per wavefront (together they are q_alg)
+    # algorithmic bytes per wavefront (together they are q_two)
     fused_nnz, nf, ns = sched["fused_nnz"], sched["n_fused_rows"], sched["n_spill_rows"]
     c_bytes = bcol * ccol * es
     q_wf0 = b_bytes + c_bytes + fused_nnz * (4 + es) + 4 * nf + nf * ccol * es + ns * ccol * es
-    q_wf1 = q_alg - q_wf0
+    q_wf1 = q_two - q_wf0
     gemm_flops = 0 if sparse else 2 * n * bcol * ccol
     dom_is_wf0 = ms_wf0 >= ms_wf1
     dom_ms, dom_q = (ms_wf0, q_wf0) if dom_is_wf0 else (ms_wf1, q_wf1)
+    if execution != "wavefronts":
+        # the whole call: one launch in one pass, whose step time is its duration and the launch gap
+        dom_ms, dom_q, dom_is_wf0 = ms_fused, q_alg, True
     dname = "f32" if es == 4 else "f64"
     t_mem = dom_q / (HBM_PEAK_GBS * 1e9)
     t_mfma = (gemm_flops / (MFMA_PEAK_TFLOPS[dname] * 1e12)) if dom_is_wf0 else 0.0
@@ -283,7 +300,9 @@ def measure(cfg, args, steps, warmup, headline):
         roofline = dict(bound="hbm", achieved=dom_q / (dom_ms * 1e-3) / 1e9, peak=HBM_PEAK_GBS,
                         unit="GB/s")
     roofline["frac"] = roofline["achieved"] / roofline["peak"]
-    if not dom_is_wf0:
+    if execution != "wavefronts":
+        kernel = CALL_KERNELS[execution]
+    elif not dom_is_wf0:
         kernel = "k_packed_spmm"
     elif sched["first_wavefront_streams"]:
         kernel = "k_csr_spmm" if sparse else "k_gemm"
@@ -309,6 +328,7 @@ def measure(cfg, args, steps, warmup, headline):
         "steps": steps,
         "ms_per_step": ms_fused,
         "value": flops / (ms_fused * 1e-3) / 1e9,
+        "execution": execution,
         "tile_params": params,
         "buffer_sets": n_sets,
         "useful_flops": int(flops),
@@ -428,7 +448,7 @@ def main():
             r = measure(other, args, max(args.steps, PER_CONFIG_STEPS[other]), args.warmup,
                         headline=False)
             per_config[f"cfg{other}"] = {
-                "workload": r["workload"], "dtype": r["dtype"], "steps": r["steps"],
+                "workload": r["workload"], "dtype": r["dtype"], "steps": r["steps"], "execution": r["execution"],
                 "fused_ms": r["ms_per_step"], "unfused_ms": r["unfused_ms_per_step"],
                 "speedup_vs_unfused": r["speedup_vs_unfused"],
                 "useful_gflops": r["value"], "hbm_alg_gbs": r["hbm_alg_gbs"],
@@ -459,7 +479,7 @@ def main():
         "config": {"workload": head["workload"], "tile_params": head["tile_params"],
                    "buffer_sets": head["buffer_sets"], "useful_flops": head["useful_flops"]},
     }
-    for k in ("hbm_alg_gbs", "hbm_alg_frac", "step_bound", "alg_bytes", "alg_bytes_unfused", "unfused_ms_per_step",
+    for k in ("execution", "hbm_alg_gbs", "hbm_alg_frac", "step_bound", "alg_bytes", "alg_bytes_unfused", "unfused_ms_per_step",
               "speedup_vs_unfused", "median7_ms", "warm_ms", "graph_ms", "kernels_ms", "fused_ratio",
               "spill_fraction", "first_rows_fraction", "schedule", "plan_ms", "schedule_ms",
               "amortisation_runs"):
