@@ -38,17 +38,17 @@ def run_point(extra, steps, warmup):
 
 def row_of(label, d):
     if "error" in d:
-        return f"| {label} | failed: {d['error']} |||||||"
+        return f"| {label} | failed: {d['error']} ||||||||"
     k = d["kernels_ms"]
     return (f"| {label} | {d['ms_per_step']:.4f} | {d['unfused_ms_per_step']:.4f} | "
             f"{d['speedup_vs_unfused']:.2f} | {d['value']:.0f} | {d['hbm_alg_gbs']:.0f} | "
-            f"{k['wavefront0']:.4f} / {k['wavefront1']:.4f} | "
+            f"{d['execution']} | {k['wavefront0']:.4f} / {k['wavefront1']:.4f} | "
             f"{d['fused_ratio']['rows']:.2f} / {d['fused_ratio']['nnz']:.2f} | "
             f"{d['schedule']['tiles']} x {d['schedule']['col_slice']} |")
 
 
 HEAD = ("| point | fused ms | unfused ms | speedup | useful GFLOP/s | algorithmic GB/s | "
-        "wavefront 0 / 1 ms | fused rows / nnz | tiles x slice |\n|---|---|---|---|---|---|---|---|---|")
+        "execution | wavefront 0 / 1 ms | fused rows / nnz | tiles x slice |\n|---|---|---|---|---|---|---|---|---|---|")
 
 
 def main():
