@@ -416,9 +416,17 @@ template <typename T, int KS, int NBC> int run_chain(ChainLaunch a, hipStream_t 
     static ChainSetup cs;
     auto kernel = k_gather_gemm<T, KS, NBC>;
     // A launch with few blocks of rows is spread over the machine by column groups too (the rows are then
-    // gathered once per group, and a workgroup stages its part of C only).
+    // gathered once per group, and a workgroup stages its part of C only): as far as the machine holds all
+    // its waves at once, half of them where C is small and little is saved (us, all groups in one workgroup /
+    // as chosen: bands of 17 entries, fp64 128 -> 128, n = 4096 34.3 / 21.4, 8192 40.7 / 27.5, 16384 40.9 /
+    // 32.1; fp32 128 -> 128 20.1 / 11.8, 23.7 / 13.3, 23.8 / 18.9; with twice the waves 51.5 at n = 16384 in fp64,
+    // 34.7 / 24.0 at 32768 in fp32; C of 32 KiB, fp64 32 -> 128, n = 16384, 12.0 / 11.1 with one group each).
     const int64_t group_lds = (int64_t)NBC * KS * Tr<T>::V * 64 * (int64_t)sizeof(T);
-    a.groups_per_wg = a.n_blocks < 2 * a.n_cu ? 1 : a.n_groups;
+    const int64_t held = (int64_t)a.n_cu * (a.n_groups * group_lds <= 40 * 1024 ? 4 : 8);
+    a.groups_per_wg = 1;
+    while (a.n_blocks >= 2 * a.n_cu && a.groups_per_wg < a.n_groups &&
+           (int64_t)a.n_blocks * ((a.n_groups + a.groups_per_wg - 1) / a.groups_per_wg) > held)
+        ++a.groups_per_wg;
     const int n_y = (a.n_groups + a.groups_per_wg - 1) / a.groups_per_wg;
     const int64_t lds_c = a.groups_per_wg * group_lds;
     // Waves per workgroup: one copy of C per workgroup, so the more LDS it takes the more waves have

@@ -115,3 +115,22 @@ def test_long_rows_among_short_ones_are_cut(dtype, bcol, ccol, kind):
         assert np.array_equal(c.run().astype(np.float64), oracle.chain(A, B, C)[0])
     finally:
         c.close()
+
+
+@pytest.mark.parametrize("dtype,bcol,ccol,n", [
+    (np.float64, 128, 128, 8000),      # 4 column groups, one per workgroup, as many waves as the machine holds
+    (np.float64, 128, 128, 16000),     # two per workgroup
+    (np.float64, 127, 95, 16000),      # 3 groups: two and one
+    (np.float64, 128, 128, 33000),     # all in one
+    (np.float32, 100, 120, 16000), (np.float32, 16, 300, 12000), (np.float32, 16, 300, 4000), (np.float64, 96, 70, 9000)])
+def test_column_groups_of_the_one_pass_chain_over_workgroups(dtype, bcol, ccol, n):
+    import paper_2407_00243_amd as tf
+    from gpu_util import Case
+    A = ti.random_local_csr(n, 5, 5, 0.0, dtype, 31, int_values=True, empty_row_prob=0.0)
+    B, C = ti.dense_small_int(n, bcol, dtype, 5), ti.dense_small_int(bcol, ccol, dtype, 6)
+    c = Case(ti.Problem("chain", "gemm_spmm", np.dtype(dtype), A, B, C))
+    try:
+        assert c.plan.schedule()["execution"] == tf.TF_EXECUTE_ONE_PASS
+        assert np.array_equal(c.run().astype(np.float64), oracle.chain(A, B, C)[0])
+    finally:
+        c.close()
