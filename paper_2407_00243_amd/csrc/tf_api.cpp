@@ -104,6 +104,8 @@ struct tf_plan {
         int64_t n_units = 0;
         bool sorted = false;
         int32_t rows_per_pass = 1;
+        size_t partial_at = 0;             // bytes into the plan's workspace: sums of the pieces of cut rows
+        void *arrived = nullptr;           // counts of those done
         tf::PackDev dev() const {
             tf::PackDev d;
             d.units = static_cast<const tf::UnitDesc *>(units);
@@ -154,14 +156,20 @@ void add_pack(Arena &arena, tf_plan::PackBufs &b, const tf::RowPack &pk) {
     arena.add(pk.rows, b.rows);
     arena.add(pk.idx32, b.idx);
     arena.add(pk.vals, b.vals);
+    if (!pk.arrived.empty()) arena.add(pk.arrived, b.arrived);
     b.n_units = (int64_t)pk.units.size();
     b.sorted = pk.sorted;
     b.rows_per_pass = pk.rows_per_pass;
+}
+// Bytes for the sums of the rows that are cut over several units of the pack, operand rows in `lay`.
+size_t partial_bytes(const tf::RowPack &pk, const tf::D1Layout &lay, int es) {
+    return ((size_t)pk.n_pieces * lay.n_sl * lay.sw * es + 255) / 256 * 256;
 }
 // the packed entries live on the device from here on; the row lists stay for the schedule view
 void drop_entries(tf::RowPack &pk) {
     tf::RawVec<int32_t>().swap(pk.idx32);
     tf::RawVec<unsigned char>().swap(pk.vals);
+    std::vector<int32_t>().swap(pk.arrived);
 }
 
 // column -> (slice, offset inside the slice) of a workspace: a shift and a mask; with one slice the
@@ -223,6 +231,8 @@ tf::PackedSpmmLaunch packed_args(const tf_plan *p, const tf_plan::PackBufs &b, c
     w.ldx = lay.sw;
     w.x_slice_stride = lay.slice_stride();
     w.rows_per_pass = b.rows_per_pass;
+    w.partial = static_cast<char *>(p->d1.p) + b.partial_at;
+    w.arrived = static_cast<int32_t *>(b.arrived);
     w.Y = D;
     w.ccol = (int32_t)p->ccol;
     return w;
@@ -614,8 +624,19 @@ tf_status tf_plan_create(const tf_csr *A, int64_t bCol, int64_t cCol, int32_t b_
             arena.add(sc.chain.vals, p->chain_vals);
             p->chain_zeros = sc.chain.vals.size() - tf::kChainZeroRows * tf::kChainRowBytes;
         }
+        // behind the rows of the workspace: the sums of cut rows, for each pack (B is gathered whole, and with
+        // `all` only where its rows take as many lanes as a slice of D1 does)
+        tf::D1Layout y = sc.d1;
+        if (sc.gather_first) {
+            y.n_sl = 1;
+            y.sw = (int32_t)bCol;
+        }
+        const bool y_wider = sc.gather_first_shares && y.sw > sc.d1.n_sl * sc.d1.sw;
+        p->wf1.partial_at = ((size_t)sc.d1.elements() * es + 255) / 256 * 256;
+        p->all.partial_at = p->wf1.partial_at + partial_bytes(sc.wf1, sc.d1, es);
+        p->gf.partial_at = p->all.partial_at + partial_bytes(sc.all, y_wider ? y : sc.d1, es);
         hipError_t e = arena.upload(p->arrays);
-        if (e == hipSuccess) e = p->d1.alloc((size_t)sc.d1.elements() * es);
+        if (e == hipSuccess) e = p->d1.alloc(p->gf.partial_at + partial_bytes(sc.gf, y, es));
         if (e == hipSuccess && sc.plain_pair) e = p->d1_pair.alloc((size_t)p->unf_layout().elements() * es);
         if (e != hipSuccess) return hip_fail(e, "allocating the plan's device memory");
         sc.tile_meta.reset();

@@ -65,6 +65,7 @@ struct PackRules {
     int max_rows;        // most rows per unit
     int64_t max_slots;   // most padded entries per unit
     int split_groups;    // lane groups available for splitting long rows; 0 = never split
+    int64_t cut_slots;   // longer rows are cut into pieces of at most that many slots, one per unit
 };
 
 int pow2_at_least(int64_t x) {
@@ -166,6 +167,25 @@ void pack_rows(const int32_t *rowptr, const int32_t *colidx, const unsigned char
         const int64_t len0 = len(list[pos]);
         int64_t L = len0;
         int64_t take = 1;
+        if (rules.split_groups > 1 && len0 >= kSplitMinSlots && len0 > rules.cut_slots) {
+            const int64_t pieces = (len0 + rules.cut_slots - 1) / rules.cut_slots;
+            const int64_t slots = round_up((len0 + pieces - 1) / pieces, 4);      // (each starts at a multiple of four)
+            u.n_rows = 1;
+            u.split = rules.split_groups;
+            u.first_piece = out.n_pieces;
+            u.cut_row = out.n_cut_rows++;
+            u.pieces = (int32_t)((len0 + slots - 1) / slots);
+            for (int32_t k = 0; k < u.pieces; ++k) {
+                u.slots = (int32_t)std::min(slots, len0 - k * slots);
+                u.piece = out.n_pieces++;
+                out.units.push_back(u);
+                u.entry_base += slots;
+            }
+            at = (at + len0 + 3) / 4 * 4;
+            ++pos;
+            continue;
+        }
+        u.pieces = 1;
         if (rules.split_groups > 1 && len0 >= kSplitMinSlots) {
             int split = pow2_at_least((len0 + kSplitPartSlots - 1) / kSplitPartSlots);
             split = std::min(split, rules.split_groups);
@@ -193,6 +213,7 @@ void pack_rows(const int32_t *rowptr, const int32_t *colidx, const unsigned char
         at = (at + take * L + 3) / 4 * 4;
         pos += take;
     }
+    out.arrived.assign((size_t)out.n_cut_rows * kXcds, 0);
     const int64_t end = at + kPackSpareSlots;         // spare zero entries behind the last unit
     out.idx32.resize((size_t)end);
     out.vals.resize((size_t)end * es);
@@ -209,7 +230,13 @@ void pack_rows(const int32_t *rowptr, const int32_t *colidx, const unsigned char
         unsigned char *vp = out.vals.data() + (size_t)u.entry_base * es;
         for (int64_t q = 0; q < u.n_rows; ++q) {
             const int32_t j = out.rows[(size_t)u.row_begin + (size_t)q];
-            const int64_t k0 = rowptr[j], ln = len(j);
+            int64_t k0 = rowptr[j], ln = len(j);
+            if (u.pieces > 1) {
+                // (all pieces of a row but the last have the same length)
+                const int32_t p = u.piece - u.first_piece;
+                k0 = p + 1 < u.pieces ? k0 + p * L : k0 + ln - L;
+                ln = L;
+            }
             for (int64_t sl = 0; sl < ln; ++sl) *ip++ = (int32_t)local(colidx[k0 + sl]);
             std::memcpy(vp, vals + (size_t)k0 * es, (size_t)ln * es);
             // padding repeats the last entry's index with value 0 (units of empty rows have L = 0)
@@ -316,12 +343,14 @@ TileBlock pack_tile(const int32_t *rowptr, const int32_t *colidx, const unsigned
 // Units of a packed row list of `count` rows: a unit is one workgroup; short lists are cut into
 // smaller units (down to one row per lane group) so that they still spread over the machine.
 static PackRules pack_rules(const InspectorInput &in, int64_t count, int sw) {
-    const int groups = kSpmmThreads / lane_group(sw, lane_elems(in.dtype, in.ccol, sw));
+    const int elems = lane_elems(in.dtype, in.ccol, sw), groups = kSpmmThreads / lane_group(sw, elems);
     const int64_t want = std::min<int64_t>(kUnitRows, (count + 1023) / 1024);
     // whole passes of the lane groups: a power of two of rows for each
     int rows = groups;
     while (2 * rows <= want) rows *= 2;
-    return PackRules{std::min(rows, kUnitRows), kUnitSlots, groups};
+    // (rows wider than a wave's load: pieces as much longer, so that their sums take no more memory than entries)
+    const int64_t cut = (int64_t)groups * kCutSlots * ((sw + 64 * elems - 1) / (64 * elems));
+    return PackRules{std::min(rows, kUnitRows), kUnitSlots, groups, cut};
 }
 
 // The gather kernel stages the entries of a unit whose rows are not split in LDS arrays of
@@ -964,7 +993,8 @@ tf_status build_schedule(const InspectorInput &in, Schedule &s, std::string &err
     }
     s.wf1_rows = s.wf1.rows;
     s.wf1_unit_ptr.clear();
-    for (const UnitDesc &u : s.wf1.units) s.wf1_unit_ptr.push_back(u.row_begin);
+    for (const UnitDesc &u : s.wf1.units)
+        if (u.piece == u.first_piece) s.wf1_unit_ptr.push_back(u.row_begin);     // (a cut row is one unit there)
     s.wf1_unit_ptr.push_back((int32_t)s.wf1_rows.size());
     TF_TICK("second-wavefront units");
     return TF_OK;

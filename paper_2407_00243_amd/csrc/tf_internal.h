@@ -26,6 +26,12 @@ constexpr int kPackSpareSlots = 8 * 64 + 8;  // zero entries behind the last uni
                                          // group (64 lanes at most), which may reach that far past the last row
 constexpr int kSplitMinSlots = 128;      // rows at least this long are split over several lane groups
 constexpr int kSplitPartSlots = 96;      // target slots per part of a split row
+// Slots per lane group beyond which a row is cut over several workgroups: eight round trips to memory, one
+// after the other, of eight gathers each.  The hub of a graph in one workgroup is the longest chain of the
+// launch: R-MAT graph of 100003 rows, fp64, rows of 64 columns, 94 us, cut 71; 150000 rows, fp32, 41 columns
+// 66 / 52; 30000 rows, fp32, 64 columns 19.8 / 10.8; 2^20 rows, 32 columns 192 / 177.  (At 48, 96 and 192 slots
+// a few per cent either way.)
+constexpr int kCutSlots = 64;
 // a row long enough to be split gets at least two parts: units whose rows are not split are staged
 // in LDS whole (kUnitSlots entries at most), so a row that long must never end up in one
 static_assert(kSplitMinSlots > kSplitPartSlots && kSplitMinSlots <= kUnitSlots,
@@ -200,13 +206,18 @@ inline int64_t fused_lds_bytes(int dtype, int b_is_sparse, int bcol, int ccol, i
 
 // One unit of a packed row list: n_rows rows, all padded to `slots` entries, stored row after
 // row from entry_base on.  split > 1: every row is shared by `split` lane groups, each summing
-// a contiguous part of the slots.
+// a contiguous part of the slots.  pieces > 1: the unit holds a piece of one row that is cut over that
+// many consecutive units (and split over all lane groups of each).
 struct UnitDesc {
     int64_t entry_base;
     int32_t row_begin;    // position of the unit's first row in the list
     int32_t n_rows;
     int32_t slots;
     int32_t split;
+    int32_t pieces;
+    int32_t piece;        // number of the piece, over all cut rows of the list
+    int32_t first_piece;  // of the same row
+    int32_t cut_row;      // number of the cut row
 };
 
 // A list of rows of A re-packed for the gather kernels: per unit a uniform padded row length,
@@ -232,6 +243,8 @@ struct RowPack {
     RawVec<unsigned char> vals;          // packed values, element size of the plan's dtype
     bool sorted = false;                 // rows were re-ordered by length
     int32_t rows_per_pass = 1;           // rows that a lane group of the gather kernel works on at a time
+    int32_t n_pieces = 0, n_cut_rows = 0;  // rows cut over several units
+    std::vector<int32_t> arrived;        // zeros: a count per cut row and slice (at most kXcds)
     int64_t entries() const { return (int64_t)idx32.size(); }
 };
 
@@ -464,6 +477,8 @@ struct PackedSpmmLaunch {
     int64_t x_slice_stride;           // elements between the slices of X
     int32_t ldx;                      // elements between the rows of a slice
     int32_t rows_per_pass;            // R of the kernel instantiation: 1, 2 or 4
+    void *partial;                    // sums of the pieces of cut rows: [piece][slice][sw]
+    int32_t *arrived;                 // pieces of a cut row that are done: [cut row][slice], zeros between launches
     void *Y;                          // row-major, ccol columns
     int32_t ccol;
 };

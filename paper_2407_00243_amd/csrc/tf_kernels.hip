@@ -1349,10 +1349,54 @@ __global__ __launch_bounds__(kSpmmThreads) void k_packed_spmm(const PackedSpmmLa
                 for (int pp = 0; pp < d.split; ++pp)
 #pragma unroll
                     for (int i = 0; i < VV; ++i) sum[i] += red[((grp + pp) * G + gl) * VV + i];
-                store_any<T, VV>(Y + (int64_t)rows[d.row_begin + row_i] * ccol + col, sum);
+                if (d.pieces > 1) {
+                    T *p = static_cast<T *>(a.partial) + ((int64_t)d.piece * a.n_xs + slice) * a.sw + col;
+#pragma unroll
+                    for (int i = 0; i < VV; ++i) __hip_atomic_store(p + i, sum[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                } else {
+                    store_any<T, VV>(Y + (int64_t)rows[d.row_begin + row_i] * ccol + col, sum);
+                }
             }
             __syncthreads();
         }
+    }
+    if (d.pieces <= 1) return;
+    // A row cut over several workgroups: whoever is done last adds up the sums of all pieces, in their order.
+    // The sums go past the L2 (device-scope stores and loads), and are there before the count is raised.
+    __shared__ int32_t done_s;
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    int32_t *arrived = a.arrived + (int64_t)d.cut_row * a.n_xs + slice;
+    if (threadIdx.x == 0)
+        done_s = __hip_atomic_fetch_add(arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (done_s != d.pieces - 1) return;
+    if (threadIdx.x == 0) __hip_atomic_store(arrived, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int cb = 0; cb < w; cb += G * VV) {
+        const bool active = cb + VV * gl < w;
+        const int col = min(cb + VV * gl, w - VV);
+        T acc[VV];
+#pragma unroll
+        for (int i = 0; i < VV; ++i) acc[i] = T(0);
+        const T *p = static_cast<const T *>(a.partial) + ((int64_t)d.first_piece * a.n_xs + slice) * a.sw + col;
+        for (int k = grp; k < d.pieces; k += ngrp) {
+            const T *pk = p + (int64_t)k * a.n_xs * a.sw;
+#pragma unroll
+            for (int i = 0; i < VV; ++i) acc[i] += __hip_atomic_load(pk + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+#pragma unroll
+        for (int i = 0; i < VV; ++i) red[(grp * G + gl) * VV + i] = acc[i];
+        __syncthreads();
+        if (grp == 0 && active) {
+            T sum[VV];
+#pragma unroll
+            for (int i = 0; i < VV; ++i) sum[i] = T(0);
+            for (int g = 0; g < min(ngrp, d.pieces); ++g)
+#pragma unroll
+                for (int i = 0; i < VV; ++i) sum[i] += red[(g * G + gl) * VV + i];
+            store_any<T, VV>(Y + (int64_t)rows[d.row_begin] * ccol + col, sum);
+        }
+        __syncthreads();
     }
 }
 

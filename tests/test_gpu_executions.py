@@ -134,3 +134,34 @@ def test_column_groups_of_the_one_pass_chain_over_workgroups(dtype, bcol, ccol, 
         assert np.array_equal(c.run().astype(np.float64), oracle.chain(A, B, C)[0])
     finally:
         c.close()
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("kind,bcol,ccol,slices", [
+    ("spmm", 0, 64, 1), ("spmm", 0, 64, 2), ("spmm", 0, 30, 0), ("spmm", 0, 300, 0), ("gemm", 128, 41, 0),
+    ("gemm", 128, 128, 4), ("gemm", 32, 92, 0)])
+def test_rows_cut_over_several_workgroups(dtype, kind, bcol, ccol, slices):
+    """Rows around every length at which a row is split over the lane groups of a workgroup, and cut over
+    several workgroups (64 entries for each lane group of 256 threads), in the second wavefront, in Y = A B and
+    in the unfused second operation.  The counts of the pieces are back at zero after every run."""
+    from gpu_util import Case
+    n = 30011
+    rng = np.random.default_rng(12)
+    lens = rng.integers(0, 9, n)
+    hubs = [64 * g + d for g in (4, 8, 16, 32, 64) for d in (-1, 0, 1, 3)] + [127, 128, 129, 6001, 12345, 20000]
+    lens[rng.permutation(n)[:len(hubs)]] = hubs
+    rowptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    colidx = rng.integers(0, n, rowptr[-1]).astype(np.int32)
+    A = ti.Csr(n, n, rowptr, colidx, rng.integers(-2, 3, colidx.size).astype(dtype))
+    sparse = kind == "spmm"
+    B = ti.random_local_csr(n, 50, 4, 0.0, dtype, 22, int_values=True) if sparse else ti.dense_small_int(n, bcol, dtype, 5)
+    C = ti.dense_small_int(n if sparse else bcol, ccol, dtype, 6)
+    D_ref, _ = oracle.chain(A, B, C)
+    c = Case(ti.Problem("hubs", kind + "_spmm", np.dtype(dtype), A, B, C), gather_slices=slices)
+    try:
+        s = c.plan.schedule()
+        assert np.array_equal(np.unique(s["wf1_unit_ptr"]), s["wf1_unit_ptr"])      # a cut row is in one unit
+        for fused in (True, True, False, True, False):
+            assert np.array_equal(c.run(fused).astype(np.float64), D_ref)
+    finally:
+        c.close()
