@@ -39,23 +39,20 @@ struct DevBuf {
     hipError_t alloc(size_t bytes) { return hipMalloc(&p, bytes ? bytes : 16); }
 };
 
-// Arrays that live and die together.  Small ones share one device allocation and one copy; large ones
-// have their own (a plan of 150 MB took 9 ms longer to make out of one allocation).
+// Arrays that live and die together.  Small ones share one device allocation and one copy; large ones have
+// their own (a plan of 150 MB took 9 ms longer to make out of one allocation).
 struct Arena {
+    static constexpr size_t kSmall = (size_t)64 << 10;
     struct Item {
         const void *src;
-        size_t bytes, at;
+        size_t bytes;
         void **dst;
     };
     std::vector<Item> items;
-    size_t total = 0;
     template <typename V, typename A> void add(const std::vector<V, A> &v, void *&dst) {
         add(v.data(), v.size() * sizeof(V), dst);
     }
-    void add(const void *src, size_t bytes, void *&dst) {
-        items.push_back(Item{src, bytes, total, &dst});
-        total += (bytes + 271) / 256 * 256;            // (never empty, 256-byte aligned)
-    }
+    void add(const void *src, size_t bytes, void *&dst) { items.push_back(Item{src, bytes, &dst}); }
     hipError_t upload(std::vector<std::unique_ptr<DevBuf>> &bufs) {
         auto alloc = [&](size_t bytes, void *&p) {
             bufs.emplace_back(new DevBuf);
@@ -64,19 +61,26 @@ struct Arena {
             return e;
         };
         hipError_t e = hipSuccess;
-        if (total <= ((size_t)4 << 20)) {
-            void *base = nullptr;
-            if ((e = alloc(total, base)) != hipSuccess) return e;
-            std::vector<char> host(total);
-            for (const Item &i : items) {
-                *i.dst = static_cast<char *>(base) + i.at;
-                if (i.bytes) std::memcpy(host.data() + i.at, i.src, i.bytes);
-            }
-            return total ? hipMemcpy(base, host.data(), total, hipMemcpyHostToDevice) : e;
-        }
+        size_t total = 0, shared = 0;
+        for (const Item &i : items) total += i.bytes;
+        const size_t small = total <= ((size_t)4 << 20) ? total : kSmall;
+        for (const Item &i : items)
+            if (i.bytes <= small) shared += (i.bytes + 271) / 256 * 256;       // (never empty, 256-byte aligned)
+        std::vector<char> host(shared);
+        void *base = nullptr;
+        if (shared && (e = alloc(shared, base)) != hipSuccess) return e;
+        size_t at = 0;
         for (const Item &i : items) {
+            if (i.bytes > small) continue;
+            *i.dst = static_cast<char *>(base) + at;
+            if (i.bytes) std::memcpy(host.data() + at, i.src, i.bytes);
+            at += (i.bytes + 271) / 256 * 256;
+        }
+        if (shared && (e = hipMemcpy(base, host.data(), shared, hipMemcpyHostToDevice)) != hipSuccess) return e;
+        for (const Item &i : items) {
+            if (i.bytes <= small) continue;
             if ((e = alloc(i.bytes, *i.dst)) != hipSuccess) return e;
-            if (i.bytes && (e = hipMemcpy(*i.dst, i.src, i.bytes, hipMemcpyHostToDevice)) != hipSuccess) return e;
+            if ((e = hipMemcpy(*i.dst, i.src, i.bytes, hipMemcpyHostToDevice)) != hipSuccess) return e;
         }
         return e;
     }
@@ -100,18 +104,20 @@ struct tf_plan {
     }
     double plan_seconds = 0.0;
     struct PackBufs {
-        void *units = nullptr, *rows = nullptr, *idx = nullptr, *vals = nullptr;
-        int64_t n_units = 0;
+        void *blocks = nullptr, *rows = nullptr, *lens = nullptr, *idx = nullptr, *vals = nullptr, *cuts = nullptr;
+        int32_t n_blocks = 0, n_cut_blocks = 0;
         bool sorted = false;
-        int32_t rows_per_pass = 1;
         size_t partial_at = 0;             // bytes into the plan's workspace: sums of the pieces of cut rows
         void *arrived = nullptr;           // counts of those done
         tf::PackDev dev() const {
             tf::PackDev d;
-            d.units = static_cast<const tf::UnitDesc *>(units);
+            d.blocks = static_cast<const tf::GatherBlock *>(blocks);
             d.rows = static_cast<const int32_t *>(rows);
-            d.idx = idx;
+            d.lens = static_cast<const int32_t *>(lens);
+            d.idx = static_cast<const int32_t *>(idx);
             d.vals = vals;
+            d.cuts = static_cast<const tf::CutBlock *>(cuts);
+            d.n_cut_blocks = n_cut_blocks;
             return d;
         }
     };
@@ -152,14 +158,18 @@ tf_status check_csr_host(int64_t n_rows, int64_t n_cols, int64_t nnz, const int3
 }
 
 void add_pack(Arena &arena, tf_plan::PackBufs &b, const tf::RowPack &pk) {
-    arena.add(pk.units, b.units);
+    arena.add(pk.blocks, b.blocks);
     arena.add(pk.rows, b.rows);
+    arena.add(pk.lens, b.lens);
     arena.add(pk.idx32, b.idx);
     arena.add(pk.vals, b.vals);
-    if (!pk.arrived.empty()) arena.add(pk.arrived, b.arrived);
-    b.n_units = (int64_t)pk.units.size();
+    if (!pk.cuts.empty()) {
+        arena.add(pk.cuts, b.cuts);
+        arena.add(pk.arrived, b.arrived);
+    }
+    b.n_blocks = (int32_t)pk.blocks.size();
+    b.n_cut_blocks = (int32_t)pk.cuts.size();
     b.sorted = pk.sorted;
-    b.rows_per_pass = pk.rows_per_pass;
 }
 // Bytes for the sums of the rows that are cut over several units of the pack, operand rows in `lay`.
 size_t partial_bytes(const tf::RowPack &pk, const tf::D1Layout &lay, int es) {
@@ -170,6 +180,8 @@ void drop_entries(tf::RowPack &pk) {
     tf::RawVec<int32_t>().swap(pk.idx32);
     tf::RawVec<unsigned char>().swap(pk.vals);
     std::vector<int32_t>().swap(pk.arrived);
+    std::vector<int32_t>().swap(pk.lens);
+    std::vector<tf::GatherBlock>().swap(pk.blocks);
 }
 
 // column -> (slice, offset inside the slice) of a workspace: a shift and a mask; with one slice the
@@ -220,7 +232,8 @@ tf::PackedSpmmLaunch packed_args(const tf_plan *p, const tf_plan::PackBufs &b, c
                                  const tf::D1Layout &lay, void *D) {
     tf::PackedSpmmLaunch w{};
     w.dtype = p->dtype;
-    w.n_units = b.n_units;
+    w.n_blocks = b.n_blocks;
+    w.n_cu = p->n_cu;
     w.contiguous = b.sorted ? 0 : 1;
     // operand offsets inside a slice are formed in 32 bits unless the slice spans 4 GiB or more
     w.wide = (double)lay.slice_stride() * tf::elem_size(p->dtype) >= 4294967296.0 ? 1 : 0;
@@ -230,7 +243,6 @@ tf::PackedSpmmLaunch packed_args(const tf_plan *p, const tf_plan::PackBufs &b, c
     w.sw = lay.sw;
     w.ldx = lay.sw;
     w.x_slice_stride = lay.slice_stride();
-    w.rows_per_pass = b.rows_per_pass;
     w.partial = static_cast<char *>(p->d1.p) + b.partial_at;
     w.arrived = static_cast<int32_t *>(b.arrived);
     w.Y = D;
@@ -379,6 +391,7 @@ tf_status run_gather_first(const tf_plan *p, const void *B, const void *C, void 
     y.rows = p->n;
     tf::PackedSpmmLaunch w = packed_args(p, p->s.gather_first_shares ? p->all : p->gf, B, y, ws);
     w.ccol = (int32_t)p->bcol;
+    w.read_next = 1;
     int e = tf::launch_packed_spmm(w, stream);
     if (e) return hip_fail((hipError_t)e, "launching the SpMM");
     tf::GemmLaunch g{};
@@ -586,8 +599,7 @@ tf_status tf_plan_create(const tf_csr *A, int64_t bCol, int64_t cCol, int32_t b_
             *out = p;
             return TF_OK;
         }
-        if ((p->has_baseline || sc.plain_pair) && !tf::build_baseline_pack(in, sc))
-            return fail(TF_EUNSUPPORTED, "internal: a unit of the baseline exceeds the staging arrays of the gather kernel");
+        if (p->has_baseline || sc.plain_pair) tf::build_baseline_pack(in, sc);
         // the launch must fit the device whatever the schedule's own estimate said
         auto launch_lds = [&]() {
             return tf::fused_lds_bytes(p->dtype, p->b_is_sparse, (int)bCol, (int)cCol, p->s.col_slice,
@@ -598,8 +610,7 @@ tf_status tf_plan_create(const tf_csr *A, int64_t bCol, int64_t cCol, int32_t b_
         if (launch_lds() > lds_limit) p->s.second_block_in_lds = false;
         if (launch_lds() > lds_limit)
             return fail(TF_EUNSUPPORTED, "a tile does not fit the LDS of this device");
-        if (sc.gather_first && !tf::build_gather_first(in, sc, p->has_baseline))
-            return fail(TF_EUNSUPPORTED, "internal: a unit exceeds the staging arrays of the gather kernel");
+        if (sc.gather_first) tf::build_gather_first(in, sc, p->has_baseline);
         Arena arena;
         arena.add(sc.tile_desc, p->tile_desc);
         arena.add(sc.tile_meta.get(), sc.tile_meta_bytes, p->tile_meta);

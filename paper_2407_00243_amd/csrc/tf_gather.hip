@@ -1,0 +1,331 @@
+// Y = A X over a packed list of rows of A (RowPack): the second wavefront, the second operation of the unfused
+// baseline and of the plain pair, and Y = A B of the gather-first order.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <type_traits>
+
+#include "tf_device.h"
+
+namespace tf {
+namespace {
+
+// X is the D1 workspace (n_xs column slices of sw columns; idx is a slot) or a dense B (one slice).
+//
+// A wave owns a block of 64 / G virtual rows at a time (a row, or one of the 2^k parts that the rows of the
+// block are cut into), G neighbouring lanes each; a lane holds 16 bytes of its row's columns.  The block's
+// entries are gathered in passes of E per row: fetched a pass ahead with one coalesced load per 64 of them,
+// turned into byte offsets of rows of X on the way to LDS (once per entry, not once per lane), read back
+// from there by the lanes of their row.  Workgroups stay for all blocks of their share, four at a time, one
+// for each wave; no barrier is passed, and the first gathers of the next block are on their way before a
+// block's sums are stored.
+//
+// Slices: every XCD takes n_xs eighths of the blocks, of at most two slices, one after the other; an XCD's L2
+// then holds sw-wide pieces of the hot rows instead of whole rows, and the eight caches hold different data.
+// Blocks in the order of the rows (contiguous): an eighth is a range of blocks, through which the XCD's
+// workgroups move side by side; blocks sorted by their slots are dealt back and forth, longest first.
+//
+// A row too long for one block takes the four blocks of a workgroup, whose waves add up their sums through LDS
+// (the blocks of such rows come first), or several times that: these sums go past the L2 (device-scope stores
+// and loads) and are there before the count of finished pieces is raised; the workgroup that is done last adds
+// them up in their order.
+template <typename T, int VV, int G, bool WIDE>
+__global__ __launch_bounds__(kSpmmThreads, gather_waves(dtype_of<T>())) void k_packed_spmm(
+    const PackedSpmmLaunch a, const GatherBlock *__restrict__ blocks, const int32_t *__restrict__ rows,
+    const int32_t *__restrict__ lens, const int32_t *__restrict__ idx, const T *__restrict__ val,
+    const CutBlock *__restrict__ cuts, const T *__restrict__ X0, T *Y0) {
+    constexpr int E = kGatherEntries, NR = 64 / G, NE = NR * E > 64 ? NR * E / 64 : 1;
+    typedef std::conditional_t<WIDE, uint64_t, uint32_t> Off;
+    typedef T Vec16 __attribute__((ext_vector_type(Tr<T>::V)));
+    typedef std::conditional_t<VV == 1, T, Vec16> X16;                          // a lane's columns of a row,
+    typedef std::conditional_t<VV == 1, T, typename Piece16<T>::Vec> XAny;      // in device memory
+    auto part = [](const X16 &x, int i) __attribute__((always_inline)) {
+        if constexpr (VV == 1) return x;
+        else return x[i];
+    };
+    __shared__ __align__(16) Off off_s[kSpmmThreads / 64][NR * E];
+    __shared__ __align__(16) T val_s[kSpmmThreads / 64][NR * E];
+    __shared__ __align__(16) T sum_s[kSpmmThreads / 64][G * VV];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int gl = lane % G, v = lane / G;
+    Off *off_w = off_s[wave];
+    T *val_w = val_s[wave];
+    const Off row_bytes = (Off)a.ldx * (Off)sizeof(T);
+    // (quads: the blocks of a workgroup)
+    const int n_wg = (int)(gridDim.x / kXcds), my = (int)(blockIdx.x / kXcds);
+    const int n_quads = a.n_blocks / kGatherQuad, eighth = (n_quads + kXcds - 1) / kXcds;
+    const int n_cb = (a.sw + G * VV - 1) / (G * VV);        // column blocks of a slice (rows wider than a wave's load)
+
+    int32_t ci[NE];
+    T vi[NE];
+    auto fetch = [&](uint32_t slot) __attribute__((always_inline)) {
+        const int64_t at = (int64_t)slot * NR + (lane & (NR * E - 1));
+#pragma unroll
+        for (int k = 0; k < NE; ++k) ci[k] = idx[at + 64 * k];
+#pragma unroll
+        for (int k = 0; k < NE; ++k) vi[k] = val[at + 64 * k];
+    };
+    auto put = [&]() __attribute__((always_inline)) {
+        if (NR * E >= 64 || lane < NR * E) {
+#pragma unroll
+            for (int k = 0; k < NE; ++k) {
+                const int l = lane + 64 * k, to = l % NR * E + l / NR;
+                off_w[to] = (Off)(uint32_t)ci[k] * row_bytes;
+                val_w[to] = vi[k];
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+    };
+
+    for (int at = (int)(blockIdx.x % kXcds) * a.n_xs, left = a.n_xs; left > 0;) {
+        const int slice = at / kXcds, e0 = at % kXcds, n_e = min(left, kXcds - e0);
+        at += n_e;
+        left -= n_e;
+        const int w = min(a.sw, a.ccol - slice * a.sw);     // columns of this slice
+        // quad of the workgroup's k-th round: the XCD's quads in their order, or dealt back and forth
+        const int end = a.contiguous ? min(n_quads, (e0 + n_e) * eighth) : n_quads;
+        auto quad_of = [&](int k) __attribute__((always_inline)) {
+            if (a.contiguous) return e0 * eighth + k * n_wg + my;
+            const int j = k * n_wg + (k & 1 ? n_wg - 1 - my : my);
+            return j / n_e * kXcds + e0 + j % n_e;
+        };
+        for (int cb = 0; cb < n_cb && cb * G * VV < w; ++cb) {
+            const bool active = cb * G * VV + VV * gl < w;
+            const int col = min(cb * G * VV + VV * gl, w - VV);
+            const char *__restrict__ X = reinterpret_cast<const char *>(X0 + (int64_t)slice * a.x_slice_stride);
+            const Off lane_bytes = (Off)col * (Off)sizeof(T);
+            T *Yl = Y0 + slice * a.sw + col;
+
+            X16 x[E];
+            T acc[VV];
+            auto issue = [&](int n) __attribute__((always_inline)) {
+                Off o[E];
+#pragma unroll
+                for (int e = 0; e < E; e += 16 / (int)sizeof(Off))
+                    load_pack<Off, 16 / (int)sizeof(Off)>(*reinterpret_cast<Off(*)[16 / sizeof(Off)]>(&o[e]), off_w + v * E + e);
+                // (all offsets in one trip to LDS; what x held is dead: said so, or the compiler keeps it beside what is
+                // loaded)
+#pragma unroll
+                for (int e = 0; e < E; ++e) asm volatile("" : "+v"(o[e]));
+#pragma unroll
+                for (int e = 0; e < E; ++e) asm volatile("" : "=v"(x[e]));
+#pragma unroll
+                for (int e = 0; e < E; ++e)
+                    if (e < n) x[e] = *reinterpret_cast<const XAny *>(X + (Off)(o[e] + lane_bytes));
+            };
+            // n_real: entries of the lane's row among the pass's; what lies beyond adds nothing, whatever X holds
+            auto consume = [&](bool whole, int n_real) __attribute__((always_inline)) {
+                T f[E];
+#pragma unroll
+                for (int e = 0; e < E; e += Tr<T>::V)
+                    load_pack<T, Tr<T>::V>(*reinterpret_cast<T(*)[Tr<T>::V]>(&f[e]), val_w + v * E + e);
+                if (whole) {
+#pragma unroll
+                    for (int e = 0; e < E; ++e)
+#pragma unroll
+                        for (int i = 0; i < VV; ++i) acc[i] += f[e] * part(x[e], i);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < E; ++e)
+#pragma unroll
+                        for (int i = 0; i < VV; ++i) acc[i] += (e < n_real ? f[e] : T(0)) * (e < n_real ? part(x[e], i) : T(0));
+                }
+                __builtin_amdgcn_wave_barrier();
+            };
+            auto slots = [](const GatherBlock &b) { return (int)(b.size & 0xffff); };
+            auto row_at = [&](const GatherBlock &b) __attribute__((always_inline)) {
+                const int each = (b.info >> 3) & 7;
+                const int at = each ? v * gather_short_rows(each, G) + gl % gather_short_rows(each, G) : v >> (b.info & 7);
+                return b.row_begin + max(0, min(at, (int)(b.info >> 6) - 1));
+            };
+            auto put_row = [&](int32_t row, const T(&v)[VV]) __attribute__((always_inline)) {
+                XAny y;
+                if constexpr (VV == 1) y = v[0];
+                else
+#pragma unroll
+                    for (int i = 0; i < VV; ++i) y[i] = v[i];
+                XAny *to = reinterpret_cast<XAny *>(Yl + (int64_t)row * a.ccol);
+                // (a Y that is not read again soon passes through the L2: what it would evict there is)
+                if (a.read_next) *to = y;
+                else __builtin_nontemporal_store(y, to);
+            };
+            auto finish = [&](const GatherBlock &b, int32_t row, int at_block) __attribute__((always_inline)) {
+                const int slog = (int)(b.info & 7);
+                for (int m = G; m < G << slog; m <<= 1) {
+#pragma unroll
+                    for (int i = 0; i < VV; ++i) acc[i] += __shfl_xor(acc[i], m, 64);
+                }
+                bool store = active && (v & ((1 << slog) - 1)) == 0 && (v >> slog) < (int)(b.info >> 6);
+                const bool cut = at_block < a.pack.n_cut_blocks;      // (the same for all four blocks of the quad)
+                if (cut) {
+                    if (v == 0) store_pack<T, VV>(&sum_s[wave][gl * VV], acc);
+                    __syncthreads();
+                    if (wave == 0) {
+#pragma unroll
+                        for (int i = 0; i < VV; ++i) acc[i] = T(0);
+                        for (int k = 0; k < kGatherQuad; ++k)
+#pragma unroll
+                            for (int i = 0; i < VV; ++i) acc[i] += sum_s[k][gl * VV + i];
+                    }
+                    __syncthreads();
+                    if (wave != 0) return;
+                }
+                if (cut && cuts[at_block].pieces > 1) {
+                    const CutBlock c = cuts[at_block];
+                    const int64_t pitch = (int64_t)a.n_xs * a.sw;
+                    T *p = static_cast<T *>(a.partial) + slice * a.sw + col;
+                    if (store) {
+#pragma unroll
+                        for (int i = 0; i < VV; ++i)
+                            __hip_atomic_store(p + c.piece * pitch + i, acc[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    }
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+                    __builtin_amdgcn_s_waitcnt(0);
+                    int32_t *arrived = a.arrived + ((int64_t)c.row * a.n_xs + slice) * n_cb + cb;
+                    int32_t done = 0;
+                    if (lane == 0)
+                        done = __hip_atomic_fetch_add(arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (__builtin_amdgcn_readfirstlane(done) != c.pieces - 1) return;
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+                    if (lane == 0) __hip_atomic_store(arrived, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+                    for (int i = 0; i < VV; ++i) acc[i] = T(0);
+                    for (int k = v; k < c.pieces; k += NR) {
+#pragma unroll
+                        for (int i = 0; i < VV; ++i)
+                            acc[i] += __hip_atomic_load(p + (c.first_piece + k) * pitch + i, __ATOMIC_RELAXED,
+                                                        __HIP_MEMORY_SCOPE_AGENT);
+                    }
+                    for (int m = G; m < 64; m <<= 1) {
+#pragma unroll
+                        for (int i = 0; i < VV; ++i) acc[i] += __shfl_xor(acc[i], m, 64);
+                    }
+                }
+                if (store) put_row(row, acc);
+            };
+            // rows of S entries, several to a lane group: the pass holds all of them
+            auto finish_short = [&](auto each, const GatherBlock &b, int32_t row) __attribute__((always_inline)) {
+                constexpr int S = decltype(each)::value, R = gather_short_rows(S, G);
+                T f[E];
+#pragma unroll
+                for (int e = 0; e < E; e += Tr<T>::V)
+                    load_pack<T, Tr<T>::V>(*reinterpret_cast<T(*)[Tr<T>::V]>(&f[e]), val_w + v * E + e);
+#pragma unroll
+                for (int k = 0; k < R; ++k) {
+                    T y[VV];
+#pragma unroll
+                    for (int i = 0; i < VV; ++i) y[i] = T(0);
+#pragma unroll
+                    for (int e = k * S; e < k * S + S; ++e)
+#pragma unroll
+                        for (int i = 0; i < VV; ++i) y[i] += f[e] * part(x[e], i);
+                    const int32_t to = __shfl(row, v * G + k, 64);
+                    if (active && v * R + k < (int)(b.info >> 6)) put_row(to, y);
+                }
+                __builtin_amdgcn_wave_barrier();
+            };
+
+            int k = 0, u = quad_of(k);
+            if (u >= end) continue;
+            int at_d = u * kGatherQuad + wave, at_n = at_d;
+            GatherBlock d = blocks[at_d], dn = d;
+            int32_t row = rows[row_at(d)], len = lens[row_at(d)];
+            fetch(d.slot_base);
+            u = quad_of(++k);
+            bool has_next = u < end;
+            if (has_next) dn = blocks[at_n = u * kGatherQuad + wave];
+            put();
+            fetch(slots(d) > E ? d.slot_base + E : dn.slot_base);
+            issue(min(E, slots(d)));
+            for (;;) {
+                u = quad_of(++k);
+                const bool has_next2 = has_next && u < end;
+                GatherBlock dnn = dn;
+                int at_nn = at_n;
+                if (has_next2) dnn = blocks[at_nn = u * kGatherQuad + wave];
+#pragma unroll
+                for (int i = 0; i < VV; ++i) acc[i] = T(0);
+                // entries of the lane's (virtual) row
+                const int n_d = slots(d), whole = (int)(d.size >> 16), skip = at_d < a.pack.n_cut_blocks ? cuts[at_d].skip : 0;
+                const int real = min(n_d, len - (v & ((1 << (d.info & 7)) - 1)) * n_d - skip);
+                const int each = (d.info >> 3) & 7;
+                if (each) {
+                    if (G >= 8 && each == 1) finish_short(std::integral_constant<int, 1>(), d, row);
+                    else if (G >= 4 && each == 2) finish_short(std::integral_constant<int, 2>(), d, row);
+                    else if (G >= 2 && each == 3) finish_short(std::integral_constant<int, 3>(), d, row);
+                    else if (G >= 2) finish_short(std::integral_constant<int, 4>(), d, row);
+                } else {
+                    consume(whole >= E, real);
+                }
+                for (int s0 = E; s0 < n_d; s0 += E) {
+                    put();
+                    fetch(s0 + E < n_d ? d.slot_base + s0 + E : dn.slot_base);
+                    issue(min(E, n_d - s0));
+                    consume(whole >= s0 + E, real - s0);
+                }
+                // the next block's first gathers go out before this one's sums are stored (none after the last)
+                put();
+                const int32_t row_n = rows[row_at(dn)], len_n = lens[row_at(dn)];
+                fetch(slots(dn) > E ? dn.slot_base + E : dnn.slot_base);
+                issue(has_next ? min(E, slots(dn)) : 0);
+                if (!each) finish(d, row, at_d);
+                if (!has_next) break;
+                d = dn;
+                dn = dnn;
+                at_d = at_n;
+                at_n = at_nn;
+                row = row_n;
+                len = len_n;
+                has_next = has_next2;
+            }
+        }
+    }
+}
+
+template <typename T, int VV, int G, bool WIDE> int run_packed(const PackedSpmmLaunch &a, hipStream_t st) {
+    static const int wg_per_cu = resident_per_cu(k_packed_spmm<T, VV, G, WIDE>, kSpmmThreads, 0, 8);
+    const int64_t quads = ((int64_t)a.n_blocks / kGatherQuad + kXcds - 1) / kXcds * a.n_xs;        // of an XCD
+    const int64_t per_xcd = std::min<int64_t>(quads, std::max(1, a.n_cu / kXcds) * (int64_t)wg_per_cu);
+    (void)hipGetLastError();      // an error left by an earlier, unrelated call is not this launch's
+    k_packed_spmm<T, VV, G, WIDE><<<dim3((unsigned)(per_xcd * kXcds)), dim3(kSpmmThreads), 0, st>>>(
+        a, a.pack.blocks, a.pack.rows, a.pack.lens, a.pack.idx, static_cast<const T *>(a.pack.vals), a.pack.cuts,
+        static_cast<const T *>(a.X), static_cast<T *>(a.Y));
+    return (int)hipGetLastError();
+}
+
+template <typename T, bool WIDE> int run_packed_group(const PackedSpmmLaunch &a, hipStream_t st) {
+    constexpr int V = Tr<T>::V;
+    const int elems = lane_elems(a.dtype, a.ccol, a.sw);
+    const int group = lane_group(a.sw, elems);
+    if (elems == 1) {
+        // (rows narrower than 16 bytes)
+        switch (group) {
+            case 1: return run_packed<T, 1, 1, WIDE>(a, st);
+            case 2: return run_packed<T, 1, 2, WIDE>(a, st);
+            case 4: return run_packed<T, 1, 4, WIDE>(a, st);
+        }
+        return (int)hipErrorInvalidValue;
+    }
+    switch (group) {
+        case 1: return run_packed<T, V, 1, WIDE>(a, st);
+        case 2: return run_packed<T, V, 2, WIDE>(a, st);
+        case 4: return run_packed<T, V, 4, WIDE>(a, st);
+        case 8: return run_packed<T, V, 8, WIDE>(a, st);
+        case 16: return run_packed<T, V, 16, WIDE>(a, st);
+        case 32: return run_packed<T, V, 32, WIDE>(a, st);
+        case 64: return run_packed<T, V, 64, WIDE>(a, st);
+    }
+    return (int)hipErrorInvalidValue;
+}
+
+}  // namespace
+
+int launch_packed_spmm(const PackedSpmmLaunch &a, void *stream) {
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    if (a.n_blocks == 0) return 0;
+    if (a.n_xs < 1 || a.n_xs > kXcds || a.n_blocks % kGatherQuad) return (int)hipErrorInvalidValue;
+    if (a.dtype == TF_F32) return a.wide ? run_packed_group<float, true>(a, st) : run_packed_group<float, false>(a, st);
+    return a.wide ? run_packed_group<double, true>(a, st) : run_packed_group<double, false>(a, st);
+}
+
+}  // namespace tf

@@ -62,17 +62,10 @@ void split_tile(const Schedule &s, Range r, bool allow_split, std::vector<Range>
 namespace {
 
 struct PackRules {
-    int max_rows;        // most rows per unit
-    int64_t max_slots;   // most padded entries per unit
-    int split_groups;    // lane groups available for splitting long rows; 0 = never split
-    int64_t cut_slots;   // longer rows are cut into pieces of at most that many slots, one per unit
+    int nr;              // virtual rows of a block
+    int64_t longest;     // most slots of a virtual row: longer rows are cut
+    int counts;          // counts of finished pieces per cut row (slices x column blocks)
 };
-
-int pow2_at_least(int64_t x) {
-    int g = 1;
-    while (g < x) g *= 2;
-    return g;
-}
 
 // Host threads for per-tile or per-unit work: one for small matrices, else up to 16.
 int host_threads(int64_t nnz, int64_t n_items, int64_t min_items_per_thread) {
@@ -106,148 +99,241 @@ template <typename Fn> void for_each_item(int64_t count, int nthreads, Fn fn) {
     if (failed) throw std::bad_alloc();
 }
 
-// Re-packs the rows `list` of the CSR matrix into units of uniform padded length and appends
-// them to `out` (see RowPack).  local(c) maps a column index to what the kernel should index
-// its operand with.  First the units are cut (row lengths only), then their entries are filled
-// in, unit by unit on the host threads: a unit's place in the arrays follows from the cuts.
+// Re-packs the rows `list` of the CSR matrix into blocks of equal slots (see RowPack).  local(c) maps a column
+// index to what the kernel should index its operand with.  First the blocks are cut (row lengths only), then
+// their entries are filled in, block by block on the host threads: a block's place follows from the cuts.
 template <typename LocalFn>
 void pack_rows(const int32_t *rowptr, const int32_t *colidx, const unsigned char *vals, int es,
-               std::vector<int32_t> list, const PackRules &rules, bool may_sort, LocalFn local,
-               RowPack &out) {
-    auto len = [&](int32_t j) { return (int64_t)rowptr[j + 1] - rowptr[j]; };
-    const int64_t count = (int64_t)list.size();
-    // empty rows last, so that no unit mixes them with rows that need padding entries
-    std::stable_partition(list.begin(), list.end(), [&](int32_t j) { return len(j) > 0; });
-    int64_t real = 0;
-    for (int32_t j : list) real += len(j);
-    if (may_sort && count > 0) {
-        // padded size in the given order; re-order by length when padding would cost over 15 %
-        int64_t padded = 0;
-        for (int64_t p0 = 0; p0 < count; p0 += rules.max_rows) {
-            const int64_t p1 = std::min(count, p0 + rules.max_rows);
+               std::vector<int32_t> list, const PackRules &rules, LocalFn local, RowPack &out) {
+    out = RowPack();
+    const int64_t count = (int64_t)list.size(), nr = rules.nr;
+    std::vector<int32_t> &lens = out.lens;
+    lens.resize((size_t)count);
+    int64_t real = 0, longest = 0, shortest = 0, padded = 0;
+    bool empty_inside = false;
+    auto measure = [&]() {
+        real = longest = padded = 0;
+        shortest = INT32_MAX;
+        empty_inside = false;
+        for (int64_t p0 = 0; p0 < count; p0 += nr) {
+            const int64_t p1 = std::min(count, p0 + nr);
             int64_t mx = 0;
-            for (int64_t q = p0; q < p1; ++q) mx = std::max(mx, len(list[q]));
+            for (int64_t q = p0; q < p1; ++q) {
+                const int32_t j = list[(size_t)q], l = rowptr[j + 1] - rowptr[j];
+                lens[(size_t)q] = l;
+                real += l;
+                mx = std::max<int64_t>(mx, l);
+                shortest = std::min<int64_t>(shortest, l);
+                empty_inside = empty_inside || (l > 0 && q > 0 && lens[(size_t)q - 1] == 0);
+            }
+            longest = std::max(longest, mx);
             padded += mx * (p1 - p0);
         }
-        if (padded > real + real * 15 / 100) {
-            // longest first, rows of one length in their given order: by counting when the
-            // lengths are a small range, else by comparison
-            int64_t longest = 0;
-            for (int32_t j : list) longest = std::max(longest, len(j));
-            if (longest <= 4 * count + 1024) {
-                std::vector<int64_t> start((size_t)longest + 2, 0);
-                for (int32_t j : list) ++start[(size_t)(longest - len(j)) + 1];
-                for (size_t b = 1; b < start.size(); ++b) start[b] += start[b - 1];
-                std::vector<int32_t> sorted((size_t)count);
-                for (int32_t j : list) sorted[(size_t)start[(size_t)(longest - len(j))]++] = j;
-                list.swap(sorted);
-            } else {
-                std::stable_sort(list.begin(), list.end(),
-                                 [&](int32_t a, int32_t b) { return len(a) > len(b); });
-            }
-            out.sorted = true;
-        }
+    };
+    measure();
+    // empty rows last, so that no block mixes them with rows that need padding entries
+    if (empty_inside) {
+        std::stable_partition(list.begin(), list.end(), [&](int32_t j) { return rowptr[j + 1] > rowptr[j]; });
+        measure();
     }
-    // A lane group works on as many rows at a time as a full unit holds for it, four at most: more would
-    // fetch rows again that it has (short lists, whose time is the longest unit's chain of passes: graph
-    // of 12504 rows, fp64, 24 columns, second wavefront 30 us with four rows per pass, now 12).
-    if (rules.split_groups > 0)
-        out.rows_per_pass = std::min(4, std::max(1, rules.max_rows / rules.split_groups));
-    const int64_t list_base = (int64_t)out.rows.size();
-    out.rows.insert(out.rows.end(), list.begin(), list.end());
-    const size_t first_unit = out.units.size();
-    // every unit starts at a multiple of four entries (16-byte aligned pieces for the kernels'
-    // bulk copies, which may also read up to three entries past a unit's end)
-    int64_t at = (int64_t)out.idx32.size();
-    int64_t pos = 0;
-    while (pos < count) {
-        UnitDesc u{};
-        u.row_begin = (int32_t)(list_base + pos);
-        u.entry_base = at;
-        const int64_t len0 = len(list[pos]);
-        int64_t L = len0;
-        int64_t take = 1;
-        if (rules.split_groups > 1 && len0 >= kSplitMinSlots && len0 > rules.cut_slots) {
-            const int64_t pieces = (len0 + rules.cut_slots - 1) / rules.cut_slots;
-            const int64_t slots = round_up((len0 + pieces - 1) / pieces, 4);      // (each starts at a multiple of four)
-            u.n_rows = 1;
-            u.split = rules.split_groups;
-            u.first_piece = out.n_pieces;
-            u.cut_row = out.n_cut_rows++;
-            u.pieces = (int32_t)((len0 + slots - 1) / slots);
-            for (int32_t k = 0; k < u.pieces; ++k) {
-                u.slots = (int32_t)std::min(slots, len0 - k * slots);
-                u.piece = out.n_pieces++;
-                out.units.push_back(u);
-                u.entry_base += slots;
+    // re-order by length when padding would cost over 15 %: longest first, rows of one length in their given
+    // order; by counting when the lengths are a small range, else by comparison
+    if (padded > real + real * 15 / 100) {
+        if (longest <= 4 * count + 1024) {
+            std::vector<int64_t> start((size_t)longest + 2, 0);
+            for (int32_t l : lens) ++start[(size_t)(longest - l) + 1];
+            for (size_t b = 1; b < start.size(); ++b) start[b] += start[b - 1];
+            std::vector<int32_t> by_len((size_t)count);
+            for (int64_t q = 0; q < count; ++q)
+                by_len[(size_t)start[(size_t)(longest - lens[(size_t)q])]++] = list[(size_t)q];
+            list.swap(by_len);
+        } else {
+            std::stable_sort(list.begin(), list.end(), [&](int32_t a, int32_t b) {
+                return rowptr[a + 1] - rowptr[a] > rowptr[b + 1] - rowptr[b];
+            });
+        }
+        for (int64_t q = 0; q < count; ++q) lens[(size_t)q] = rowptr[list[(size_t)q] + 1] - rowptr[list[(size_t)q]];
+        out.sorted = true;
+    }
+    out.rows = std::move(list);
+    // rows cut over several blocks come first, in whole quads: pieces of equal length, and equal blocks of whole
+    // slots inside them, so that only the last ones are padded
+    const int64_t one_block = nr * rules.longest, quad = one_block * kGatherQuad;
+    int log_nr = 0;
+    while (1 << log_nr < nr) ++log_nr;
+    if (longest > one_block)
+        for (int64_t pos = 0; pos < count; ++pos) {
+            const int64_t len0 = lens[(size_t)pos];
+            if (len0 <= one_block) {
+                if (out.sorted) break;
+                continue;
             }
-            at = (at + len0 + 3) / 4 * 4;
+            const int64_t pieces = (len0 + quad - 1) / quad;
+            const int64_t slots = (len0 + pieces * nr * kGatherQuad - 1) / (pieces * nr * kGatherQuad);
+            GatherBlock b{};
+            b.row_begin = (int32_t)pos;
+            b.info = (uint32_t)log_nr | 1u << 6;
+            CutBlock cut{0, 0, out.n_cut_rows++, out.n_pieces, (int32_t)((len0 + slots * nr * kGatherQuad - 1) / (slots * nr * kGatherQuad))};
+            for (int64_t k = 0; k < len0;) {
+                cut.piece = out.n_pieces++;
+                for (int m = 0; m < kGatherQuad; ++m, k += slots * nr) {
+                    const int64_t l = std::max<int64_t>(0, std::min(slots * nr, len0 - k)), here = (l + nr - 1) / nr;
+                    b.size = (uint32_t)(here | std::max<int64_t>(0, l - (nr - 1) * here) << 16);
+                    cut.skip = (int32_t)std::min(k, len0);
+                    out.blocks.push_back(b);
+                    out.cuts.push_back(cut);
+                }
+            }
+        }
+    // parts that the other rows are cut into inside their block (log2)
+    auto cut_of = [&](int64_t l) {
+        int c = 0;
+        while ((l + (1 << c) - 1) >> c > rules.longest) ++c;
+        return c;
+    };
+    const size_t first_whole = out.blocks.size();
+    int64_t pos = 0;
+    if (!out.sorted && shortest > 0 && real > 4 * count && longest <= rules.longest) {
+        // (the plain case, on the host threads: as many rows in every block)
+        out.blocks.resize((size_t)((count + nr - 1) / nr));
+        pos = count;
+        for_each_item((int64_t)out.blocks.size(), host_threads(real, count, 32768), [&](int64_t k) {
+            const auto at = lens.begin() + k * nr, end = lens.begin() + std::min(count, (k + 1) * nr);
+            out.blocks[(size_t)k].row_begin = (int32_t)(k * nr);
+            out.blocks[(size_t)k].size = (uint32_t)*std::max_element(at, end) | (uint32_t)*std::min_element(at, end) << 16;
+            out.blocks[(size_t)k].info = (uint32_t)(end - at) << 6;
+        });
+    }
+    while (pos < count) {
+        const int64_t len0 = lens[(size_t)pos];
+        if (len0 > one_block) {
             ++pos;
             continue;
         }
-        u.pieces = 1;
-        if (rules.split_groups > 1 && len0 >= kSplitMinSlots) {
-            int split = pow2_at_least((len0 + kSplitPartSlots - 1) / kSplitPartSlots);
-            split = std::min(split, rules.split_groups);
-            const int cap = rules.split_groups / split;
-            while (take < cap && pos + take < count && len(list[pos + take]) >= kSplitMinSlots) {
-                L = std::max(L, len(list[pos + take]));
-                ++take;
-            }
-            u.split = split;
-        } else {
-            u.split = 1;
-            while (take < rules.max_rows && pos + take < count) {
-                const int64_t ln = len(list[pos + take]);
-                if ((ln == 0) != (len0 == 0)) break;
-                if (rules.split_groups > 1 && ln >= kSplitMinSlots) break;
-                const int64_t nl = std::max(L, ln);
-                if (nl * (take + 1) > rules.max_slots) break;
-                L = nl;
-                ++take;
+        // rows of one to four entries: as many as the slots of a pass hold, where enough of them follow each other
+        const int64_t together = gather_short_rows((int)std::min<int64_t>(len0, 5), 64 / (int)nr);
+        if (together > 1) {
+            int64_t run = 1;
+            while (run < nr * together && pos + run < count && lens[(size_t)(pos + run)] == len0) ++run;
+            if (2 * run > nr * together || (run > nr && pos + run == count)) {
+                GatherBlock b{};
+                b.row_begin = (int32_t)pos;
+                b.size = (uint32_t)(together * len0) * 0x10001u;
+                b.info = (uint32_t)len0 << 3 | (uint32_t)run << 6;
+                out.blocks.push_back(b);
+                pos += run;
+                continue;
             }
         }
-        u.n_rows = (int32_t)take;
-        u.slots = (int32_t)L;
-        out.units.push_back(u);
-        at = (at + take * L + 3) / 4 * 4;
+        const int c = cut_of(len0);
+        int64_t mx = len0, mn = len0, take = 1;
+        while (take < nr >> c && pos + take < count) {
+            const int64_t ln = lens[(size_t)(pos + take)];
+            if ((ln == 0) != (len0 == 0) || ln > one_block || (ln != len0 && cut_of(ln) != c)) break;
+            mx = std::max(mx, ln);
+            mn = std::min(mn, ln);
+            ++take;
+        }
+        const int64_t slots = (mx + (1 << c) - 1) >> c;
+        GatherBlock b{};
+        b.row_begin = (int32_t)pos;
+        b.size = (uint32_t)(slots | std::max<int64_t>(0, mn - ((1 << c) - 1) * slots) << 16);
+        b.info = (uint32_t)c | (uint32_t)take << 6;
+        out.blocks.push_back(b);
         pos += take;
     }
-    out.arrived.assign((size_t)out.n_cut_rows * kXcds, 0);
-    const int64_t end = at + kPackSpareSlots;         // spare zero entries behind the last unit
-    out.idx32.resize((size_t)end);
-    out.vals.resize((size_t)end * es);
-    const int64_t n_new = (int64_t)(out.units.size() - first_unit);
-    if (n_new == 0) {
-        std::memset(out.idx32.data() + at, 0, (size_t)kPackSpareSlots * 4);
-        std::memset(out.vals.data() + (size_t)at * es, 0, (size_t)kPackSpareSlots * es);
+    if (out.sorted) {
+        // (rows cut into parts have half of the longest slots or more, whole rows come in their order)
+        size_t end = first_whole;
+        while (end < out.blocks.size() && out.blocks[end].slots() * 2 >= rules.longest) ++end;
+        std::stable_sort(out.blocks.begin() + (int64_t)first_whole, out.blocks.begin() + (int64_t)end,
+                         [](const GatherBlock &x, const GatherBlock &y) { return x.slots() > y.slots(); });
     }
-    for_each_item(n_new, host_threads(real, n_new, 64), [&](int64_t k) {
-        const UnitDesc &u = out.units[first_unit + (size_t)k];
-        const int64_t next = k + 1 < n_new ? out.units[first_unit + (size_t)k + 1].entry_base : end;
-        const int64_t L = u.slots;
-        int32_t *ip = out.idx32.data() + u.entry_base;
-        unsigned char *vp = out.vals.data() + (size_t)u.entry_base * es;
-        for (int64_t q = 0; q < u.n_rows; ++q) {
-            const int32_t j = out.rows[(size_t)u.row_begin + (size_t)q];
-            int64_t k0 = rowptr[j], ln = len(j);
-            if (u.pieces > 1) {
-                // (all pieces of a row but the last have the same length)
-                const int32_t p = u.piece - u.first_piece;
-                k0 = p + 1 < u.pieces ? k0 + p * L : k0 + ln - L;
-                ln = L;
+    while (out.blocks.size() % kGatherQuad) out.blocks.push_back(GatherBlock{});
+    int64_t slot = 0;
+    for (GatherBlock &b : out.blocks) {
+        b.slot_base = (uint32_t)slot;
+        slot += b.slots();
+    }
+    out.arrived.assign((size_t)out.n_cut_rows * (size_t)rules.counts, 0);
+    // spare entries behind the last block: the kernel fetches passes ahead, and whole passes
+    const int64_t end = slot * nr, spare = std::max<int64_t>(64, 2 * kGatherEntries * nr);
+    out.idx32.resize((size_t)(end + spare));
+    out.vals.resize((size_t)(end + spare) * es);
+    std::memset(out.idx32.data() + end, 0, (size_t)spare * 4);
+    std::memset(out.vals.data() + (size_t)end * es, 0, (size_t)spare * es);
+    auto fill = [&](auto tag) {
+        typedef decltype(tag) T;
+        const T *from = reinterpret_cast<const T *>(vals);
+        T *to = reinterpret_cast<T *>(out.vals.data());
+        auto fill_block = [&](const GatherBlock &b) {
+            const int64_t slots = b.slots(), at = &b - out.blocks.data();
+            if (slots == 0) return;
+            const int c = (int)(b.info & 7), each = (int)(b.info >> 3 & 7), n_rows = (int)(b.info >> 6);
+            const int64_t skip = at < (int64_t)out.cuts.size() ? out.cuts[(size_t)at].skip : 0;
+            if (each) {
+                int32_t *ip = out.idx32.data() + (int64_t)b.slot_base * nr;
+                T *vp = to + (int64_t)b.slot_base * nr;
+                const int together = (int)slots / each;
+                for (int s = 0; s < (int)slots; ++s)
+                    for (int v = 0; v < nr; ++v) {
+                        const int ri = v * together + s / each;        // (past the block's end: not stored)
+                        const int64_t k = rowptr[out.rows[(size_t)(b.row_begin + std::min(ri, n_rows - 1))]] + s % each;
+                        *ip++ = (int32_t)local(colidx[k]);
+                        *vp++ = from[k];
+                    }
+                return;
             }
-            for (int64_t sl = 0; sl < ln; ++sl) *ip++ = (int32_t)local(colidx[k0 + sl]);
-            std::memcpy(vp, vals + (size_t)k0 * es, (size_t)ln * es);
-            // padding repeats the last entry's index with value 0 (units of empty rows have L = 0)
-            for (int64_t sl = ln; sl < L; ++sl) *ip++ = (int32_t)local(colidx[k0 + ln - 1]);
-            std::memset(vp + (size_t)ln * es, 0, (size_t)(L - ln) * es);
-            vp += (size_t)L * es;
-        }
-        const int64_t filled = u.entry_base + (int64_t)u.n_rows * L;
-        std::memset(out.idx32.data() + filled, 0, (size_t)(next - filled) * 4);
-        std::memset(out.vals.data() + (size_t)filled * es, 0, (size_t)(next - filled) * es);
-    });
+            if (nr == 1 && (int64_t)(b.size >> 16) == slots) {
+                const int64_t k0 = rowptr[out.rows[(size_t)b.row_begin]] + skip;
+                for (int64_t s = 0; s < slots; ++s) out.idx32[(size_t)(b.slot_base + s)] = (int32_t)local(colidx[k0 + s]);
+                std::memcpy(to + b.slot_base, from + k0, (size_t)slots * sizeof(T));
+                return;
+            }
+            const int32_t *col[64];
+            const T *value[64];
+            int64_t n_real[64];
+            for (int v = 0; v < nr; ++v) {
+                // (virtual rows past the block's end repeat its last row without its values; they are not stored)
+                const int32_t j = out.rows[(size_t)(b.row_begin + std::min(v >> c, n_rows - 1))];
+                const int64_t k1 = rowptr[j + 1], k0 = rowptr[j] + skip + (v & ((1 << c) - 1)) * slots;
+                n_real[v] = (v >> c) < n_rows ? std::max<int64_t>(0, std::min(slots, k1 - k0)) : 0;
+                // (padding names the row's last column)
+                col[v] = n_real[v] > 0 ? colidx + k0 : colidx + k1 - 1;
+                value[v] = n_real[v] > 0 ? from + k0 : from;
+            }
+            int32_t *ip = out.idx32.data() + (int64_t)b.slot_base * nr;
+            T *vp = to + (int64_t)b.slot_base * nr;
+            int64_t s = 0;
+            const int used = n_rows << c;
+            for (; s < (int64_t)(b.size >> 16); ++s, ip += nr, vp += nr) {
+                for (int v = 0; v < used; ++v) {
+                    ip[v] = (int32_t)local(col[v][s]);
+                    vp[v] = value[v][s];
+                }
+                for (int v = used; v < nr; ++v) {
+                    ip[v] = (int32_t)local(col[v][0]);
+                    vp[v] = T(0);
+                }
+            }
+            for (; s < slots; ++s)
+                for (int v = 0; v < nr; ++v) {
+                    const bool in = s < n_real[v];
+                    *ip++ = (int32_t)local(col[v][in ? s : std::max<int64_t>(0, n_real[v] - 1)]);
+                    *vp++ = in ? value[v][s] : T(0);
+                }
+        };
+        // (threads share the slots evenly, not the blocks: the longest come first)
+        const int64_t parts = host_threads(real, (int64_t)out.blocks.size(), 64);
+        for_each_item(parts, (int)parts, [&](int64_t part) {
+            auto at = std::lower_bound(out.blocks.begin(), out.blocks.end(), slot * part / parts,
+                                       [](const GatherBlock &b, int64_t s) { return (int64_t)b.slot_base < s; });
+            for (; at != out.blocks.end() && (part + 1 == parts || (int64_t)at->slot_base < slot * (part + 1) / parts); ++at)
+                fill_block(*at);
+        });
+    };
+    if (es == 8) fill(double());
+    else fill(float());
 }
 
 }  // namespace
@@ -340,26 +426,20 @@ TileBlock pack_tile(const int32_t *rowptr, const int32_t *colidx, const unsigned
 
 }  // namespace
 
-// Units of a packed row list of `count` rows: a unit is one workgroup; short lists are cut into
-// smaller units (down to one row per lane group) so that they still spread over the machine.
-static PackRules pack_rules(const InspectorInput &in, int64_t count, int sw) {
-    const int elems = lane_elems(in.dtype, in.ccol, sw), groups = kSpmmThreads / lane_group(sw, elems);
-    const int64_t want = std::min<int64_t>(kUnitRows, (count + 1023) / 1024);
-    // whole passes of the lane groups: a power of two of rows for each
-    int rows = groups;
-    while (2 * rows <= want) rows *= 2;
-    // (rows wider than a wave's load: pieces as much longer, so that their sums take no more memory than entries)
-    const int64_t cut = (int64_t)groups * kCutSlots * ((sw + 64 * elems - 1) / (64 * elems));
-    return PackRules{std::min(rows, kUnitRows), kUnitSlots, groups, cut};
-}
-
-// The gather kernel stages the entries of a unit whose rows are not split in LDS arrays of
-// kUnitSlots entries; a unit beyond that would write past them.  pack_rows never cuts one (rows that
-// long are split), this is the check behind that.
-static bool units_fit_staging(const RowPack &pk) {
-    for (const UnitDesc &u : pk.units)
-        if (u.split <= 1 && (int64_t)u.n_rows * u.slots > kUnitSlots) return false;
-    return true;
+// How rows of `sw` columns (of ccol, in column slices) are packed for the gather kernel; `entries` of them in all.
+static PackRules pack_rules(const InspectorInput &in, int64_t ccol, int64_t entries, const D1Layout &lay) {
+    const int elems = lane_elems(in.dtype, ccol, lay.sw), group = lane_group(lay.sw, elems);
+    PackRules r;
+    r.nr = 64 / group;
+    const int64_t n_cb = (lay.sw + group * elems - 1) / (group * elems);
+    r.counts = (int)(lay.n_sl * n_cb);
+    // slots that a wave has on average when all blocks are dealt out
+    const int64_t waves = (int64_t)std::max(1, in.n_cu) * 4 * gather_waves(in.dtype);
+    const int64_t mean = entries / r.nr * lay.n_sl / waves;
+    // (rows wider than a wave's load: as much longer, so that the sums of their pieces take no more memory than
+    // their entries; below the 16 bits of a block's size)
+    r.longest = std::min<int64_t>(32760, std::min<int64_t>(256, std::max<int64_t>(32, round_up(mean / 2, kGatherEntries))) * n_cb);
+    return r;
 }
 
 tf_status build_schedule(const InspectorInput &in, Schedule &s, std::string &err) {
@@ -984,17 +1064,17 @@ tf_status build_schedule(const InspectorInput &in, Schedule &s, std::string &err
 
     TF_TICK("tile blocks, row arrays");
     // ---- balance: units of the second wavefront --------------------------------------------
-    const PackRules wf1_rules = pack_rules(in, (int64_t)wf1.size(), s.d1.sw);
+    int64_t wf1_nnz = 0;
+    for (int32_t j : wf1) wf1_nnz += in.rowptr[j + 1] - in.rowptr[j];
     auto slot_of = [&](int32_t c) { return s.spill_slot[(size_t)c]; };
-    pack_rows(in.rowptr, in.colidx, vals, es, wf1, wf1_rules, true, slot_of, s.wf1);
-    if (!units_fit_staging(s.wf1)) {
-        err = "internal: a unit of the second wavefront exceeds the staging arrays of the gather kernel";
-        return TF_EUNSUPPORTED;
-    }
+    pack_rows(in.rowptr, in.colidx, vals, es, std::move(wf1), pack_rules(in, in.ccol, wf1_nnz, s.d1), slot_of, s.wf1);
     s.wf1_rows = s.wf1.rows;
     s.wf1_unit_ptr.clear();
-    for (const UnitDesc &u : s.wf1.units)
-        if (u.piece == u.first_piece) s.wf1_unit_ptr.push_back(u.row_begin);     // (a cut row is one unit there)
+    // (a row that is cut over several blocks is one unit there)
+    for (size_t k = 0; k < s.wf1.blocks.size(); ++k)
+        if (s.wf1.blocks[k].info >> 6 && (k >= s.wf1.cuts.size() || s.wf1.cuts[k].skip == 0))
+            s.wf1_unit_ptr.push_back(s.wf1.blocks[k].row_begin);
+    if (!std::is_sorted(s.wf1_unit_ptr.begin(), s.wf1_unit_ptr.end())) std::sort(s.wf1_unit_ptr.begin(), s.wf1_unit_ptr.end());
     s.wf1_unit_ptr.push_back((int32_t)s.wf1_rows.size());
     TF_TICK("second-wavefront units");
     return TF_OK;
@@ -1182,7 +1262,7 @@ void choose_gather_first(const InspectorInput &in, Schedule &s) {
     s.gather_first = 5 * touched(in.bcol) <= 4 * touched(in.ccol);
 }
 
-bool build_gather_first(const InspectorInput &in, Schedule &s, bool have_all) {
+void build_gather_first(const InspectorInput &in, Schedule &s, bool have_all) {
     const int64_t n = in.n, es = elem_size(in.dtype);
     const int group = lane_group((int)in.bcol, lane_elems(in.dtype, in.bcol, in.bcol));
     const int group_all = lane_group(s.d1.sw, lane_elems(in.dtype, in.ccol, s.d1.sw));
@@ -1190,16 +1270,14 @@ bool build_gather_first(const InspectorInput &in, Schedule &s, bool have_all) {
     if (!s.gather_first_shares) {
         std::vector<int32_t> all((size_t)n);
         std::iota(all.begin(), all.end(), 0);
-        InspectorInput as_b = in;
-        as_b.ccol = in.bcol;
-        pack_rows(in.rowptr, in.colidx, static_cast<const unsigned char *>(in.vals), (int)es, all,
-                  pack_rules(as_b, n, (int)in.bcol), true, [](int32_t c) { return c; }, s.gf);
-        if (!units_fit_staging(s.gf)) return false;
+        D1Layout b;
+        b.sw = (int32_t)in.bcol;
+        pack_rows(in.rowptr, in.colidx, static_cast<const unsigned char *>(in.vals), (int)es, std::move(all),
+                  pack_rules(in, in.bcol, in.nnz, b), [](int32_t c) { return c; }, s.gf);
     }
     s.gf_info.resize((size_t)n);
     for (int64_t j = 0; j < n; ++j)
         s.gf_info[(size_t)j] = in.rowptr[j + 1] > in.rowptr[j] ? kInfoSpill | (uint32_t)j : kInfoZero;
-    return true;
 }
 
 // A CSR B and a D1 that the caches hold whole: tiles save no memory traffic then, and what is left of them
@@ -1216,13 +1294,11 @@ bool plain_pair_is_faster(const InspectorInput &in, const Schedule &s) {
     return in.n * in.ccol * elem_size(in.dtype) <= 12000000;
 }
 
-bool build_baseline_pack(const InspectorInput &in, Schedule &s) {
+void build_baseline_pack(const InspectorInput &in, Schedule &s) {
     std::vector<int32_t> all((size_t)in.n);
     std::iota(all.begin(), all.end(), 0);
-    auto ident = [](int32_t c) { return c; };
-    pack_rows(in.rowptr, in.colidx, static_cast<const unsigned char *>(in.vals), elem_size(in.dtype),
-              all, pack_rules(in, in.n, s.d1.sw), true, ident, s.all);
-    return units_fit_staging(s.all);
+    pack_rows(in.rowptr, in.colidx, static_cast<const unsigned char *>(in.vals), elem_size(in.dtype), std::move(all),
+              pack_rules(in, in.ccol, in.nnz, s.d1), [](int32_t c) { return c; }, s.all);
 }
 
 }  // namespace tf

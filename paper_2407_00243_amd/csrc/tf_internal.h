@@ -19,23 +19,8 @@ constexpr int kXcds = 8;                 // XCDs of the device: consecutive work
 constexpr int kFusedThreads = 512;       // workgroup size of the fused kernels
 constexpr int kSpmmThreads = 256;        // workgroup size of the row-list SpMM kernel
 constexpr int kWantedTileRows = 256;     // a default column slice is narrowed until tiles this large fit
-constexpr int kUnitRows = 64;            // most rows in one unit of a packed row list
-constexpr int kUnitSlots = 2048;         // most padded entries (rows x slots) in one such unit (they are staged in LDS)
-constexpr int kPackSpareSlots = 8 * 64 + 8;  // zero entries behind the last unit of a packed row list: the gather kernel
-                                         // fetches the entries of split rows in windows of 8 slots per lane of a lane
-                                         // group (64 lanes at most), which may reach that far past the last row
-constexpr int kSplitMinSlots = 128;      // rows at least this long are split over several lane groups
-constexpr int kSplitPartSlots = 96;      // target slots per part of a split row
-// Slots per lane group beyond which a row is cut over several workgroups: eight round trips to memory, one
-// after the other, of eight gathers each.  The hub of a graph in one workgroup is the longest chain of the
-// launch: R-MAT graph of 100003 rows, fp64, rows of 64 columns, 94 us, cut 71; 150000 rows, fp32, 41 columns
-// 66 / 52; 30000 rows, fp32, 64 columns 19.8 / 10.8; 2^20 rows, 32 columns 192 / 177.  (At 48, 96 and 192 slots
-// a few per cent either way.)
-constexpr int kCutSlots = 64;
-// a row long enough to be split gets at least two parts: units whose rows are not split are staged
-// in LDS whole (kUnitSlots entries at most), so a row that long must never end up in one
-static_assert(kSplitMinSlots > kSplitPartSlots && kSplitMinSlots <= kUnitSlots,
-              "rows of kSplitMinSlots entries or more must be split");
+constexpr int kGatherEntries = 8;        // entries per row that the gather kernel has in flight
+constexpr int kGatherQuad = kSpmmThreads / 64;   // blocks that its workgroups take at a time
 constexpr int kGatherSliceBytes = 128;    // narrowest column slice of the gather kernel chosen by default, bytes
 
 // Per D1 row of a tile, beside its row id: one info word.  kInfoSpill: the row is also stored to
@@ -73,6 +58,15 @@ inline int lane_group(int cols, int vv) {
     while (g * vv < cols && g < 64) g *= 2;
     return g;
 }
+
+// Rows of `each` entries (1 to 4) that a virtual row of G lanes holds; 1: such blocks are not made.
+constexpr int gather_short_rows(int each, int G) {
+    const int r = each == 1 ? 8 : each == 2 ? 4 : 2;
+    return each < 1 || each > 4 || G < r ? 1 : r;
+}
+// Waves per SIMD that the gather kernel is held to: one more spills some 40 bytes a lane (R-MAT graphs, rows of 32 and
+// 64 fp32 columns, 30000 to 300000 rows: 3 to 20 % slower).
+constexpr int gather_waves(int dtype) { return dtype == TF_F64 ? 4 : 5; }
 
 inline int elem_size(int dtype) { return dtype == TF_F64 ? 8 : 4; }
 inline int vec_elems(int dtype) { return dtype == TF_F64 ? 2 : 4; }   // elements per 16 bytes
@@ -204,25 +198,30 @@ inline int64_t fused_lds_bytes(int dtype, int b_is_sparse, int bcol, int ccol, i
     return fused_lds_layout(dtype, b_is_sparse, bcol, ccol, cs, max_tile_rows, s_lds, need_tile).total;
 }
 
-// One unit of a packed row list: n_rows rows, all padded to `slots` entries, stored row after
-// row from entry_base on.  split > 1: every row is shared by `split` lane groups, each summing
-// a contiguous part of the slots.  pieces > 1: the unit holds a piece of one row that is cut over that
-// many consecutive units (and split over all lane groups of each).
-struct UnitDesc {
-    int64_t entry_base;
-    int32_t row_begin;    // position of the unit's first row in the list
-    int32_t n_rows;
-    int32_t slots;
-    int32_t split;
+// One block of a packed row list: what a wave of the gather kernel works on at a time.  It holds `nr` virtual
+// rows (nr = 64 lanes over the lanes of a row): rows, or the 2^k equal parts that each row of the block is cut
+// into, in adjacent lane groups; or nr parts of one row that takes the four blocks of a workgroup, or several
+// times that (pieces).  The list is a whole number of fours, filled up with blocks of no rows.
+struct GatherBlock {
+    uint32_t slot_base;    // first slot of the block: entry (slot s, virtual row v) is at (slot_base + s) nr + v
+    int32_t row_begin;     // position of the block's first row in the list
+    uint32_t size;         // slots of every virtual row (0: the block's rows are empty) | slots that hold an entry
+                           // in all of them << 16
+    uint32_t info;         // k (3 bits) | e (3 bits) | rows of the block << 6; e > 0: rows of e entries each, several to
+                           // a virtual row (gather_short_rows), one after the other in its slots
+    int slots() const { return (int)(size & 0xffff); }
+};
+// The blocks of rows that are cut over several come first; for each of them:
+struct CutBlock {
+    int32_t skip;          // entries of the row before the block's
+    int32_t piece;         // number of the piece, over all cut rows
+    int32_t row;           // number of the cut row
+    int32_t first_piece;   // its first piece
     int32_t pieces;
-    int32_t piece;        // number of the piece, over all cut rows of the list
-    int32_t first_piece;  // of the same row
-    int32_t cut_row;      // number of the cut row
 };
 
-// A list of rows of A re-packed for the gather kernels: per unit a uniform padded row length,
-// so the kernels need no row pointers and no per-row bounds.  Padding repeats the row's last
-// column index with value 0.
+// A list of rows of A re-packed for the gather kernel.  Padding repeats the row's last column index with
+// value 0; the kernel leaves it out of the sums.
 // A vector whose resize() leaves the new elements uninitialised: the packed arrays are sized once
 // and then written in full by the host threads, which are also the first to touch their pages.
 template <typename T> struct NoInitAlloc : std::allocator<T> {
@@ -237,15 +236,16 @@ template <typename T> struct NoInitAlloc : std::allocator<T> {
 template <typename T> using RawVec = std::vector<T, NoInitAlloc<T>>;
 
 struct RowPack {
-    std::vector<UnitDesc> units;
+    std::vector<GatherBlock> blocks;
     std::vector<int32_t> rows;           // row ids, list order
+    std::vector<int32_t> lens;           // their entries
     RawVec<int32_t> idx32;               // column indices
     RawVec<unsigned char> vals;          // packed values, element size of the plan's dtype
     bool sorted = false;                 // rows were re-ordered by length
-    int32_t rows_per_pass = 1;           // rows that a lane group of the gather kernel works on at a time
-    int32_t n_pieces = 0, n_cut_rows = 0;  // rows cut over several units
-    std::vector<int32_t> arrived;        // zeros: a count per cut row and slice (at most kXcds)
-    int64_t entries() const { return (int64_t)idx32.size(); }
+    int32_t n_pieces = 0;
+    int32_t n_cut_rows = 0;              // rows cut over several blocks
+    std::vector<CutBlock> cuts;          // their blocks
+    std::vector<int32_t> arrived;        // zeros: counts of their finished pieces, per slice and column block
 };
 
 // ---- the chain in one pass, D = (A B) C (dense B) -----------------------------------------------
@@ -410,8 +410,7 @@ struct InspectorInput {
 tf_status build_schedule(const InspectorInput &in, Schedule &out, std::string &err);
 // The packed copy of all rows of A that the unfused baseline's second operation runs on
 // (Schedule::all).  Not part of the fused schedule and not counted in its time.
-// (false: a unit exceeds the gather kernel's staging arrays; never expected)
-bool build_baseline_pack(const InspectorInput &in, Schedule &s);
+void build_baseline_pack(const InspectorInput &in, Schedule &s);
 // Decides whether the fused calls of the plan run the chain in one pass, and packs A for it (entries =
 // false: the blocks only).
 void build_chain_pack(const InspectorInput &in, Schedule &s, bool entries);
@@ -420,7 +419,7 @@ bool plain_pair_is_faster(const InspectorInput &in, const Schedule &s);
 // Decides whether they run it as Y = A B, D = Y C (Schedule::gather_first).
 void choose_gather_first(const InspectorInput &in, Schedule &s);
 // Packs A for that (have_all: `all` is packed).
-bool build_gather_first(const InspectorInput &in, Schedule &s, bool have_all);
+void build_gather_first(const InspectorInput &in, Schedule &s, bool have_all);
 
 
 // ---------------------------------------------------------------- device launch interface
@@ -432,10 +431,11 @@ struct CsrDev {
 };
 
 struct PackDev {
-    const UnitDesc *units = nullptr;
-    const int32_t *rows = nullptr;
-    const void *idx = nullptr;        // int32 or uint16
+    const GatherBlock *blocks = nullptr;
+    const int32_t *rows = nullptr, *lens = nullptr, *idx = nullptr;
     const void *vals = nullptr;
+    const CutBlock *cuts = nullptr;
+    int32_t n_cut_blocks = 0;
 };
 
 struct FusedLaunch {
@@ -465,22 +465,23 @@ struct FusedLaunch {
     int64_t d1_slice_stride;          // elements
 };
 
-// Y[row] = sum over the packed entries of the row of val * X[idx]; one unit per workgroup.
+// Y[row] = sum over the packed entries of the row of val * X[idx].
 struct PackedSpmmLaunch {
     int32_t dtype;
-    int64_t n_units;
-    int32_t contiguous;               // 1: neighbouring units share an XCD; 0: round robin (one slice only)
+    int32_t n_blocks;
+    int32_t contiguous;               // 1: neighbouring blocks share an XCD; 0: round robin
     int32_t wide;                     // 1: X spans 4 GiB or more (64-bit operand offsets)
-    PackDev pack;                     // int32 indices: rows (slots) of X
+    int32_t n_cu;                     // compute units of the device
+    PackDev pack;                     // indices: rows (slots) of X
     const void *X;                    // D1 workspace in the layout below, or a dense B
-    int32_t n_xs, sw;                 // column slices (1, 2, 4 or 8; each handled by 8 / n_xs XCDs) of sw columns
+    int32_t n_xs, sw;                 // column slices (1 to 8; each XCD handles n_xs eighths of one or two) of sw columns
     int64_t x_slice_stride;           // elements between the slices of X
     int32_t ldx;                      // elements between the rows of a slice
-    int32_t rows_per_pass;            // R of the kernel instantiation: 1, 2 or 4
     void *partial;                    // sums of the pieces of cut rows: [piece][slice][sw]
-    int32_t *arrived;                 // pieces of a cut row that are done: [cut row][slice], zeros between launches
+    int32_t *arrived;                 // pieces of a cut row that are done: [cut row][slice][column block], zeros between launches
     void *Y;                          // row-major, ccol columns
     int32_t ccol;
+    int32_t read_next;                // 1: the next launch reads Y
 };
 
 // Y[j] = S[j, :] X for a caller-supplied CSR matrix S, `rows_per_wg` consecutive rows per workgroup.

@@ -206,24 +206,6 @@ __device__ __forceinline__ void rows_dot(T (&acc)[R][N], const IdxT *__restrict_
     }
 }
 
-// ------------------------------------------------------------------------------------------
-// Packed row lists (see RowPack): every row of a unit has `slots` entries, so the gather loop has
-// a wave-uniform trip count and needs neither row pointers nor bounds on individual entries.
-//
-// X is addressed as  base + idx * ldx + lane offset.  For operands below 4 GiB (and for LDS)
-// the offset is formed in 32 bits, which lets the load use a scalar base plus a 32-bit lane
-// offset; WIDE selects 64-bit arithmetic for larger operands.
-template <typename T, int N, bool WIDE>
-__device__ __forceinline__ void load_x(T (&x)[N], const T *X, uint32_t c, uint32_t ldx,
-                                       uint32_t lane_off) {
-    if (WIDE) {
-        load_any<T, N>(x, X + ((uint64_t)c * ldx + lane_off));
-    } else {
-        const uint32_t off = (c * ldx + lane_off) * (uint32_t)sizeof(T);
-        load_any<T, N>(x, reinterpret_cast<const T *>(reinterpret_cast<const char *>(X) + off));
-    }
-}
-
 // B operand of one 16-row block, all k: KS vectors of V elements per lane.
 template <typename T, int KS> struct BFrag {
     T v[KS][Tr<T>::V];
@@ -1128,278 +1110,6 @@ __global__ __launch_bounds__(kFusedSparseThreads) void k_fused_spmm_spmm(const F
     }
 }
 
-// Packed-row SpMM: Y[row][:] = sum over the row's packed entries of val * X[idx][:], one unit
-// (and one column slice) per workgroup: the second wavefront, and the second operation of the
-// unfused baseline.  X is the D1 workspace: n_xs column slices of sw columns, idx is a row (slot)
-// of it.
-//
-// With one slice a workgroup handles whole rows.  With n_xs = 2, 4 or 8 slices, workgroup b (which
-// the hardware places on XCD b % 8) handles slice (b % 8) % n_xs of unit (b / 8) (8 / n_xs) +
-// (b % 8) / n_xs: an XCD only ever touches one slice of X, so its L2 holds sw-wide pieces of the
-// hot rows instead of whole rows, and the eight caches hold different data.
-//
-// The entries of a unit are contiguous (n_rows x slots): the workgroup first copies them to LDS
-// with coalesced 16-byte loads, then every lane group reads the entries of its rows from there
-// (an LDS broadcast) instead of fetching each index and value through the vector memory path
-// once per lane.  A lane group works on R rows at a time and keeps E entries of each in flight.
-// Units whose rows are split hand their partial sums through LDS and add them in a fixed order.
-template <typename T, bool FAST, bool WIDE, int R>
-__global__ __launch_bounds__(kSpmmThreads) void k_packed_spmm(const PackedSpmmLaunch a) {
-    constexpr int VV = FAST ? Tr<T>::V : 1;
-    constexpr int E = R >= 4 ? 4 : 8;
-    __shared__ __align__(16) int32_t idx_s[kUnitSlots + 4];
-    __shared__ __align__(16) T val_s[kUnitSlots + 4];
-    T *red = val_s;                                     // split units do not stage their entries
-    int64_t u;
-    int slice = 0;
-    if (a.n_xs == 1) {
-        u = a.contiguous ? xcd_contiguous(blockIdx.x, a.n_units) : (int64_t)blockIdx.x;
-    } else {
-        const int x = blockIdx.x % kXcds, per = kXcds / a.n_xs;
-        slice = x % a.n_xs;
-        u = (int64_t)(blockIdx.x / kXcds) * per + x / a.n_xs;
-    }
-    if (u >= a.n_units) return;
-    const UnitDesc d = a.pack.units[u];
-    const int ccol = a.ccol;
-    const int c0 = slice * a.sw;
-    const int w = min(a.sw, ccol - c0);                 // columns of this slice
-    const int G = min(64, pow2_at_least((a.sw + VV - 1) / VV));
-    const int gl = threadIdx.x % G, grp = threadIdx.x / G, ngrp = blockDim.x / G;
-    const int32_t *__restrict__ rows = a.pack.rows;
-    const int32_t *__restrict__ idx = static_cast<const int32_t *>(a.pack.idx);
-    const T *__restrict__ val = static_cast<const T *>(a.pack.vals);
-    const T *__restrict__ X = static_cast<const T *>(a.X) + (int64_t)slice * a.x_slice_stride;
-    const uint32_t ldx = (uint32_t)a.ldx;
-    T *__restrict__ Y = static_cast<T *>(a.Y) + c0;
-    if (d.split <= 1) {
-        const int n_ent = d.n_rows * d.slots;
-        {
-            // unit bases are multiples of four entries; the copy may run up to three entries over
-            const Piece *src_i = reinterpret_cast<const Piece *>(idx + d.entry_base);
-            Piece *dst_i = reinterpret_cast<Piece *>(idx_s);
-            for (int e = threadIdx.x; e < (n_ent + 3) / 4; e += blockDim.x) dst_i[e] = src_i[e];
-            constexpr int PV = 16 / (int)sizeof(T);
-            const Piece *src_v = reinterpret_cast<const Piece *>(val + d.entry_base);
-            Piece *dst_v = reinterpret_cast<Piece *>(val_s);
-            for (int e = threadIdx.x; e < (n_ent + PV - 1) / PV; e += blockDim.x) dst_v[e] = src_v[e];
-        }
-        int32_t rid[R];
-        {
-            // row ids of this group's first rows, on their way while the entries are copied
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const int i = grp + r * ngrp;
-                rid[r] = rows[d.row_begin + (i < d.n_rows ? i : 0)];
-            }
-        }
-        __syncthreads();
-        const int L = d.slots;
-        for (int cb = 0; cb < w; cb += G * VV) {
-            const bool active = cb + VV * gl < w;
-            const int col = min(cb + VV * gl, w - VV);
-            const uint32_t lane_off = active ? (uint32_t)col : 0u;      // idle lanes read column 0
-            for (int i0 = grp; i0 < d.n_rows; i0 += ngrp * R) {
-                int at[R];
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    const int i = i0 + r * ngrp;
-                    at[r] = (i < d.n_rows ? i : i0) * L;
-                }
-                if (i0 != grp || cb != 0) {
-#pragma unroll
-                    for (int r = 0; r < R; ++r) {
-                        const int i = i0 + r * ngrp;
-                        rid[r] = rows[d.row_begin + (i < d.n_rows ? i : i0)];
-                    }
-                }
-                T acc[R][VV];
-#pragma unroll
-                for (int r = 0; r < R; ++r)
-#pragma unroll
-                    for (int i = 0; i < VV; ++i) acc[r][i] = T(0);
-                // E entries of each of the R rows per pass, from slot sl on.  The last pass of a row
-                // may reach past the row's end: its surplus slots re-read the last entry (same
-                // address: no extra traffic) with a zero value, so that the whole remainder is one
-                // round trip to memory instead of one per entry (most rows of a graph are short).
-                auto pass = [&](auto masked_c, int sl) {
-                    constexpr bool MASKED = decltype(masked_c)::value;
-                    uint32_t c[R][E];
-                    T v[R][E];
-                    T x[R][E][VV];
-#pragma unroll
-                    for (int r = 0; r < R; ++r)
-#pragma unroll
-                        for (int e = 0; e < E; ++e) {
-                            const bool in = !MASKED || sl + e < L;
-                            const int at_e = at[r] + (in ? sl + e : L - 1);
-                            c[r][e] = (uint32_t)idx_s[at_e];
-                            v[r][e] = in ? val_s[at_e] : T(0);
-                        }
-#pragma unroll
-                    for (int r = 0; r < R; ++r)
-#pragma unroll
-                        for (int e = 0; e < E; ++e) load_x<T, VV, WIDE>(x[r][e], X, c[r][e], ldx, lane_off);
-#pragma unroll
-                    for (int r = 0; r < R; ++r)
-#pragma unroll
-                        for (int e = 0; e < E; ++e) {
-                            // (a surplus slot adds nothing, whatever the operand holds)
-                            if (MASKED && sl + e >= L) continue;
-#pragma unroll
-                            for (int i = 0; i < VV; ++i) acc[r][i] += v[r][e] * x[r][e][i];
-                        }
-                };
-                int sl = 0;
-                for (; sl + E <= L; sl += E) pass(std::false_type(), sl);
-                if (sl < L) pass(std::true_type(), sl);
-                if (active) {
-#pragma unroll
-                    for (int r = 0; r < R; ++r)
-                        if (i0 + r * ngrp < d.n_rows)
-                            store_any<T, VV>(Y + (int64_t)rid[r] * ccol + col, acc[r]);
-                }
-            }
-        }
-        return;
-    }
-    for (int cb = 0; cb < w; cb += G * VV) {
-        const bool active = cb + VV * gl < w;
-        const int col = min(cb + VV * gl, w - VV);
-        const uint32_t lane_off = active ? (uint32_t)col : 0u;      // idle lanes read column 0
-        {
-            // group -> (row, part); `split` groups share a row, each takes a range of the slots
-            const int row_i = grp / d.split, part = grp % d.split;
-            const int chunk = (d.slots + d.split - 1) / d.split;
-            const int s0 = min(d.slots, part * chunk), s1 = min(d.slots, s0 + chunk);
-            T acc[VV];
-#pragma unroll
-            for (int i = 0; i < VV; ++i) acc[i] = T(0);
-            // The entries of the group's part travel through LDS as well, a window of 8 G slots at a
-            // time: the G lanes fetch them with coalesced loads (one word per lane and load instead of
-            // the same word for every lane), put them into the group's piece of the staging arrays,
-            // and read them back as broadcasts, 8 per pass.  The next window's entries are in flight
-            // while the current window is gathered.  A group is part of one wave and LDS operations
-            // of a wave complete in order, so no workgroup barrier is involved.
-            const int WS = 8 * G;
-            int32_t *gi = idx_s + grp * WS;
-            T *gv = val_s + grp * WS;
-            const bool has_row = row_i < d.n_rows;
-            const int64_t at = d.entry_base + (int64_t)(has_row ? row_i : 0) * d.slots;
-            const int32_t *__restrict__ ip = idx + at;
-            const T *__restrict__ vp = val + at;
-            // Lane gl fetches the eight consecutive slots 8 gl .. 8 gl + 7 of a window (one address,
-            // eight immediate offsets).  A window may reach past the end of the part, of the row and,
-            // for the last row of the list, of the packed arrays, which therefore end with
-            // kPackSpareSlots zero entries: whatever index is read there names a valid row, and
-            // slots past the part's end are left out of the sum.
-            int32_t ci[8];
-            T vi[8];
-            const int32_t *__restrict__ ipl = ip + 8 * gl;
-            const T *__restrict__ vpl = vp + 8 * gl;
-            auto fetch_window = [&](int w0) {
-#pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    ci[k] = ipl[w0 + k];
-                    vi[k] = vpl[w0 + k];
-                }
-            };
-            if (has_row && s0 < s1) {
-                fetch_window(s0);
-                for (int w0 = s0; w0 < s1; w0 += WS) {
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) {
-                        gi[8 * gl + k] = ci[k];
-                        gv[8 * gl + k] = vi[k];
-                    }
-                    if (w0 + WS < s1) fetch_window(w0 + WS);
-                    __builtin_amdgcn_wave_barrier();
-                    asm volatile("" ::: "memory");
-                    const int n_here = min(WS, s1 - w0);
-                    for (int p0 = 0; p0 < n_here; p0 += 8) {
-                        uint32_t c[8];
-                        T v[8];
-                        T x[8][VV];
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) {
-                            c[e] = (uint32_t)gi[p0 + e];
-                            v[e] = gv[p0 + e];
-                        }
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) load_x<T, VV, WIDE>(x[e], X, c[e], ldx, lane_off);
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) {
-                            if (p0 + e >= n_here) continue;      // (a surplus slot adds nothing)
-#pragma unroll
-                            for (int i = 0; i < VV; ++i) acc[i] += v[e] * x[e][i];
-                        }
-                    }
-                    __builtin_amdgcn_wave_barrier();
-                    asm volatile("" ::: "memory");
-                }
-            }
-            __syncthreads();          // the staging arrays become the partial sums
-#pragma unroll
-            for (int i = 0; i < VV; ++i) red[(grp * G + gl) * VV + i] = acc[i];
-            __syncthreads();
-            if (part == 0 && row_i < d.n_rows && active) {
-                T sum[VV];
-#pragma unroll
-                for (int i = 0; i < VV; ++i) sum[i] = T(0);
-                for (int pp = 0; pp < d.split; ++pp)
-#pragma unroll
-                    for (int i = 0; i < VV; ++i) sum[i] += red[((grp + pp) * G + gl) * VV + i];
-                if (d.pieces > 1) {
-                    T *p = static_cast<T *>(a.partial) + ((int64_t)d.piece * a.n_xs + slice) * a.sw + col;
-#pragma unroll
-                    for (int i = 0; i < VV; ++i) __hip_atomic_store(p + i, sum[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                } else {
-                    store_any<T, VV>(Y + (int64_t)rows[d.row_begin + row_i] * ccol + col, sum);
-                }
-            }
-            __syncthreads();
-        }
-    }
-    if (d.pieces <= 1) return;
-    // A row cut over several workgroups: whoever is done last adds up the sums of all pieces, in their order.
-    // The sums go past the L2 (device-scope stores and loads), and are there before the count is raised.
-    __shared__ int32_t done_s;
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    int32_t *arrived = a.arrived + (int64_t)d.cut_row * a.n_xs + slice;
-    if (threadIdx.x == 0)
-        done_s = __hip_atomic_fetch_add(arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __syncthreads();
-    if (done_s != d.pieces - 1) return;
-    if (threadIdx.x == 0) __hip_atomic_store(arrived, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    for (int cb = 0; cb < w; cb += G * VV) {
-        const bool active = cb + VV * gl < w;
-        const int col = min(cb + VV * gl, w - VV);
-        T acc[VV];
-#pragma unroll
-        for (int i = 0; i < VV; ++i) acc[i] = T(0);
-        const T *p = static_cast<const T *>(a.partial) + ((int64_t)d.first_piece * a.n_xs + slice) * a.sw + col;
-        for (int k = grp; k < d.pieces; k += ngrp) {
-            const T *pk = p + (int64_t)k * a.n_xs * a.sw;
-#pragma unroll
-            for (int i = 0; i < VV; ++i) acc[i] += __hip_atomic_load(pk + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-#pragma unroll
-        for (int i = 0; i < VV; ++i) red[(grp * G + gl) * VV + i] = acc[i];
-        __syncthreads();
-        if (grp == 0 && active) {
-            T sum[VV];
-#pragma unroll
-            for (int i = 0; i < VV; ++i) sum[i] = T(0);
-            for (int g = 0; g < min(ngrp, d.pieces); ++g)
-#pragma unroll
-                for (int i = 0; i < VV; ++i) sum[i] += red[(g * G + gl) * VV + i];
-            store_any<T, VV>(Y + (int64_t)rows[d.row_begin] * ccol + col, sum);
-        }
-        __syncthreads();
-    }
-}
-
 // CSR SpMM over a caller-supplied matrix: Y[j][:] = sum_k S.vals[k] X[S.colidx[k]][:], consecutive
 // rows per workgroup.  The first operation of the unfused SpMM-SpMM baseline (row_info = nullptr:
 // every row goes to the workspace, slot = row), and the first wavefront of a CSR-B plan that needs
@@ -1784,32 +1494,6 @@ int launch_fused_spmm_spmm(const FusedLaunch &a, void *stream) {
     if (a.dtype == TF_F32)
         return fast ? run_fused_spmm<float, true>(a, st) : run_fused_spmm<float, false>(a, st);
     return fast ? run_fused_spmm<double, true>(a, st) : run_fused_spmm<double, false>(a, st);
-}
-
-int launch_packed_spmm(const PackedSpmmLaunch &a, void *stream) {
-    hipStream_t st = static_cast<hipStream_t>(stream);
-    if (a.n_units == 0) return 0;
-    if (a.n_xs != 1 && a.n_xs != 2 && a.n_xs != 4 && a.n_xs != 8) return (int)hipErrorInvalidValue;
-    const bool fast = lane_elems(a.dtype, a.ccol, a.sw) > 1;
-    // one workgroup per unit and slice; with slices, 8 / n_xs units per round of eight workgroups
-    const int64_t rounds = (a.n_units * a.n_xs + kXcds - 1) / kXcds;
-    const dim3 grid((unsigned)(rounds * kXcds)), block(kSpmmThreads);
-    (void)hipGetLastError();
-#define TF_GO2(T, W)                                                                     \
-    do {                                                                                 \
-        if (!fast) k_packed_spmm<T, false, W, 4><<<grid, block, 0, st>>>(a);             \
-        else if (a.rows_per_pass == 1) k_packed_spmm<T, true, W, 1><<<grid, block, 0, st>>>(a); \
-        else if (a.rows_per_pass == 2) k_packed_spmm<T, true, W, 2><<<grid, block, 0, st>>>(a); \
-        else k_packed_spmm<T, true, W, 4><<<grid, block, 0, st>>>(a);                    \
-    } while (0)
-#define TF_GO(T)                                                                         \
-    do {                                                                                 \
-        if (a.wide) TF_GO2(T, true); else TF_GO2(T, false);                              \
-    } while (0)
-    if (a.dtype == TF_F32) TF_GO(float); else TF_GO(double);
-#undef TF_GO
-#undef TF_GO2
-    return (int)hipGetLastError();
 }
 
 int launch_csr_spmm(const CsrSpmmLaunch &a, void *stream) {

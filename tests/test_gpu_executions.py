@@ -136,23 +136,28 @@ def test_column_groups_of_the_one_pass_chain_over_workgroups(dtype, bcol, ccol, 
         c.close()
 
 
-@pytest.mark.parametrize("dtype", [np.float32, np.float64])
-@pytest.mark.parametrize("kind,bcol,ccol,slices", [
-    ("spmm", 0, 64, 1), ("spmm", 0, 64, 2), ("spmm", 0, 30, 0), ("spmm", 0, 300, 0), ("gemm", 128, 41, 0),
-    ("gemm", 128, 128, 4), ("gemm", 32, 92, 0)])
-def test_rows_cut_over_several_workgroups(dtype, kind, bcol, ccol, slices):
-    """Rows around every length at which a row is split over the lane groups of a workgroup, and cut over
-    several workgroups (64 entries for each lane group of 256 threads), in the second wavefront, in Y = A B and
-    in the unfused second operation.  The counts of the pieces are back at zero after every run."""
-    from gpu_util import Case
-    n = 30011
-    rng = np.random.default_rng(12)
-    lens = rng.integers(0, 9, n)
-    hubs = [64 * g + d for g in (4, 8, 16, 32, 64) for d in (-1, 0, 1, 3)] + [127, 128, 129, 6001, 12345, 20000]
+def _hubs(n, dtype, rng, values):
+    """Far rows, among them some around every length at which a row is cut into parts of a block, takes a block, the
+    four blocks of a workgroup, or several times that (32 entries for each part, 1 to 64 parts a block)."""
+    lens = rng.integers(0, 9, n)            # (thousands of rows of one to four entries: several to a lane group)
+    hubs = [32 * g + d for g in (1, 2, 4, 8, 16, 32, 64, 128, 256) for d in (-1, 0, 1, 3)] + [6001, 12345, 20000]
     lens[rng.permutation(n)[:len(hubs)]] = hubs
     rowptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
     colidx = rng.integers(0, n, rowptr[-1]).astype(np.int32)
-    A = ti.Csr(n, n, rowptr, colidx, rng.integers(-2, 3, colidx.size).astype(dtype))
+    return ti.Csr(n, n, rowptr, colidx, values(colidx.size).astype(dtype))
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("kind,bcol,ccol,slices", [
+    ("spmm", 0, 64, 1), ("spmm", 0, 64, 2), ("spmm", 0, 30, 0), ("spmm", 0, 300, 0), ("spmm", 0, 1, 0), ("spmm", 0, 3, 0),
+    ("spmm", 0, 4, 0), ("spmm", 0, 8, 0), ("spmm", 0, 13, 0), ("gemm", 128, 41, 0), ("gemm", 128, 128, 4), ("gemm", 32, 92, 0)])
+def test_rows_cut_over_lane_groups_waves_and_workgroups(dtype, kind, bcol, ccol, slices):
+    """In the second wavefront, in Y = A B and in the unfused second operation, for every number of lanes per row.
+    The counts of the pieces are back at zero after every run."""
+    from gpu_util import Case
+    n = 30011
+    rng = np.random.default_rng(12)
+    A = _hubs(n, dtype, rng, lambda k: rng.integers(-2, 3, k))
     sparse = kind == "spmm"
     B = ti.random_local_csr(n, 50, 4, 0.0, dtype, 22, int_values=True) if sparse else ti.dense_small_int(n, bcol, dtype, 5)
     C = ti.dense_small_int(n if sparse else bcol, ccol, dtype, 6)
@@ -162,6 +167,29 @@ def test_rows_cut_over_several_workgroups(dtype, kind, bcol, ccol, slices):
         s = c.plan.schedule()
         assert np.array_equal(np.unique(s["wf1_unit_ptr"]), s["wf1_unit_ptr"])      # a cut row is in one unit
         for fused in (True, True, False, True, False):
+            assert np.array_equal(c.run(fused).astype(np.float64), D_ref)
+    finally:
+        c.close()
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("ccol,slices", [(128, 4), (130, 0)])
+def test_padding_of_gathered_rows_adds_nothing(dtype, ccol, slices):
+    """Blocks of rows of unequal length, and of rows cut into unequal parts, are padded: where D1 holds infinities, a
+    row of D is infinite if its row of A reads one of them, and its finite sum if not."""
+    from gpu_util import Case
+    n, bcol = 30011, 32
+    rng = np.random.default_rng(13)
+    A = _hubs(n, dtype, rng, lambda k: rng.integers(1, 3, k))
+    B, C = rng.integers(1, 4, (n, bcol)).astype(dtype), rng.integers(1, 4, (bcol, ccol)).astype(dtype)
+    hit = rng.random(n) < 0.002
+    D_ref, _ = oracle.chain(A, np.where(hit[:, None], dtype(0), B), C)
+    D_ref[np.unique(np.repeat(np.arange(n), np.diff(A.rowptr))[hit[A.colidx]])] = np.inf
+    B[hit] = np.inf
+    c = Case(ti.Problem("padding", "gemm_spmm", np.dtype(dtype), A, B, C), gather_slices=slices)
+    try:
+        assert c.plan.schedule()["first_wavefront_streams"] and np.isinf(D_ref).any() and np.isfinite(D_ref).any()
+        for fused in (True, False):
             assert np.array_equal(c.run(fused).astype(np.float64), D_ref)
     finally:
         c.close()
