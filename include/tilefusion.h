@@ -82,7 +82,8 @@ typedef struct tf_tile_params {
     int32_t gather_slices;   /* column slices of the D1 workspace, each gathered by its own XCDs
                                 in the second wavefront: 1, 2, 4 or 8, slices of a power of two
                                 of columns, at least 16 and at least 64 bytes.  Default: 1 for
-                                matrices whose rows stay near the diagonal, more for matrices
+                                matrices whose rows stay near the diagonal, slices of 128 bytes
+                                (any number of them up to 8) or rows padded to that for matrices
                                 whose rows reach far (graphs), see tf_schedule_view.d1_slices   */
     int32_t reserved0;
 } tf_tile_params;
@@ -190,7 +191,8 @@ typedef struct tf_schedule_view {
     int32_t d1_slices;          /* workspace layout: d1_slices column slices of d1_slice_cols     */
     int32_t d1_slice_cols;      /* columns, slice after slice, each d1_rows x d1_slice_cols       */
     int64_t d1_rows;            /* row-major: element (slot, c) is at (c / d1_slice_cols) d1_rows
-                                   d1_slice_cols + slot d1_slice_cols + c mod d1_slice_cols       */
+                                   d1_slice_cols + slot d1_slice_cols + c mod d1_slice_cols; the
+                                   slices may hold more than cCol columns, the last of them padding */
     int32_t first_wavefront_streams; /* 1: no fused row reads the LDS tile (all are direct rows), so
                                    the first wavefront runs without tiles in LDS, streaming through
                                    the rows like the plain first operation                        */

@@ -117,7 +117,6 @@ struct tf_plan {
             d.idx = static_cast<const int32_t *>(idx);
             d.vals = vals;
             d.cuts = static_cast<const tf::CutBlock *>(cuts);
-            d.n_cut_blocks = n_cut_blocks;
             return d;
         }
     };
@@ -233,6 +232,7 @@ tf::PackedSpmmLaunch packed_args(const tf_plan *p, const tf_plan::PackBufs &b, c
     tf::PackedSpmmLaunch w{};
     w.dtype = p->dtype;
     w.n_blocks = b.n_blocks;
+    w.n_cut_blocks = b.n_cut_blocks;
     w.n_cu = p->n_cu;
     w.contiguous = b.sorted ? 0 : 1;
     // operand offsets inside a slice are formed in 32 bits unless the slice spans 4 GiB or more
@@ -312,6 +312,7 @@ void gemm_workspace(tf::GemmLaunch &g, void *ws, const tf::D1Layout &lay) {
     g.d1_sw_shift = sw_shift(lay);
     g.d1_sw_mask = sw_mask(lay);
     g.d1_slice_stride = lay.slice_stride();
+    g.d1_cols = (int32_t)lay.columns();
 }
 tf::CsrSpmmLaunch csr_spmm_args(const tf_plan *p, const tf_csr *B, const void *C, void *ws,
                                 const tf::D1Layout &lay) {
@@ -386,11 +387,11 @@ tf_status run_plain_pair(const tf_plan *p, const tf_csr *B, const void *C, void 
 }
 // Y = A B into the workspace, D = Y C (dense B).
 tf_status run_gather_first(const tf_plan *p, const void *B, const void *C, void *D, void *ws, void *stream) {
-    tf::D1Layout y;
-    y.sw = (int32_t)p->bcol;
-    y.rows = p->n;
+    const tf::D1Layout y = tf::gather_first_slices(p->dtype, p->n, p->bcol);
     tf::PackedSpmmLaunch w = packed_args(p, p->s.gather_first_shares ? p->all : p->gf, B, y, ws);
-    w.ccol = (int32_t)p->bcol;
+    w.ccol = w.ldx = (int32_t)p->bcol;             // (slices of whole rows of B)
+    w.x_slice_stride = y.sw;
+    w.wide = (double)y.elements() * tf::elem_size(p->dtype) >= 4294967296.0 ? 1 : 0;
     w.read_next = 1;
     int e = tf::launch_packed_spmm(w, stream);
     if (e) return hip_fail((hipError_t)e, "launching the SpMM");
@@ -441,9 +442,8 @@ tf_status second_wavefront(const tf_plan *p, void *D, void *ws, void *stream) {
 // Workspace of tf_gemm_spmm_static: one array per GPU, part of the loaded code object, so that
 // the call needs no allocation at all.  In host code the array's name is only a handle; its
 // device address is looked up once per device and used from then on.
-constexpr size_t kStaticScratchBytes = (size_t)64 << 20;
 constexpr int kMaxDevices = 64;
-static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
+static __device__ __align__(256) unsigned char scratch[tf::kStaticScratchBytes];
 std::mutex g_scratch_mutex;
 void *g_scratch_ptr[kMaxDevices] = {};
 
@@ -637,12 +637,8 @@ tf_status tf_plan_create(const tf_csr *A, int64_t bCol, int64_t cCol, int32_t b_
         }
         // behind the rows of the workspace: the sums of cut rows, for each pack (B is gathered whole, and with
         // `all` only where its rows take as many lanes as a slice of D1 does)
-        tf::D1Layout y = sc.d1;
-        if (sc.gather_first) {
-            y.n_sl = 1;
-            y.sw = (int32_t)bCol;
-        }
-        const bool y_wider = sc.gather_first_shares && y.sw > sc.d1.n_sl * sc.d1.sw;
+        const tf::D1Layout y = sc.gather_first ? tf::gather_first_slices(p->dtype, n, bCol) : sc.d1;
+        const bool y_wider = sc.gather_first_shares && y.columns() > sc.d1.columns();
         p->wf1.partial_at = ((size_t)sc.d1.elements() * es + 255) / 256 * 256;
         p->all.partial_at = p->wf1.partial_at + partial_bytes(sc.wf1, sc.d1, es);
         p->gf.partial_at = p->all.partial_at + partial_bytes(sc.all, y_wider ? y : sc.d1, es);
@@ -801,10 +797,10 @@ tf_status tf_gemm_spmm_static(const tf_plan *p, const void *B, const void *C, vo
     if (st != TF_OK) return st;
     if (!B || !aligned16(B)) return fail(TF_EINVAL, "B must be a 16-byte aligned device pointer");
     const size_t need = (size_t)p->s.d1.elements() * (size_t)tf::elem_size(p->dtype);
-    if (need > kStaticScratchBytes)
+    if (need > (size_t)tf::kStaticScratchBytes)
         return fail(TF_EUNSUPPORTED, "the plan's D1 workspace (" + std::to_string(need) +
                                          " bytes) exceeds the static workspace of " +
-                                         std::to_string(kStaticScratchBytes) + " bytes");
+                                         std::to_string(tf::kStaticScratchBytes) + " bytes");
     const int32_t execution = p->fused_execution();      // (as tf_gemm_spmm: the same sums in the same order)
     if (execution == TF_EXECUTE_ONE_PASS) return run_chain(p, B, C, D, stream);
     void *ws = nullptr;

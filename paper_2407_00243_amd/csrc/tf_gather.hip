@@ -33,7 +33,7 @@ template <typename T, int VV, int G, bool WIDE>
 __global__ __launch_bounds__(kSpmmThreads, gather_waves(dtype_of<T>())) void k_packed_spmm(
     const PackedSpmmLaunch a, const GatherBlock *__restrict__ blocks, const int32_t *__restrict__ rows,
     const int32_t *__restrict__ lens, const int32_t *__restrict__ idx, const T *__restrict__ val,
-    const CutBlock *__restrict__ cuts, const T *__restrict__ X0, T *Y0) {
+    const CutBlock *__restrict__ cuts, const T *__restrict__ X0, T *Y0, T *partial, int32_t *all_arrived) {
     constexpr int E = kGatherEntries, NR = 64 / G, NE = NR * E > 64 ? NR * E / 64 : 1;
     typedef std::conditional_t<WIDE, uint64_t, uint32_t> Off;
     typedef T Vec16 __attribute__((ext_vector_type(Tr<T>::V)));
@@ -53,8 +53,8 @@ __global__ __launch_bounds__(kSpmmThreads, gather_waves(dtype_of<T>())) void k_p
     const Off row_bytes = (Off)a.ldx * (Off)sizeof(T);
     // (quads: the blocks of a workgroup)
     const int n_wg = (int)(gridDim.x / kXcds), my = (int)(blockIdx.x / kXcds);
-    const int n_quads = a.n_blocks / kGatherQuad, eighth = (n_quads + kXcds - 1) / kXcds;
-    const int n_cb = (a.sw + G * VV - 1) / (G * VV);        // column blocks of a slice (rows wider than a wave's load)
+    const int n_quads = (uint32_t)a.n_blocks / kGatherQuad, eighth = (uint32_t)(n_quads + kXcds - 1) / kXcds;
+    const int n_cb = (uint32_t)(a.sw + G * VV - 1) / (G * VV);        // column blocks of a slice (rows wider than a wave's load)
 
     int32_t ci[NE];
     T vi[NE];
@@ -77,7 +77,9 @@ __global__ __launch_bounds__(kSpmmThreads, gather_waves(dtype_of<T>())) void k_p
         __builtin_amdgcn_wave_barrier();
     };
 
-    for (int at = (int)(blockIdx.x % kXcds) * a.n_xs, left = a.n_xs; left > 0;) {
+    // (n_xs > 0: a loop that ends with its test, or the arguments are fetched in two rounds)
+    int at = (int)(blockIdx.x % kXcds) * a.n_xs, left = a.n_xs;
+    do {
         const int slice = at / kXcds, e0 = at % kXcds, n_e = min(left, kXcds - e0);
         at += n_e;
         left -= n_e;
@@ -87,9 +89,11 @@ __global__ __launch_bounds__(kSpmmThreads, gather_waves(dtype_of<T>())) void k_p
         auto quad_of = [&](int k) __attribute__((always_inline)) {
             if (a.contiguous) return e0 * eighth + k * n_wg + my;
             const int j = k * n_wg + (k & 1 ? n_wg - 1 - my : my);
-            return j / n_e * kXcds + e0 + j % n_e;
+            const int q = n_e == 1 ? j : (int)__umulhi((uint32_t)j, a.reciprocal[n_e]);       // j / n_e
+            return q * kXcds + e0 + j - q * n_e;
         };
-        for (int cb = 0; cb < n_cb && cb * G * VV < w; ++cb) {
+        int cb = 0;
+        do {
             const bool active = cb * G * VV + VV * gl < w;
             const int col = min(cb * G * VV + VV * gl, w - VV);
             const char *__restrict__ X = reinterpret_cast<const char *>(X0 + (int64_t)slice * a.x_slice_stride);
@@ -113,17 +117,21 @@ __global__ __launch_bounds__(kSpmmThreads, gather_waves(dtype_of<T>())) void k_p
                 for (int e = 0; e < E; ++e)
                     if (e < n) x[e] = *reinterpret_cast<const XAny *>(X + (Off)(o[e] + lane_bytes));
             };
-            // n_real: entries of the lane's row among the pass's; what lies beyond adds nothing, whatever X holds
-            auto consume = [&](bool whole, int n_real) __attribute__((always_inline)) {
+            // whole: all virtual rows have the n entries of the pass; else n_real: those of the lane's row, and what lies
+            // beyond adds nothing, whatever X holds
+            auto consume = [&](int n, bool whole, int n_real) __attribute__((always_inline)) {
                 T f[E];
 #pragma unroll
                 for (int e = 0; e < E; e += Tr<T>::V)
                     load_pack<T, Tr<T>::V>(*reinterpret_cast<T(*)[Tr<T>::V]>(&f[e]), val_w + v * E + e);
                 if (whole) {
 #pragma unroll
-                    for (int e = 0; e < E; ++e)
+                    for (int e = 0; e < E; ++e) {
+                        if (e < n) {
 #pragma unroll
-                        for (int i = 0; i < VV; ++i) acc[i] += f[e] * part(x[e], i);
+                            for (int i = 0; i < VV; ++i) acc[i] += f[e] * part(x[e], i);
+                        }
+                    }
                 } else {
 #pragma unroll
                     for (int e = 0; e < E; ++e)
@@ -156,7 +164,7 @@ __global__ __launch_bounds__(kSpmmThreads, gather_waves(dtype_of<T>())) void k_p
                     for (int i = 0; i < VV; ++i) acc[i] += __shfl_xor(acc[i], m, 64);
                 }
                 bool store = active && (v & ((1 << slog) - 1)) == 0 && (v >> slog) < (int)(b.info >> 6);
-                const bool cut = at_block < a.pack.n_cut_blocks;      // (the same for all four blocks of the quad)
+                const bool cut = at_block < a.n_cut_blocks;      // (the same for all four blocks of the quad)
                 if (cut) {
                     if (v == 0) store_pack<T, VV>(&sum_s[wave][gl * VV], acc);
                     __syncthreads();
@@ -173,7 +181,7 @@ __global__ __launch_bounds__(kSpmmThreads, gather_waves(dtype_of<T>())) void k_p
                 if (cut && cuts[at_block].pieces > 1) {
                     const CutBlock c = cuts[at_block];
                     const int64_t pitch = (int64_t)a.n_xs * a.sw;
-                    T *p = static_cast<T *>(a.partial) + slice * a.sw + col;
+                    T *p = partial + slice * a.sw + col;
                     if (store) {
 #pragma unroll
                         for (int i = 0; i < VV; ++i)
@@ -181,7 +189,7 @@ __global__ __launch_bounds__(kSpmmThreads, gather_waves(dtype_of<T>())) void k_p
                     }
                     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
                     __builtin_amdgcn_s_waitcnt(0);
-                    int32_t *arrived = a.arrived + ((int64_t)c.row * a.n_xs + slice) * n_cb + cb;
+                    int32_t *arrived = all_arrived + ((int64_t)c.row * a.n_xs + slice) * n_cb + cb;
                     int32_t done = 0;
                     if (lane == 0)
                         done = __hip_atomic_fetch_add(arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -226,7 +234,7 @@ __global__ __launch_bounds__(kSpmmThreads, gather_waves(dtype_of<T>())) void k_p
             };
 
             int k = 0, u = quad_of(k);
-            if (u >= end) continue;
+            if (u >= end) break;
             int at_d = u * kGatherQuad + wave, at_n = at_d;
             GatherBlock d = blocks[at_d], dn = d;
             int32_t row = rows[row_at(d)], len = lens[row_at(d)];
@@ -246,7 +254,7 @@ __global__ __launch_bounds__(kSpmmThreads, gather_waves(dtype_of<T>())) void k_p
 #pragma unroll
                 for (int i = 0; i < VV; ++i) acc[i] = T(0);
                 // entries of the lane's (virtual) row
-                const int n_d = slots(d), whole = (int)(d.size >> 16), skip = at_d < a.pack.n_cut_blocks ? cuts[at_d].skip : 0;
+                const int n_d = slots(d), whole = (int)(d.size >> 16), skip = at_d < a.n_cut_blocks ? cuts[at_d].skip : 0;
                 const int real = min(n_d, len - (v & ((1 << (d.info & 7)) - 1)) * n_d - skip);
                 const int each = (d.info >> 3) & 7;
                 if (each) {
@@ -255,18 +263,22 @@ __global__ __launch_bounds__(kSpmmThreads, gather_waves(dtype_of<T>())) void k_p
                     else if (G >= 2 && each == 3) finish_short(std::integral_constant<int, 3>(), d, row);
                     else if (G >= 2) finish_short(std::integral_constant<int, 4>(), d, row);
                 } else {
-                    consume(whole >= E, real);
+                    consume(min(E, n_d), whole >= min(E, n_d), real);
                 }
                 for (int s0 = E; s0 < n_d; s0 += E) {
                     put();
                     fetch(s0 + E < n_d ? d.slot_base + s0 + E : dn.slot_base);
                     issue(min(E, n_d - s0));
-                    consume(whole >= s0 + E, real - s0);
+                    consume(min(E, n_d - s0), whole >= min(s0 + E, n_d), real - s0);
                 }
                 // the next block's first gathers go out before this one's sums are stored (none after the last)
-                put();
-                const int32_t row_n = rows[row_at(dn)], len_n = lens[row_at(dn)];
-                fetch(slots(dn) > E ? dn.slot_base + E : dnn.slot_base);
+                int32_t row_n = 0, len_n = 0;
+                if (has_next) {
+                    put();
+                    row_n = rows[row_at(dn)];
+                    len_n = lens[row_at(dn)];
+                    fetch(slots(dn) > E ? dn.slot_base + E : dnn.slot_base);
+                }
                 issue(has_next ? min(E, slots(dn)) : 0);
                 if (!each) finish(d, row, at_d);
                 if (!has_next) break;
@@ -278,8 +290,8 @@ __global__ __launch_bounds__(kSpmmThreads, gather_waves(dtype_of<T>())) void k_p
                 len = len_n;
                 has_next = has_next2;
             }
-        }
-    }
+        } while (++cb < n_cb && cb * G * VV < w);
+    } while (left > 0);
 }
 
 template <typename T, int VV, int G, bool WIDE> int run_packed(const PackedSpmmLaunch &a, hipStream_t st) {
@@ -289,7 +301,7 @@ template <typename T, int VV, int G, bool WIDE> int run_packed(const PackedSpmmL
     (void)hipGetLastError();      // an error left by an earlier, unrelated call is not this launch's
     k_packed_spmm<T, VV, G, WIDE><<<dim3((unsigned)(per_xcd * kXcds)), dim3(kSpmmThreads), 0, st>>>(
         a, a.pack.blocks, a.pack.rows, a.pack.lens, a.pack.idx, static_cast<const T *>(a.pack.vals), a.pack.cuts,
-        static_cast<const T *>(a.X), static_cast<T *>(a.Y));
+        static_cast<const T *>(a.X), static_cast<T *>(a.Y), static_cast<T *>(a.partial), a.arrived);
     return (int)hipGetLastError();
 }
 
@@ -320,7 +332,9 @@ template <typename T, bool WIDE> int run_packed_group(const PackedSpmmLaunch &a,
 
 }  // namespace
 
-int launch_packed_spmm(const PackedSpmmLaunch &a, void *stream) {
+int launch_packed_spmm(const PackedSpmmLaunch &launch, void *stream) {
+    PackedSpmmLaunch a = launch;
+    for (uint32_t k = 2; k <= kXcds; ++k) a.reciprocal[k] = 0xffffffffu / k + 1;
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (a.n_blocks == 0) return 0;
     if (a.n_xs < 1 || a.n_xs > kXcds || a.n_blocks % kGatherQuad) return (int)hipErrorInvalidValue;

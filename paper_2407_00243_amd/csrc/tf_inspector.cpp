@@ -12,6 +12,7 @@
 #include <algorithm>
 #include <atomic>
 #include <chrono>
+#include <cmath>
 #include <cstdlib>
 #include <cstring>
 #include <numeric>
@@ -63,7 +64,7 @@ namespace {
 
 struct PackRules {
     int nr;              // virtual rows of a block
-    int64_t longest;     // most slots of a virtual row: longer rows are cut
+    int64_t longest;     // most slots of a virtual row: rows of more than nr times that take several blocks
     int counts;          // counts of finished pieces per cut row (slices x column blocks)
 };
 
@@ -111,12 +112,17 @@ void pack_rows(const int32_t *rowptr, const int32_t *colidx, const unsigned char
     lens.resize((size_t)count);
     int64_t real = 0, longest = 0, shortest = 0, padded = 0;
     bool empty_inside = false;
+    // rows that are measured against each other: those of a workgroup, up to 64 in long lists (a block of one
+    // row is never padded, but an XCD that takes the long rows of an unsorted list holds the others up: R-MAT
+    // graph of 300000 rows, fp64, 128 columns, one slice, 1702 us, sorted 448)
+    int64_t window = std::min<int64_t>(64, nr * kGatherQuad);
+    while (2 * window <= std::min<int64_t>(64, (count + 1023) / 1024)) window *= 2;
     auto measure = [&]() {
         real = longest = padded = 0;
         shortest = INT32_MAX;
         empty_inside = false;
-        for (int64_t p0 = 0; p0 < count; p0 += nr) {
-            const int64_t p1 = std::min(count, p0 + nr);
+        for (int64_t p0 = 0; p0 < count; p0 += window) {
+            const int64_t p1 = std::min(count, p0 + window);
             int64_t mx = 0;
             for (int64_t q = p0; q < p1; ++q) {
                 const int32_t j = list[(size_t)q], l = rowptr[j + 1] - rowptr[j];
@@ -136,7 +142,7 @@ void pack_rows(const int32_t *rowptr, const int32_t *colidx, const unsigned char
         std::stable_partition(list.begin(), list.end(), [&](int32_t j) { return rowptr[j + 1] > rowptr[j]; });
         measure();
     }
-    // re-order by length when padding would cost over 15 %: longest first, rows of one length in their given
+    // re-order by length when rows of equal length in every window would cost over 15 %: longest first, rows of one length in their given
     // order; by counting when the lengths are a small range, else by comparison
     if (padded > real + real * 15 / 100) {
         if (longest <= 4 * count + 1024) {
@@ -188,7 +194,7 @@ void pack_rows(const int32_t *rowptr, const int32_t *colidx, const unsigned char
     // parts that the other rows are cut into inside their block (log2)
     auto cut_of = [&](int64_t l) {
         int c = 0;
-        while ((l + (1 << c) - 1) >> c > rules.longest) ++c;
+        while ((l + (1 << c) - 1) >> c > rules.longest && c < log_nr) ++c;
         return c;
     };
     const size_t first_whole = out.blocks.size();
@@ -243,7 +249,7 @@ void pack_rows(const int32_t *rowptr, const int32_t *colidx, const unsigned char
         pos += take;
     }
     if (out.sorted) {
-        // (rows cut into parts have half of the longest slots or more, whole rows come in their order)
+        // (rows cut into parts have half of a part's slots or more, whole rows come in their order)
         size_t end = first_whole;
         while (end < out.blocks.size() && out.blocks[end].slots() * 2 >= rules.longest) ++end;
         std::stable_sort(out.blocks.begin() + (int64_t)first_whole, out.blocks.begin() + (int64_t)end,
@@ -425,6 +431,22 @@ TileBlock pack_tile(const int32_t *rowptr, const int32_t *colidx, const unsigned
 }
 
 }  // namespace
+
+// Columns between the rows of a workspace whose rows are shorter than a cache line, ccol or more: rows that straddle
+// lines cost a request each time they do, padding makes the array larger.  (R-MAT graphs, fp32, 23 columns, second
+// wavefront, us, rows of 92, 96 and 128 bytes: 100000 rows 21.6 / 20.3 / 17.5, 2^20 rows 258 / 240 / 194.)
+static int64_t row_pitch(int64_t ccol, int64_t es) {
+    const int64_t row = ccol * es;
+    auto cost = [&](int64_t pitch) {
+        int lines = 0;
+        for (int k = 0; k < 32; ++k) lines += (k * pitch % kGatherSliceBytes + row - 1) / kGatherSliceBytes + 1;
+        return lines / 32.0 * std::pow((double)pitch / (double)row, 0.4);
+    };
+    int64_t best = row;
+    for (int64_t p = 32; p <= kGatherSliceBytes; p *= 2)
+        if (p >= row && p < 2 * row && cost(p) < cost(best)) best = p;
+    return best / es;
+}
 
 // How rows of `sw` columns (of ccol, in column slices) are packed for the gather kernel; `entries` of them in all.
 static PackRules pack_rules(const InspectorInput &in, int64_t ccol, int64_t entries, const D1Layout &lay) {
@@ -936,12 +958,14 @@ tf_status build_schedule(const InspectorInput &in, Schedule &s, std::string &err
     // On a matrix whose rows reach far (a graph) every XCD's L2 sees the same hot rows of D1 and
     // holds them all, whole: the eight caches together are worth one.  With n_sl slices each XCD
     // gathers sw-wide pieces of the rows, so the hot set is spread over the caches, at the price of
-    // reading the packed entries of A once per slice.  Matrices whose rows stay near the diagonal
-    // (stencils, bands) keep one slice, and so do workspaces of 64 MiB and less: neither line is drawn from a
-    // sweep.  (7-point stencil 64^3, fp64, 64 columns, one slice: two requests in five hit the L2, 253 MB
-    // fetched for 99 MB of spilled rows.)
+    // reading the packed entries of A once per slice.  Slices of one cache line each, up to eight (R-MAT graphs,
+    // second wavefront, us, whole rows / slices of two lines / of one: 30000 rows fp32 128 columns 23.1 / 17.9 /
+    // 17.0; 100000 rows fp64 64 columns 63.9 / 56.3 / 55.8, fp32 64 columns 30.0 / - / 28.6; 300000 rows fp64 128
+    // columns 574 / 476 (two slices) / 373 (eight); 2^20 rows fp32 128 columns 930 / 837 / 703; of half a line,
+    // 2^20 rows, 1111).  Matrices whose rows stay near the diagonal (stencils, bands) keep one slice.
     {
         int n_sl = 1;
+        int64_t sw = in.ccol;
         auto usable = [&](int k) {
             if (k == 1) return true;
             if (in.ccol % v || in.ccol % k) return false;
@@ -951,6 +975,7 @@ tf_status build_schedule(const InspectorInput &in, Schedule &s, std::string &err
             const int64_t sw = in.ccol / k;
             return sw % 16 == 0 && (sw & (sw - 1)) == 0 && sw * es >= 64;
         };
+        s.d1.rows = std::max<int64_t>(1, s.n_spill_rows);
         if (in.gather_slices > 0) {
             if ((in.gather_slices != 1 && in.gather_slices != 2 && in.gather_slices != 4 &&
                  in.gather_slices != 8) || !usable(in.gather_slices)) {
@@ -959,19 +984,28 @@ tf_status build_schedule(const InspectorInput &in, Schedule &s, std::string &err
                 return TF_EINVAL;
             }
             n_sl = in.gather_slices;
-        } else if (!wf1.empty()) {
-            const double row_bytes = (double)in.ccol * es;
-            const bool large = (double)s.n_spill_rows * row_bytes > 64.0 * 1048576.0;
-            if (far_rows && large)
-                for (int k = 8; k > 1; k /= 2)
-                    if (usable(k) && in.ccol / k * es >= kGatherSliceBytes) {
-                        n_sl = k;
-                        break;
-                    }
+            sw = in.ccol / n_sl;
+        } else if (!wf1.empty() && far_rows) {
+            if (in.ccol * es > kGatherSliceBytes) {
+                int64_t w = kGatherSliceBytes / es;
+                while (w * kXcds < in.ccol) w *= 2;
+                // (the last slice may be narrower in use, down to one lane's 16 bytes)
+                if ((in.ccol - 1) % w + 1 >= v && (s.n_slices == 1 || cs % 16 == 0)) {
+                    sw = w;
+                    n_sl = (int)((in.ccol + w - 1) / w);
+                }
+            } else {
+                sw = row_pitch(in.ccol, es);
+            }
+            // (the entry point with the library's own workspace takes what it took)
+            const int64_t bytes = s.d1.rows * es;
+            if (!in.b_is_sparse && bytes * n_sl * sw > kStaticScratchBytes && bytes * in.ccol <= kStaticScratchBytes) {
+                n_sl = 1;
+                sw = in.ccol;
+            }
         }
         s.d1.n_sl = n_sl;
-        s.d1.sw = (int32_t)(in.ccol / n_sl);
-        s.d1.rows = std::max<int64_t>(1, s.n_spill_rows);
+        s.d1.sw = (int32_t)sw;
     }
     TF_TICK("spill set, slots, layout");
     // ---- per-tile blocks (see TileDesc) ---------------------------------------------------
@@ -1257,21 +1291,20 @@ void choose_gather_first(const InspectorInput &in, Schedule &s) {
     // only where the caller has left the whole choice to the library
     if (!s.automatic || in.col_slice || in.gather_slices || !in.whole_fast_mem) return;
     if (!s.chain.blocks.empty() || !s.streaming) return;
-    if (n > (int64_t)kInfoSlotMask || n * in.bcol > s.d1.elements()) return;
+    if (n > (int64_t)kInfoSlotMask || n * in.bcol > s.d1.rows * in.ccol) return;
     auto touched = [&](int64_t cols) { return cols * es % 64 ? cols * es + 64 : cols * es; };
     s.gather_first = 5 * touched(in.bcol) <= 4 * touched(in.ccol);
 }
 
 void build_gather_first(const InspectorInput &in, Schedule &s, bool have_all) {
     const int64_t n = in.n, es = elem_size(in.dtype);
-    const int group = lane_group((int)in.bcol, lane_elems(in.dtype, in.bcol, in.bcol));
+    const D1Layout b = gather_first_slices(in.dtype, n, in.bcol);
+    const int group = lane_group(b.sw, lane_elems(in.dtype, in.bcol, b.sw));
     const int group_all = lane_group(s.d1.sw, lane_elems(in.dtype, in.ccol, s.d1.sw));
     s.gather_first_shares = have_all && group == group_all;
     if (!s.gather_first_shares) {
         std::vector<int32_t> all((size_t)n);
         std::iota(all.begin(), all.end(), 0);
-        D1Layout b;
-        b.sw = (int32_t)in.bcol;
         pack_rows(in.rowptr, in.colidx, static_cast<const unsigned char *>(in.vals), (int)es, std::move(all),
                   pack_rules(in, in.bcol, in.nnz, b), [](int32_t c) { return c; }, s.gf);
     }

@@ -21,7 +21,8 @@ constexpr int kSpmmThreads = 256;        // workgroup size of the row-list SpMM 
 constexpr int kWantedTileRows = 256;     // a default column slice is narrowed until tiles this large fit
 constexpr int kGatherEntries = 8;        // entries per row that the gather kernel has in flight
 constexpr int kGatherQuad = kSpmmThreads / 64;   // blocks that its workgroups take at a time
-constexpr int kGatherSliceBytes = 128;    // narrowest column slice of the gather kernel chosen by default, bytes
+constexpr int kGatherSliceBytes = 128;   // a cache line: column slices of the gather kernel chosen by default, bytes
+constexpr int64_t kStaticScratchBytes = (int64_t)64 << 20;   // workspace of tf_gemm_spmm_static
 
 // Per D1 row of a tile, beside its row id: one info word.  kInfoSpill: the row is also stored to
 // the D1 workspace, at the slot in the low bits (a row that the second wavefront reads).
@@ -48,7 +49,25 @@ struct D1Layout {
     int64_t rows = 0;
     int64_t slice_stride() const { return rows * sw; }
     int64_t elements() const { return (int64_t)n_sl * rows * sw; }
+    int64_t columns() const { return (int64_t)n_sl * sw; }
 };
+
+// Column slices in which the rows of a dense B are gathered: one cache line each, where rows are whole lines
+// (rows of slices that begin anywhere in a line would touch more of them); `rows` rows of bcol columns,
+// element (i, c) at i bcol + c whatever the slices.
+inline D1Layout gather_first_slices(int dtype, int64_t rows, int64_t bcol) {
+    const int64_t es = dtype == TF_F64 ? 8 : 4;
+    D1Layout l;
+    l.rows = rows;
+    l.sw = (int32_t)bcol;
+    if (bcol * es % kGatherSliceBytes) return l;
+    int64_t k = bcol * es / kGatherSliceBytes;
+    while (k > kXcds && k % 2 == 0) k /= 2;
+    if (k > kXcds) return l;
+    l.n_sl = (int32_t)k;
+    l.sw = (int32_t)(bcol / k);
+    return l;
+}
 
 // Lanes that share one row in the gather kernels: each lane owns vv columns (vv = elements per
 // 16 bytes when rows are 16-byte aligned, else 1); the group is the smallest power of two of
@@ -435,7 +454,6 @@ struct PackDev {
     const int32_t *rows = nullptr, *lens = nullptr, *idx = nullptr;
     const void *vals = nullptr;
     const CutBlock *cuts = nullptr;
-    int32_t n_cut_blocks = 0;
 };
 
 struct FusedLaunch {
@@ -467,21 +485,22 @@ struct FusedLaunch {
 
 // Y[row] = sum over the packed entries of the row of val * X[idx].
 struct PackedSpmmLaunch {
-    int32_t dtype;
-    int32_t n_blocks;
-    int32_t contiguous;               // 1: neighbouring blocks share an XCD; 0: round robin
-    int32_t wide;                     // 1: X spans 4 GiB or more (64-bit operand offsets)
-    int32_t n_cu;                     // compute units of the device
-    PackDev pack;                     // indices: rows (slots) of X
-    const void *X;                    // D1 workspace in the layout below, or a dense B
-    int32_t n_xs, sw;                 // column slices (1 to 8; each XCD handles n_xs eighths of one or two) of sw columns
     int64_t x_slice_stride;           // elements between the slices of X
+    int32_t n_xs, sw;                 // column slices (1 to 8; each XCD handles n_xs eighths of one or two) of sw columns
     int32_t ldx;                      // elements between the rows of a slice
+    int32_t n_blocks, n_cut_blocks;
+    int32_t ccol;
+    int32_t contiguous;               // 1: neighbouring blocks share an XCD; 0: round robin
+    int32_t read_next;                // 1: the next launch reads Y
+    uint32_t reciprocal[kXcds + 1];   // (set by the launcher) 2^32 / k, rounded up: block counts divided by k
+    int32_t dtype;
     void *partial;                    // sums of the pieces of cut rows: [piece][slice][sw]
     int32_t *arrived;                 // pieces of a cut row that are done: [cut row][slice][column block], zeros between launches
+    PackDev pack;                     // indices: rows (slots) of X
+    const void *X;                    // D1 workspace in the layout above, or a dense B
     void *Y;                          // row-major, ccol columns
-    int32_t ccol;
-    int32_t read_next;                // 1: the next launch reads Y
+    int32_t wide;                     // 1: X spans 4 GiB or more (64-bit operand offsets)
+    int32_t n_cu;                     // compute units of the device
 };
 
 // Y[j] = S[j, :] X for a caller-supplied CSR matrix S, `rows_per_wg` consecutive rows per workgroup.
@@ -509,6 +528,7 @@ struct GemmLaunch {
     int32_t c_ldk, c_ldc;             // element (k, c) of the multiplier is C[k c_ldk + c c_ldc]
     void *D1;                         // workspace layout: slices of d1_sw columns
     int32_t d1_sw_shift, d1_sw_mask, d1_sw;
+    int32_t d1_cols;                  // columns of the workspace, cCol or more: the products' zeros fill what is padding
     int64_t d1_slice_stride;
     // first wavefront of a plan without an LDS tile (else nullptr): info word per row (kInfo*),
     // diagonal entry of the direct rows (nullptr: none), and D

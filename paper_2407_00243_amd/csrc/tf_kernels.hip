@@ -1200,7 +1200,7 @@ template <typename T, int NB, int KS, bool FAST, bool INFO>
 __global__ __launch_bounds__(kFusedThreads) void k_gemm(const GemmLaunch a) {
     const int slice = blockIdx.y;
     const int c0 = slice * a.cs;
-    const int w = min(a.cs, a.ccol - c0);
+    const int w = min(a.cs, a.ccol - c0), w_d1 = c0 + w < a.ccol ? w : a.d1_cols - c0;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
     const int g = lane >> 4, r = lane & 15;
     T *Cl = reinterpret_cast<T *>(tf_smem);
@@ -1237,7 +1237,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_gemm(const GemmLaunch a) {
                 const int cb = c0 + 16 * nb;        // the workspace is cut into slices of d1_sw columns
                 store_acc4<T>(D1 + (int64_t)(cb >> a.d1_sw_shift) * a.d1_slice_stride +
                                         row * a.d1_sw + (cb & a.d1_sw_mask) + 4 * g,
-                                    acc[nb], nb, g, w);
+                                    acc[nb], nb, g, w_d1);
             }
         } else {
             if (ri.info & kInfoSpill) {
@@ -1247,7 +1247,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_gemm(const GemmLaunch a) {
                     const int cb = c0 + 16 * nb;
                     store_acc4<T>(D1 + (int64_t)(cb >> a.d1_sw_shift) * a.d1_slice_stride +
                                             slot * a.d1_sw + (cb & a.d1_sw_mask) + 4 * g,
-                                        acc[nb], nb, g, w);
+                                        acc[nb], nb, g, w_d1);
                 }
             }
             if (ri.info & (kInfoDirect | kInfoZero)) {

@@ -193,3 +193,38 @@ def test_padding_of_gathered_rows_adds_nothing(dtype, ccol, slices):
             assert np.array_equal(c.run(fused).astype(np.float64), D_ref)
     finally:
         c.close()
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("kind,bcol,ccol", [("gemm", 64, 41), ("gemm", 128, 33), ("gemm", 36, 96), ("gemm", 128, 70), ("gemm", 20, 23),
+                                            ("gemm", 64, 260), ("gemm", 64, 128), ("spmm", 0, 41), ("spmm", 0, 23), ("spmm", 0, 70),
+                                            ("spmm", 0, 300)])
+def test_slices_of_one_cache_line_and_padded_rows(dtype, kind, bcol, ccol):
+    """A workspace whose slices and rows the library chooses: whole lines, the last one partly used, three and more
+    slices (shared unevenly by the eight XCDs), rows padded to a line; and Y = A B over slices of rows of B."""
+    import paper_2407_00243_amd as tf
+    from gpu_util import Case, read_workspace
+    n = max(60013, 14000000 // (ccol * np.dtype(dtype).itemsize))         # (rows that reach beyond an L2)
+    rng = np.random.default_rng(14)
+    A = _hubs(n, dtype, rng, lambda k: rng.integers(-2, 3, k))
+    sparse = kind == "spmm"
+    B = _rows_of(rng.integers(0, 6, n), dtype, rng) if sparse else ti.dense_small_int(n, bcol, dtype, 5)
+    C = ti.dense_small_int(n if sparse else bcol, ccol, dtype, 6)
+    D_ref, _ = oracle.chain(A, B, C)
+    c = Case(ti.Problem("lines", kind + "_spmm", np.dtype(dtype), A, B, C))
+    try:
+        s = c.plan.schedule()
+        es, line = np.dtype(dtype).itemsize, s["d1_slice_cols"] * np.dtype(dtype).itemsize
+        assert s["far_rows"] and (s["d1_slices"] - 1) * s["d1_slice_cols"] < ccol <= s["d1_slices"] * s["d1_slice_cols"]
+        if ccol * es > 128 and (ccol - 1) % (128 // es) + 1 >= 16 // es and ccol * es <= 1024:
+            assert line == 128
+        for fused in (True, False, True):
+            assert np.array_equal(c.run(fused).astype(np.float64), D_ref)
+        c.plan.workspace()
+        assert np.array_equal(c.run().astype(np.float64), D_ref)
+        ws = read_workspace(c.plan, s, ccol, dtype)
+        rows = np.flatnonzero(s["spill_slot"] >= 0)
+        eye = ti.Csr(n, n, np.arange(n + 1, dtype=np.int32), np.arange(n, dtype=np.int32), np.ones(n, dtype))
+        assert np.array_equal(ws[s["spill_slot"][rows]].astype(np.float64), oracle.chain(eye, B, C)[0][rows])
+    finally:
+        c.close()
