@@ -2,6 +2,7 @@
 // two-launch execution (first wavefront, then second wavefront, in stream order).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 #include <chrono>
 #include <cstdio>
@@ -318,8 +319,11 @@ tf::CsrSpmmLaunch csr_spmm_args(const tf_plan *p, const tf_csr *B, const void *C
                                 const tf::D1Layout &lay) {
     tf::CsrSpmmLaunch f{};
     f.dtype = p->dtype;
-    f.rows_per_wg = tf::kCsrRowsPerWg;
-    f.n_rows = p->n;
+    f.n_rows = (int32_t)p->n;
+    f.n_cu = p->n_cu;
+    tf::csr_slices(p->s.far_rows, p->dtype, p->bcol, p->ccol, f.n_xs, f.x_sw);
+    f.mean_len = (int32_t)(B->nnz / std::max<int64_t>(1, p->n));
+    f.x_bytes = p->bcol * p->ccol * tf::elem_size(p->dtype);
     f.S.rowptr = B->rowptr;
     f.S.colidx = B->colidx;
     f.S.vals = B->vals;

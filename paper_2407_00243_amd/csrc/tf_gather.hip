@@ -1,5 +1,6 @@
-// Y = A X over a packed list of rows of A (RowPack): the second wavefront, the second operation of the unfused
-// baseline and of the plain pair, and Y = A B of the gather-first order.
+// The kernels that gather rows: Y = A X over a packed list of rows of A (RowPack; the second wavefront, the second
+// operation of the unfused baseline and of the plain pair, and Y = A B of the gather-first order), and Y = S X for a
+// caller-supplied CSR matrix S.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -294,6 +295,210 @@ __global__ __launch_bounds__(kSpmmThreads, gather_waves(dtype_of<T>())) void k_p
     } while (left > 0);
 }
 
+// Y[j] = S[j, :] X for a caller-supplied CSR matrix S: the first operation of the unfused SpMM-SpMM baseline and of
+// the plain pair (row_info = nullptr: every row goes to the workspace, slot = row), and the first wavefront of a
+// CSR-B plan that needs no tile in LDS (row_info: what happens to a finished D1 row, see kInfo*; a row whose D1
+// row nobody reads and that the plan leaves out counts as empty, nothing of it is fetched).
+//
+// As k_packed_spmm, for rows as they come: a wave owns 64 / G consecutive rows at a time and takes E entries of each
+// per pass.  What the passes need of the rows' extents is read two blocks ahead, entries a pass ahead, the first
+// gathers of the next block go out before a block's rows are stored.  Every XCD takes n_xs eighths of the rows, of
+// at most two column slices of X.  The time of a block is that of its longest row.
+template <typename T, int VV, int G, bool WIDE>
+__global__ __launch_bounds__(kSpmmThreads, 4) void k_csr_spmm(
+    const CsrSpmmLaunch a, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
+    const T *__restrict__ vals, const T *__restrict__ X0, const uint32_t *__restrict__ row_info,
+    const T *__restrict__ row_scale, T *Y, T *D) {
+    constexpr int E = G < 4 ? 4 : kGatherEntries, NR = 64 / G, NE = NR * E > 64 ? NR * E / 64 : 1;
+    typedef std::conditional_t<WIDE, uint64_t, uint32_t> Off;
+    typedef T Vec16 __attribute__((ext_vector_type(Tr<T>::V)));
+    typedef std::conditional_t<VV == 1, T, Vec16> X16;                          // a lane's columns of a row,
+    typedef std::conditional_t<VV == 1, T, typename Piece16<T>::Vec> XAny;      // in device memory
+    auto part = [](const X16 &x, int i) __attribute__((always_inline)) {
+        if constexpr (VV == 1) return x;
+        else return x[i];
+    };
+    __shared__ __align__(16) Off off_s[kSpmmThreads / 64][NR * E];
+    __shared__ __align__(16) T val_s[kSpmmThreads / 64][NR * E];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int gl = lane % G, v = lane / G;
+    Off *off_w = off_s[wave];
+    T *val_w = val_s[wave];
+    const Off row_bytes = (Off)a.ccol * (Off)sizeof(T);
+    const int n_rows = a.n_rows;
+    const int n_waves = (int)(gridDim.x / kXcds) * (kSpmmThreads / 64);
+    const int my = (int)(blockIdx.x / kXcds) * (kSpmmThreads / 64) + wave;
+    const int n_blocks = (uint32_t)(n_rows + NR - 1) / NR, eighth = (uint32_t)(n_blocks + kXcds - 1) / kXcds;
+    const int n_cb = (uint32_t)(a.x_sw + G * VV - 1) / (G * VV);
+
+    // of a block: the extents of the rows whose entries the lane fetches, and of the row that it sums up
+    struct Rows {
+        int32_t kb[NE], ke[NE], len;
+        uint32_t info;
+        T scale;
+    };
+    typedef int32_t Extent __attribute__((ext_vector_type(2), aligned(4)));
+    auto read_rows = [&](int u) __attribute__((always_inline)) {
+        Rows b;
+        const int j = min(u * NR + v, n_rows - 1);
+        uint32_t info = 0;
+#pragma unroll
+        for (int k = 0; k < NE; ++k) {
+            const int r = min(u * NR + (lane % (NR * E) + 64 * k) / E, n_rows - 1);
+            const Extent x = *reinterpret_cast<const Extent *>(rowptr + r);
+            b.kb[k] = x[0];
+            b.ke[k] = x[1];
+            if (row_info) {
+                info = row_info[r];
+                if (info & kInfoSkip) b.ke[k] = b.kb[k];
+            }
+        }
+        if constexpr (NE == 1) {
+            // (the lane's row is that of a lane v E; with eight lanes a row, its own)
+            b.len = b.ke[0] - b.kb[0];
+            if constexpr (G != E) {
+                b.len = __shfl(b.len, v * E, 64);
+                info = __shfl(info, v * E, 64);
+            }
+        } else {
+            const Extent x = *reinterpret_cast<const Extent *>(rowptr + j);
+            info = row_info ? row_info[j] : 0u;
+            b.len = info & kInfoSkip ? 0 : x[1] - x[0];
+        }
+        b.info = row_info ? info : kInfoSpill | (uint32_t)j;
+        b.scale = row_scale ? row_scale[j] : T(0);
+        if (u * NR + v >= n_rows) {
+            b.len = 0;
+            b.info = 0;
+        }
+        return b;
+    };
+    int32_t ci[NE];
+    T vi[NE];
+    auto fetch = [&](const Rows &b, int s) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < NE; ++k) {
+            const int at = b.kb[k] + s + lane % E;
+            ci[k] = 0;
+            vi[k] = T(0);
+            if (at < b.ke[k]) {
+                ci[k] = colidx[at];
+                vi[k] = vals[at];
+            }
+        }
+    };
+    auto put = [&]() __attribute__((always_inline)) {
+        if (NR * E >= 64 || lane < NR * E) {
+#pragma unroll
+            for (int k = 0; k < NE; ++k) {
+                off_w[lane + 64 * k] = (Off)(uint32_t)ci[k] * row_bytes;
+                val_w[lane + 64 * k] = vi[k];
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+    };
+    auto any = [](bool x) { return __builtin_amdgcn_ballot_w64(x) != 0; };
+
+    int at = (int)(blockIdx.x % kXcds) * a.n_xs, left = a.n_xs;
+    do {
+        const int slice = at / kXcds, e0 = at % kXcds, n_e = min(left, kXcds - e0);
+        at += n_e;
+        left -= n_e;
+        const int w = min(a.x_sw, a.ccol - slice * a.x_sw);     // columns of this slice
+        const int end = min(n_blocks, (e0 + n_e) * eighth);
+        int cb = 0;
+        do {
+            const bool active = cb * G * VV + VV * gl < w;
+            const int col = slice * a.x_sw + min(cb * G * VV + VV * gl, w - VV);
+            const char *__restrict__ X = reinterpret_cast<const char *>(X0);
+            const Off lane_bytes = (Off)col * (Off)sizeof(T);
+            // the lane's columns of a row of the workspace (slices of y_sw columns) and of D
+            T *Yl = Y + (int64_t)(col >> a.y_sw_shift) * a.y_slice_stride + (col & a.y_sw_mask);
+            T *Dl = D + col;
+            X16 x[E];
+            T acc[VV];
+            // left: entries that the lane's row has from this pass on
+            auto issue = [&](int rest) __attribute__((always_inline)) {
+                Off o[E];
+#pragma unroll
+                for (int e = 0; e < E; e += 16 / (int)sizeof(Off))
+                    load_pack<Off, 16 / (int)sizeof(Off)>(*reinterpret_cast<Off(*)[16 / sizeof(Off)]>(&o[e]), off_w + v * E + e);
+#pragma unroll
+                for (int e = 0; e < E; ++e) asm volatile("" : "+v"(o[e]));
+#pragma unroll
+                for (int e = 0; e < E; ++e) asm volatile("" : "=v"(x[e]));
+#pragma unroll
+                for (int e = 0; e < E; ++e)
+                    if (any(e < rest)) x[e] = *reinterpret_cast<const XAny *>(X + (Off)(o[e] + lane_bytes));
+            };
+            auto consume = [&](int rest) __attribute__((always_inline)) {
+                T f[E];
+#pragma unroll
+                for (int e = 0; e < E; e += Tr<T>::V)
+                    load_pack<T, Tr<T>::V>(*reinterpret_cast<T(*)[Tr<T>::V]>(&f[e]), val_w + v * E + e);
+                if (!any(rest < E)) {
+#pragma unroll
+                    for (int e = 0; e < E; ++e)
+#pragma unroll
+                        for (int i = 0; i < VV; ++i) acc[i] += f[e] * part(x[e], i);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < E; ++e)
+#pragma unroll
+                        for (int i = 0; i < VV; ++i) acc[i] += (e < rest ? f[e] : T(0)) * (e < rest ? part(x[e], i) : T(0));
+                }
+                __builtin_amdgcn_wave_barrier();
+            };
+            auto finish = [&](const Rows &b, int u) __attribute__((always_inline)) {
+                if (!active) return;
+                if (b.info & kInfoSpill) store_any<T, VV>(Yl + (int64_t)(b.info & kInfoSlotMask) * a.y_sw, acc);
+                if (b.info & (kInfoDirect | kInfoZero)) {
+                    XAny y;
+                    if constexpr (VV == 1) y = (b.info & kInfoZero) ? T(0) : b.scale * acc[0];
+                    else
+#pragma unroll
+                        for (int i = 0; i < VV; ++i) y[i] = (b.info & kInfoZero) ? T(0) : b.scale * acc[i];
+                    // (D is not read again: what it would evict from the L2 is)
+                    __builtin_nontemporal_store(y, reinterpret_cast<XAny *>(Dl + (int64_t)(u * NR + v) * a.ccol));
+                }
+            };
+
+            int u = e0 * eighth + my;
+            if (u >= end) break;
+            Rows d = read_rows(u), dn = read_rows(min(u + n_waves, end - 1));
+            fetch(d, 0);
+            put();
+            fetch(any(d.len > E) ? d : dn, any(d.len > E) ? E : 0);
+            issue(d.len);
+            for (;;) {
+                const bool has_next = u + n_waves < end;
+                const Rows dnn = read_rows(min(u + 2 * n_waves, end - 1));
+#pragma unroll
+                for (int i = 0; i < VV; ++i) acc[i] = T(0);
+                consume(d.len);
+                for (int s0 = E; any(d.len > s0); s0 += E) {
+                    put();
+                    const bool more = any(d.len > s0 + E);
+                    fetch(more ? d : dn, more ? s0 + E : 0);
+                    issue(d.len - s0);
+                    consume(d.len - s0);
+                }
+                if (has_next) {
+                    put();
+                    const bool more = any(dn.len > E);
+                    fetch(more ? dn : dnn, more ? E : 0);
+                }
+                issue(has_next ? dn.len : 0);
+                finish(d, u);
+                if (!has_next) break;
+                d = dn;
+                dn = dnn;
+                u += n_waves;
+            }
+        } while (++cb < n_cb && cb * G * VV < w);
+    } while (left > 0);
+}
+
 template <typename T, int VV, int G, bool WIDE> int run_packed(const PackedSpmmLaunch &a, hipStream_t st) {
     static const int wg_per_cu = resident_per_cu(k_packed_spmm<T, VV, G, WIDE>, kSpmmThreads, 0, 8);
     const int64_t quads = ((int64_t)a.n_blocks / kGatherQuad + kXcds - 1) / kXcds * a.n_xs;        // of an XCD
@@ -305,29 +510,62 @@ template <typename T, int VV, int G, bool WIDE> int run_packed(const PackedSpmmL
     return (int)hipGetLastError();
 }
 
-template <typename T, bool WIDE> int run_packed_group(const PackedSpmmLaunch &a, hipStream_t st) {
+template <typename T, int VV, int G, bool WIDE> int run_csr(const CsrSpmmLaunch &a, hipStream_t st) {
+    static const int most = resident_per_cu(k_csr_spmm<T, VV, G, WIDE>, kSpmmThreads, 0, 8);
+    // Rows of X from beyond the L2: more requests on their way than the fabric takes only slow it down (us, two, three
+    // and four workgroups per compute unit: 2^20 rows of eight, fp32 32 columns 184 / 191 / 191; 200000 of eight, fp64
+    // 64 columns 120 / 127 / 127; 200000 of five, fp32 64 46.6 / 42.8 / 44.4; 10^6 of four, fp32 32 106 / 99 / 104;
+    // where X is smaller, 12.8 MB, 17.1 / 15.3 / 15.3).
+    int wg_per_cu = most;
+    if (a.x_bytes >= 40000000) wg_per_cu = std::min(most, std::max(2, (14 + a.mean_len) / std::max(1, a.mean_len + 1)));
+    const int64_t blocks = ((int64_t)a.n_rows + 64 / G - 1) / (64 / G), items = (blocks + kXcds - 1) / kXcds * a.n_xs;
+    const int64_t per_xcd = std::min<int64_t>((items + kSpmmThreads / 64 - 1) / (kSpmmThreads / 64),
+                                              std::max(1, a.n_cu / kXcds) * (int64_t)wg_per_cu);
+    (void)hipGetLastError();
+    k_csr_spmm<T, VV, G, WIDE><<<dim3((unsigned)(per_xcd * kXcds)), dim3(kSpmmThreads), 0, st>>>(
+        a, a.S.rowptr, a.S.colidx, static_cast<const T *>(a.S.vals), static_cast<const T *>(a.X), a.row_info,
+        static_cast<const T *>(a.row_scale), static_cast<T *>(a.Y), static_cast<T *>(a.D));
+    return (int)hipGetLastError();
+}
+
+// Calls f(VV, G) with compile-time constants: columns and lanes of rows in column slices of sw of the ccol columns.
+template <typename T, typename L> int dispatch_group(int64_t ccol, int sw, L &&f) {
     constexpr int V = Tr<T>::V;
-    const int elems = lane_elems(a.dtype, a.ccol, a.sw);
-    const int group = lane_group(a.sw, elems);
+    const int elems = lane_elems(dtype_of<T>(), ccol, sw), group = lane_group(sw, elems);
+#define TF_G(VVV, GV) return f(std::integral_constant<int, VVV>(), std::integral_constant<int, GV>())
     if (elems == 1) {
         // (rows narrower than 16 bytes)
         switch (group) {
-            case 1: return run_packed<T, 1, 1, WIDE>(a, st);
-            case 2: return run_packed<T, 1, 2, WIDE>(a, st);
-            case 4: return run_packed<T, 1, 4, WIDE>(a, st);
+            case 1: TF_G(1, 1);
+            case 2: TF_G(1, 2);
+            case 4: TF_G(1, 4);
         }
         return (int)hipErrorInvalidValue;
     }
     switch (group) {
-        case 1: return run_packed<T, V, 1, WIDE>(a, st);
-        case 2: return run_packed<T, V, 2, WIDE>(a, st);
-        case 4: return run_packed<T, V, 4, WIDE>(a, st);
-        case 8: return run_packed<T, V, 8, WIDE>(a, st);
-        case 16: return run_packed<T, V, 16, WIDE>(a, st);
-        case 32: return run_packed<T, V, 32, WIDE>(a, st);
-        case 64: return run_packed<T, V, 64, WIDE>(a, st);
+        case 1: TF_G(V, 1);
+        case 2: TF_G(V, 2);
+        case 4: TF_G(V, 4);
+        case 8: TF_G(V, 8);
+        case 16: TF_G(V, 16);
+        case 32: TF_G(V, 32);
+        case 64: TF_G(V, 64);
     }
+#undef TF_G
     return (int)hipErrorInvalidValue;
+}
+
+template <typename T> int run_packed_group(const PackedSpmmLaunch &a, hipStream_t st) {
+    return dispatch_group<T>(a.ccol, a.sw, [&](auto vv, auto g) {
+        constexpr int VV = decltype(vv)::value, G = decltype(g)::value;
+        return a.wide ? run_packed<T, VV, G, true>(a, st) : run_packed<T, VV, G, false>(a, st);
+    });
+}
+template <typename T> int run_csr_group(const CsrSpmmLaunch &a, hipStream_t st) {
+    return dispatch_group<T>(a.ccol, a.x_sw, [&](auto vv, auto g) {
+        constexpr int VV = decltype(vv)::value, G = decltype(g)::value;
+        return a.x_bytes >= ((int64_t)1 << 32) ? run_csr<T, VV, G, true>(a, st) : run_csr<T, VV, G, false>(a, st);
+    });
 }
 
 }  // namespace
@@ -338,8 +576,14 @@ int launch_packed_spmm(const PackedSpmmLaunch &launch, void *stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (a.n_blocks == 0) return 0;
     if (a.n_xs < 1 || a.n_xs > kXcds || a.n_blocks % kGatherQuad) return (int)hipErrorInvalidValue;
-    if (a.dtype == TF_F32) return a.wide ? run_packed_group<float, true>(a, st) : run_packed_group<float, false>(a, st);
-    return a.wide ? run_packed_group<double, true>(a, st) : run_packed_group<double, false>(a, st);
+    return a.dtype == TF_F32 ? run_packed_group<float>(a, st) : run_packed_group<double>(a, st);
+}
+
+int launch_csr_spmm(const CsrSpmmLaunch &a, void *stream) {
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    if (a.n_rows == 0) return 0;
+    if (a.n_xs < 1 || a.n_xs > kXcds) return (int)hipErrorInvalidValue;
+    return a.dtype == TF_F32 ? run_csr_group<float>(a, st) : run_csr_group<double>(a, st);
 }
 
 }  // namespace tf

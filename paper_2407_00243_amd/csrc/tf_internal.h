@@ -69,6 +69,22 @@ inline D1Layout gather_first_slices(int dtype, int64_t rows, int64_t bcol) {
     return l;
 }
 
+// Column slices in which a CSR B gathers rows of C: one cache line each, where rows are whole lines and a slice of C is
+// not far from what an L2 holds.  The pattern of B is not known; rows of A that reach far stand for it.  (Random rows of
+// eight entries, first operation, us, whole rows / slices: 20000 rows fp64 64 columns 12.0 / 8.7, 40000 fp32 128, six
+// entries, 19.9 / 14.8, 60000 fp64 128 75 / 65, 100003 fp64 64 60.8 / 57.7, 100000 fp32 64 31.0 / 29.3; beyond: 200000
+// rows fp32 64, five entries, 42.8 / 44.2, 300000 fp32 128 177 / 198.)
+inline void csr_slices(bool far_rows, int dtype, int64_t c_rows, int64_t ccol, int32_t &n_sl, int32_t &sw) {
+    const int64_t row = ccol * (dtype == TF_F64 ? 8 : 4);
+    n_sl = 1;
+    sw = (int32_t)ccol;
+    if (!far_rows || row % kGatherSliceBytes) return;
+    const int64_t k = row / kGatherSliceBytes;
+    if (k < 2 || k > kXcds || c_rows * kGatherSliceBytes > ((int64_t)16 << 20)) return;
+    n_sl = (int32_t)k;
+    sw = (int32_t)(ccol / k);
+}
+
 // Lanes that share one row in the gather kernels: each lane owns vv columns (vv = elements per
 // 16 bytes when rows are 16-byte aligned, else 1); the group is the smallest power of two of
 // lanes that covers `cols` columns, at most one wave.
@@ -133,7 +149,6 @@ inline int lds_row_granule(int b_is_sparse) { return b_is_sparse ? 1 : kRowGranu
 // kSparseEntryCap entries of each into LDS (two loads per row for the whole tile instead of a
 // chain of dependent loads per row); bytes of LDS per tile row that this takes.
 constexpr int kSparseEntryCap = 8;
-constexpr int kCsrRowsPerWg = 64;        // rows of one workgroup of the unfused CSR SpMM
 inline int64_t lds_sparse_b_bytes_per_row(int dtype) {
     return 2 * 8 + kSparseEntryCap * (4 + (int64_t)elem_size(dtype));    // extents of two tiles
 }
@@ -503,20 +518,23 @@ struct PackedSpmmLaunch {
     int32_t n_cu;                     // compute units of the device
 };
 
-// Y[j] = S[j, :] X for a caller-supplied CSR matrix S, `rows_per_wg` consecutive rows per workgroup.
+// Y[j] = S[j, :] X for a caller-supplied CSR matrix S.
 struct CsrSpmmLaunch {
-    int32_t dtype;
-    int64_t n_rows;
-    int32_t rows_per_wg;
-    CsrDev S;
-    const void *X;
-    void *Y;                          // D1 workspace layout: slices of y_sw columns
-    int32_t ccol;
-    int32_t y_sw_shift, y_sw_mask, y_sw;
     int64_t y_slice_stride;
+    int32_t n_rows;
+    int32_t n_xs, x_sw;               // column slices (1 to 8) of x_sw columns in which rows of X are gathered
+    int32_t ccol;
+    int32_t y_sw_shift, y_sw_mask, y_sw;   // D1 workspace layout: slices of y_sw columns
+    int32_t dtype;
+    CsrDev S;
+    const void *X;                    // row-major, ccol columns
+    void *Y;
     const uint32_t *row_info;         // as in GemmLaunch
     const void *row_scale;
     void *D;
+    int64_t x_bytes;
+    int32_t mean_len;                 // entries per row of S
+    int32_t n_cu;                     // compute units of the device
 };
 
 struct GemmLaunch {

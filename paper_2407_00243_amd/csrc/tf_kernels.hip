@@ -1,12 +1,10 @@
-// gfx950 kernels of the tile-fusion path  D = A (B C).
+// gfx950 kernels of the tile-fusion path  D = A (B C)  (the gather kernels are in tf_gather.hip, the chain in one
+// pass in tf_chain.hip).
 //
 //   k_fused_gemm_spmm   first wavefront, dense B   (paper Section 3.2, fused GeMM-SpMM listing)
 //   k_fused_spmm_spmm   first wavefront, CSR B     (Section 3.2, fused SpMM-SpMM listing)
-//   k_packed_spmm       second wavefront (rows whose D1 rows come from device memory); also the
-//                       SpMM of the unfused baseline
 //   k_gemm              D1 = B C for all rows: the GeMM of the unfused baseline, and the first
 //                       wavefront of a dense-B plan that needs no tile in LDS
-//   k_csr_spmm          D1 = B C for a CSR B, likewise
 //
 // A fused workgroup owns one tile (a list of D1 rows) and one column slice.  It produces the
 // tile's D1 rows into LDS -- by MFMA for a dense B, by a row gather over C for a CSR B -- stores
@@ -1110,80 +1108,6 @@ __global__ __launch_bounds__(kFusedSparseThreads) void k_fused_spmm_spmm(const F
     }
 }
 
-// CSR SpMM over a caller-supplied matrix: Y[j][:] = sum_k S.vals[k] X[S.colidx[k]][:], consecutive
-// rows per workgroup.  The first operation of the unfused SpMM-SpMM baseline (row_info = nullptr:
-// every row goes to the workspace, slot = row), and the first wavefront of a CSR-B plan that needs
-// no tile in LDS (row_info set, see k_gemm).
-template <typename T, bool FAST>
-__global__ __launch_bounds__(kSpmmThreads) void k_csr_spmm(const CsrSpmmLaunch a) {
-    constexpr int VV = FAST ? Tr<T>::V : 1;
-    const int64_t n_wg = (a.n_rows + a.rows_per_wg - 1) / a.rows_per_wg;
-    const int64_t u = xcd_contiguous(blockIdx.x, n_wg);
-    if (u >= n_wg) return;
-    const int64_t r0 = u * a.rows_per_wg;
-    const int64_t r1 = r0 + a.rows_per_wg < a.n_rows ? r0 + a.rows_per_wg : a.n_rows;
-    const int ccol = a.ccol;
-    const int G = min(64, pow2_at_least((ccol + VV - 1) / VV));
-    const int gl = threadIdx.x % G, grp = threadIdx.x / G, ngrp = blockDim.x / G;
-    const T *__restrict__ vals = static_cast<const T *>(a.S.vals);
-    const T *__restrict__ X = static_cast<const T *>(a.X);
-    T *__restrict__ Y = static_cast<T *>(a.Y);
-    // the rows of the workgroup are staged once (see stage_extents), then gathered per column block
-    __shared__ __align__(16) int32_t ext_s[2 * kCsrRowsPerWg];
-    __shared__ __align__(16) int32_t idx_s[kSparseEntryCap * kCsrRowsPerWg];
-    __shared__ __align__(16) T val_s[kSparseEntryCap * kCsrRowsPerWg];
-    const int rows = (int)(r1 - r0);
-    if (!a.row_info) {
-        stage_extents(rows, ext_s, a.S.rowptr, [&](int i) { return r0 + i; });
-    } else {
-        // a row whose D1 row nobody reads and that the plan leaves out counts as empty here: nothing
-        // of it is fetched (its gathers name row 0 of X with a zero value)
-        for (int i = threadIdx.x; i < rows; i += (int)blockDim.x) {
-            const int64_t rid = r0 + i;
-            const int kb = a.S.rowptr[rid], ke = a.S.rowptr[rid + 1];
-            ext_s[2 * i] = kb;
-            ext_s[2 * i + 1] = (a.row_info[rid] & kInfoSkip) ? 0 : ke - kb;
-        }
-    }
-    __syncthreads();
-    stage_entries<T>(rows, ext_s, idx_s, val_s, a.S.colidx, vals);
-    for (int cb = 0; cb < ccol; cb += G * VV) {
-        const bool active = cb + VV * gl < ccol;
-        const int col = min(cb + VV * gl, ccol - VV);
-        // the lane's columns of a row of the workspace (slices of y_sw columns)
-        T *Yl = Y + (int64_t)(col >> a.y_sw_shift) * a.y_slice_stride + (col & a.y_sw_mask);
-        if (!a.row_info) {
-            gather_staged_rows<T, VV, 2>(rows, ext_s, idx_s, val_s, a.S.colidx, vals, X + col, ccol,
-                                         active, grp, ngrp, [](int) { return 0; },
-                                         [&](int pos, int, const T(&acc)[VV]) {
-                                             store_any<T, VV>(Yl + (r0 + pos) * a.y_sw, acc);
-                                         });
-        } else {
-            // first wavefront of a plan without an LDS tile: what happens to a finished D1 row is
-            // told by its info word (see k_gemm)
-            struct RowInfo {
-                uint32_t info;
-                T sc;
-            };
-            const T *scale = static_cast<const T *>(a.row_scale);
-            T *Dl = static_cast<T *>(a.D) + col;
-            gather_staged_rows<T, VV, 2>(
-                rows, ext_s, idx_s, val_s, a.S.colidx, vals, X + col, ccol, active, grp, ngrp,
-                [&](int pos) { return RowInfo{a.row_info[r0 + pos], scale ? scale[r0 + pos] : T(0)}; },
-                [&](int pos, const RowInfo &ri, const T(&acc)[VV]) {
-                    if (ri.info & kInfoSpill)
-                        store_any<T, VV>(Yl + (int64_t)(ri.info & kInfoSlotMask) * a.y_sw, acc);
-                    if (ri.info & (kInfoDirect | kInfoZero)) {
-                        T x[VV];
-#pragma unroll
-                        for (int i = 0; i < VV; ++i) x[i] = (ri.info & kInfoZero) ? T(0) : ri.sc * acc[i];
-                        store_any<T, VV>(Dl + (r0 + pos) * ccol, x);
-                    }
-                });
-        }
-    }
-}
-
 // D1 = B C for all rows, one 16-row block per wave at a time, the next block's rows of B in
 // flight while the current one is multiplied (KS > 0, as above).
 // KS > 0, FAST: bCol = 4 V KS exactly; not FAST: any bCol from V up to there, rows of B at any element.
@@ -1494,25 +1418,6 @@ int launch_fused_spmm_spmm(const FusedLaunch &a, void *stream) {
     if (a.dtype == TF_F32)
         return fast ? run_fused_spmm<float, true>(a, st) : run_fused_spmm<float, false>(a, st);
     return fast ? run_fused_spmm<double, true>(a, st) : run_fused_spmm<double, false>(a, st);
-}
-
-int launch_csr_spmm(const CsrSpmmLaunch &a, void *stream) {
-    hipStream_t st = static_cast<hipStream_t>(stream);
-    if (a.n_rows == 0) return 0;
-    // the kernel stages the rows of a workgroup in LDS arrays of this many rows
-    if (a.rows_per_wg < 1 || a.rows_per_wg > kCsrRowsPerWg) return (int)hipErrorInvalidValue;
-    const bool fast = lane_elems(a.dtype, a.ccol, a.ccol) > 1;
-    const int64_t n_wg = (a.n_rows + a.rows_per_wg - 1) / a.rows_per_wg;
-    const dim3 grid((unsigned)((n_wg + kXcds - 1) / kXcds * kXcds)), block(kSpmmThreads);
-    (void)hipGetLastError();
-    if (a.dtype == TF_F32) {
-        if (fast) k_csr_spmm<float, true><<<grid, block, 0, st>>>(a);
-        else k_csr_spmm<float, false><<<grid, block, 0, st>>>(a);
-    } else {
-        if (fast) k_csr_spmm<double, true><<<grid, block, 0, st>>>(a);
-        else k_csr_spmm<double, false><<<grid, block, 0, st>>>(a);
-    }
-    return (int)hipGetLastError();
 }
 
 int launch_gemm(const GemmLaunch &a, void *stream) {
