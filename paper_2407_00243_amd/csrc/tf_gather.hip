@@ -517,7 +517,7 @@ template <typename T, int VV, int G, bool WIDE> int run_csr(const CsrSpmmLaunch 
     // 64 columns 120 / 127 / 127; 200000 of five, fp32 64 46.6 / 42.8 / 44.4; 10^6 of four, fp32 32 106 / 99 / 104;
     // where X is smaller, 12.8 MB, 17.1 / 15.3 / 15.3).
     int wg_per_cu = most;
-    if (a.x_bytes >= 40000000) wg_per_cu = std::min(most, std::max(2, (14 + a.mean_len) / std::max(1, a.mean_len + 1)));
+    if (a.x_bytes >= 40000000 && a.mean_len > 0) wg_per_cu = std::min(most, std::max(2, (14 + a.mean_len) / std::max(1, a.mean_len + 1)));
     const int64_t blocks = ((int64_t)a.n_rows + 64 / G - 1) / (64 / G), items = (blocks + kXcds - 1) / kXcds * a.n_xs;
     const int64_t per_xcd = std::min<int64_t>((items + kSpmmThreads / 64 - 1) / (kSpmmThreads / 64),
                                               std::max(1, a.n_cu / kXcds) * (int64_t)wg_per_cu);
