@@ -125,7 +125,7 @@ typedef struct tf_tile_params {
 #define TF_EXECUTE_WAVEFRONTS 0    /* the schedule: fused tiles, then the leftover rows               */
 #define TF_EXECUTE_ONE_PASS 1      /* dense B, rows near the diagonal: D = (A B) C in one launch      */
 #define TF_EXECUTE_GATHER_FIRST 2  /* dense B, graph, narrow B: Y = A B for all rows, then D = Y C    */
-#define TF_EXECUTE_PLAIN_PAIR 3    /* CSR B, small D1: D1 = B C and D = A D1 over all rows            */
+#define TF_EXECUTE_PLAIN_PAIR 3    /* CSR B, D1 held by the caches: D1 = B C and D = A D1 over all rows */
 
 typedef struct tf_plan tf_plan; /* opaque, library-owned */
 
@@ -254,7 +254,7 @@ tf_status tf_gemm_spmm_static(const tf_plan *plan, const void *B, const void *C,
 /* Fused execution with CSR B (Section 3.2, fused SpMM-SpMM listing).  B must be on the device,
  * n x bCol with the plan's bCol and dtype; C is bCol x cCol.  B may alias A's arrays.  A
  * TF_EXECUTE_PLAIN_PAIR plan runs the two operations over all rows instead, with all of D1 in an array
- * of its own (12 MB at most), unless tf_plan_workspace was called.
+ * of its own (80 MB at most), unless tf_plan_workspace was called.
  * B's arrays live on the device and are NOT validated by the execution calls (only its shape
  * and element type are): a well-formed CSR (monotone rowptr with rowptr[0] = 0, 0 <= column <
  * bCol) is the caller's precondition; tf_csr_validate checks it where that is in doubt. */

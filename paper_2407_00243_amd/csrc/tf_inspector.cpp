@@ -1313,18 +1313,25 @@ void build_gather_first(const InspectorInput &in, Schedule &s, bool have_all) {
         s.gf_info[(size_t)j] = in.rowptr[j + 1] > in.rowptr[j] ? kInfoSpill | (uint32_t)j : kInfoZero;
 }
 
-// A CSR B and a D1 that the caches hold whole: tiles save no memory traffic then, and what is left of them
-// is their chain of barriers and dependent loads.  The two operations over all rows, D1 = B C and
-// D = A D1, are the faster pair up to about 12 MB of D1 (us per execution, tiles / plain pair: 3D stencil
-// fp32 20^3 x 32, 1 MB, 18.9 / 8.9; 32^3 x 80, 10.5 MB, 32.7 / 19.3; 2D stencil fp32 150^2 x 100, 9 MB, 27.6
-// / 18.1; band of 30000 rows fp64 x 32, 7.7 MB, 40.6 / 28.5; beyond: 2D fp64 150^2 x 100, 18 MB, 26.8 /
-// 31.6; 2D fp32 400^2 x 32, 20.5 MB, 24.5 / 28.5).
+// A CSR B and a D1 that the caches hold whole: tiles save little memory traffic then, and what is left of them
+// is their chain of barriers and dependent loads, which grows with the entries per row.  The two operations over
+// all rows, D1 = B C and D = A D1, are the faster pair up to a size of D1 that grows with the entries per row and
+// with the share of D1's rows that the tiles would have to write and read again anyway (us per execution, tiles
+// / plain pair: 3D stencil, 70 % written again, fp32 32^3 x 80, 10.5 MB, 32.7 / 19.3; 42^3 x 64, 19 MB, 27.6 /
+// 23.1; 79^3 x 16, 32 MB, 49 / 40; beyond: 66^3 x 64, 74 MB, 71 / 93; 2D stencil, 30 %, fp64 246^2 x 32, 15.5 MB,
+// 25.3 / 20.1; beyond: 419^2 x 32, 45 MB, 40 / 41; 337^2 x 114, 104 MB, 91 / 130; band of 21 entries per row
+// fp64, 50781 x 128, 52 MB, 136 / 94; of 33 fp32, 359422 x 32, 46 MB, 168 / 161; of 7, 5 % written again, fp32
+// 29472 x 69, 8 MB, 22.5 / 17.2; beyond: fp64 27863 x 64, 14 MB, 19.4 / 20.5; fp32 94792 x 64, 24 MB, 24 / 26.
+// Of 11, 8 %: fp64 159683 x 37, 47 MB, 127 / 96; fp32 298908 x 64, 77 MB, 96 / 115.)  80 MB bounds what a plan
+// keeps in device memory for it.
 bool plain_pair_is_faster(const InspectorInput &in, const Schedule &s) {
     if (!in.b_is_sparse || in.n == 0 || in.nnz == 0 || s.streaming) return false;
     // only where the caller has left the whole choice to the library
     if (!s.automatic || in.col_slice || in.gather_slices || !in.whole_fast_mem || (in.flags & TF_FLAG_SKIP_UNREAD))
         return false;
-    return in.n * in.ccol * elem_size(in.dtype) <= 12000000;
+    const double per_row = (double)in.nnz / (double)in.n, spilled = (double)s.d1.rows / (double)in.n;
+    const double chain = std::max(0.0, per_row - 2), most = (1.7e6 + 0.2e6 * chain) * chain * (1 + 6 * std::min(0.4, spilled));
+    return (double)(in.n * in.ccol * elem_size(in.dtype)) <= std::min(80e6, std::max(12e6, most));
 }
 
 void build_baseline_pack(const InspectorInput &in, Schedule &s) {

@@ -228,3 +228,27 @@ def test_slices_of_one_cache_line_and_padded_rows(dtype, kind, bcol, ccol):
         assert np.array_equal(ws[s["spill_slot"][rows]].astype(np.float64), oracle.chain(eye, B, C)[0][rows])
     finally:
         c.close()
+
+
+@pytest.mark.parametrize("dtype,n,h,ccol", [(np.float64, 40001, 10, 41), (np.float32, 60000, 6, 70),
+                                            (np.float64, 20001, 2, 79), (np.float32, 30001, 1, 33)])
+def test_both_operations_over_all_rows_of_a_large_band(dtype, n, h, ccol):
+    """CSR B, D1 beyond 12 MB: rows with many entries run as the plain pair, the pair and the tiles give the
+    exact D for small-integer entries."""
+    from gpu_util import Case
+    import paper_2407_00243_amd as tf
+    rng = np.random.default_rng(n)
+    cols = np.arange(n)[:, None] + np.arange(-h, h + 1)
+    keep = (cols >= 0) & (cols < n)
+    rowptr = np.concatenate([[0], np.cumsum(keep.sum(1))]).astype(np.int32)
+    A = ti.Csr(n, n, rowptr, cols[keep].astype(np.int32), rng.integers(-2, 3, int(rowptr[-1])).astype(dtype))
+    prob = ti.Problem("band", "spmm_spmm", np.dtype(dtype), A, A, ti.dense_small_int(n, ccol, dtype, 6))
+    D_ref, _ = oracle.chain(prob.A, prob.B, prob.C)
+    for given, expected in ((dict(), tf.TF_EXECUTE_WAVEFRONTS if h == 2 else tf.TF_EXECUTE_PLAIN_PAIR),
+                            (dict(gather_slices=1), tf.TF_EXECUTE_WAVEFRONTS)):
+        c = Case(prob, **given)
+        try:
+            assert c.plan.schedule()["execution"] == expected
+            assert np.array_equal(c.run().astype(np.float64), D_ref)
+        finally:
+            c.close()
