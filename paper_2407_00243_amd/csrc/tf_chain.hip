@@ -135,10 +135,17 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS, NBC))
     const unsigned char *ex_r = ex + r * 64 + (g ^ (r >> 2)) * 16;
 
     // blocks of this wave: every XCD has a contiguous range, through which its waves move side by side
-    // (rows of B that neighbouring blocks share stay in that XCD's L2)
-    const int per = (a.n_blocks + kXcds - 1) / kXcds, xcd = blockIdx.x % kXcds;
-    const int end = min(a.n_blocks, (xcd + 1) * per), step = (int)(gridDim.x / kXcds) * nwaves;
-    int blk = xcd * per + (int)(blockIdx.x / kXcds) * nwaves + wave;
+    // (rows of B that neighbouring blocks share stay in that XCD's L2); wide rows: after a.whole_rounds the blocks
+    // that are left are dealt over the workgroups (narrow ones gain 5 % at most, and lose up to 4 to the longer
+    // start: bands of 15204 rows, fp32 19 -> 16, 8.8 -> 9.1 us)
+    const int per = (a.n_blocks + kXcds - 1) / kXcds, xcd = blockIdx.x % kXcds, wg = (int)(blockIdx.x / kXcds);
+    const int end = min(a.n_blocks, (xcd + 1) * per), n_wg = (int)(gridDim.x / kXcds), step = n_wg * nwaves;
+    auto block_after = [&](int b) __attribute__((always_inline)) {
+        if constexpr (KS < kChainSpreadDepth) return b + step;
+        const int dealt = xcd * per + a.whole_rounds * step;
+        return b + step < dealt ? b + step : b < dealt ? dealt + wave * n_wg + wg : end;
+    };
+    int blk = xcd * per + wg * nwaves + wave;
 
     // The entries of a pass: fetched a pass ahead, 64 (four slots of sixteen rows) per load, put into
     // LDS when their turn comes, read back by the lanes of their row.  A column becomes the address of its
@@ -182,7 +189,7 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS, NBC))
         d = blocks[blk];
         row = row_id(d);
         fetch(d.slot_base);
-        dn = blocks[min(blk + step, end - 1)];
+        dn = blocks[min(block_after(blk), end - 1)];
     }
     // pieces of a row of B that may reach past bCol are moved back so that they end with the row, and put
     // right after the sums are complete
@@ -277,9 +284,9 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS, NBC))
     }
 
     for (;;) {
-        const int next = blk + step;
+        const int next = block_after(blk);
         const bool has_next = next < end;
-        const ChainBlock dnn = blocks[min(next + step, end - 1)];
+        const ChainBlock dnn = blocks[min(block_after(next), end - 1)];
 #pragma unroll
         for (int h = 0; h < RS; ++h)
 #pragma unroll
@@ -453,6 +460,14 @@ template <typename T, int KS, int NBC> int run_chain(ChainLaunch a, hipStream_t 
     const int64_t want = ((int64_t)a.n_blocks + waves - 1) / waves;
     int64_t grid = std::min<int64_t>(want, (int64_t)a.n_cu * wg_per_cu);
     grid = (grid + kXcds - 1) / kXcds * kXcds;
+    // Blocks of the last round, which does not take all waves: neighbouring blocks to neighbouring waves like the
+    // others, or over all workgroups.  The latter where a workgroup fills a compute unit, which would have two blocks
+    // for every wave while others have one (2D stencils, fp32 128 -> 128, 200^2 30.9 -> 24.9 us, 300^2 43.6 -> 42.8; fp64
+    // 200^2 53.9 -> 44.8), and where the round is short.  Else neighbours: they share rows of B (3D stencil 60^3, fp32
+    // 32 -> 32, 40 % of the waves, 17.8 us, 18.9 when spread).
+    const int64_t wave_slots = grid / kXcds * waves, per = ((int64_t)a.n_blocks + kXcds - 1) / kXcds;
+    const bool spread = waves == kChainThreads / 64 || per % wave_slots * 16 <= wave_slots;
+    a.whole_rounds = (int32_t)(spread ? std::max<int64_t>(1, per / wave_slots) : per / wave_slots + 2);
     (void)hipGetLastError();      // an error left by an earlier, unrelated call is not this launch's
     kernel<<<dim3((unsigned)grid, (unsigned)n_y), dim3(64 * waves), lds, st>>>(
         a, a.blocks, a.rows, a.idx, static_cast<const T *>(a.vals), static_cast<const char *>(a.B), a.D);

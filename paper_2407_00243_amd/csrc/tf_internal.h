@@ -301,6 +301,7 @@ struct ChainPack {
 };
 constexpr int kChainThreads = 512;       // largest workgroup of the kernel
 constexpr int kChainMaxEntries = 8;      // most entries per row in flight
+constexpr int kChainSpreadDepth = 6;     // depth from which the blocks of a last round may be dealt over the workgroups
 constexpr int kChainLongRow = 1024;      // longest row a block takes
 constexpr int kChainMaxCut = 4;          // log2 of the most parts that a row is cut into
 constexpr int32_t kChainPad = -1;        // the column of a padding entry: zeros are read in the place of a row of B
@@ -571,6 +572,7 @@ struct ChainLaunch {
     const void *zeros;                // kChainZeroRows x kChainRowBytes
     const void *B, *C;
     void *D;
+    int32_t whole_rounds;             // (set by the launcher) rounds of blocks in their order; the rest is dealt out
 };
 
 // Each returns hipError_t as int (0 = success).  `stream` is a hipStream_t.

@@ -49,6 +49,16 @@ def test_rows_cut_into_parts_and_several_passes(dtype, per_row):
     _check(A, 24, 24, dtype)
 
 
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("bcol,ccol,n", [(128, 128, 32768), (128, 128, 32785), (128, 128, 40000), (128, 128, 65600),
+                                         (128, 16, 33000), (80, 64, 50033)])
+def test_rounds_that_do_not_take_all_waves(dtype, bcol, ccol, n):
+    """Blocks that are left after whole rounds are dealt over the workgroups (256 compute units, 2048 to 3072 waves:
+    none, one, a fifth of the waves and a few, after one round and after two)."""
+    A = ti.random_local_csr(n, 9, 4, 0.0, dtype, 24, int_values=True, empty_row_prob=0.0)
+    _check(A, bcol, ccol, dtype)
+
+
 @pytest.mark.parametrize("empty", [0.3, 0.97])
 def test_rows_of_many_lengths_and_empty_rows(empty):
     """Rows sorted by length inside windows; empty rows are zeros even where B holds no finite number."""
