@@ -11,6 +11,22 @@
 namespace tf {
 namespace {
 
+// What the kernels below are given beside the arrays that they read.  Small matrices wait for the host, whose time for a launch
+// grows with the number and the bytes of its arguments; among them are 256 of the grid's sizes where a kernel asks for these, so the
+// workgroups per XCD are handed over (the pair of launches, arguments of 504 and 440 bytes, 20 in all: 7.7 us of the host's
+// time per call in some processes, 9.4 in others; 128 and 104, 14 in all: 7.5 and 8.7).
+struct PackedArgs {
+    void *Y, *partial;
+    int32_t *arrived;
+    int64_t x_slice_stride;
+    int32_t n_xs, sw, ldx, n_blocks, n_cut_blocks, ccol, contiguous, read_next, n_wg;
+};
+struct CsrArgs {
+    void *Y, *D;
+    int64_t y_slice_stride;
+    int32_t n_rows, n_xs, x_sw, ccol, y_sw_shift, y_sw_mask, y_sw, n_wg;
+};
+
 // X is the D1 workspace (n_xs column slices of sw columns; idx is a slot) or a dense B (one slice).
 //
 // A wave owns a block of 64 / G virtual rows at a time (a row, or one of the 2^k parts that the rows of the
@@ -37,9 +53,11 @@ namespace {
 // entries and the next one's offsets in flight at any time.
 template <typename T, int VV, int G, bool WIDE>
 __global__ __launch_bounds__(kSpmmThreads, gather_waves(dtype_of<T>())) void k_packed_spmm(
-    const PackedSpmmLaunch a, const GatherBlock *__restrict__ blocks, const int32_t *__restrict__ rows,
+    const PackedArgs a, const GatherBlock *__restrict__ blocks, const int32_t *__restrict__ rows,
     const int32_t *__restrict__ lens, const int32_t *__restrict__ idx, const T *__restrict__ val,
-    const CutBlock *__restrict__ cuts, const T *__restrict__ X0, T *Y0, T *partial, int32_t *all_arrived) {
+    const CutBlock *__restrict__ cuts, const T *__restrict__ X0) {
+    T *const Y0 = static_cast<T *>(a.Y), *const partial = static_cast<T *>(a.partial);
+    int32_t *const all_arrived = a.arrived;
     constexpr int E = kGatherEntries, NR = 64 / G, NE = NR * E > 64 ? NR * E / 64 : 1;
     typedef std::conditional_t<WIDE, uint64_t, uint32_t> Off;
     typedef T Vec16 __attribute__((ext_vector_type(Tr<T>::V)));
@@ -58,7 +76,7 @@ __global__ __launch_bounds__(kSpmmThreads, gather_waves(dtype_of<T>())) void k_p
     T *val_w = val_s[wave];
     const Off row_bytes = (Off)a.ldx * (Off)sizeof(T);
     // (quads: the blocks of a workgroup)
-    const int n_wg = (int)(gridDim.x / kXcds), my = (int)(blockIdx.x / kXcds);
+    const int n_wg = a.n_wg, my = (int)(blockIdx.x / kXcds);
     const int n_quads = (uint32_t)a.n_blocks / kGatherQuad, eighth = (uint32_t)(n_quads + kXcds - 1) / kXcds;
     const int n_cb = (uint32_t)(a.sw + G * VV - 1) / (G * VV);        // column blocks of a slice (rows wider than a wave's load)
 
@@ -90,12 +108,15 @@ __global__ __launch_bounds__(kSpmmThreads, gather_waves(dtype_of<T>())) void k_p
         at += n_e;
         left -= n_e;
         const int w = min(a.sw, a.ccol - slice * a.sw);     // columns of this slice
+        uint32_t reciprocal = 0;                            // 2^32 / n_e, rounded up
+#pragma unroll
+        for (int k = 2; k <= kXcds; ++k) reciprocal = n_e == k ? 0xffffffffu / k + 1 : reciprocal;
         // quad of the workgroup's k-th round: the XCD's quads in their order, or dealt back and forth
         const int end = a.contiguous ? min(n_quads, (e0 + n_e) * eighth) : n_quads;
         auto quad_of = [&](int k) __attribute__((always_inline)) {
             if (a.contiguous) return e0 * eighth + k * n_wg + my;
             const int j = k * n_wg + (k & 1 ? n_wg - 1 - my : my);
-            const int q = n_e == 1 ? j : (int)__umulhi((uint32_t)j, a.reciprocal[n_e]);       // j / n_e
+            const int q = n_e == 1 ? j : (int)__umulhi((uint32_t)j, reciprocal);       // j / n_e
             return q * kXcds + e0 + j - q * n_e;
         };
         int cb = 0;
@@ -313,9 +334,10 @@ __global__ __launch_bounds__(kSpmmThreads, gather_waves(dtype_of<T>())) void k_p
 // entries behind barriers); 3000 rows of 49, 100 columns, both operations 13.8 us (44.4).
 template <typename T, int VV, int G, bool WIDE>
 __global__ __launch_bounds__(kSpmmThreads, 4) void k_csr_spmm(
-    const CsrSpmmLaunch a, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
+    const CsrArgs a, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
     const T *__restrict__ vals, const T *__restrict__ X0, const uint32_t *__restrict__ row_info,
-    const T *__restrict__ row_scale, T *Y, T *D) {
+    const T *__restrict__ row_scale) {
+    T *const Y = static_cast<T *>(a.Y), *const D = static_cast<T *>(a.D);
     constexpr int E = G < 4 ? 4 : kGatherEntries, NR = 64 / G, NE = NR * E > 64 ? NR * E / 64 : 1;
     typedef std::conditional_t<WIDE, uint64_t, uint32_t> Off;
     typedef T Vec16 __attribute__((ext_vector_type(Tr<T>::V)));
@@ -333,7 +355,7 @@ __global__ __launch_bounds__(kSpmmThreads, 4) void k_csr_spmm(
     T *val_w = val_s[wave];
     const Off row_bytes = (Off)a.ccol * (Off)sizeof(T);
     const int n_rows = a.n_rows;
-    const int n_waves = (int)(gridDim.x / kXcds) * (kSpmmThreads / 64);
+    const int n_waves = a.n_wg * (kSpmmThreads / 64);
     const int my = (int)(blockIdx.x / kXcds) * (kSpmmThreads / 64) + wave;
     const int n_blocks = (uint32_t)(n_rows + NR - 1) / NR, eighth = (uint32_t)(n_blocks + kXcds - 1) / kXcds;
     const int n_cb = (uint32_t)(a.x_sw + G * VV - 1) / (G * VV);
@@ -512,8 +534,8 @@ template <typename T, int VV, int G, bool WIDE> int run_packed(const PackedSpmmL
     const int64_t per_xcd = std::min<int64_t>(quads, std::max(1, a.n_cu / kXcds) * (int64_t)wg_per_cu);
     (void)hipGetLastError();      // an error left by an earlier, unrelated call is not this launch's
     k_packed_spmm<T, VV, G, WIDE><<<dim3((unsigned)(per_xcd * kXcds)), dim3(kSpmmThreads), 0, st>>>(
-        a, a.pack.blocks, a.pack.rows, a.pack.lens, a.pack.idx, static_cast<const T *>(a.pack.vals), a.pack.cuts,
-        static_cast<const T *>(a.X), static_cast<T *>(a.Y), static_cast<T *>(a.partial), a.arrived);
+        {a.Y, a.partial, a.arrived, a.x_slice_stride, a.n_xs, a.sw, a.ldx, a.n_blocks, a.n_cut_blocks, a.ccol, a.contiguous, a.read_next, (int32_t)per_xcd}, a.pack.blocks, a.pack.rows, a.pack.lens, a.pack.idx, static_cast<const T *>(a.pack.vals), a.pack.cuts,
+        static_cast<const T *>(a.X));
     return (int)hipGetLastError();
 }
 
@@ -530,8 +552,8 @@ template <typename T, int VV, int G, bool WIDE> int run_csr(const CsrSpmmLaunch 
                                               std::max(1, a.n_cu / kXcds) * (int64_t)wg_per_cu);
     (void)hipGetLastError();
     k_csr_spmm<T, VV, G, WIDE><<<dim3((unsigned)(per_xcd * kXcds)), dim3(kSpmmThreads), 0, st>>>(
-        a, a.S.rowptr, a.S.colidx, static_cast<const T *>(a.S.vals), static_cast<const T *>(a.X), a.row_info,
-        static_cast<const T *>(a.row_scale), static_cast<T *>(a.Y), static_cast<T *>(a.D));
+        {a.Y, a.D, a.y_slice_stride, a.n_rows, a.n_xs, a.x_sw, a.ccol, a.y_sw_shift, a.y_sw_mask, a.y_sw, (int32_t)per_xcd}, a.S.rowptr, a.S.colidx, static_cast<const T *>(a.S.vals), static_cast<const T *>(a.X), a.row_info,
+        static_cast<const T *>(a.row_scale));
     return (int)hipGetLastError();
 }
 
@@ -577,9 +599,7 @@ template <typename T> int run_csr_group(const CsrSpmmLaunch &a, hipStream_t st) 
 
 }  // namespace
 
-int launch_packed_spmm(const PackedSpmmLaunch &launch, void *stream) {
-    PackedSpmmLaunch a = launch;
-    for (uint32_t k = 2; k <= kXcds; ++k) a.reciprocal[k] = 0xffffffffu / k + 1;
+int launch_packed_spmm(const PackedSpmmLaunch &a, void *stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (a.n_blocks == 0) return 0;
     if (a.n_xs < 1 || a.n_xs > kXcds || a.n_blocks % kGatherQuad) return (int)hipErrorInvalidValue;

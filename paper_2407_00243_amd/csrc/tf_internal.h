@@ -508,7 +508,6 @@ struct PackedSpmmLaunch {
     int32_t ccol;
     int32_t contiguous;               // 1: neighbouring blocks share an XCD; 0: round robin
     int32_t read_next;                // 1: the next launch reads Y
-    uint32_t reciprocal[kXcds + 1];   // (set by the launcher) 2^32 / k, rounded up: block counts divided by k
     int32_t dtype;
     void *partial;                    // sums of the pieces of cut rows: [piece][slice][sw]
     int32_t *arrived;                 // pieces of a cut row that are done: [cut row][slice][column block], zeros between launches
