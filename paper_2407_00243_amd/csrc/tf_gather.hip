@@ -394,7 +394,7 @@ __global__ __launch_bounds__(kSpmmThreads, 4) void k_csr_spmm(
             info = row_info ? row_info[j] : 0u;
             b.len = info & kInfoSkip ? 0 : x[1] - x[0];
         }
-        b.info = row_info ? info : kInfoSpill | (uint32_t)j;
+        b.info = d1_info(row_info != nullptr, info);
         b.scale = row_scale ? row_scale[j] : T(0);
         if (u * NR + v >= n_rows) {
             b.len = 0;
@@ -480,7 +480,8 @@ __global__ __launch_bounds__(kSpmmThreads, 4) void k_csr_spmm(
             };
             auto finish = [&](const Rows &b, int u) __attribute__((always_inline)) {
                 if (!active) return;
-                if (b.info & kInfoSpill) store_any<T, VV>(Yl + (int64_t)(b.info & kInfoSlotMask) * a.y_sw, acc);
+                const int64_t j = (int64_t)u * NR + v;
+                if (b.info & kInfoSpill) store_any<T, VV>(Yl + d1_slot(row_info != nullptr, b.info, j) * a.y_sw, acc);
                 if (b.info & (kInfoDirect | kInfoZero)) {
                     XAny y;
                     if constexpr (VV == 1) y = (b.info & kInfoZero) ? T(0) : b.scale * acc[0];
@@ -488,7 +489,7 @@ __global__ __launch_bounds__(kSpmmThreads, 4) void k_csr_spmm(
 #pragma unroll
                         for (int i = 0; i < VV; ++i) y[i] = (b.info & kInfoZero) ? T(0) : b.scale * acc[i];
                     // (D is not read again: what it would evict from the L2 is)
-                    __builtin_nontemporal_store(y, reinterpret_cast<XAny *>(Dl + (int64_t)(u * NR + v) * a.ccol));
+                    __builtin_nontemporal_store(y, reinterpret_cast<XAny *>(Dl + j * a.ccol));
                 }
             };
 

@@ -37,6 +37,12 @@ constexpr uint32_t kInfoZero = 0x20000000u;
 // reads this D1 row, it is not computed.
 constexpr uint32_t kInfoSkip = 0x10000000u;
 constexpr uint32_t kInfoSlotMask = 0x0fffffffu;
+// A finished D1 row in k_csr_spmm: its info word, which without row_info says that the row is stored to the workspace,
+// and the slot there, which then is the row's own number (it may take more bits than an info word has).
+constexpr uint32_t d1_info(bool has_info, uint32_t info) { return has_info ? info : kInfoSpill; }
+constexpr int64_t d1_slot(bool has_info, uint32_t info, int64_t row) {
+    return has_info ? (int64_t)(info & kInfoSlotMask) : row;
+}
 
 // Where the D1 rows that cross tiles live in device memory: `n_sl` column slices of `sw` columns
 // each (the last may be narrower in use, never in storage), slice after slice, each slice a dense

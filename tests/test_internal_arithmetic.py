@@ -1,0 +1,37 @@
+"""Index arithmetic that the kernels share with the host, at sizes whose arrays no test would allocate: small C++
+programs over the library's internal header."""
+import os
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2407_00243_amd", "csrc")
+
+
+def run_cpp(tmp_path, body):
+    """Compiles and runs `body` as main(); CHECK(x) ends it with the line number."""
+    src, exe = str(tmp_path / "main.cpp"), str(tmp_path / "main")
+    with open(src, "w") as f:
+        f.write('#include <cstdio>\n#include "tf_internal.h"\nusing namespace tf;\n'
+                "#define CHECK(x) do { if (!(x)) { std::printf(\"line %d: %s\\n\", __LINE__, #x); return 1; } } while (0)\n"
+                "int main() {\n" + body + "\nreturn 0;\n}\n")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-fsanitize=undefined", "-fno-sanitize-recover=all", "-I", CSRC, src,
+                    "-o", exe], check=True)
+    res = subprocess.run([exe], capture_output=True, text=True)
+    assert res.returncode == 0, res.stdout + res.stderr
+
+
+def test_rows_beyond_the_slot_bits_of_an_info_word(tmp_path):
+    """Without info words row j of B C goes to slot j, up to the last row that a plan takes, and nowhere else; with
+    them to the slot in the word."""
+    run_cpp(tmp_path, """
+    const int64_t rows[] = {0, 1, ((int64_t)1 << 28) - 1, (int64_t)1 << 28, ((int64_t)1 << 29) + 5, ((int64_t)1 << 30) + 7,
+                            ((int64_t)1 << 31) - 3};
+    for (int64_t j : rows) {
+        const uint32_t info = d1_info(false, 0);
+        CHECK(info & kInfoSpill);
+        CHECK(!(info & (kInfoDirect | kInfoZero | kInfoSkip)));
+        CHECK(d1_slot(false, info, j) == j);
+        const uint32_t given = kInfoDirect | kInfoSpill | 77u;
+        CHECK(d1_info(true, given) == given && d1_slot(true, given, j) == 77);
+    }""")
