@@ -354,10 +354,9 @@ __global__ __launch_bounds__(kSpmmThreads, 4) void k_csr_spmm(
     Off *off_w = off_s[wave];
     T *val_w = val_s[wave];
     const Off row_bytes = (Off)a.ccol * (Off)sizeof(T);
-    const int n_rows = a.n_rows;
-    const int n_waves = a.n_wg * (kSpmmThreads / 64);
-    const int my = (int)(blockIdx.x / kXcds) * (kSpmmThreads / 64) + wave;
-    const int n_blocks = (uint32_t)(n_rows + NR - 1) / NR, eighth = (uint32_t)(n_blocks + kXcds - 1) / kXcds;
+    const CsrBlocks all{(uint32_t)a.n_rows, NR};
+    const uint32_t n_waves = (uint32_t)a.n_wg * (kSpmmThreads / 64);
+    const uint32_t my = blockIdx.x / kXcds * (kSpmmThreads / 64) + (uint32_t)wave;
     const int n_cb = (uint32_t)(a.x_sw + G * VV - 1) / (G * VV);
 
     // of a block: the extents of the rows whose entries the lane fetches, and of the row that it sums up
@@ -367,13 +366,13 @@ __global__ __launch_bounds__(kSpmmThreads, 4) void k_csr_spmm(
         T scale;
     };
     typedef int32_t Extent __attribute__((ext_vector_type(2), aligned(4)));
-    auto read_rows = [&](int u) __attribute__((always_inline)) {
+    auto read_rows = [&](uint32_t u) __attribute__((always_inline)) {
         Rows b;
-        const int j = min(u * NR + v, n_rows - 1);
+        const uint32_t j = all.row(u, v);
         uint32_t info = 0;
 #pragma unroll
         for (int k = 0; k < NE; ++k) {
-            const int r = min(u * NR + (lane % (NR * E) + 64 * k) / E, n_rows - 1);
+            const uint32_t r = all.row(u, (lane % (NR * E) + 64 * k) / E);
             const Extent x = *reinterpret_cast<const Extent *>(rowptr + r);
             b.kb[k] = x[0];
             b.ke[k] = x[1];
@@ -396,7 +395,7 @@ __global__ __launch_bounds__(kSpmmThreads, 4) void k_csr_spmm(
         }
         b.info = d1_info(row_info != nullptr, info);
         b.scale = row_scale ? row_scale[j] : T(0);
-        if (u * NR + v >= n_rows) {
+        if (!all.has(u, v)) {
             b.len = 0;
             b.info = 0;
         }
@@ -404,13 +403,13 @@ __global__ __launch_bounds__(kSpmmThreads, 4) void k_csr_spmm(
     };
     int32_t ci[NE];
     T vi[NE];
-    auto fetch = [&](const Rows &b, int s) __attribute__((always_inline)) {
+    auto fetch = [&](const Rows &b, uint32_t s) __attribute__((always_inline)) {
 #pragma unroll
         for (int k = 0; k < NE; ++k) {
-            const int at = b.kb[k] + s + lane % E;
             ci[k] = 0;
             vi[k] = T(0);
-            if (at < b.ke[k]) {
+            if (has_entry(b.kb[k], b.ke[k], s + lane % E)) {
+                const int at = b.kb[k] + (int)(s + lane % E);
                 ci[k] = colidx[at];
                 vi[k] = vals[at];
             }
@@ -434,7 +433,7 @@ __global__ __launch_bounds__(kSpmmThreads, 4) void k_csr_spmm(
         at += n_e;
         left -= n_e;
         const int w = min(a.x_sw, a.ccol - slice * a.x_sw);     // columns of this slice
-        const int end = min(n_blocks, (e0 + n_e) * eighth);
+        const uint32_t end = all.end(e0 + n_e);
         int cb = 0;
         do {
             const bool active = cb * G * VV + VV * gl < w;
@@ -478,9 +477,9 @@ __global__ __launch_bounds__(kSpmmThreads, 4) void k_csr_spmm(
                 }
                 __builtin_amdgcn_wave_barrier();
             };
-            auto finish = [&](const Rows &b, int u) __attribute__((always_inline)) {
+            auto finish = [&](const Rows &b, uint32_t u) __attribute__((always_inline)) {
                 if (!active) return;
-                const int64_t j = (int64_t)u * NR + v;
+                const int64_t j = u * NR + (uint32_t)v;
                 if (b.info & kInfoSpill) store_any<T, VV>(Yl + d1_slot(row_info != nullptr, b.info, j) * a.y_sw, acc);
                 if (b.info & (kInfoDirect | kInfoZero)) {
                     XAny y;
@@ -493,7 +492,7 @@ __global__ __launch_bounds__(kSpmmThreads, 4) void k_csr_spmm(
                 }
             };
 
-            int u = e0 * eighth + my;
+            uint32_t u = e0 * all.eighth() + my;
             if (u >= end) break;
             Rows d = read_rows(u), dn = read_rows(min(u + n_waves, end - 1));
             fetch(d, 0);
@@ -506,12 +505,12 @@ __global__ __launch_bounds__(kSpmmThreads, 4) void k_csr_spmm(
 #pragma unroll
                 for (int i = 0; i < VV; ++i) acc[i] = T(0);
                 consume(d.len);
-                for (int s0 = E; any(d.len > s0); s0 += E) {
+                for (uint32_t s0 = E; any(has_entry(0, d.len, s0)); s0 += E) {
                     put();
-                    const bool more = any(d.len > s0 + E);
+                    const bool more = any(has_entry(0, d.len, s0 + E));
                     fetch(more ? d : dn, more ? s0 + E : 0);
-                    issue(d.len - s0);
-                    consume(d.len - s0);
+                    issue(d.len - (int)s0);
+                    consume(d.len - (int)s0);
                 }
                 if (has_next) {
                     put();

@@ -43,6 +43,19 @@ constexpr uint32_t d1_info(bool has_info, uint32_t info) { return has_info ? inf
 constexpr int64_t d1_slot(bool has_info, uint32_t info, int64_t row) {
     return has_info ? (int64_t)(info & kInfoSlotMask) : row;
 }
+// Rows of S in k_csr_spmm, `nr` consecutive ones a block; every XCD takes eighths of the blocks.  Unsigned: row, block and
+// entry numbers run past the last one, which may be 2^31 - 2.
+struct CsrBlocks {
+    uint32_t n_rows, nr;
+    constexpr uint32_t count() const { return (n_rows + nr - 1) / nr; }
+    constexpr uint32_t eighth() const { return (count() + kXcds - 1) / kXcds; }
+    constexpr uint32_t end(uint32_t eighths) const { return eighths * eighth() < count() ? eighths * eighth() : count(); }
+    constexpr bool has(uint32_t block, uint32_t v) const { return block * nr + v < n_rows; }
+    constexpr uint32_t row(uint32_t block, uint32_t v) const { return has(block, v) ? block * nr + v : n_rows - 1; }
+};
+// Is there an entry number s (which may lie as far behind the row as another row of its block is long) in the row of
+// the entries begin to end - 1?
+constexpr bool has_entry(int32_t begin, int32_t end, uint32_t s) { return s < (uint32_t)(end - begin); }
 
 // Where the D1 rows that cross tiles live in device memory: `n_sl` column slices of `sw` columns
 // each (the last may be narrower in use, never in storage), slice after slice, each slice a dense

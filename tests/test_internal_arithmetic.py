@@ -35,3 +35,28 @@ def test_rows_beyond_the_slot_bits_of_an_info_word(tmp_path):
         const uint32_t given = kInfoDirect | kInfoSpill | 77u;
         CHECK(d1_info(true, given) == given && d1_slot(true, given, j) == 77);
     }""")
+
+
+def test_rows_and_entries_at_the_end_of_32_bits(tmp_path):
+    """Blocks cover the rows once, numbers past the end are none; a row that begins near the last possible entry has
+    its own entries and no others, however long the rows beside it are.  (In 64 bits here, to compare with.)"""
+    run_cpp(tmp_path, """
+    for (uint32_t n : {1u, 63u, 64u, 1000u, 0x7fffffbfu, 0x7ffffffeu})
+        for (uint32_t nr : {1u, 2u, 8u, 64u}) {
+            const CsrBlocks b{n, nr};
+            const uint64_t count = ((uint64_t)n + nr - 1) / nr, eighth = (count + 7) / 8;
+            CHECK(b.count() == count && b.eighth() == eighth);
+            for (uint64_t e = 1; e <= 8; ++e) CHECK(b.end(e) == (e * eighth < count ? e * eighth : count));
+            for (uint64_t u : {(uint64_t)0, count / 2, count - 1, count})
+                for (uint64_t v = 0; v < nr; ++v) {
+                    CHECK(b.has(u, v) == (u * nr + v < n));
+                    CHECK(b.row(u, v) == (u * nr + v < n ? u * nr + v : n - 1));
+                }
+        }
+    for (int64_t begin : {(int64_t)0, (int64_t)5, (int64_t)0x7ffffff0, (int64_t)0x7ffffffe})
+        for (int64_t len : {0, 1, 7, 15})
+            for (int64_t s : {(int64_t)0, (int64_t)1, (int64_t)8, (int64_t)16, (int64_t)1 << 20, (int64_t)0x7fffffff,
+                              (int64_t)0x7fffffff + 7}) {
+                const int64_t end = begin + len <= 0x7fffffff ? begin + len : 0x7fffffff;
+                CHECK(has_entry((int32_t)begin, (int32_t)end, (uint32_t)s) == (begin + s < end));
+            }""")
