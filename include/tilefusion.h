@@ -242,7 +242,8 @@ tf_status tf_gemm_spmm(const tf_plan *plan, const void *B, const void *C, void *
  * plan's workspace (the D1 rows that cross tiles; Y = A B of a TF_EXECUTE_GATHER_FIRST plan; nothing
  * of a TF_EXECUTE_ONE_PASS plan) goes to a fixed array of 64 MiB that is part of the library's code
  * object (one copy per GPU, held until the process ends).  (The few sums of rows that are cut over
- * several workgroups stay in the plan's own memory.)  The call allocates nothing.
+ * several workgroups go to memory of the plan that its other calls do not use.)  The call allocates
+ * nothing.
  * A plan whose workspace (tf_schedule_view: d1_slices x d1_rows x d1_slice_cols elements) exceeds
  * 64 MiB is rejected with TF_EUNSUPPORTED.  All calls on one GPU share that GPU's array, whatever
  * the plan: calls that overlap in time on one GPU race (serialise them on one stream).  The array

@@ -89,6 +89,9 @@ struct Arena {
 
 }  // namespace
 
+// The arrays that executions keep rows of D1 or of Y = A B in.
+enum Workspace { kPlanWorkspace, kStaticWorkspace, kPairWorkspace, kUnfusedWorkspace, kWorkspaces };
+
 struct tf_plan {
     int64_t n = 0, nnz = 0, bcol = 0, ccol = 0;
     int32_t dtype = 0, b_is_sparse = 0;
@@ -108,8 +111,9 @@ struct tf_plan {
         void *blocks = nullptr, *rows = nullptr, *lens = nullptr, *idx = nullptr, *vals = nullptr, *cuts = nullptr;
         int32_t n_blocks = 0, n_cut_blocks = 0;
         bool sorted = false;
-        size_t partial_at = 0;             // bytes into the plan's workspace: sums of the pieces of cut rows
-        void *arrived = nullptr;           // counts of those done
+        // sums of the pieces of cut rows (bytes into cut_sums) and counts of those done (into cut_counts), for each
+        // workspace that the pack is run with: executions that share no workspace share nothing that is written
+        int64_t partial_at[kWorkspaces] = {}, count_at[kWorkspaces] = {};
         tf::PackDev dev() const {
             tf::PackDev d;
             d.blocks = static_cast<const tf::GatherBlock *>(blocks);
@@ -129,6 +133,8 @@ struct tf_plan {
     void *chain_blocks = nullptr, *chain_rows = nullptr, *chain_idx = nullptr, *chain_vals = nullptr;
     int32_t n_chain_blocks = 0;
     size_t chain_zeros = 0;                // bytes into chain_vals
+    void *cut_counts = nullptr;
+    DevBuf cut_sums;
     DevBuf d1;                             // fused path: one slot per spilled D1 row
     DevBuf d1_pair;                        // plain pair of operations: all rows of D1
     bool has_baseline = false;             // the packed copy of all rows of A exists
@@ -163,23 +169,23 @@ void add_pack(Arena &arena, tf_plan::PackBufs &b, const tf::RowPack &pk) {
     arena.add(pk.lens, b.lens);
     arena.add(pk.idx32, b.idx);
     arena.add(pk.vals, b.vals);
-    if (!pk.cuts.empty()) {
-        arena.add(pk.cuts, b.cuts);
-        arena.add(pk.arrived, b.arrived);
-    }
+    if (!pk.cuts.empty()) arena.add(pk.cuts, b.cuts);
     b.n_blocks = (int32_t)pk.blocks.size();
     b.n_cut_blocks = (int32_t)pk.cuts.size();
     b.sorted = pk.sorted;
 }
-// Bytes for the sums of the rows that are cut over several units of the pack, operand rows in `lay`.
-size_t partial_bytes(const tf::RowPack &pk, const tf::D1Layout &lay, int es) {
-    return ((size_t)pk.n_pieces * lay.n_sl * lay.sw * es + 255) / 256 * 256;
+// Places of the sums and counts of the pack's cut rows for runs with the workspace, operand rows in `lay`.
+void add_cuts(tf_plan::PackBufs &b, const tf::RowPack &pk, const tf::D1Layout &lay, int es, Workspace w,
+              int64_t &sums, int64_t &counts) {
+    b.partial_at[w] = sums;
+    b.count_at[w] = counts;
+    sums += tf::round_up(pk.n_pieces * lay.columns() * es, 256);
+    counts += tf::round_up(pk.n_counts, 64);
 }
 // the packed entries live on the device from here on; the row lists stay for the schedule view
 void drop_entries(tf::RowPack &pk) {
     tf::RawVec<int32_t>().swap(pk.idx32);
     tf::RawVec<unsigned char>().swap(pk.vals);
-    std::vector<int32_t>().swap(pk.arrived);
     std::vector<int32_t>().swap(pk.lens);
     std::vector<tf::GatherBlock>().swap(pk.blocks);
 }
@@ -228,7 +234,7 @@ tf::FusedLaunch fused_args(const tf_plan *p, const void *C, void *D) {
     return a;
 }
 
-tf::PackedSpmmLaunch packed_args(const tf_plan *p, const tf_plan::PackBufs &b, const void *X,
+tf::PackedSpmmLaunch packed_args(const tf_plan *p, const tf_plan::PackBufs &b, Workspace ws, const void *X,
                                  const tf::D1Layout &lay, void *D) {
     tf::PackedSpmmLaunch w{};
     w.dtype = p->dtype;
@@ -244,19 +250,11 @@ tf::PackedSpmmLaunch packed_args(const tf_plan *p, const tf_plan::PackBufs &b, c
     w.sw = lay.sw;
     w.ldx = lay.sw;
     w.x_slice_stride = lay.slice_stride();
-    w.partial = static_cast<char *>(p->d1.p) + b.partial_at;
-    w.arrived = static_cast<int32_t *>(b.arrived);
+    w.partial = static_cast<char *>(p->cut_sums.p) + b.partial_at[ws];
+    w.arrived = static_cast<uint32_t *>(p->cut_counts) + b.count_at[ws];
     w.Y = D;
     w.ccol = (int32_t)p->ccol;
     return w;
-}
-
-tf::PackedSpmmLaunch second_wavefront_args(const tf_plan *p, void *D) {
-    return packed_args(p, p->wf1, p->d1.p, p->s.d1, D);
-}
-
-tf::PackedSpmmLaunch all_rows_args(const tf_plan *p, void *D) {
-    return packed_args(p, p->all, p->d1_unf.p, p->unf_layout(), D);
 }
 
 // The unfused baseline's workspace holds all n rows of D1; it is allocated when first needed.
@@ -382,17 +380,19 @@ tf_status first_wavefront_sparse(const tf_plan *p, const tf_csr *B, const void *
     return TF_OK;
 }
 // D1 = B C and D = A D1 over all rows (CSR B).
-tf_status run_plain_pair(const tf_plan *p, const tf_csr *B, const void *C, void *D, void *ws, void *stream) {
+tf_status run_plain_pair(const tf_plan *p, const tf_csr *B, const void *C, void *D, Workspace which, void *ws,
+                         void *stream) {
     int e = tf::launch_csr_spmm(csr_spmm_args(p, B, C, ws, p->unf_layout()), stream);
     if (e) return hip_fail((hipError_t)e, "launching the first SpMM");
-    e = tf::launch_packed_spmm(packed_args(p, p->all, ws, p->unf_layout(), D), stream);
+    e = tf::launch_packed_spmm(packed_args(p, p->all, which, ws, p->unf_layout(), D), stream);
     if (e) return hip_fail((hipError_t)e, "launching the second SpMM");
     return TF_OK;
 }
 // Y = A B into the workspace, D = Y C (dense B).
-tf_status run_gather_first(const tf_plan *p, const void *B, const void *C, void *D, void *ws, void *stream) {
+tf_status run_gather_first(const tf_plan *p, const void *B, const void *C, void *D, Workspace which, void *ws,
+                           void *stream) {
     const tf::D1Layout y = tf::gather_first_slices(p->dtype, p->n, p->bcol);
-    tf::PackedSpmmLaunch w = packed_args(p, p->s.gather_first_shares ? p->all : p->gf, B, y, ws);
+    tf::PackedSpmmLaunch w = packed_args(p, p->s.gather_first_shares ? p->all : p->gf, which, B, y, ws);
     w.ccol = w.ldx = (int32_t)p->bcol;             // (slices of whole rows of B)
     w.x_slice_stride = y.sw;
     w.wide = (double)y.elements() * tf::elem_size(p->dtype) >= 4294967296.0 ? 1 : 0;
@@ -435,10 +435,8 @@ tf_status run_chain(const tf_plan *p, const void *B, const void *C, void *D, voi
     if (e) return hip_fail((hipError_t)e, "launching the chain");
     return TF_OK;
 }
-tf_status second_wavefront(const tf_plan *p, void *D, void *ws, void *stream) {
-    tf::PackedSpmmLaunch w = second_wavefront_args(p, D);
-    w.X = ws;
-    const int e = tf::launch_packed_spmm(w, stream);
+tf_status second_wavefront(const tf_plan *p, void *D, Workspace which, void *ws, void *stream) {
+    const int e = tf::launch_packed_spmm(packed_args(p, p->wf1, which, ws, p->s.d1, D), stream);
     if (e) return hip_fail((hipError_t)e, "launching the second wavefront");
     return TF_OK;
 }
@@ -639,15 +637,22 @@ tf_status tf_plan_create(const tf_csr *A, int64_t bCol, int64_t cCol, int32_t b_
             arena.add(sc.chain.vals, p->chain_vals);
             p->chain_zeros = sc.chain.vals.size() - tf::kChainZeroRows * tf::kChainRowBytes;
         }
-        // behind the rows of the workspace: the sums of cut rows, for each pack (B is gathered whole, and with
-        // `all` only where its rows take as many lanes as a slice of D1 does)
-        const tf::D1Layout y = sc.gather_first ? tf::gather_first_slices(p->dtype, n, bCol) : sc.d1;
-        const bool y_wider = sc.gather_first_shares && y.columns() > sc.d1.columns();
-        p->wf1.partial_at = ((size_t)sc.d1.elements() * es + 255) / 256 * 256;
-        p->all.partial_at = p->wf1.partial_at + partial_bytes(sc.wf1, sc.d1, es);
-        p->gf.partial_at = p->all.partial_at + partial_bytes(sc.all, y_wider ? y : sc.d1, es);
+        int64_t sums = 0, counts = 0;
+        add_cuts(p->wf1, sc.wf1, sc.d1, es, kPlanWorkspace, sums, counts);
+        if (!p->b_is_sparse) add_cuts(p->wf1, sc.wf1, sc.d1, es, kStaticWorkspace, sums, counts);
+        if (p->has_baseline) add_cuts(p->all, sc.all, p->unf_layout(), es, kUnfusedWorkspace, sums, counts);
+        if (sc.plain_pair) add_cuts(p->all, sc.all, p->unf_layout(), es, kPairWorkspace, sums, counts);
+        if (sc.gather_first) {
+            // (with `all`: rows of B take as many lanes as a slice of D1, and no more slices or columns)
+            const tf::D1Layout y = tf::gather_first_slices(p->dtype, n, bCol), &lay = sc.gather_first_shares ? sc.d1 : y;
+            for (Workspace w : {kPlanWorkspace, kStaticWorkspace})
+                add_cuts(sc.gather_first_shares ? p->all : p->gf, sc.gather_first_shares ? sc.all : sc.gf, lay, es, w, sums, counts);
+        }
+        const std::vector<uint32_t> zeros((size_t)counts, 0);
+        if (counts) arena.add(zeros, p->cut_counts);
         hipError_t e = arena.upload(p->arrays);
-        if (e == hipSuccess) e = p->d1.alloc(p->gf.partial_at + partial_bytes(sc.gf, y, es));
+        if (e == hipSuccess) e = p->d1.alloc((size_t)sc.d1.elements() * es);
+        if (e == hipSuccess && sums) e = p->cut_sums.alloc((size_t)sums);
         if (e == hipSuccess && sc.plain_pair) e = p->d1_pair.alloc((size_t)p->unf_layout().elements() * es);
         if (e != hipSuccess) return hip_fail(e, "allocating the plan's device memory");
         sc.tile_meta.reset();
@@ -790,10 +795,10 @@ tf_status tf_gemm_spmm(const tf_plan *p, const void *B, const void *C, void *D, 
     if (!B || !aligned16(B)) return fail(TF_EINVAL, "B must be a 16-byte aligned device pointer");
     const int32_t execution = p->fused_execution();
     if (execution == TF_EXECUTE_ONE_PASS) return run_chain(p, B, C, D, stream);
-    if (execution == TF_EXECUTE_GATHER_FIRST) return run_gather_first(p, B, C, D, p->d1.p, stream);
+    if (execution == TF_EXECUTE_GATHER_FIRST) return run_gather_first(p, B, C, D, kPlanWorkspace, p->d1.p, stream);
     st = first_wavefront_dense(p, B, C, D, p->d1.p, stream);
     if (st != TF_OK) return st;
-    return second_wavefront(p, D, p->d1.p, stream);
+    return second_wavefront(p, D, kPlanWorkspace, p->d1.p, stream);
 }
 
 tf_status tf_gemm_spmm_static(const tf_plan *p, const void *B, const void *C, void *D, void *stream) {
@@ -810,12 +815,12 @@ tf_status tf_gemm_spmm_static(const tf_plan *p, const void *B, const void *C, vo
     void *ws = nullptr;
     st = static_scratch(&ws);
     if (st != TF_OK) return st;
-    if (execution == TF_EXECUTE_GATHER_FIRST) return run_gather_first(p, B, C, D, ws, stream);
+    if (execution == TF_EXECUTE_GATHER_FIRST) return run_gather_first(p, B, C, D, kStaticWorkspace, ws, stream);
     // every spilled row is written by the first wavefront before the second one reads it: nothing
     // in the array has to start at zero
     st = first_wavefront_dense(p, B, C, D, ws, stream);
     if (st != TF_OK) return st;
-    return second_wavefront(p, D, ws, stream);
+    return second_wavefront(p, D, kStaticWorkspace, ws, stream);
 }
 
 tf_status tf_spmm_spmm(const tf_plan *p, const tf_csr *B, const void *C, void *D, void *stream) {
@@ -823,10 +828,10 @@ tf_status tf_spmm_spmm(const tf_plan *p, const tf_csr *B, const void *C, void *D
     if (st != TF_OK) return st;
     st = check_sparse_b(p, B);
     if (st != TF_OK) return st;
-    if (p->fused_execution() == TF_EXECUTE_PLAIN_PAIR) return run_plain_pair(p, B, C, D, p->d1_pair.p, stream);
+    if (p->fused_execution() == TF_EXECUTE_PLAIN_PAIR) return run_plain_pair(p, B, C, D, kPairWorkspace, p->d1_pair.p, stream);
     st = first_wavefront_sparse(p, B, C, D, p->d1.p, stream);
     if (st != TF_OK) return st;
-    return second_wavefront(p, D, p->d1.p, stream);
+    return second_wavefront(p, D, kPlanWorkspace, p->d1.p, stream);
 }
 
 tf_status tf_run_wavefront(const tf_plan *p, int32_t wavefront, const void *B_dense,
@@ -834,7 +839,7 @@ tf_status tf_run_wavefront(const tf_plan *p, int32_t wavefront, const void *B_de
     if (!p) return fail(TF_EINVAL, "null argument");
     tf_status st = check_exec(p, p->b_is_sparse, C, D);
     if (st != TF_OK) return st;
-    if (wavefront == 1) return second_wavefront(p, D, p->d1.p, stream);
+    if (wavefront == 1) return second_wavefront(p, D, kPlanWorkspace, p->d1.p, stream);
     if (wavefront != 0) return fail(TF_EINVAL, "wavefront must be 0 or 1");
     if (p->b_is_sparse) {
         st = check_sparse_b(p, B_csr);
@@ -861,7 +866,7 @@ tf_status tf_unfused_gemm_spmm(const tf_plan *p, const void *B, const void *C, v
     gemm_workspace(g, p->d1_unf.p, p->unf_layout());
     int e = tf::launch_gemm(g, stream);
     if (e) return hip_fail((hipError_t)e, "launching the GeMM");
-    e = tf::launch_packed_spmm(all_rows_args(p, D), stream);
+    e = tf::launch_packed_spmm(packed_args(p, p->all, kUnfusedWorkspace, p->d1_unf.p, p->unf_layout(), D), stream);
     if (e) return hip_fail((hipError_t)e, "launching the SpMM");
     return TF_OK;
 }
@@ -874,7 +879,7 @@ tf_status tf_unfused_spmm_spmm(const tf_plan *p, const tf_csr *B, const void *C,
     if (st != TF_OK) return st;
     st = prepare_unfused(p);
     if (st != TF_OK) return st;
-    return run_plain_pair(p, B, C, D, p->d1_unf.p, stream);
+    return run_plain_pair(p, B, C, D, kUnfusedWorkspace, p->d1_unf.p, stream);
 }
 
 }  // extern "C"

@@ -17,7 +17,7 @@ namespace {
 // time per call in some processes, 9.4 in others; 128 and 104, 14 in all: 7.5 and 8.7).
 struct PackedArgs {
     void *Y, *partial;
-    int32_t *arrived;
+    uint32_t *arrived;
     int64_t x_slice_stride;
     int32_t n_xs, sw, ldx, n_blocks, n_cut_blocks, ccol, contiguous, read_next, n_wg;
 };
@@ -45,7 +45,8 @@ struct CsrArgs {
 // A row too long for one block takes the four blocks of a workgroup, whose waves add up their sums through LDS
 // (the blocks of such rows come first), or several times that: these sums go past the L2 (device-scope stores
 // and loads) and are there before the count of finished pieces is raised; the workgroup that is done last adds
-// them up in their order.
+// them up, in an order that does not depend on theirs.  The count goes round: every launch raises it by as many as
+// there are pieces, so that it is back at zero after any number of launches, whatever they ran beside.
 //
 // Bound by the fabric behind the L2 where rows reach far: R-MAT graph of 2^20 vertices, fp32, 128 columns in four
 // slices, 709 us, 5.0 GB cross the memory interface at 7.0 TB/s (units staged by a workgroup behind a barrier: 747
@@ -57,7 +58,7 @@ __global__ __launch_bounds__(kSpmmThreads, gather_waves(dtype_of<T>())) void k_p
     const int32_t *__restrict__ lens, const int32_t *__restrict__ idx, const T *__restrict__ val,
     const CutBlock *__restrict__ cuts, const T *__restrict__ X0) {
     T *const Y0 = static_cast<T *>(a.Y), *const partial = static_cast<T *>(a.partial);
-    int32_t *const all_arrived = a.arrived;
+    uint32_t *const all_arrived = a.arrived;
     constexpr int E = kGatherEntries, NR = 64 / G, NE = NR * E > 64 ? NR * E / 64 : 1;
     typedef std::conditional_t<WIDE, uint64_t, uint32_t> Off;
     typedef T Vec16 __attribute__((ext_vector_type(Tr<T>::V)));
@@ -216,13 +217,12 @@ __global__ __launch_bounds__(kSpmmThreads, gather_waves(dtype_of<T>())) void k_p
                     }
                     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
                     __builtin_amdgcn_s_waitcnt(0);
-                    int32_t *arrived = all_arrived + ((int64_t)c.row * a.n_xs + slice) * n_cb + cb;
-                    int32_t done = 0;
-                    if (lane == 0)
-                        done = __hip_atomic_fetch_add(arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    if (__builtin_amdgcn_readfirstlane(done) != c.pieces - 1) return;
+                    uint32_t *arrived = all_arrived + ((int64_t)c.row * a.n_xs + slice) * n_cb + cb;
+                    const uint32_t last = (uint32_t)__builtin_amdgcn_readfirstlane(c.pieces) - 1;
+                    uint32_t done = 0;
+                    if (lane == 0) done = atomicInc(arrived, last);
+                    if ((uint32_t)__builtin_amdgcn_readfirstlane(done) != last) return;
                     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-                    if (lane == 0) __hip_atomic_store(arrived, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
                     for (int i = 0; i < VV; ++i) acc[i] = T(0);
                     for (int k = v; k < c.pieces; k += NR) {

@@ -261,7 +261,7 @@ void pack_rows(const int32_t *rowptr, const int32_t *colidx, const unsigned char
         b.slot_base = (uint32_t)slot;
         slot += b.slots();
     }
-    out.arrived.assign((size_t)out.n_cut_rows * (size_t)rules.counts, 0);
+    out.n_counts = (int64_t)out.n_cut_rows * rules.counts;
     // spare entries behind the last block: the kernel fetches passes ahead, and whole passes
     const int64_t end = slot * nr, spare = std::max<int64_t>(64, 2 * kGatherEntries * nr);
     out.idx32.resize((size_t)(end + spare));

@@ -298,7 +298,7 @@ struct RowPack {
     int32_t n_pieces = 0;
     int32_t n_cut_rows = 0;              // rows cut over several blocks
     std::vector<CutBlock> cuts;          // their blocks
-    std::vector<int32_t> arrived;        // zeros: counts of their finished pieces, per slice and column block
+    int64_t n_counts = 0;                // counts of their finished pieces, per slice and column block
 };
 
 // ---- the chain in one pass, D = (A B) C (dense B) -----------------------------------------------
@@ -529,7 +529,7 @@ struct PackedSpmmLaunch {
     int32_t read_next;                // 1: the next launch reads Y
     int32_t dtype;
     void *partial;                    // sums of the pieces of cut rows: [piece][slice][sw]
-    int32_t *arrived;                 // pieces of a cut row that are done: [cut row][slice][column block], zeros between launches
+    uint32_t *arrived;                // pieces of a cut row that are done: [cut row][slice][column block], zeros between launches
     PackDev pack;                     // indices: rows (slots) of X
     const void *X;                    // D1 workspace in the layout above, or a dense B
     void *Y;                          // row-major, ccol columns

@@ -252,3 +252,68 @@ def test_both_operations_over_all_rows_of_a_large_band(dtype, n, h, ccol):
             assert np.array_equal(c.run().astype(np.float64), D_ref)
         finally:
             c.close()
+
+
+@pytest.mark.parametrize("bcol,ccol,expected", [(64, 32, "WAVEFRONTS"), (32, 128, "GATHER_FIRST")])
+def test_static_calls_beside_calls_of_the_same_plan(bcol, ccol, expected):
+    """Rows cut over several workgroups: a call with the library's own workspace shares no sums and no counts with the
+    plan's other calls, on streams of their own and one after the other."""
+    import torch
+    import paper_2407_00243_amd as tf
+    from gpu_util import Case
+    n = 30011
+    rng = np.random.default_rng(15)
+    A = _hubs(n, np.float32, rng, lambda k: rng.integers(-2, 3, k))
+    B, C = ti.dense_small_int(n, bcol, np.float32, 5), ti.dense_small_int(bcol, ccol, np.float32, 6)
+    D_ref, _ = oracle.chain(A, B, C)
+    c = Case(ti.Problem("beside", "gemm_spmm", np.dtype(np.float32), A, B, C))
+    try:
+        assert c.plan.schedule()["execution"] == getattr(tf, "TF_EXECUTE_" + expected)
+        c.plan.prepare_unfused()
+        calls = [c.plan.run, lambda *a: tf.tf_gemm_spmm_static(c.plan.handle, *a), c.plan.run_unfused]
+        streams = [torch.cuda.Stream() for _ in calls]
+        Ds = [[torch.full((n, ccol), float("nan"), device="cuda") for _ in range(8)] for _ in calls]
+        torch.cuda.synchronize()
+        for k in range(8):
+            # (the unfused call of a gather-first plan may run over the row list of the others)
+            for call, stream, D in zip(calls, streams, Ds):
+                call(c.B, c.C, D[k], stream.cuda_stream)
+        torch.cuda.synchronize()
+        for D in Ds:
+            for d in D:
+                assert np.array_equal(d.cpu().numpy().astype(np.float64), D_ref)
+    finally:
+        c.close()
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+def test_unfused_calls_beside_the_plain_pair(dtype):
+    """Both run over the packed copy of all rows, with sums and counts of their own for rows that are cut."""
+    import torch
+    import paper_2407_00243_amd as tf
+    from gpu_util import Case
+    n, ccol = 20011, 32
+    rng = np.random.default_rng(16)
+    lens = np.full(n, 5)
+    lens[rng.permutation(n)[:40]] = rng.integers(1, 16000, 40)
+    rowptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    near = np.clip(np.repeat(np.arange(n), lens) + np.concatenate([np.arange(k) - k // 2 for k in lens]), 0, n - 1)
+    A = ti.Csr(n, n, rowptr, near.astype(np.int32), rng.integers(-2, 3, near.size).astype(dtype))
+    C = ti.dense_small_int(n, ccol, dtype, 6)
+    D_ref, _ = oracle.chain(A, A, C)
+    c = Case(ti.Problem("beside", "spmm_spmm", np.dtype(dtype), A, A, C))
+    try:
+        assert c.plan.schedule()["execution"] == tf.TF_EXECUTE_PLAIN_PAIR
+        c.plan.prepare_unfused()
+        streams = [torch.cuda.Stream() for _ in range(2)]
+        Ds = [[torch.full((n, ccol), float("nan"), device="cuda", dtype=c.tdtype) for _ in range(6)] for _ in streams]
+        torch.cuda.synchronize()
+        for k in range(6):
+            c.plan.run(c.B, c.C, Ds[0][k], streams[0].cuda_stream)
+            c.plan.run_unfused(c.B, c.C, Ds[1][k], streams[1].cuda_stream)
+        torch.cuda.synchronize()
+        for D in Ds:
+            for d in D:
+                assert np.array_equal(d.cpu().numpy().astype(np.float64), D_ref)
+    finally:
+        c.close()
