@@ -643,7 +643,6 @@ tf_status tf_plan_create(const tf_csr *A, int64_t bCol, int64_t cCol, int32_t b_
         if (p->has_baseline) add_cuts(p->all, sc.all, p->unf_layout(), es, kUnfusedWorkspace, sums, counts);
         if (sc.plain_pair) add_cuts(p->all, sc.all, p->unf_layout(), es, kPairWorkspace, sums, counts);
         if (sc.gather_first) {
-            // (with `all`: rows of B take as many lanes as a slice of D1, and no more slices or columns)
             const tf::D1Layout y = tf::gather_first_slices(p->dtype, n, bCol), &lay = sc.gather_first_shares ? sc.d1 : y;
             for (Workspace w : {kPlanWorkspace, kStaticWorkspace})
                 add_cuts(sc.gather_first_shares ? p->all : p->gf, sc.gather_first_shares ? sc.all : sc.gf, lay, es, w, sums, counts);

@@ -90,15 +90,6 @@ __device__ __forceinline__ int pow2_at_least(int x) {
     return g;
 }
 
-// Consecutive workgroup ids are dealt round-robin to the eight XCDs, each with its own L2.
-// Work items that touch neighbouring rows (adjacent tiles, the column slices of one tile, adjacent
-// units of the second wavefront) should share an L2, so item ids are handed out in eight
-// contiguous ranges, one per XCD: workgroup b works on item (b % 8) * ceil(total / 8) + b / 8.
-__device__ __forceinline__ int64_t xcd_contiguous(int64_t bid, int64_t total) {
-    const int64_t per = (total + kXcds - 1) / kXcds;
-    return (bid % kXcds) * per + bid / kXcds;
-}
-
 template <typename T> constexpr int dtype_of() { return sizeof(T) == 8 ? TF_F64 : TF_F32; }
 
 extern __shared__ __align__(16) unsigned char tf_smem[];

@@ -1299,14 +1299,15 @@ void choose_gather_first(const InspectorInput &in, Schedule &s) {
 void build_gather_first(const InspectorInput &in, Schedule &s, bool have_all) {
     const int64_t n = in.n, es = elem_size(in.dtype);
     const D1Layout b = gather_first_slices(in.dtype, n, in.bcol);
-    const int group = lane_group(b.sw, lane_elems(in.dtype, in.bcol, b.sw));
-    const int group_all = lane_group(s.d1.sw, lane_elems(in.dtype, in.ccol, s.d1.sw));
-    s.gather_first_shares = have_all && group == group_all;
+    const PackRules rules = pack_rules(in, in.bcol, in.nnz, b), all_rules = pack_rules(in, in.ccol, in.nnz, s.d1);
+    // (the sums and counts of cut rows of `all` have the places that rows of D1 need)
+    s.gather_first_shares = have_all && rules.nr == all_rules.nr && rules.counts <= all_rules.counts &&
+                            b.columns() <= s.d1.columns();
     if (!s.gather_first_shares) {
         std::vector<int32_t> all((size_t)n);
         std::iota(all.begin(), all.end(), 0);
         pack_rows(in.rowptr, in.colidx, static_cast<const unsigned char *>(in.vals), (int)es, std::move(all),
-                  pack_rules(in, in.bcol, in.nnz, b), [](int32_t c) { return c; }, s.gf);
+                  rules, [](int32_t c) { return c; }, s.gf);
     }
     s.gf_info.resize((size_t)n);
     for (int64_t j = 0; j < n; ++j)
