@@ -1325,6 +1325,7 @@ void build_gather_first(const InspectorInput &in, Schedule &s, bool have_all) {
 // 29472 x 69, 8 MB, 22.5 / 17.2; beyond: fp64 27863 x 64, 14 MB, 19.4 / 20.5; fp32 94792 x 64, 24 MB, 24 / 26.
 // Of 11, 8 %: fp64 159683 x 37, 47 MB, 127 / 96; fp32 298908 x 64, 77 MB, 96 / 115.)  80 MB bounds what a plan
 // keeps in device memory for it.
+constexpr double kPlainPairBytes = 80e6;
 bool plain_pair_is_faster(const InspectorInput &in, const Schedule &s) {
     if (!in.b_is_sparse || in.n == 0 || in.nnz == 0 || s.streaming) return false;
     // only where the caller has left the whole choice to the library
@@ -1332,7 +1333,8 @@ bool plain_pair_is_faster(const InspectorInput &in, const Schedule &s) {
         return false;
     const double per_row = (double)in.nnz / (double)in.n, spilled = (double)s.d1.rows / (double)in.n;
     const double chain = std::max(0.0, per_row - 2), most = (1.7e6 + 0.2e6 * chain) * chain * (1 + 6 * std::min(0.4, spilled));
-    return (double)(in.n * in.ccol * elem_size(in.dtype)) <= std::min(80e6, std::max(12e6, most));
+    // (rows and slices as the workspace lays them out: padded to whole lines where rows reach far)
+    return (double)(in.n * s.d1.columns() * elem_size(in.dtype)) <= std::min(kPlainPairBytes, std::max(12e6, most));
 }
 
 void build_baseline_pack(const InspectorInput &in, Schedule &s) {

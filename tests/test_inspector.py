@@ -443,3 +443,23 @@ def test_rows_of_equal_length_hold_no_wave_up(n, h, dtype, bcol, ccol):
     rowptr = np.concatenate([[0], np.cumsum(np.bincount(rows[keep], minlength=n))]).astype(np.int32)
     A = ti.Csr(n, n, rowptr, cols[keep].astype(np.int32), np.ones(keep.sum(), dtype))
     assert plan_schedule(A, bcol, ccol, False)["execution"] == tf.TF_EXECUTE_ONE_PASS
+
+
+def near_and_far(n, per_row, dtype, seed):
+    """Rows near the diagonal, and a quarter of them, together, with columns anywhere."""
+    rng = np.random.default_rng(seed)
+    cols = np.arange(n)[:, None] + np.arange(per_row) - per_row // 2
+    far = np.arange(n) % 2048 >= 1536
+    cols[far] = rng.integers(0, n, (int(far.sum()), per_row))
+    return ti.Csr(n, n, np.arange(0, n * per_row + 1, per_row, dtype=np.int32),
+                  np.clip(cols, 0, n - 1).astype(np.int32).ravel(), np.ones(n * per_row, dtype))
+
+
+@pytest.mark.parametrize("n,ccol", [(1000000, 17), (500000, 36)])
+def test_rows_of_the_plain_pair_take_80_megabytes_at_most(n, ccol):
+    """As they are laid out: rows of a workspace may be padded to whole cache lines."""
+    s = plan_schedule(near_and_far(n, 10, np.float32, 1), n, ccol, True)
+    assert s["far_rows"] and not s["first_wavefront_streams"]
+    assert s["d1_slices"] * s["d1_slice_cols"] > ccol and n * ccol * 4 < 80e6
+    assert n * s["d1_slices"] * s["d1_slice_cols"] * 4 > 80e6
+    assert s["execution"] == tf.TF_EXECUTE_WAVEFRONTS
