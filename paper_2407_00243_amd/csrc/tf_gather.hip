@@ -329,7 +329,7 @@ __global__ __launch_bounds__(kSpmmThreads, gather_waves(dtype_of<T>())) void k_p
 // As k_packed_spmm, for rows as they come: a wave owns 64 / G consecutive rows at a time and takes E entries of each
 // per pass.  What the passes need of the rows' extents is read two blocks ahead, entries a pass ahead, the first
 // gathers of the next block go out before a block's rows are stored.  Every XCD takes n_xs eighths of the rows, of
-// at most two column slices of X.  The time of a block is that of its longest row.  Bound as k_packed_spmm: 2^20 rows
+// at most two column slices of X.  The time of a block is that of its longest row; which wave takes which, CsrWalk.  Bound as k_packed_spmm: 2^20 rows
 // of eight random columns, fp32, 32 columns, 182 us, 5.8 TB/s of gathered lines (184 us when workgroups staged
 // entries behind barriers); 3000 rows of 49, 100 columns, both operations 13.8 us (44.4).
 template <typename T, int VV, int G, bool WIDE>
@@ -492,16 +492,18 @@ __global__ __launch_bounds__(kSpmmThreads, 4) void k_csr_spmm(
                 }
             };
 
-            uint32_t u = e0 * all.eighth() + my;
-            if (u >= end) break;
-            Rows d = read_rows(u), dn = read_rows(min(u + n_waves, end - 1));
+            CsrWalk u{e0 * all.eighth() + my, my};
+            if (u.at >= end) break;
+            CsrWalk un = u.next(n_waves);
+            Rows d = read_rows(u.at), dn = read_rows(min(un.at, end - 1));
             fetch(d, 0);
             put();
             fetch(any(d.len > E) ? d : dn, any(d.len > E) ? E : 0);
             issue(d.len);
             for (;;) {
-                const bool has_next = u + n_waves < end;
-                const Rows dnn = read_rows(min(u + 2 * n_waves, end - 1));
+                const bool has_next = un.at < end;
+                const CsrWalk unn = un.next(n_waves);
+                const Rows dnn = read_rows(min(unn.at, end - 1));
 #pragma unroll
                 for (int i = 0; i < VV; ++i) acc[i] = T(0);
                 consume(d.len);
@@ -518,11 +520,12 @@ __global__ __launch_bounds__(kSpmmThreads, 4) void k_csr_spmm(
                     fetch(more ? dn : dnn, more ? E : 0);
                 }
                 issue(has_next ? dn.len : 0);
-                finish(d, u);
+                finish(d, u.at);
                 if (!has_next) break;
                 d = dn;
                 dn = dnn;
-                u += n_waves;
+                u = un;
+                un = unn;
             }
         } while (++cb < n_cb && cb * G * VV < w);
     } while (left > 0);

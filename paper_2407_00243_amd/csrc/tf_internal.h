@@ -53,6 +53,18 @@ struct CsrBlocks {
     constexpr bool has(uint32_t block, uint32_t v) const { return block * nr + v < n_rows; }
     constexpr uint32_t row(uint32_t block, uint32_t v) const { return has(block, v) ? block * nr + v : n_rows - 1; }
 };
+// The blocks that one of `waves` waves takes, which move through a range side by side: block `at`, numbered within its
+// round by `place`.  Every round begins three waves further: rows with many entries sit at multiples of powers of two in
+// the graphs that are made by recursion, and at a fixed place the same wave would take them all (a b c d = .57 .19 .19 .05,
+// 2^20 rows, 512 waves: that wave has 25224 passes, now 5050, of which the longest row alone takes 4967).
+constexpr uint32_t kCsrTurn = 3;
+struct CsrWalk {
+    uint32_t at, place;
+    constexpr CsrWalk next(uint32_t waves) const {
+        const uint32_t to = place + kCsrTurn;
+        return to < waves ? CsrWalk{at + waves + kCsrTurn, to} : CsrWalk{at + kCsrTurn, to - waves};
+    }
+};
 // Is there an entry number s (which may lie as far behind the row as another row of its block is long) in the row of
 // the entries begin to end - 1?
 constexpr bool has_entry(int32_t begin, int32_t end, uint32_t s) { return s < (uint32_t)(end - begin); }

@@ -60,3 +60,34 @@ def test_rows_and_entries_at_the_end_of_32_bits(tmp_path):
                 const int64_t end = begin + len <= 0x7fffffff ? begin + len : 0x7fffffff;
                 CHECK(has_entry((int32_t)begin, (int32_t)end, (uint32_t)s) == (begin + s < end));
             }""")
+
+
+def test_every_block_is_taken_once_and_long_rows_by_different_waves(tmp_path):
+    """CsrWalk over ranges of all lengths; rows whose entries fall with the bits set in their number (the expected
+    degrees of a recursive graph, largest at multiples of the powers of two): the busiest wave has about twice the
+    longest row or its share at most; at a fixed place in every round it has 4 to 7 times that."""
+    run_cpp(tmp_path, """
+    for (uint32_t waves : {4u, 8u, 12u, 256u, 320u, 512u})
+        for (uint32_t count : {1u, 3u, 4u, 5u, 511u, 512u, 513u, 4096u, 131072u}) {
+            std::vector<int> taken(count, 0);
+            int64_t busiest = 0, all = 0, longest = 0;
+            for (uint32_t w = 0; w < waves; ++w) {
+                int64_t passes = 0;
+                uint32_t last = 0;
+                for (CsrWalk u{w, w}; u.at < count; u = u.next(waves)) {
+                    CHECK(u.place < waves && (u.at == w || u.at > last));
+                    last = u.at;
+                    ++taken[u.at];
+                    double entries = 32.0 * count;
+                    for (uint32_t k = u.at; k; k &= k - 1) entries *= 0.32;
+                    const int64_t mine = 1 + (int64_t)entries / 8;
+                    passes += mine;
+                    longest = mine > longest ? mine : longest;
+                }
+                busiest = passes > busiest ? passes : busiest;
+                all += passes;
+            }
+            for (int k : taken) CHECK(k == 1);
+            // (launches of several blocks a wave have 128 waves and more on an XCD)
+            if (waves >= 128) CHECK(busiest <= 2.25 * (longest > all / waves ? longest : all / waves));
+        }""")
