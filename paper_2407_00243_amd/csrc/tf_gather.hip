@@ -543,13 +543,10 @@ template <typename T, int VV, int G, bool WIDE> int run_packed(const PackedSpmmL
 }
 
 template <typename T, int VV, int G, bool WIDE> int run_csr(const CsrSpmmLaunch &a, hipStream_t st) {
-    static const int most = resident_per_cu(k_csr_spmm<T, VV, G, WIDE>, kSpmmThreads, 0, 8);
-    // Rows of X from beyond the L2: more requests on their way than the fabric takes only slow it down (us, two, three
-    // and four workgroups per compute unit: 2^20 rows of eight, fp32 32 columns 184 / 191 / 191; 200000 of eight, fp64
-    // 64 columns 120 / 127 / 127; 200000 of five, fp32 64 46.6 / 42.8 / 44.4; 10^6 of four, fp32 32 106 / 99 / 104;
-    // where X is smaller, 12.8 MB, 17.1 / 15.3 / 15.3).
-    int wg_per_cu = most;
-    if (a.x_bytes >= 40000000 && a.mean_len > 0) wg_per_cu = std::min(most, std::max(2, (14 + a.mean_len) / std::max(1, a.mean_len + 1)));
+    // (all that the machine holds: two per compute unit where X is beyond the caches and rows of S have six entries and
+    // more are 0 to 5 % faster for random columns, but up to 65 % slower for columns near the diagonal, 85 % with long
+    // rows among them, and S is not known before the call)
+    static const int wg_per_cu = resident_per_cu(k_csr_spmm<T, VV, G, WIDE>, kSpmmThreads, 0, 8);
     const int64_t blocks = ((int64_t)a.n_rows + 64 / G - 1) / (64 / G), items = (blocks + kXcds - 1) / kXcds * a.n_xs;
     const int64_t per_xcd = std::min<int64_t>((items + kSpmmThreads / 64 - 1) / (kSpmmThreads / 64),
                                               std::max(1, a.n_cu / kXcds) * (int64_t)wg_per_cu);

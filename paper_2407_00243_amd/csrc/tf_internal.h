@@ -564,7 +564,6 @@ struct CsrSpmmLaunch {
     const void *row_scale;
     void *D;
     int64_t x_bytes;
-    int32_t mean_len;                 // entries per row of S, 0: rows that stay near the diagonal
     int32_t n_cu;                     // compute units of the device
 };
 
