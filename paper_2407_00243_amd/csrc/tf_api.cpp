@@ -390,7 +390,7 @@ tf_status run_plain_pair(const tf_plan *p, const tf_csr *B, const void *C, void 
 // Y = A B into the workspace, D = Y C (dense B).
 tf_status run_gather_first(const tf_plan *p, const void *B, const void *C, void *D, Workspace which, void *ws,
                            void *stream) {
-    const tf::D1Layout y = tf::gather_first_slices(p->dtype, p->n, p->bcol);
+    const tf::D1Layout y = tf::gather_first_slices(p->dtype, p->n, p->bcol, p->s.reuse);
     tf::PackedSpmmLaunch w = packed_args(p, p->s.gather_first_shares ? p->all : p->gf, which, B, y, ws);
     w.ccol = w.ldx = (int32_t)p->bcol;             // (slices of whole rows of B)
     w.x_slice_stride = y.sw;
@@ -642,7 +642,7 @@ tf_status tf_plan_create(const tf_csr *A, int64_t bCol, int64_t cCol, int32_t b_
         if (p->has_baseline) add_cuts(p->all, sc.all, p->unf_layout(), es, kUnfusedWorkspace, sums, counts);
         if (sc.plain_pair) add_cuts(p->all, sc.all, p->unf_layout(), es, kPairWorkspace, sums, counts);
         if (sc.gather_first) {
-            const tf::D1Layout y = tf::gather_first_slices(p->dtype, n, bCol), &lay = sc.gather_first_shares ? sc.d1 : y;
+            const tf::D1Layout y = tf::gather_first_slices(p->dtype, n, bCol, sc.reuse), &lay = sc.gather_first_shares ? sc.d1 : y;
             for (Workspace w : {kPlanWorkspace, kStaticWorkspace})
                 add_cuts(sc.gather_first_shares ? p->all : p->gf, sc.gather_first_shares ? sc.all : sc.gf, lay, es, w, sums, counts);
         }

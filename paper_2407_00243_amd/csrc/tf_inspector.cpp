@@ -448,6 +448,26 @@ static int64_t row_pitch(int64_t ccol, int64_t es) {
     return best / es;
 }
 
+// Share of sampled entries whose column is among those of other sampled ones, as many as an L2 has cache lines
+// (Schedule::reuse).  Samples are runs of neighbouring entries, one in each equal part of A.
+static double column_reuse(const InspectorInput &in) {
+    constexpr int64_t run = 16, lines = ((int64_t)4 << 20) / kGatherSliceBytes;
+    if (in.nnz < run) return 1.0;
+    std::vector<uint64_t> seen((size_t)(in.n + 63) / 64, 0);
+    auto sample = [&](int64_t runs, uint64_t seed, auto f) {
+        for (int64_t i = 0; i < runs; ++i) {
+            const int64_t lo = in.nnz * i / runs, hi = in.nnz * (i + 1) / runs;
+            seed = seed * 6364136223846793005u + 1442695040888963407u;
+            const int64_t at = std::min(in.nnz - run, lo + (int64_t)(seed >> 33) % std::max<int64_t>(1, hi - lo));
+            for (int64_t e = 0; e < run; ++e) f(in.colidx[at + e]);
+        }
+    };
+    sample(lines / run, 1, [&](int32_t c) { seen[(size_t)c / 64] |= (uint64_t)1 << c % 64; });
+    int64_t hits = 0;
+    sample(lines / run / 4, 2, [&](int32_t c) { hits += seen[(size_t)c / 64] >> c % 64 & 1; });
+    return (double)hits / (double)(lines / 4);
+}
+
 // How rows of `sw` columns (of ccol, in column slices) are packed for the gather kernel; `entries` of them in all.
 static PackRules pack_rules(const InspectorInput &in, int64_t ccol, int64_t entries, const D1Layout &lay) {
     const int elems = lane_elems(in.dtype, ccol, lay.sw), group = lane_group(lay.sw, elems);
@@ -732,6 +752,7 @@ tf_status build_schedule(const InspectorInput &in, Schedule &s, std::string &err
         s.far_b_share = cnt > 0 ? (double)far / (double)cnt : 0.0;
     }
     s.far_rows = far_rows;
+    if (far_rows) s.reuse = column_reuse(in);
     bool demote_lds_rows = false;
     std::vector<uint8_t> known_spill;      // spill set of the chosen tiling, when it was evaluated
     Tiling tiling;
@@ -990,9 +1011,11 @@ tf_status build_schedule(const InspectorInput &in, Schedule &s, std::string &err
                 int64_t w = kGatherSliceBytes / es;
                 while (w * kXcds < in.ccol) w *= 2;
                 // (the last slice may be narrower in use, down to one lane's 16 bytes)
-                if ((in.ccol - 1) % w + 1 >= v && (s.n_slices == 1 || cs % 16 == 0)) {
+                const int64_t k = (in.ccol + w - 1) / w;
+                if ((in.ccol - 1) % w + 1 >= v && (s.n_slices == 1 || cs % 16 == 0) &&
+                    line_slices_pay(k * w * es, in.ccol * es, s.reuse)) {
                     sw = w;
-                    n_sl = (int)((in.ccol + w - 1) / w);
+                    n_sl = (int)k;
                 }
             } else {
                 sw = row_pitch(in.ccol, es);
@@ -1298,7 +1321,7 @@ void choose_gather_first(const InspectorInput &in, Schedule &s) {
 
 void build_gather_first(const InspectorInput &in, Schedule &s, bool have_all) {
     const int64_t n = in.n, es = elem_size(in.dtype);
-    const D1Layout b = gather_first_slices(in.dtype, n, in.bcol);
+    const D1Layout b = gather_first_slices(in.dtype, n, in.bcol, s.reuse);
     const PackRules rules = pack_rules(in, in.bcol, in.nnz, b), all_rules = pack_rules(in, in.ccol, in.nnz, s.d1);
     // (the sums and counts of cut rows of `all` have the places that rows of D1 need)
     s.gather_first_shares = have_all && rules.nr == all_rules.nr && rules.counts <= all_rules.counts &&

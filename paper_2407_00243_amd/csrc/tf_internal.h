@@ -83,15 +83,27 @@ struct D1Layout {
     int64_t columns() const { return (int64_t)n_sl * sw; }
 };
 
+// Do slices of one cache line pay, `laid_out` bytes of them for rows of row_bytes?  They move that much more and read the
+// entries of A once per slice; they save what an L2 then holds: `reuse` is the share of entries whose column is among as
+// many others as it holds lines (Schedule::reuse).  Second wavefront, rows of 36 to 128 columns, both types, 130 points
+// (slices / whole rows, us: R-MAT graph of 2^20, .44, fp32 128 columns 701 / 973, 400000, .56, 236 / 344; uniform columns, 8
+// a row, 60000 rows, .44, 28.5 / 39.2; 250000, .14, 162 / 165, fp64 90 columns 283 / 265; 700000, .05, fp32 128 columns 488 /
+// 458, 36 columns 275 / 214, fp64 90 columns 1013 / 727).  Below .3 the line is a fit: 0.8 % above the better way on average and 7
+// at most, where slices in any case are 6 and 39; from .3 on slices gain up to 39 %, and lose only where rows are little
+// longer than a line (fp32, 36 columns, 78 % more to move, up to 23 %).
+inline bool line_slices_pay(int64_t laid_out, int64_t row_bytes, double reuse) {
+    return reuse >= 0.3 || (double)laid_out <= (0.9 + 1.25 * reuse) * (double)row_bytes;
+}
+
 // Column slices in which the rows of a dense B are gathered: one cache line each, where rows are whole lines
 // (rows of slices that begin anywhere in a line would touch more of them); `rows` rows of bcol columns,
 // element (i, c) at i bcol + c whatever the slices.
-inline D1Layout gather_first_slices(int dtype, int64_t rows, int64_t bcol) {
+inline D1Layout gather_first_slices(int dtype, int64_t rows, int64_t bcol, double reuse) {
     const int64_t es = dtype == TF_F64 ? 8 : 4;
     D1Layout l;
     l.rows = rows;
     l.sw = (int32_t)bcol;
-    if (bcol * es % kGatherSliceBytes) return l;
+    if (bcol * es % kGatherSliceBytes || !line_slices_pay(bcol * es, bcol * es, reuse)) return l;
     int64_t k = bcol * es / kGatherSliceBytes;
     while (k > kXcds && k % 2 == 0) k /= 2;
     if (k > kXcds) return l;
@@ -446,6 +458,8 @@ struct Schedule {
     ChainPack chain;               // all rows re-packed for the one-pass chain; no blocks: not used
     // The chain as Y = A B, D = Y C (see choose_gather_first).
     bool gather_first = false;
+    double reuse = 1.0;                    // (rows that reach far) share of entries of A whose column is among those of
+                                           // as many other entries as an L2 holds cache lines
     bool gather_first_shares = false;      // Y is gathered with `all`, else with `gf`
     RowPack gf;
     std::vector<uint32_t> gf_info;         // info word per row of Y: its row of D, or zeros

@@ -455,7 +455,7 @@ def near_and_far(n, per_row, dtype, seed):
                   np.clip(cols, 0, n - 1).astype(np.int32).ravel(), np.ones(n * per_row, dtype))
 
 
-@pytest.mark.parametrize("n,ccol", [(1000000, 17), (500000, 36)])
+@pytest.mark.parametrize("n,ccol", [(1000000, 17), (800000, 23)])
 def test_rows_of_the_plain_pair_take_80_megabytes_at_most(n, ccol):
     """As they are laid out: rows of a workspace may be padded to whole cache lines."""
     s = plan_schedule(near_and_far(n, 10, np.float32, 1), n, ccol, True)
@@ -463,3 +463,26 @@ def test_rows_of_the_plain_pair_take_80_megabytes_at_most(n, ccol):
     assert s["d1_slices"] * s["d1_slice_cols"] > ccol and n * ccol * 4 < 80e6
     assert n * s["d1_slices"] * s["d1_slice_cols"] * 4 > 80e6
     assert s["execution"] == tf.TF_EXECUTE_WAVEFRONTS
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("sparse", [False, True])
+@pytest.mark.parametrize("ccol", [36, 90, 128])
+def test_workspace_is_cut_into_lines_where_columns_are_named_again(dtype, sparse, ccol):
+    """Far rows of equal length: half of the entries in 3000 columns, slices of one line; columns all alike, and more
+    than the caches hold, whole rows unless slices move no more bytes."""
+    n, per_row = 600000, 4
+    rng = np.random.default_rng(9)
+    lay = {}
+    for hot in (False, True):
+        cols = rng.integers(0, n, (n, per_row))
+        if hot:
+            cols[:, :per_row // 2] = rng.permutation(n)[:3000][rng.integers(0, 3000, (n, per_row // 2))]
+        A = ti.Csr(n, n, np.arange(0, n * per_row + 1, per_row, dtype=np.int32), cols.astype(np.int32).ravel(),
+                   np.ones(n * per_row, dtype))
+        s = plan_schedule(A, n if sparse else 96, ccol, sparse)
+        assert s["far_rows"]
+        lay[hot] = (s["d1_slices"], s["d1_slice_cols"])
+    line = 128 // np.dtype(dtype).itemsize
+    assert lay[True] == (-(-ccol // line), line)
+    assert lay[False] == (1, ccol)
