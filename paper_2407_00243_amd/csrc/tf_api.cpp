@@ -242,6 +242,7 @@ tf::PackedSpmmLaunch packed_args(const tf_plan *p, const tf_plan::PackBufs &b, W
     w.n_cut_blocks = b.n_cut_blocks;
     w.n_cu = p->n_cu;
     w.contiguous = b.sorted ? 0 : 1;
+    w.few_waves = p->s.reuse < 0.5 ? 1 : 0;
     // operand offsets inside a slice are formed in 32 bits unless the slice spans 4 GiB or more
     w.wide = (double)lay.slice_stride() * tf::elem_size(p->dtype) >= 4294967296.0 ? 1 : 0;
     w.pack = b.dev();

@@ -532,7 +532,12 @@ __global__ __launch_bounds__(kSpmmThreads, 4) void k_csr_spmm(
 }
 
 template <typename T, int VV, int G, bool WIDE> int run_packed(const PackedSpmmLaunch &a, hipStream_t st) {
-    static const int wg_per_cu = resident_per_cu(k_packed_spmm<T, VV, G, WIDE>, kSpmmThreads, 0, 8);
+    // Where most rows come from beyond the L2, more requests on their way than two workgroups per compute unit have only
+    // get in each other's way; where the L2 has them, they hide its latency (130 points, us, all / two: uniform columns, fp64
+    // 36 columns, 700000 rows 342 / 313, 250000 119 / 110; R-MAT graph of 2^20, fp32, 90 columns 599 / 579; never slower below
+    // half of the entries named again, up to 12 % slower at .58, 37 % at .7).
+    static const int most = resident_per_cu(k_packed_spmm<T, VV, G, WIDE>, kSpmmThreads, 0, 8);
+    const int wg_per_cu = a.few_waves ? std::min(most, 2) : most;
     const int64_t quads = ((int64_t)a.n_blocks / kGatherQuad + kXcds - 1) / kXcds * a.n_xs;        // of an XCD
     const int64_t per_xcd = std::min<int64_t>(quads, std::max(1, a.n_cu / kXcds) * (int64_t)wg_per_cu);
     (void)hipGetLastError();      // an error left by an earlier, unrelated call is not this launch's

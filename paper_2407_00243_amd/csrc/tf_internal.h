@@ -553,6 +553,7 @@ struct PackedSpmmLaunch {
     int32_t ccol;
     int32_t contiguous;               // 1: neighbouring blocks share an XCD; 0: round robin
     int32_t read_next;                // 1: the next launch reads Y
+    int32_t few_waves;                // 1: most rows of X come from beyond the L2
     int32_t dtype;
     void *partial;                    // sums of the pieces of cut rows: [piece][slice][sw]
     uint32_t *arrived;                // pieces of a cut row that are done: [cut row][slice][column block], zeros between launches
