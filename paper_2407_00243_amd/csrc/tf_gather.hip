@@ -331,14 +331,16 @@ __global__ __launch_bounds__(kSpmmThreads, gather_waves(dtype_of<T>())) void k_p
 // gathers of the next block go out before a block's rows are stored.  Every XCD takes n_xs eighths of the rows, of
 // at most two column slices of X.  The time of a block is that of its longest row; which wave takes which, CsrWalk.  Bound as k_packed_spmm: 2^20 rows
 // of eight random columns, fp32, 32 columns, 182 us, 5.8 TB/s of gathered lines (184 us when workgroups staged
-// entries behind barriers); 3000 rows of 49, 100 columns, both operations 13.8 us (44.4).
+// entries behind barriers); 3000 rows of 49, 100 columns, both operations 13.8 us (44.4).  Rows of one or two lanes are
+// fetched for by all lanes alike, eight entries a pass as the others (four, to have registers for 64 extents a lane: 30000
+// rows of a graph, fp32, 6 columns, both operations 382 us, now 321; the extents come from the rows' lanes once a block).
 template <typename T, int VV, int G, bool WIDE>
-__global__ __launch_bounds__(kSpmmThreads, 4) void k_csr_spmm(
+__global__ __launch_bounds__(kSpmmThreads, csr_waves(dtype_of<T>(), G)) void k_csr_spmm(
     const CsrArgs a, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
     const T *__restrict__ vals, const T *__restrict__ X0, const uint32_t *__restrict__ row_info,
     const T *__restrict__ row_scale) {
     T *const Y = static_cast<T *>(a.Y), *const D = static_cast<T *>(a.D);
-    constexpr int E = G < 4 ? 4 : kGatherEntries, NR = 64 / G, NE = NR * E > 64 ? NR * E / 64 : 1;
+    constexpr int E = kGatherEntries, NR = 64 / G, NE = NR * E > 64 ? NR * E / 64 : 1;
     typedef std::conditional_t<WIDE, uint64_t, uint32_t> Off;
     typedef T Vec16 __attribute__((ext_vector_type(Tr<T>::V)));
     typedef std::conditional_t<VV == 1, T, Vec16> X16;                          // a lane's columns of a row,
@@ -359,39 +361,26 @@ __global__ __launch_bounds__(kSpmmThreads, 4) void k_csr_spmm(
     const uint32_t my = blockIdx.x / kXcds * (kSpmmThreads / 64) + (uint32_t)wave;
     const int n_cb = (uint32_t)(a.x_sw + G * VV - 1) / (G * VV);
 
-    // of a block: the extents of the rows whose entries the lane fetches, and of the row that it sums up
+    // of a block: the extent of the row whose entries the lane fetches (where these are several rows, that of the one that
+    // it sums up), and what becomes of the row that it sums up
     struct Rows {
-        int32_t kb[NE], ke[NE], len;
+        int32_t kb, ke, len;
         uint32_t info;
         T scale;
     };
     typedef int32_t Extent __attribute__((ext_vector_type(2), aligned(4)));
     auto read_rows = [&](uint32_t u) __attribute__((always_inline)) {
         Rows b;
-        const uint32_t j = all.row(u, v);
-        uint32_t info = 0;
-#pragma unroll
-        for (int k = 0; k < NE; ++k) {
-            const uint32_t r = all.row(u, (lane % (NR * E) + 64 * k) / E);
-            const Extent x = *reinterpret_cast<const Extent *>(rowptr + r);
-            b.kb[k] = x[0];
-            b.ke[k] = x[1];
-            if (row_info) {
-                info = row_info[r];
-                if (info & kInfoSkip) b.ke[k] = b.kb[k];
-            }
-        }
-        if constexpr (NE == 1) {
+        const uint32_t j = all.row(u, v), r = NE > 1 ? j : all.row(u, lane % (NR * E) / E);
+        const Extent x = *reinterpret_cast<const Extent *>(rowptr + r);
+        uint32_t info = row_info ? row_info[r] : 0u;
+        b.kb = x[0];
+        b.ke = info & kInfoSkip ? x[0] : x[1];
+        b.len = b.ke - b.kb;
+        if constexpr (NE == 1 && G != E) {
             // (the lane's row is that of a lane v E; with eight lanes a row, its own)
-            b.len = b.ke[0] - b.kb[0];
-            if constexpr (G != E) {
-                b.len = __shfl(b.len, v * E, 64);
-                info = __shfl(info, v * E, 64);
-            }
-        } else {
-            const Extent x = *reinterpret_cast<const Extent *>(rowptr + j);
-            info = row_info ? row_info[j] : 0u;
-            b.len = info & kInfoSkip ? 0 : x[1] - x[0];
+            b.len = __shfl(b.len, v * E, 64);
+            info = __shfl(info, v * E, 64);
         }
         b.info = d1_info(row_info != nullptr, info);
         b.scale = row_scale ? row_scale[j] : T(0);
@@ -401,15 +390,28 @@ __global__ __launch_bounds__(kSpmmThreads, 4) void k_csr_spmm(
         }
         return b;
     };
-    int32_t ci[NE];
+    int32_t ci[NE], fb[NE], fe[NE];
     T vi[NE];
-    auto fetch = [&](const Rows &b, uint32_t s) __attribute__((always_inline)) {
+    // the block whose entries are fetched from here on
+    auto aim = [&](const Rows &b) __attribute__((always_inline)) {
 #pragma unroll
         for (int k = 0; k < NE; ++k) {
+            fb[k] = b.kb;
+            fe[k] = b.ke;
+            if constexpr (NE > 1) {
+                fb[k] = __shfl(b.kb, (lane + 64 * k) / E * G, 64);
+                fe[k] = __shfl(b.ke, (lane + 64 * k) / E * G, 64);
+            }
+        }
+    };
+    auto fetch = [&](uint32_t s0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < NE; ++k) {
+            const uint32_t s = s0 + lane % E;
             ci[k] = 0;
             vi[k] = T(0);
-            if (has_entry(b.kb[k], b.ke[k], s + lane % E)) {
-                const int at = b.kb[k] + (int)(s + lane % E);
+            if (has_entry(fb[k], fe[k], s)) {
+                const int at = fb[k] + (int)s;
                 ci[k] = colidx[at];
                 vi[k] = vals[at];
             }
@@ -496,9 +498,15 @@ __global__ __launch_bounds__(kSpmmThreads, 4) void k_csr_spmm(
             if (u.at >= end) break;
             CsrWalk un = u.next(n_waves);
             Rows d = read_rows(u.at), dn = read_rows(min(un.at, end - 1));
-            fetch(d, 0);
+            // the entries of the pass behind: the block's next, or the first of the next block
+            auto fetch_next = [&](bool more, uint32_t s, const Rows &next) __attribute__((always_inline)) {
+                if (!more) aim(next);
+                fetch(more ? s : 0);
+            };
+            aim(d);
+            fetch(0);
             put();
-            fetch(any(d.len > E) ? d : dn, any(d.len > E) ? E : 0);
+            fetch_next(any(d.len > E), E, dn);
             issue(d.len);
             for (;;) {
                 const bool has_next = un.at < end;
@@ -509,17 +517,15 @@ __global__ __launch_bounds__(kSpmmThreads, 4) void k_csr_spmm(
                 consume(d.len);
                 for (uint32_t s0 = E; any(has_entry(0, d.len, s0)); s0 += E) {
                     put();
-                    const bool more = any(has_entry(0, d.len, s0 + E));
-                    fetch(more ? d : dn, more ? s0 + E : 0);
+                    fetch_next(any(has_entry(0, d.len, s0 + E)), s0 + E, dn);
                     issue(d.len - (int)s0);
                     consume(d.len - (int)s0);
                 }
                 if (has_next) {
                     put();
-                    const bool more = any(dn.len > E);
-                    fetch(more ? dn : dnn, more ? E : 0);
+                    fetch_next(any(dn.len > E), E, dnn);
                 }
-                issue(has_next ? dn.len : 0);
+                issue(has_next ? dn.len : 0);      // (none after the last)
                 finish(d, u.at);
                 if (!has_next) break;
                 d = dn;

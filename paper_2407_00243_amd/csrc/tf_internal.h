@@ -145,6 +145,8 @@ constexpr int gather_short_rows(int each, int G) {
 // Waves per SIMD that the gather kernel is held to: one more spills some 40 bytes a lane (R-MAT graphs, rows of 32 and
 // 64 fp32 columns, 30000 to 300000 rows: 3 to 20 % slower).
 constexpr int gather_waves(int dtype) { return dtype == TF_F64 ? 4 : 5; }
+// The same for rows of a caller's matrix, G lanes each: the extents and entries of 64 or 32 rows a wave take registers.
+constexpr int csr_waves(int dtype, int G) { return dtype == TF_F64 ? (G == 1 ? 2 : G == 2 ? 3 : 4) : G == 1 ? 3 : 4; }
 
 inline int elem_size(int dtype) { return dtype == TF_F64 ? 8 : 4; }
 inline int vec_elems(int dtype) { return dtype == TF_F64 ? 2 : 4; }   // elements per 16 bytes
