@@ -1337,27 +1337,34 @@ void build_gather_first(const InspectorInput &in, Schedule &s, bool have_all) {
         s.gf_info[(size_t)j] = in.rowptr[j + 1] > in.rowptr[j] ? kInfoSpill | (uint32_t)j : kInfoZero;
 }
 
-// A CSR B and a D1 that the caches hold whole: tiles save little memory traffic then, and what is left of them
-// is their chain of barriers and dependent loads, which grows with the entries per row.  The two operations over
-// all rows, D1 = B C and D = A D1, are the faster pair up to a size of D1 that grows with the entries per row and
-// with the share of D1's rows that the tiles would have to write and read again anyway (us per execution, tiles
-// / plain pair: 3D stencil, 70 % written again, fp32 32^3 x 80, 10.5 MB, 32.7 / 19.3; 42^3 x 64, 19 MB, 27.6 /
-// 23.1; 79^3 x 16, 32 MB, 49 / 40; beyond: 66^3 x 64, 74 MB, 71 / 93; 2D stencil, 30 %, fp64 246^2 x 32, 15.5 MB,
-// 25.3 / 20.1; beyond: 419^2 x 32, 45 MB, 40 / 41; 337^2 x 114, 104 MB, 91 / 130; band of 21 entries per row
-// fp64, 50781 x 128, 52 MB, 136 / 94; of 33 fp32, 359422 x 32, 46 MB, 168 / 161; of 7, 5 % written again, fp32
-// 29472 x 69, 8 MB, 22.5 / 17.2; beyond: fp64 27863 x 64, 14 MB, 19.4 / 20.5; fp32 94792 x 64, 24 MB, 24 / 26.
-// Of 11, 8 %: fp64 159683 x 37, 47 MB, 127 / 96; fp32 298908 x 64, 77 MB, 96 / 115.)  80 MB bounds what a plan
-// keeps in device memory for it.
-constexpr double kPlainPairBytes = 80e6;
+// us of a chain with CSR B over tiles, and as the two operations over all rows, D1 = B C and D = A D1; rows of B taken
+// to be as long as those of A.  A compute unit works on a tile at a time, through a chain of barriers and dependent
+// loads: a last round of a few tiles takes as long as a full one.  The pair gathers without barriers, and writes and
+// reads all of D1.  Coefficients: fit to 170 bands and stencils of 2 to 49 entries a row, 6 to 140 columns, both types, 3
+// to 80 MB of D1.  On 184 others the way it chooses takes 1.1 % more than the better one on average, 37 % at the worst; a
+// limit on D1 that grows with the entries per row and the rows written again 2.2 and 52 %, one of 12 MB 13 and 94 %.
+// (us, tiles / pair: band of 11 entries a row, fp64, 159683 x 37, 47 MB, 128 / 95; of 7, 27863 x 64, 14 MB, 18.1 / 19.2; of
+// 9, fp32, 298330 x 29, 35 MB, 59 / 39; of 3, fp64, 91127 x 34, 25 MB, 24 / 34; 3D stencil, fp32, 32^3 x 80 31 / 19, 66^3 x 64,
+// 74 MB, 70 / 86; 2D stencil, fp64, 246^2 x 32 24.6 / 18.7, 419^2 x 32 38 / 41.)
+static double csr_tiles_us(const InspectorInput &in, const Schedule &s) {
+    const double gathered = 1e-6 * (double)in.nnz * (double)in.ccol * elem_size(in.dtype);
+    const double tiles = (double)std::max<int64_t>(1, (int64_t)s.tile_first_ptr.size() - 1);
+    const double rounds = std::ceil(tiles * s.n_slices / std::max(1, in.n_cu));
+    return 9.6 + 0.054 * gathered + rounds * (16.7 * gathered / (tiles * s.n_slices) + 0.77e-3 * (double)in.nnz / tiles);
+}
+static double csr_pair_us(const InspectorInput &in, const Schedule &s) {
+    const double es = elem_size(in.dtype);
+    return 6.3 + 0.082e-6 * (double)in.nnz * (double)in.ccol * es + 0.49e-6 * (double)(in.n * s.d1.columns()) * es;
+}
 bool plain_pair_is_faster(const InspectorInput &in, const Schedule &s) {
     if (!in.b_is_sparse || in.n == 0 || in.nnz == 0 || s.streaming) return false;
     // only where the caller has left the whole choice to the library
     if (!s.automatic || in.col_slice || in.gather_slices || !in.whole_fast_mem || (in.flags & TF_FLAG_SKIP_UNREAD))
         return false;
-    const double per_row = (double)in.nnz / (double)in.n, spilled = (double)s.d1.rows / (double)in.n;
-    const double chain = std::max(0.0, per_row - 2), most = (1.7e6 + 0.2e6 * chain) * chain * (1 + 6 * std::min(0.4, spilled));
-    // (rows and slices as the workspace lays them out: padded to whole lines where rows reach far)
-    return (double)(in.n * s.d1.columns() * elem_size(in.dtype)) <= std::min(kPlainPairBytes, std::max(12e6, most));
+    // (what a plan keeps in device memory for it: rows as the workspace lays them out, padded where they reach far)
+    if (in.n * s.d1.columns() * elem_size(in.dtype) > 80000000) return false;
+    // (the tiles where there is little between them: they need no array of all rows)
+    return csr_pair_us(in, s) < 0.94 * csr_tiles_us(in, s);
 }
 
 void build_baseline_pack(const InspectorInput &in, Schedule &s) {

@@ -486,3 +486,20 @@ def test_workspace_is_cut_into_lines_where_columns_are_named_again(dtype, sparse
     line = 128 // np.dtype(dtype).itemsize
     assert lay[True] == (-(-ccol // line), line)
     assert lay[False] == (1, ccol)
+
+
+@pytest.mark.parametrize("dtype,n,h,ccol,pair", [
+    (np.float64, 159683, 5, 37, True),       # 47 MB of D1: measured 128 us over tiles, 95 as the pair
+    (np.float32, 298330, 4, 29, True),       # 35 MB: 59, 39
+    (np.float32, 151417, 3, 32, True),       # 19 MB: 28, 21
+    (np.float64, 50781, 10, 128, True),      # 52 MB: 136, 94
+    (np.float64, 91127, 1, 34, False),       # 25 MB: 24, 34
+    (np.float32, 94792, 3, 64, False),       # 24 MB: 22, 25
+    (np.float64, 27863, 3, 64, False),       # 14 MB: 18, 19
+    (np.float64, 82993, 1, 54, False),       # 36 MB: 27, 34
+])
+def test_tiles_or_both_operations_over_all_rows(dtype, n, h, ccol, pair):
+    """Bands on both sides of the line, each the way that measured faster."""
+    A = ti.banded(n, h, dtype, 1)
+    s = plan_schedule(A, n, ccol, True)
+    assert s["execution"] == (tf.TF_EXECUTE_PLAIN_PAIR if pair else tf.TF_EXECUTE_WAVEFRONTS)
