@@ -321,6 +321,7 @@ tf::CsrSpmmLaunch csr_spmm_args(const tf_plan *p, const tf_csr *B, const void *C
     f.n_rows = (int32_t)p->n;
     f.n_cu = p->n_cu;
     tf::csr_slices(p->s.far_rows, p->dtype, p->bcol, p->ccol, f.n_xs, f.x_sw);
+    f.mean_len = (int32_t)((B->nnz + p->n - 1) / std::max<int64_t>(1, p->n));
     f.x_bytes = p->bcol * p->ccol * tf::elem_size(p->dtype);
     f.S.rowptr = B->rowptr;
     f.S.colidx = B->colidx;

@@ -334,13 +334,13 @@ __global__ __launch_bounds__(kSpmmThreads, gather_waves(dtype_of<T>())) void k_p
 // entries behind barriers); 3000 rows of 49, 100 columns, both operations 13.8 us (44.4).  Rows of one or two lanes are
 // fetched for by all lanes alike, eight entries a pass as the others (four, to have registers for 64 extents a lane: 30000
 // rows of a graph, fp32, 6 columns, both operations 382 us, now 321; the extents come from the rows' lanes once a block).
-template <typename T, int VV, int G, bool WIDE>
+template <typename T, int VV, int G, int E, bool WIDE>
 __global__ __launch_bounds__(kSpmmThreads, csr_waves(dtype_of<T>(), G)) void k_csr_spmm(
     const CsrArgs a, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
     const T *__restrict__ vals, const T *__restrict__ X0, const uint32_t *__restrict__ row_info,
     const T *__restrict__ row_scale) {
     T *const Y = static_cast<T *>(a.Y), *const D = static_cast<T *>(a.D);
-    constexpr int E = kGatherEntries, NR = 64 / G, NE = NR * E > 64 ? NR * E / 64 : 1;
+    constexpr int NR = 64 / G, NE = NR * E > 64 ? NR * E / 64 : 1;
     typedef std::conditional_t<WIDE, uint64_t, uint32_t> Off;
     typedef T Vec16 __attribute__((ext_vector_type(Tr<T>::V)));
     typedef std::conditional_t<VV == 1, T, Vec16> X16;                          // a lane's columns of a row,
@@ -553,16 +553,16 @@ template <typename T, int VV, int G, bool WIDE> int run_packed(const PackedSpmmL
     return (int)hipGetLastError();
 }
 
-template <typename T, int VV, int G, bool WIDE> int run_csr(const CsrSpmmLaunch &a, hipStream_t st) {
+template <typename T, int VV, int G, int E, bool WIDE> int run_csr(const CsrSpmmLaunch &a, hipStream_t st) {
     // (all that the machine holds: two per compute unit where X is beyond the caches and rows of S have six entries and
     // more are 0 to 5 % faster for random columns, but up to 65 % slower for columns near the diagonal, 85 % with long
     // rows among them, and S is not known before the call)
-    static const int wg_per_cu = resident_per_cu(k_csr_spmm<T, VV, G, WIDE>, kSpmmThreads, 0, 8);
+    static const int wg_per_cu = resident_per_cu(k_csr_spmm<T, VV, G, E, WIDE>, kSpmmThreads, 0, 8);
     const int64_t blocks = ((int64_t)a.n_rows + 64 / G - 1) / (64 / G), items = (blocks + kXcds - 1) / kXcds * a.n_xs;
     const int64_t per_xcd = std::min<int64_t>((items + kSpmmThreads / 64 - 1) / (kSpmmThreads / 64),
                                               std::max(1, a.n_cu / kXcds) * (int64_t)wg_per_cu);
     (void)hipGetLastError();
-    k_csr_spmm<T, VV, G, WIDE><<<dim3((unsigned)(per_xcd * kXcds)), dim3(kSpmmThreads), 0, st>>>(
+    k_csr_spmm<T, VV, G, E, WIDE><<<dim3((unsigned)(per_xcd * kXcds)), dim3(kSpmmThreads), 0, st>>>(
         {a.Y, a.D, a.y_slice_stride, a.n_rows, a.n_xs, a.x_sw, a.ccol, a.y_sw_shift, a.y_sw_mask, a.y_sw, (int32_t)per_xcd}, a.S.rowptr, a.S.colidx, static_cast<const T *>(a.S.vals), static_cast<const T *>(a.X), a.row_info,
         static_cast<const T *>(a.row_scale));
     return (int)hipGetLastError();
@@ -604,7 +604,15 @@ template <typename T> int run_packed_group(const PackedSpmmLaunch &a, hipStream_
 template <typename T> int run_csr_group(const CsrSpmmLaunch &a, hipStream_t st) {
     return dispatch_group<T>(a.ccol, a.x_sw, [&](auto vv, auto g) {
         constexpr int VV = decltype(vv)::value, G = decltype(g)::value;
-        return a.x_bytes >= ((int64_t)1 << 32) ? run_csr<T, VV, G, true>(a, st) : run_csr<T, VV, G, false>(a, st);
+        // entries a pass: rows of one and two lanes, 64 and 32 in a wave, pay for passes that their entries do not fill
+        // (30000 rows of three, fp32, 8 columns, both operations: four 6.35 us, eight 6.92; longer rows: k_csr_spmm)
+        auto run = [&](auto e) {
+            constexpr int E = decltype(e)::value;
+            return a.x_bytes >= ((int64_t)1 << 32) ? run_csr<T, VV, G, E, true>(a, st) : run_csr<T, VV, G, E, false>(a, st);
+        };
+        if constexpr (G <= 2)
+            if (a.mean_len <= 4) return run(std::integral_constant<int, 4>());
+        return run(std::integral_constant<int, kGatherEntries>());
     });
 }
 

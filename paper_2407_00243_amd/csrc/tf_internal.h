@@ -581,6 +581,7 @@ struct CsrSpmmLaunch {
     const void *row_scale;
     void *D;
     int64_t x_bytes;
+    int32_t mean_len;                 // entries per row of S
     int32_t n_cu;                     // compute units of the device
 };
 
