@@ -14,7 +14,7 @@ namespace {
 // What the kernels below are given beside the arrays that they read.  Small matrices wait for the host, whose time for a launch
 // grows with the number and the bytes of its arguments; among them are 256 of the grid's sizes where a kernel asks for these, so the
 // workgroups per XCD are handed over (the pair of launches, arguments of 504 and 440 bytes, 20 in all: 7.7 us of the host's
-// time per call in some processes, 9.4 in others; 128 and 104, 14 in all: 7.5 and 8.7).
+// time per call in some processes, 9.4 in others; 128 and 104, 15 in all: 7.5 and 8.7, and as `launch` does it now: below).
 struct PackedArgs {
     void *Y, *partial;
     uint32_t *arrived;
@@ -537,6 +537,15 @@ __global__ __launch_bounds__(kSpmmThreads, csr_waves(dtype_of<T>(), G)) void k_c
     } while (left > 0);
 }
 
+// A launch that returns its own status, in one call of the runtime; in chevrons, with the last error asked for before and after
+// it, it is five (host time of a pair of launches of small matrices, 3 processes each, us: 9.0, 9.1, 9.0; now 8.4, 7.2, 7.2).
+template <typename... P> int launch(void (*kernel)(P...), int64_t n_wg, hipStream_t st, std::decay_t<P>... args) {
+    void *at[] = {const_cast<void *>(static_cast<const void *>(&args))...};
+    const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(kernel), dim3((unsigned)n_wg), dim3(kSpmmThreads), at, 0, st);
+    if (e != hipSuccess) (void)hipGetLastError();      // (reported here, not by a later call)
+    return (int)e;
+}
+
 template <typename T, int VV, int G, bool WIDE> int run_packed(const PackedSpmmLaunch &a, hipStream_t st) {
     // Where most rows come from beyond the L2, more requests on their way than two workgroups per compute unit have only
     // get in each other's way; where the L2 has them, they hide its latency (130 points, us, all / two: uniform columns, fp64
@@ -546,11 +555,22 @@ template <typename T, int VV, int G, bool WIDE> int run_packed(const PackedSpmmL
     const int wg_per_cu = a.few_waves ? std::min(most, 2) : most;
     const int64_t quads = ((int64_t)a.n_blocks / kGatherQuad + kXcds - 1) / kXcds * a.n_xs;        // of an XCD
     const int64_t per_xcd = std::min<int64_t>(quads, std::max(1, a.n_cu / kXcds) * (int64_t)wg_per_cu);
-    (void)hipGetLastError();      // an error left by an earlier, unrelated call is not this launch's
-    k_packed_spmm<T, VV, G, WIDE><<<dim3((unsigned)(per_xcd * kXcds)), dim3(kSpmmThreads), 0, st>>>(
-        {a.Y, a.partial, a.arrived, a.x_slice_stride, a.n_xs, a.sw, a.ldx, a.n_blocks, a.n_cut_blocks, a.ccol, a.contiguous, a.read_next, (int32_t)per_xcd}, a.pack.blocks, a.pack.rows, a.pack.lens, a.pack.idx, static_cast<const T *>(a.pack.vals), a.pack.cuts,
-        static_cast<const T *>(a.X));
-    return (int)hipGetLastError();
+    PackedArgs k;
+    k.Y = a.Y;
+    k.partial = a.partial;
+    k.arrived = a.arrived;
+    k.x_slice_stride = a.x_slice_stride;
+    k.n_xs = a.n_xs;
+    k.sw = a.sw;
+    k.ldx = a.ldx;
+    k.n_blocks = a.n_blocks;
+    k.n_cut_blocks = a.n_cut_blocks;
+    k.ccol = a.ccol;
+    k.contiguous = a.contiguous;
+    k.read_next = a.read_next;
+    k.n_wg = (int32_t)per_xcd;
+    return launch(k_packed_spmm<T, VV, G, WIDE>, per_xcd * kXcds, st, k, a.pack.blocks, a.pack.rows, a.pack.lens, a.pack.idx,
+                  static_cast<const T *>(a.pack.vals), a.pack.cuts, static_cast<const T *>(a.X));
 }
 
 template <typename T, int VV, int G, int E, bool WIDE> int run_csr(const CsrSpmmLaunch &a, hipStream_t st) {
@@ -561,11 +581,21 @@ template <typename T, int VV, int G, int E, bool WIDE> int run_csr(const CsrSpmm
     const int64_t blocks = ((int64_t)a.n_rows + 64 / G - 1) / (64 / G), items = (blocks + kXcds - 1) / kXcds * a.n_xs;
     const int64_t per_xcd = std::min<int64_t>((items + kSpmmThreads / 64 - 1) / (kSpmmThreads / 64),
                                               std::max(1, a.n_cu / kXcds) * (int64_t)wg_per_cu);
-    (void)hipGetLastError();
-    k_csr_spmm<T, VV, G, E, WIDE><<<dim3((unsigned)(per_xcd * kXcds)), dim3(kSpmmThreads), 0, st>>>(
-        {a.Y, a.D, a.y_slice_stride, a.n_rows, a.n_xs, a.x_sw, a.ccol, a.y_sw_shift, a.y_sw_mask, a.y_sw, (int32_t)per_xcd}, a.S.rowptr, a.S.colidx, static_cast<const T *>(a.S.vals), static_cast<const T *>(a.X), a.row_info,
-        static_cast<const T *>(a.row_scale));
-    return (int)hipGetLastError();
+    CsrArgs k;
+    k.Y = a.Y;
+    k.D = a.D;
+    k.y_slice_stride = a.y_slice_stride;
+    k.n_rows = a.n_rows;
+    k.n_xs = a.n_xs;
+    k.x_sw = a.x_sw;
+    k.ccol = a.ccol;
+    k.y_sw_shift = a.y_sw_shift;
+    k.y_sw_mask = a.y_sw_mask;
+    k.y_sw = a.y_sw;
+    k.n_wg = (int32_t)per_xcd;
+    return launch(k_csr_spmm<T, VV, G, E, WIDE>, per_xcd * kXcds, st, k, a.S.rowptr, a.S.colidx,
+                  static_cast<const T *>(a.S.vals), static_cast<const T *>(a.X), a.row_info,
+                  static_cast<const T *>(a.row_scale));
 }
 
 // Calls f(VV, G) with compile-time constants: columns and lanes of rows in column slices of sw of the ccol columns.
