@@ -317,3 +317,71 @@ def test_unfused_calls_beside_the_plain_pair(dtype):
                 assert np.array_equal(d.cpu().numpy().astype(np.float64), D_ref)
     finally:
         c.close()
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("ccol,most", [(1, 6), (3, 13), (4, 6), (4, 13), (8, 6), (41, 9), (64, 9), (96, 9), (300, 9)])
+def test_lanes_past_a_row_of_b_add_nothing(dtype, ccol, most):
+    """CSR B, rows of no entry to thousands beside each other, C in one slice and in several: lanes without an entry
+    gather row 0 of C, which is NaN here and named by nobody; where C holds infinities, a row of D is infinite if it
+    reads one of them through B, and its finite sum if not."""
+    from gpu_util import Case
+    n = 30011
+    rng = np.random.default_rng(17)
+    A = _hubs(n, dtype, rng, lambda k: rng.integers(1, 3, k))
+    lens = rng.integers(0, most, n)
+    lens[rng.permutation(n)[:16]] = [7, 8, 9, 15, 16, 17, 63, 64, 65, 127, 300, 511, 512, 513, 1500, 3000]
+    lens[[0, n - 1]] = 257, 258
+    rowptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    colidx = rng.integers(1, n, rowptr[-1]).astype(np.int32)
+    B = ti.Csr(n, n, rowptr, colidx, rng.integers(1, 3, colidx.size).astype(dtype))
+    C = rng.integers(1, 4, (n, ccol)).astype(dtype)
+    hit = rng.random(n) < 0.002
+    D_ref, _ = oracle.chain(A, B, np.where(hit[:, None], dtype(0), C))
+    rows_of = lambda M, named: np.unique(np.repeat(np.arange(n), np.diff(M.rowptr))[named[M.colidx]])
+    hit_d1 = np.zeros(n, bool)
+    hit_d1[rows_of(B, hit)] = True
+    D_ref[rows_of(A, hit_d1)] = np.inf
+    C[hit] = np.inf
+    C[0] = np.nan
+    c = Case(ti.Problem("past", "spmm_spmm", np.dtype(dtype), A, B, C))
+    try:
+        assert np.isinf(D_ref).any() and np.isfinite(D_ref).any()
+        for fused in (True, False):
+            assert np.array_equal(c.run(fused).astype(np.float64), D_ref)
+    finally:
+        c.close()
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+def test_static_calls_with_cut_rows_slices_and_padding(dtype):
+    """The library's own workspace behind plans with rows cut over workgroups: three and more slices, rows padded to
+    a line, and Y = A B over slices of B; one after the other, so that each finds what another plan left there."""
+    import torch
+    import paper_2407_00243_amd as tf
+    from gpu_util import Case
+    es = np.dtype(dtype).itemsize
+    rng = np.random.default_rng(18)
+    cases = []
+    try:
+        for bcol, ccol, execution in ((128, 288 // es, tf.TF_EXECUTE_WAVEFRONTS), (128, 164 // es, tf.TF_EXECUTE_WAVEFRONTS),
+                                      (128, 92 // es, tf.TF_EXECUTE_WAVEFRONTS), (256 // es, 512 // es, tf.TF_EXECUTE_GATHER_FIRST)):
+            n = max(60013, 14000000 // (ccol * es))         # (rows that reach beyond an L2)
+            A = _hubs(n, dtype, rng, lambda k: rng.integers(-2, 3, k))
+            B, C = ti.dense_small_int(n, bcol, dtype, 5), ti.dense_small_int(bcol, ccol, dtype, 6)
+            c = Case(ti.Problem("static", "gemm_spmm", np.dtype(dtype), A, B, C))
+            cases.append((c, oracle.chain(A, B, C)[0]))
+            s = c.plan.schedule()
+            assert s["far_rows"] and s["execution"] == execution
+            if execution == tf.TF_EXECUTE_WAVEFRONTS:
+                assert s["d1_slices"] * s["d1_slice_cols"] > ccol
+        stream = torch.cuda.current_stream().cuda_stream
+        for _ in range(2):
+            for c, D_ref in cases:
+                D = torch.full(D_ref.shape, float("nan"), dtype=c.tdtype, device="cuda")
+                tf.tf_gemm_spmm_static(c.plan.handle, c.B, c.C, D, stream)
+                torch.cuda.synchronize()
+                assert np.array_equal(D.cpu().numpy().astype(np.float64), D_ref)
+    finally:
+        for c, _ in cases:
+            c.close()
