@@ -4,9 +4,9 @@
 // into the tile that produces the same row range exactly when every column index of that row
 // of A lies inside the range.  Step 2 halves every tile whose fast-memory footprint exceeds
 // the budget.  The GPU additions are the spill set (D1 rows that a second-wavefront row
-// reads and that therefore must also reach device memory) and the work-balanced units of the
-// second wavefront (the `balance` routine of Algorithm 1, read as: spread the leftover rows
-// over units of about equal work; rows too long for one unit get a workgroup of their own).
+// reads and that therefore must also reach device memory) and the packed blocks of the second
+// wavefront (the `balance` routine of Algorithm 1, read as: spread the leftover rows over waves, a
+// block at a time; rows too long for a block are cut over a workgroup's four or several times that).
 //
 // Pure host code: no HIP calls.
 #include <algorithm>
@@ -1120,7 +1120,7 @@ tf_status build_schedule(const InspectorInput &in, Schedule &s, std::string &err
     }
 
     TF_TICK("tile blocks, row arrays");
-    // ---- balance: units of the second wavefront --------------------------------------------
+    // ---- balance: blocks of the second wavefront -------------------------------------------
     int64_t wf1_nnz = 0;
     for (int32_t j : wf1) wf1_nnz += in.rowptr[j + 1] - in.rowptr[j];
     auto slot_of = [&](int32_t c) { return s.spill_slot[(size_t)c]; };
@@ -1173,9 +1173,10 @@ static double one_pass_us(const InspectorInput &in, double entries, double far =
 // and what the wave with the most passes of gathers takes longer than it would with blocks of mean length.  A
 // pass waits for its gathers, 0.8 us (band of 20011 rows, eight of them of 400 and of 1024 entries, uncut: fp32
 // 32 columns 48 and 116 us, 64 columns 66 and 165, fp64 128 columns 135 and 374: 0.87, 0.79 and 0.77 us a
-// pass).  Blocks are dealt to the waves of an XCD as k_gather_gemm takes them.  That some waves have a block
-// more than others is no matter of row lengths, and in the fits of one_pass_us already (band of 50000 rows of
-// 41, fp64 100 -> 100, where it was charged here too: 169 us in two wavefronts, 121 in one pass).
+// pass).  Blocks are dealt to the waves of an XCD as k_gather_gemm takes them in whole rounds; that a short last
+// round of wide rows is spread over the workgroups there is left out.  That some waves have a block more than
+// others is no matter of row lengths, and in the fits of one_pass_us already (band of 50000 rows of 41, fp64 100 ->
+// 100, where it was charged here too: 169 us in two wavefronts, 121 in one pass).
 static double one_pass_tail_us(const InspectorInput &in, const ChainPack &c, int ks, int64_t per_block) {
     const int em = chain_entries(ks);
     const int64_t nb = (int64_t)c.blocks.size(), per = (nb + kXcds - 1) / kXcds;

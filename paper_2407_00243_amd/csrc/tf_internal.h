@@ -299,8 +299,6 @@ struct CutBlock {
     int32_t pieces;
 };
 
-// A list of rows of A re-packed for the gather kernel.  Padding repeats the row's last column index with
-// value 0; the kernel leaves it out of the sums.
 // A vector whose resize() leaves the new elements uninitialised: the packed arrays are sized once
 // and then written in full by the host threads, which are also the first to touch their pages.
 template <typename T> struct NoInitAlloc : std::allocator<T> {
@@ -314,6 +312,8 @@ template <typename T> struct NoInitAlloc : std::allocator<T> {
 };
 template <typename T> using RawVec = std::vector<T, NoInitAlloc<T>>;
 
+// A list of rows of A re-packed for the gather kernel.  Padding repeats the row's last column index with
+// value 0; the kernel leaves it out of the sums.
 struct RowPack {
     std::vector<GatherBlock> blocks;
     std::vector<int32_t> rows;           // row ids, list order
