@@ -49,8 +49,8 @@ struct CsrArgs {
 // there are pieces, so that it is back at zero after any number of launches, whatever they ran beside.
 //
 // Bound by the fabric behind the L2 where rows reach far: R-MAT graph of 2^20 vertices, fp32, 128 columns in four
-// slices, 709 us, 5.0 GB cross the memory interface at 7.0 TB/s (units staged by a workgroup behind a barrier: 747
-// us, 6.8 TB/s); 32 columns 180 us, 6.5 TB/s (205 us).  By the chain of loads where they do not: hence a pass of eight
+// slices, 689 us, 4.8 GB cross the memory interface at 7.0 TB/s (units staged by a workgroup behind a barrier: 747
+// us, 6.8 TB/s); 32 columns 178 us, 6.5 TB/s (205 us).  By the chain of loads where they do not: hence a pass of eight
 // entries and the next one's offsets in flight at any time.
 template <typename T, int VV, int G, bool WIDE>
 __global__ __launch_bounds__(kSpmmThreads, gather_waves(dtype_of<T>())) void k_packed_spmm(
@@ -329,11 +329,12 @@ __global__ __launch_bounds__(kSpmmThreads, gather_waves(dtype_of<T>())) void k_p
 // As k_packed_spmm, for rows as they come: a wave owns 64 / G consecutive rows at a time and takes E entries of each
 // per pass.  What the passes need of the rows' extents is read two blocks ahead, entries a pass ahead, the first
 // gathers of the next block go out before a block's rows are stored.  Every XCD takes n_xs eighths of the rows, of
-// at most two column slices of X.  The time of a block is that of its longest row; which wave takes which, CsrWalk.  Bound as k_packed_spmm: 2^20 rows
-// of eight random columns, fp32, 32 columns, 182 us, 5.8 TB/s of gathered lines (184 us when workgroups staged
-// entries behind barriers); 3000 rows of 49, 100 columns, both operations 13.8 us (44.4).  Rows of one or two lanes are
-// fetched for by all lanes alike, eight entries a pass as the others (four, to have registers for 64 extents a lane: 30000
-// rows of a graph, fp32, 6 columns, both operations 382 us, now 321; the extents come from the rows' lanes once a block).
+// at most two column slices of X.  The time of a block is that of its longest row; which wave takes which, CsrWalk.
+// Bound as k_packed_spmm: 2^20 rows of eight random columns, fp32, 32 columns, 190 us, 5.7 TB/s of gathered lines (184
+// us when workgroups staged entries behind barriers, 181 with two workgroups per compute unit: run_csr); 3000 rows of
+// 49, 100 columns, both operations 13.8 us (44.4).  Rows of one or two lanes are fetched for by all lanes alike, eight
+// entries a pass as the others (four, to have registers for 64 extents a lane: 30000 rows of a graph, fp32, 6 columns,
+// both operations 382 us, now 321; the extents come from the rows' lanes once a block).
 template <typename T, int VV, int G, int E, bool WIDE>
 __global__ __launch_bounds__(kSpmmThreads, csr_waves(dtype_of<T>(), G)) void k_csr_spmm(
     const CsrArgs a, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
