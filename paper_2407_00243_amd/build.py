@@ -10,7 +10,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libtilefusion.so")
-SOURCES = ["tf_kernels.hip", "tf_chain.hip", "tf_gather.hip", "tf_inspector.cpp", "tf_api.cpp"]
+SOURCES = ["tf_kernels.hip", "tf_gemm.hip", "tf_chain.hip", "tf_gather.hip", "tf_inspector.cpp", "tf_api.cpp"]
 HEADERS = ["tf_internal.h", "tf_device.h", os.path.join("..", "..", "include", "tilefusion.h")]
 
 # packed-fp32 instructions are switched off for all device code

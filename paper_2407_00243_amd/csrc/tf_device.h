@@ -84,6 +84,77 @@ template <typename T, int N> __device__ __forceinline__ void store_any(T *p, con
     }
 }
 
+// fp32 products on the bf16 matrix cores (16 times the rate of the fp32 ones, and unlike these they run beside other vector
+// instructions of their SIMD).  x = h + m + l, each rounded to nearest even: 24 bits in three times eight, nothing is lost.
+// A product of two such sums is taken without m l, l m and l l, which lie below 2^-26 of it; all six others are exact, and
+// their sums are rounded once per 32 of them, the small ones before h h: against 64 bits the sums are closer than those of
+// the fp32 instructions, which round at every product (normal operands, relative error of 8192 x 16 sums of 8 / 16 / 32 / 64 /
+// 128 products: 3.4e-8 / 3.6e-8 / 3.8e-8 / 9.2e-8 / 1.5e-7, fp32 instructions 5.3e-8 / 7.3e-8 / 1.1e-7 / 1.4e-7 / 2.1e-7; all nine
+// products: the same).
+typedef __bf16 Bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 Bf16x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t Word4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
+    return __builtin_bit_cast(uint32_t, Bf16x2{(__bf16)a, (__bf16)b});
+}
+// x[0], x[1] -> words `at` of the three parts
+__device__ __forceinline__ void split_pair(Word4 (&part)[3], int at, float a, float b) {
+    const uint32_t h = bf16_pair(a, b);
+    a -= __uint_as_float(h << 16);
+    b -= __uint_as_float(h & 0xffff0000u);
+    const uint32_t m = bf16_pair(a, b);
+    a -= __uint_as_float(m << 16);
+    b -= __uint_as_float(m & 0xffff0000u);
+    part[0][at] = h;
+    part[1][at] = m;
+    part[2][at] = bf16_pair(a, b);
+}
+// D(16x16) += A(16x32) B(32x16), one wave: lane l supplies A[l % 16][8 (l / 16) + q] and B[8 (l / 16) + q][l % 16], q < 8;
+// results as for fp32 above.
+__device__ __forceinline__ floatx4 mfma16_bf16(const Word4 &a, const Word4 &b, floatx4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(Bf16x8, a), __builtin_bit_cast(Bf16x8, b), c, 0, 0, 0);
+}
+// The bf16 matrix cores take numbers below 2^-126 for zeros, and so would parts of small numbers be, or sums of their
+// products; infinities would meet zeros of the other operand's parts.  So a row of the first operand and a column of the
+// second are multiplied this way only if their largest element is 0 or lies within these bounds: what is flushed is then below
+// 2^-36 of the largest product, for 128 of them, and no sum reaches 2^127.
+constexpr float kSplitRowMin = 0x1p-64f, kSplitColMin = 0x1p-30f, kSplitMax = 0x1p60f;
+__device__ __forceinline__ bool split_exceeds(float largest, float least) {
+    return !(largest < kSplitMax) || (largest < least && largest != 0.0f);
+}
+
+// Stores the four columns a lane holds of accumulator block nb to `dst` (which points at the
+// lane's first column, 16 nb + 4 g), keeping to columns below w: 16-byte pieces, at whatever element
+// they begin, and the columns of a block that w cuts one by one.
+template <typename T>
+__device__ __forceinline__ void store_acc4(T *dst, const typename Tr<T>::Acc &a, int nb, int g, int w) {
+    constexpr int V = Tr<T>::V;
+    if (16 * nb + 16 <= w) {
+#pragma unroll
+        for (int h = 0; h < 4 / V; ++h) {
+            T tmp[V];
+#pragma unroll
+            for (int i = 0; i < V; ++i) tmp[i] = a[V * h + i];
+            store_any<T, V>(dst + V * h, tmp);
+        }
+    } else {
+#pragma unroll
+        for (int h = 0; h < 4 / V; ++h) {
+            const int col = 16 * nb + 4 * g + V * h;
+            if (col + V <= w) {
+                T tmp[V];
+#pragma unroll
+                for (int i = 0; i < V; ++i) tmp[i] = a[V * h + i];
+                store_any<T, V>(dst + V * h, tmp);
+            } else {
+#pragma unroll
+                for (int i = 0; i + 1 < V; ++i)
+                    if (col + i < w) dst[V * h + i] = a[V * h + i];
+            }
+        }
+    }
+}
+
 __device__ __forceinline__ int pow2_at_least(int x) {
     int g = 1;
     while (g < x) g <<= 1;

@@ -1,0 +1,353 @@
+// D1 = B C in fp32 for rows of B of up to 128 columns, on the bf16 matrix cores.  Other products: k_gemm in tf_kernels.hip.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <type_traits>
+
+#include "tf_device.h"
+
+namespace tf {
+namespace {
+
+// A wave multiplies blocks of 32 rows of B (two blocks of sixteen, so that what is read of C from LDS is used twice: its
+// reads then take half of what the LDS delivers).  C sits in LDS in three parts (split_pair), in operand order: per step of
+// 32 k, per block of sixteen columns, per part sixteen bytes for each lane.  Rows of B are split as their step comes, and the
+// same step of the wave's next block is fetched into the registers that this frees: a block's loads are on their way for as
+// long as a block is multiplied, ahead of its stores, which they do not wait for.
+//
+// Lane group g = lane / 16 holds of step s the elements k = 32 s + 4 g + {0 .. 3} and 32 s + 16 + 4 g + {0 .. 3} of its rows
+// (four lanes fetch 64 contiguous bytes); pieces of the last step that would reach past the row are moved back so that they
+// end with it and put right when they have arrived.
+//
+// A block with a row outside the bounds of the split (infinities, numbers that are all below 2^-64), or any block if a column
+// of C is, is multiplied again by the fp32 instructions (slow_block), which read both operands from memory.
+//
+// Bound by memory.  us, on the fp32 matrix cores / here, and bytes moved: n = 2^20, 128 -> 128, with info words 300 / 218, 4.9
+// TB/s, which is what a copy reaches; n = 150000, 128 -> 41, 36 / 31, 3.7 TB/s; n = 131072, 64 -> 128, 38 / 29.5, 3.4 TB/s.  Of
+// these, lines of D1 and D written whole and not in halves by two instructions: 244 / 231, 31 / 30, 32 / 29.5.  B passes
+// through the L2 without staying there (and D rows that leave here): what the gather that follows reads does stay (128 ->
+// 128: 231 / 218, its gather 700 / 692; 128 -> 41: 30 / 32, 55 / 45; 64 -> 128: the next execution's gather 52 / 47).
+constexpr int kRowRor8 = 0x128;      // DPP: rotate sixteen lanes by eight
+__device__ __forceinline__ uint32_t other_half(uint32_t x) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, kRowRor8, 0xf, 0xf, false); }
+
+template <int KD, int NB>
+__global__ __launch_bounds__(kFusedThreads) void k_gemm_split(const GemmLaunch a) {
+    typedef typename Piece16<float>::Vec Vec;
+    const int slice = blockIdx.y;
+    const int c0 = slice * a.cs;
+    const int w = min(a.cs, a.ccol - c0), w_d1 = c0 + w < a.ccol ? w : a.d1_cols - c0;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
+    const int g = lane >> 4, r = lane & 15;
+    Word4 *Cl = reinterpret_cast<Word4 *>(tf_smem);
+    uint32_t *cmax = reinterpret_cast<uint32_t *>(tf_smem + KD * NB * 3 * 1024);
+    const float *__restrict__ B = static_cast<const float *>(a.B), *__restrict__ C = static_cast<const float *>(a.C);
+    float *__restrict__ D1 = static_cast<float *>(a.D1), *__restrict__ D = static_cast<float *>(a.D);
+    const uint32_t n = (uint32_t)a.n, nblk = (n + 31) >> 5;
+    // contiguous range of row blocks per workgroup, waves interleaved inside it
+    const uint32_t lb0 = (uint64_t)nblk * blockIdx.x / gridDim.x, lb1 = (uint64_t)nblk * (blockIdx.x + 1) / gridDim.x;
+
+    // the last step's pieces: where they begin, as far as they are in the row
+    int last[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) last[h] = min(32 * (KD - 1) + 16 * h + 4 * g, a.bcol - 4);
+    Vec x[KD][2][2];
+    auto row_of = [&](uint32_t lb, int i) __attribute__((always_inline)) { return min(lb * 32 + 16 * i + r, n - 1); };
+    auto row_at = [&](uint32_t lb, int i) __attribute__((always_inline)) { return B + (uint64_t)row_of(lb, i) * (uint32_t)a.bcol; };
+    auto load_step = [&](int s, const float *const(&brow)[2]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                x[s][i][h] = __builtin_nontemporal_load(
+                    reinterpret_cast<const Vec *>(brow[i] + (s < KD - 1 ? 32 * s + 16 * h + 4 * g : last[h])));
+    };
+
+    // C: the first pieces of it are on their way before the first rows of B, and split while these are
+    constexpr int NC = (KD * NB * 64 + kFusedThreads - 1) / kFusedThreads;
+    float y[NC][8];
+    auto load_c = [&](int e0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < NC; ++u) {
+            const int e = e0 + u * (int)blockDim.x, l = e & 63, nb = (e >> 6) % NB, s = (e >> 6) / NB;
+            const int col = 16 * nb + (l & 15), k = 32 * s + 4 * (l >> 4);
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const int kq = k + (q < 4 ? q : 12 + q);
+                const bool in = kq < a.bcol && col < w && e < KD * NB * 64;
+                y[u][q] = C[in ? (int64_t)kq * a.c_ldk + (int64_t)(c0 + col) * a.c_ldc : 0];
+                if (!in) y[u][q] = 0.0f;
+            }
+        }
+    };
+    auto put_c = [&](int e0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < NC; ++u) {
+            const int e = e0 + u * (int)blockDim.x, l = e & 63, nb = (e >> 6) % NB;
+            if (e >= KD * NB * 64) break;
+            uint32_t most = 0;      // (bits: a NaN counts as more than infinity)
+            Word4 part[3];
+#pragma unroll
+            for (int q = 0; q < 8; q += 2) {
+                most = max(most, max(__float_as_uint(y[u][q]) & 0x7fffffffu, __float_as_uint(y[u][q + 1]) & 0x7fffffffu));
+                split_pair(part, q / 2, y[u][q], y[u][q + 1]);
+            }
+            atomicMax(&cmax[16 * nb + (l & 15)], most);
+#pragma unroll
+            for (int p = 0; p < 3; ++p) Cl[((e >> 6) * 3 + p) * 64 + l] = part[p];
+        }
+    };
+    load_c(threadIdx.x);
+    uint32_t lb = lb0 + wave;
+    {
+        const float *brow[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) brow[i] = row_at(lb, i);
+#pragma unroll
+        for (int s = 0; s < KD; ++s) load_step(s, brow);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    for (int i = threadIdx.x; i < NB * 16; i += blockDim.x) cmax[i] = 0;
+    __syncthreads();
+    put_c(threadIdx.x);
+    for (int e0 = (int)threadIdx.x + NC * (int)blockDim.x; e0 < KD * NB * 64; e0 += NC * (int)blockDim.x) {
+        load_c(e0);
+        put_c(e0);
+    }
+    __syncthreads();
+    bool c_bad = false;
+#pragma unroll
+    for (int c = 0; c < NB * 16; c += 64)
+        if (c + lane < NB * 16) c_bad |= split_exceeds(__uint_as_float(cmax[c + lane]), kSplitColMin);
+    c_bad = __builtin_amdgcn_ballot_w64(c_bad) != 0;
+
+    floatx4 acc[2][NB];
+    auto slow_block = [&](uint32_t at) __attribute__((always_inline)) {
+        int ws = w;      // (or the tests for every block of columns are made, and kept, outside of the loop)
+        asm volatile("" : "+s"(ws));
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const float *brow = row_at(at, i);
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) acc[i][nb] = floatx4{0, 0, 0, 0};
+#pragma unroll 1
+            for (int kq = 0; kq < KD * 32; ++kq) {
+                const int k = kq / 4 * 16 + 4 * g + kq % 4;
+                if (kq / 4 * 16 >= a.bcol) break;
+                const float b = k < a.bcol ? brow[k] : 0.0f;
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) {
+                    const bool in = k < a.bcol && 16 * nb + r < ws;
+                    const float c = C[in ? (int64_t)k * a.c_ldk + (int64_t)(c0 + 16 * nb + r) * a.c_ldc : 0];
+                    acc[i][nb] = mfma16(in ? c : 0.0f, b, acc[i][nb]);
+                }
+            }
+        }
+    };
+
+    for (; lb < lb1; lb += nwaves) {
+        // (the reads of C stay in the loop: in registers they would not fit)
+        if constexpr (KD * NB * 12 > 48) asm volatile("" ::: "memory");
+        // (without info words any words are read: a load behind a branch is waited for there)
+        const uint32_t *infos = a.row_info ? a.row_info : static_cast<const uint32_t *>(a.B);
+        const float *scales = a.row_scale ? static_cast<const float *>(a.row_scale) : B;
+        uint32_t info[2];
+        float scale[2], most[2] = {0.0f, 0.0f};
+        const float *brow[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            info[i] = infos[row_of(lb, i)];
+            scale[i] = scales[row_of(lb, i)];
+            brow[i] = row_at(lb + nwaves, i);
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) acc[i][nb] = floatx4{0, 0, 0, 0};
+#pragma unroll
+        for (int s = 0; s < KD; ++s) {
+            if (s == KD - 1 && a.bcol != 32 * KD) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int back = 32 * s + 16 * h + 4 * g - last[h];
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        Vec t;
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            t[q] = 0.0f;
+#pragma unroll
+                            for (int j = q; j < 4; ++j)
+                                if (back == j - q) t[q] = x[s][i][h][j];
+                        }
+                        x[s][i][h] = t;
+                    }
+                }
+            }
+            Word4 part[2][3];
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int q = 0; q < 4; q += 2) {
+                        most[i] = fmaxf(fmaxf(most[i], fabsf(x[s][i][h][q])), fabsf(x[s][i][h][q + 1]));
+                        split_pair(part[i], 2 * h + q / 2, x[s][i][h][q], x[s][i][h][q + 1]);
+                    }
+            // (the next block's loads after the split, whose registers they take, and ahead of the multiplications)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                asm volatile("" : "+v"(most[i]));
+#pragma unroll
+                for (int p = 0; p < 3; ++p) asm volatile("" : "+v"(part[i][p]));
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            load_step(s, brow);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) {
+                const Word4 *c = Cl + (s * NB + nb) * 3 * 64 + lane;
+                const Word4 ch = c[0], cm = c[64], cl = c[128];
+#define TF_MFMA(CP, BP)                                                                \
+    acc[0][nb] = mfma16_bf16(CP, part[0][BP], acc[0][nb]);                             \
+    acc[1][nb] = mfma16_bf16(CP, part[1][BP], acc[1][nb])
+                TF_MFMA(cl, 0);
+                TF_MFMA(ch, 2);
+                TF_MFMA(cm, 1);
+                TF_MFMA(cm, 0);
+                TF_MFMA(ch, 1);
+                TF_MFMA(ch, 0);
+#undef TF_MFMA
+            }
+        }
+        bool bad = c_bad;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            asm volatile("" : "+v"(info[i]), "+v"(scale[i]));      // (here, not where they are fetched)
+            float m = fmaxf(most[i], __shfl_xor(most[i], 16, 64));
+            m = fmaxf(m, __shfl_xor(m, 32, 64));
+            // (rows that are not stored may hold anything)
+            const bool used = !a.row_info || (info[i] & (kInfoSpill | kInfoDirect));
+            bad |= used && split_exceeds(m, kSplitRowMin);
+        }
+        if (__builtin_amdgcn_ballot_w64(bad)) slow_block(lb);
+        // Two blocks of columns leave together, eight rows at a time, so that an instruction writes whole lines of 128 bytes: a
+        // lane changes places with the one eight rows on.
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const uint32_t row0 = lb * 32 + 16 * i;
+            const uint32_t ri = row0 + r < n ? d1_info(a.row_info != nullptr, info[i]) : 0u, rx = other_half(ri);
+            const float scale_x = __uint_as_float(other_half(__float_as_uint(scale[i])));
+            // (to_d1: rows of the workspace, else of D)
+            auto store = [&](auto to_d1) __attribute__((always_inline)) {
+                constexpr bool TO_D1 = decltype(to_d1)::value;
+                constexpr uint32_t kinds = TO_D1 ? kInfoSpill : kInfoDirect | kInfoZero;
+                if (__builtin_amdgcn_ballot_w64((ri & kinds) != 0) == 0) return;
+                const int ws = TO_D1 ? w_d1 : w;
+                auto row_start = [&](uint32_t info, uint32_t row) __attribute__((always_inline)) {
+                    if constexpr (TO_D1) return D1 + d1_slot(a.row_info != nullptr, info, row) * a.d1_sw + 4 * g;
+                    else return D + (int64_t)row * a.ccol + c0 + 4 * g;
+                };
+                auto scaled = [&](floatx4 y, uint32_t info, float by) __attribute__((always_inline)) {
+                    if constexpr (!TO_D1)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) y[v] = info & kInfoZero ? 0.0f : by * y[v];
+                    return y;
+                };
+                auto at_col = [&](int nb) __attribute__((always_inline)) {
+                    const int cb = c0 + 16 * nb;        // the workspace is cut into slices of d1_sw columns
+                    return TO_D1 ? (int64_t)(cb >> a.d1_sw_shift) * a.d1_slice_stride + (cb & a.d1_sw_mask) : 16 * nb;
+                };
+                const bool low = r < 8;
+                const uint32_t r0 = low ? ri : rx, r1 = low ? rx : ri;
+                const float s0 = low ? scale[i] : scale_x, s1 = low ? scale_x : scale[i];
+                float *own = row_start(ri, row0 + r), *dst0 = row_start(r0, row0 + (r & 7)) + (low ? 0 : 16),
+                      *dst1 = row_start(r1, row0 + 8 + (r & 7)) + (low ? 0 : 16);
+#pragma unroll
+                for (int nb = 0; nb < NB; nb += 2) {
+                    const bool pair = nb + 1 < NB && 16 * nb + 32 <= ws && (!TO_D1 || ((c0 + 16 * nb) & a.d1_sw_mask) + 32 <= a.d1_sw);
+                    if (pair) {
+                        floatx4 y0, y1;
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            const int lo = __float_as_int(acc[i][nb][v]), hi = __float_as_int(acc[i][nb + 1 < NB ? nb + 1 : nb][v]);
+                            y0[v] = __int_as_float(__builtin_amdgcn_update_dpp(lo, hi, kRowRor8, 0xf, 0xc, false));
+                            y1[v] = __int_as_float(__builtin_amdgcn_update_dpp(hi, lo, kRowRor8, 0xf, 0x3, false));
+                        }
+                        typedef typename Piece16<float>::Vec Vec;
+                        auto put = [&](float *to, const Vec &y) __attribute__((always_inline)) {
+                            if constexpr (TO_D1) *reinterpret_cast<Vec *>(to) = y;
+                            else __builtin_nontemporal_store(y, reinterpret_cast<Vec *>(to));
+                        };
+                        if (r0 & kinds) put(dst0 + at_col(nb), scaled(y0, r0, s0));
+                        if (r1 & kinds) put(dst1 + at_col(nb), scaled(y1, r1, s1));
+                    } else if (ri & kinds) {
+                        store_acc4<float>(own + at_col(nb), scaled(acc[i][nb], ri, scale[i]), nb, g, ws);
+                        if constexpr (NB > 1)
+                            if (nb + 1 < NB) store_acc4<float>(own + at_col(nb + 1), scaled(acc[i][nb + 1], ri, scale[i]), nb + 1, g, ws);
+                    }
+                }
+            };
+            store(std::true_type());
+            store(std::false_type());
+        }
+    }
+}
+
+// ------------------------------------------------------------------------------------------ host
+
+template <int KD, int NB> int run_split(const GemmLaunch &a, hipStream_t st) {
+    const int64_t lds = split_lds_bytes(KD, NB);
+    const int64_t nblk = (a.n + 31) / 32;
+    // as many workgroups as the machine holds at once; few blocks are spread thin (see run_gemm2)
+    int nwaves = kFusedThreads / 64;
+    while (nwaves > 1 && nblk * a.n_slices < (int64_t)a.n_cu * nwaves && nwaves * 2048 >= lds) nwaves /= 2;
+    static std::mutex m;
+    static bool raised = false;
+    static int occ_waves = 0, occ = 1;
+    int wg_per_cu;
+    {
+        std::lock_guard<std::mutex> lock(m);
+        if (!raised) {
+            const int e = raise_lds_limit(k_gemm_split<KD, NB>, lds);
+            if (e) return e;
+            raised = true;
+        }
+        if (nwaves != occ_waves) {
+            occ = resident_per_cu(k_gemm_split<KD, NB>, 64 * nwaves, lds, 16);
+            occ_waves = nwaves;
+        }
+        wg_per_cu = occ;
+    }
+    const int64_t most = std::max<int64_t>(1, (int64_t)a.n_cu * wg_per_cu / a.n_slices);
+    const int64_t gx = std::min(most, (nblk + nwaves - 1) / nwaves);
+    (void)hipGetLastError();
+    k_gemm_split<KD, NB><<<dim3((unsigned)gx, (unsigned)a.n_slices), dim3(64 * nwaves), lds, st>>>(a);
+    return (int)hipGetLastError();
+}
+
+template <int KD> int run_split_nb(const GemmLaunch &a, hipStream_t st) {
+    switch (split_col_blocks(a.cs)) {
+        case 1: return run_split<KD, 1>(a, st);
+        case 2: return run_split<KD, 2>(a, st);
+        case 3: return run_split<KD, 3>(a, st);
+        case 4: return run_split<KD, 4>(a, st);
+        case 6: return run_split<KD, 6>(a, st);
+        case 8: return run_split<KD, 8>(a, st);
+    }
+    return (int)hipErrorInvalidValue;
+}
+
+}  // namespace
+
+int launch_gemm_split(const GemmLaunch &a, void *stream) {
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    switch ((a.bcol + 31) / 32) {
+        case 1: return run_split_nb<1>(a, st);
+        case 2: return run_split_nb<2>(a, st);
+        case 3: return run_split_nb<3>(a, st);
+        case 4: return run_split_nb<4>(a, st);
+    }
+    return (int)hipErrorInvalidValue;
+}
+
+}  // namespace tf

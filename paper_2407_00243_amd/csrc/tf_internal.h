@@ -198,6 +198,16 @@ inline int64_t lds_sparse_b_bytes_per_row(int dtype) {
     return 2 * 8 + kSparseEntryCap * (4 + (int64_t)elem_size(dtype));    // extents of two tiles
 }
 
+// The fp32 product on the bf16 matrix cores (k_gemm_split): rows of B of kSplitMinDepth columns (a sixteen-byte piece) and
+// more, up to kSplitMaxDepth; blocks of sixteen columns that a slice of cs columns takes, and the LDS for C in three parts.
+constexpr int kSplitMinDepth = 4, kSplitMaxDepth = 128;
+inline bool gemm_splits(int dtype, int bcol) { return dtype == TF_F32 && bcol >= kSplitMinDepth && bcol <= kSplitMaxDepth; }
+inline int split_col_blocks(int cs) {
+    const int nb = (cs + 15) / 16;
+    return nb == 5 ? 6 : nb == 7 ? 8 : nb;
+}
+constexpr int64_t split_lds_bytes(int steps, int nb) { return (int64_t)steps * nb * 3 * 1024 + nb * 16 * 4; }
+
 // Whether a wave of the dense-B kernels keeps its operands of the C slice in registers: only for
 // the specialised shallow depths (ks = bCol / (4 * elements per 16 bytes) steps, nb accumulator
 // blocks) and at most 64 registers' worth (32 for fp64, whose B buffers are twice as large).
@@ -628,6 +638,7 @@ int launch_fused_spmm_spmm(const FusedLaunch &a, void *stream);
 int launch_packed_spmm(const PackedSpmmLaunch &a, void *stream);
 int launch_csr_spmm(const CsrSpmmLaunch &a, void *stream);
 int launch_gemm(const GemmLaunch &a, void *stream);
+int launch_gemm_split(const GemmLaunch &a, void *stream);     // where gemm_splits
 int launch_chain(const ChainLaunch &a, void *stream);
 
 }  // namespace tf

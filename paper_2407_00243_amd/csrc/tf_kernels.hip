@@ -4,7 +4,8 @@
 //   k_fused_gemm_spmm   first wavefront, dense B   (paper Section 3.2, fused GeMM-SpMM listing)
 //   k_fused_spmm_spmm   first wavefront, CSR B     (Section 3.2, fused SpMM-SpMM listing)
 //   k_gemm              D1 = B C for all rows: the GeMM of the unfused baseline, and the first
-//                       wavefront of a dense-B plan that needs no tile in LDS
+//                       wavefront of a dense-B plan that needs no tile in LDS (fp32 rows of 4 to 128 columns:
+//                       k_gemm_split in tf_gemm.hip)
 //
 // A fused workgroup owns one tile (a list of D1 rows) and one column slice.  It produces the
 // tile's D1 rows into LDS -- by MFMA for a dense B, by a row gather over C for a CSR B -- stores
@@ -117,38 +118,6 @@ __device__ __forceinline__ void mfma_row_block(typename Tr<T>::Acc (&acc)[NB], c
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb)
                 acc[nb] = mfma16(Cl[((s * V + q) * NB + nb) * 64 + lane], av[q], acc[nb]);
-        }
-    }
-}
-
-// Stores the four columns a lane holds of accumulator block nb to `dst` (which points at the
-// lane's first column, 16 nb + 4 g), keeping to columns below w: 16-byte pieces, at whatever element
-// they begin, and the columns of a block that w cuts one by one.
-template <typename T>
-__device__ __forceinline__ void store_acc4(T *dst, const typename Tr<T>::Acc &a, int nb, int g, int w) {
-    constexpr int V = Tr<T>::V;
-    if (16 * nb + 16 <= w) {
-#pragma unroll
-        for (int h = 0; h < 4 / V; ++h) {
-            T tmp[V];
-#pragma unroll
-            for (int i = 0; i < V; ++i) tmp[i] = a[V * h + i];
-            store_any<T, V>(dst + V * h, tmp);
-        }
-    } else {
-#pragma unroll
-        for (int h = 0; h < 4 / V; ++h) {
-            const int col = 16 * nb + 4 * g + V * h;
-            if (col + V <= w) {
-                T tmp[V];
-#pragma unroll
-                for (int i = 0; i < V; ++i) tmp[i] = a[V * h + i];
-                store_any<T, V>(dst + V * h, tmp);
-            } else {
-#pragma unroll
-                for (int i = 0; i + 1 < V; ++i)
-                    if (col + i < w) dst[V * h + i] = a[V * h + i];
-            }
         }
     }
 }
@@ -1112,8 +1081,6 @@ __global__ __launch_bounds__(kFusedSparseThreads) void k_fused_spmm_spmm(const F
 // flight while the current one is multiplied (KS > 0, as above).
 // KS > 0, FAST: bCol = 4 V KS exactly; not FAST: any bCol from V up to there, rows of B at any element.
 // KS = 0: any bCol, nothing in flight ahead; FAST: bCol is a multiple of V.  cCol is any.
-// (Graph of 150000 rows, fp32 128 -> 41, product and gather: 229 us while an unaligned cCol took the loop
-// over k with single elements stored and gathered, 117 us with this depth and 16-byte pieces.)
 // INFO = false: the GeMM of the unfused baseline; every row goes to the workspace, slot = row.
 // INFO = true: the first wavefront of a plan none of whose fused rows reads the LDS tile (a graph:
 // the only rows that fuse hold just a diagonal entry, or nothing).  Then no tile has to sit in LDS
@@ -1317,9 +1284,8 @@ int run_gemm2(const GemmLaunch &a, hipStream_t st) {
     const int64_t lds = lds_fixed_bytes(a.dtype, 0, a.bcol, a.cs);
     const int64_t nblk = (a.n + 15) / 16;
     // As many workgroups as the machine holds at once, so that each stages C only once, the first rows of
-    // B on their way meanwhile (with up to 1024 of them most waves multiplied one block each: fp32 n =
-    // 131072, 64 -> 128, 48.5 us, now 38; n = 150000, 128 -> 41, 47 us, now 36; n = 2^20, 128 -> 128, where
-    // the matrix cores are 60 % busy, 399 us, now 374); few blocks are spread thin, as far as a wave
+    // B on their way meanwhile (with up to 1024 of them most waves multiplied one block each: on the fp32 matrix cores
+    // n = 131072, 64 -> 128, 48.5 us, so 38); few blocks are spread thin, as far as a wave
     // does not have to stage more than 4 KiB of C.
     int nwaves = kFusedThreads / 64;
     while (nwaves > 1 && nblk * a.n_slices < (int64_t)a.n_cu * nwaves && nwaves * 2048 >= lds) nwaves /= 2;
@@ -1423,6 +1389,7 @@ int launch_fused_spmm_spmm(const FusedLaunch &a, void *stream) {
 int launch_gemm(const GemmLaunch &a, void *stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (a.n == 0) return 0;
+    if (gemm_splits(a.dtype, a.bcol)) return launch_gemm_split(a, stream);
     // The depth: the smallest one that covers bCol where bCol is all of it, or where rows of B are not
     // aligned.  Aligned rows of other lengths take the loop over k, whose few registers leave room for
     // more waves (graph of 119367 rows, fp32 36 -> 128, whole chain: 146 us, 150 us with the covering
@@ -1435,8 +1402,12 @@ int launch_gemm(const GemmLaunch &a, void *stream) {
     const bool fast = exact || (!covered && a.bcol % v == 0);
     return dispatch_shape(a.dtype, a.cs, covered ? depth * kc : 1, true, [&](auto nb, auto ks) {
         constexpr int NB = decltype(nb)::value, KS = decltype(ks)::value;
-        if (a.dtype == TF_F32)
-            return fast ? run_gemm<float, NB, KS, true>(a, st) : run_gemm<float, NB, KS, false>(a, st);
+        if (a.dtype == TF_F32) {
+            // (the depths between are those of k_gemm_split)
+            if constexpr (KS == 0 || 16 * KS > kSplitMaxDepth)
+                return fast ? run_gemm<float, NB, KS, true>(a, st) : run_gemm<float, NB, KS, false>(a, st);
+            return (int)hipErrorInvalidValue;
+        }
         return fast ? run_gemm<double, NB, KS, true>(a, st) : run_gemm<double, NB, KS, false>(a, st);
     });
 }
