@@ -431,6 +431,7 @@ tf_status run_chain(const tf_plan *p, const void *B, const void *C, void *D, voi
     a.B = B;
     a.C = C;
     a.c_transposed = p->c_transposed ? 1 : 0;
+    a.lds_limit = p->lds_per_cu;
     a.D = D;
     const int e = tf::launch_chain(a, stream);
     if (e) return hip_fail((hipError_t)e, "launching the chain");

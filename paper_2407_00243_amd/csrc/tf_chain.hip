@@ -90,21 +90,90 @@ __device__ __forceinline__ void write_c(T *Cl, const CPiece<T> (&tmp)[kStageC]) 
     }
 }
 
+// fp32 on the bf16 matrix cores: C in three parts (split_pair), per group of NBC blocks of sixteen columns, per step s of
+// 32 k, per block, per part sixteen bytes for each lane l, C[32 s + {0, 16} + 4 (l / 16) + {0 .. 3}][column l % 16 of the
+// block]; elements past bCol are zeros.  An item is what four neighbouring lanes take: eight k of four columns, fetched by
+// eight loads of sixteen bytes (element by element: band of 20011 rows of 11, 64 -> 64, 9.5 us, so 8.5).  KS2: steps; CT: C
+// is transposed, its rows bCol long, else ld long; a piece of four columns that would reach past `cols` is moved back so
+// that it ends there.
+struct SplitC {
+    const float *C;      // at the first column
+    int ld, bcol, cols;
+};
+template <int KS2, bool CT>
+__device__ __forceinline__ void load_split(floatx4 (&y)[8], const SplitC &c, int item, int total) {
+    typedef typename Piece16<float>::Vec Vec;
+    const int w = item & 3, g = item >> 2 & 3, s = (item >> 4) % KS2, nbt = (item >> 4) / KS2;
+    const int col = min(16 * nbt + 4 * w, c.cols - 4);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) y[q] = floatx4{0, 0, 0, 0};
+    if (item >= total) return;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        // row of C as it is stored, first element in it, elements of the row
+        const int k = 32 * s + 4 * g + (CT ? 16 * (q / 4) : q < 4 ? q : 12 + q);
+        const int row = CT ? col + q % 4 : k, at = CT ? k : col, end = CT ? c.bcol : c.cols;
+        if (row >= (CT ? c.cols : c.bcol)) continue;
+        const float *p = c.C + (int64_t)row * (CT ? c.bcol : c.ld) + at;
+        if (at + 4 <= end) {
+            y[q] = *reinterpret_cast<const Vec *>(p);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+                if (at + j < end) y[q][j] = p[j];
+        }
+    }
+}
+// Puts an item into LDS and the largest number (bits: a NaN counts as more than infinity) of each column into cmax.
+template <int KS2, int NBC, bool CT>
+__device__ __forceinline__ void write_split(Word4 *Cl, uint32_t *cmax, const floatx4 (&y)[8], int item, int total) {
+    const int w = item & 3, g = item >> 2 & 3, s = (item >> 4) % KS2, nbt = (item >> 4) / KS2;
+    if (item >= total) return;
+    Word4 *to = Cl + ((nbt / NBC * KS2 + s) * NBC + nbt % NBC) * 3 * 64 + 16 * g + 4 * w;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        uint32_t most = 0;
+        Word4 part[3];
+#pragma unroll
+        for (int q = 0; q < 8; q += 2) {
+            const float x0 = CT ? y[q / 4 * 4 + j][q % 4] : y[q][j], x1 = CT ? y[q / 4 * 4 + j][q % 4 + 1] : y[q + 1][j];
+            most = max(most, max(__float_as_uint(x0) & 0x7fffffffu, __float_as_uint(x1) & 0x7fffffffu));
+            split_pair(part, q / 2, x0, x1);
+        }
+        atomicMax(&cmax[16 * nbt + 4 * w + j], most);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) to[64 * i + j] = part[i];
+    }
+}
+
+// What a pass gathers: N entries of R rows, P pieces each.
+template <typename Vec, int N, int R, int P> struct GatheredPieces {
+    Vec v[N][R][P];
+};
+
 // KS: 16-byte pieces per lane of a row of B (bCol <= 4 V KS), NBC: blocks of sixteen columns of D
 // multiplied at a time.
 //
-// A block's entries are gathered in passes of up to EM entries per row.  Order of a wave's work per
-// block: add up the first pass (in flight since the block before), gather and add up the others,
-// send out the first gathers of the next block, and only then multiply and store.  Loads and stores
-// of a wave complete in order on this machine, so gathers that were sent out after the stores of D
-// would wait for these to reach memory.
+// A block's entries are gathered in passes of up to EM entries per row, with as many gathers on their way as the
+// registers hold.  A wave adds up all passes of a block, multiplies, stores, and only then sends out the next block's
+// first gathers: the other waves of its SIMD are at another step meanwhile, and the entries of a row are gathered at
+// one time, so that what one wave fetches another finds in the L2 (2D stencil 512^2, fp64 128 -> 128: 357 MB fetched
+// past the L2; with the first pass on its way during the multiplications 597 MB, 195 us, so 190).
+//
+// fp32 from depth 4 on is multiplied on the bf16 matrix cores, operands split in three (tf_device.h; chain_splits).
+// These leave the other waves of their SIMD to work; behind fp32 and fp64 matrix instructions every instruction of
+// theirs waits (loads, LDS reads or sums of four waves beside four that multiply take the sum of both times, beside
+// bf16 instructions little more than the longer one).  us, before / with first gathers later and a piece of all entries
+// in turn / on the bf16 matrix cores: 2D stencil 512^2, 64 -> 64 42 / 40 / 34.5, 128 -> 128 108 / 108 / 89; band of 15204
+// rows of 41, 64 -> 64 15.8 / 14.0 / 12.5; 3D stencil 48^3, 64 -> 128 34.4 / 35.2 / 28.5.  Rows of B that are summed up
+// outside of the bounds of the split, or all if a column of C is, take the fp32 instructions, C from memory.
 template <typename T, int KS, int NBC>
 __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS, NBC)) void k_gather_gemm(
     const ChainLaunch a, const ChainBlock *__restrict__ blocks, const int32_t *__restrict__ rows,
     const int32_t *__restrict__ idx, const T *__restrict__ val, const char *__restrict__ B,
     void *D) {
     constexpr int V = Tr<T>::V, KC = 4 * V;
-    constexpr int EM = chain_entries(KS);
+    constexpr int EM = chain_entries(dtype_of<T>(), KS);
     constexpr int K0 = chain_ksteps_below(dtype_of<T>(), KS);      // pieces that are whole for certain
     typedef typename Piece16<T>::Vec Vec;
     typedef T Vec16 __attribute__((ext_vector_type(V)));
@@ -117,6 +186,8 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS, NBC))
     // 64 / LR rows at a time, RS times; piece P = pp + LR t of the rows rr + 64 h / LR
     constexpr int LR = KS % 2 == 0 ? 8 : 4, RS = LR / 4, KP = KS / RS;
     const int pp = lane % LR, rr = lane / LR;
+    constexpr bool SPLIT = chain_splits(dtype_of<T>(), KS);     // (fp32 on the bf16 matrix cores)
+    constexpr int KS2 = (KS + 1) / 2;
     T *Cl = reinterpret_cast<T *>(tf_smem);
     // the column groups of this workgroup (all of them, unless the launch has few blocks of rows)
     const int g0 = (int)blockIdx.y * a.groups_per_wg;
@@ -125,9 +196,9 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS, NBC))
     // bytes; the pieces of a row are swizzled so that the sixteen rows' pieces g sit in different
     // banks), results into rows of D (16 rows of CB blocks and 16 bytes) -- then the offsets of the
     // rows of D and the entries of a pass (NE x 64 values, then addresses of rows of B)
-    constexpr int NE = chain_entry_loads(KS), TS = chain_exchange(KS), CB = chain_store_blocks(dtype_of<T>(), KS, NBC);
+    constexpr int NE = chain_entry_loads(dtype_of<T>(), KS), TS = chain_exchange(KS), CB = chain_store_blocks(dtype_of<T>(), KS, NBC);
     constexpr int W = CB * 16 / V, PITCH = W * 16 + 16;
-    unsigned char *ex = tf_smem + a.groups_per_wg * (NBC * KS * V * 64 * (int)sizeof(T)) +
+    unsigned char *ex = tf_smem + a.groups_per_wg * (int)chain_group_lds(dtype_of<T>(), KS, NBC) +
                         wave * (int)chain_wave_lds(dtype_of<T>(), KS, NBC);
     uint32_t *er = reinterpret_cast<uint32_t *>(ex + chain_exchange_bytes(dtype_of<T>(), KS, NBC));
     T *ev = reinterpret_cast<T *>(er + 16);
@@ -206,26 +277,71 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS, NBC))
     const auto Dr = __builtin_amdgcn_make_buffer_rsrc(D, 0, (uint32_t)(a.n * a.ccol * (int64_t)sizeof(T)),
                                                       kBufferRaw);
 
-    Vec x[EM][RS][KP];
     T acc[RS][KP][V];
-    // (n is wave-uniform: a branch per entry)
-    auto issue = [&](int n) __attribute__((always_inline)) {
+    // One pass: the gathers of n entries per row (known to the compiler), a piece of all entries in turn (neighbouring entries
+    // name neighbouring rows of B, of which the piece before has fetched most: 2D stencil, fp32 64 -> 64, 39.2 -> 36.4 us), and
+    // their sum.
+    auto gather = [&](auto n_c, auto &x) __attribute__((always_inline)) {
+        constexpr int N = decltype(n_c)::value;
+        GlobalBytes p[N][RS];
+#pragma unroll
+        for (int e = 0; e < N; ++e)
+#pragma unroll
+            for (int h = 0; h < RS; ++h) p[e][h] = (GlobalBytes)(ea[e * 16 + rr + h * (64 / LR)] + first);
+#pragma unroll
+        for (int h = 0; h < RS; ++h)
+#pragma unroll
+            for (int t = 0; t < KP; ++t)
+#pragma unroll
+                for (int e = 0; e < N; ++e)
+                    x.v[e][h][t] = *(GlobalVec)(t < T0 ? p[e][h] + 16 * LR * t : p[e][h] + moved[t < T0 ? 0 : t - T0]);
+    };
+    auto add_up = [&](auto n_c, const auto &x) __attribute__((always_inline)) {
+        constexpr int N = decltype(n_c)::value;
+        // All values first: one trip to LDS and back (band of 15204 rows of 41, fp32 19 -> 16, 9.76 -> 8.95 us).
+        T w[N][RS];
+#pragma unroll
+        for (int e = 0; e < N; ++e)
+#pragma unroll
+            for (int h = 0; h < RS; ++h) w[e][h] = ev[e * 16 + rr + h * (64 / LR)];
+#pragma unroll
+        for (int e = 0; e < N; ++e)
+#pragma unroll
+            for (int h = 0; h < RS; ++h) asm volatile("" : "+v"(w[e][h]));
+#pragma unroll
+        for (int h = 0; h < RS; ++h)
+#pragma unroll
+            for (int t = 0; t < KP; ++t)
+#pragma unroll
+                for (int e = 0; e < N; ++e)
+#pragma unroll
+                    for (int q = 0; q < V; ++q) acc[h][t][q] += w[e][h] * x.v[e][h][t][q];
+        __builtin_amdgcn_wave_barrier();
+    };
+    // calls f(n) with the count (1 to EM, wave-uniform) as a constant
+    auto with_count = [&](int n, auto &&f) __attribute__((always_inline)) {
+        auto from = [&](auto &self, auto n_c) __attribute__((always_inline)) -> void {
+            constexpr int N = decltype(n_c)::value;
+            if (N == 1 || n >= N) f(n_c);
+            else if constexpr (N > 1) self(self, std::integral_constant<int, N - 1>());
+        };
+        from(from, std::integral_constant<int, EM>());
+    };
+    // The very first pass, whose sums are formed later: n entries per row (wave-uniform: a branch per entry).
+    auto send_first = [&](int n, GatheredPieces<Vec, EM, RS, KP> &x) __attribute__((always_inline)) {
 #pragma unroll
         for (int e = 0; e < EM; ++e) {
-            if (e < n) {
+            if (e >= n) continue;
 #pragma unroll
-                for (int h = 0; h < RS; ++h) {
-                    const GlobalBytes p = (GlobalBytes)(ea[e * 16 + rr + h * (64 / LR)] + first);
+            for (int h = 0; h < RS; ++h) {
+                const GlobalBytes p = (GlobalBytes)(ea[e * 16 + rr + h * (64 / LR)] + first);
 #pragma unroll
-                    for (int t = 0; t < KP; ++t)
-                        x[e][h][t] = *(GlobalVec)(t < T0 ? p + 16 * LR * t : p + moved[t < T0 ? 0 : t - T0]);
-                }
+                for (int t = 0; t < KP; ++t)
+                    x.v[e][h][t] = *(GlobalVec)(t < T0 ? p + 16 * LR * t : p + moved[t < T0 ? 0 : t - T0]);
             }
         }
     };
-    auto consume = [&](int n) __attribute__((always_inline)) {
-        // All values first: one trip to LDS and back, not one per entry behind its branch (band of 15204 rows of
-        // 41, fp32 19 -> 16, 9.76 -> 8.95 us; slots beyond the pass are read too, and not used).
+    auto add_first = [&](int n, const GatheredPieces<Vec, EM, RS, KP> &x) __attribute__((always_inline)) {
         T w[EM][RS];
 #pragma unroll
         for (int e = 0; e < EM; ++e)
@@ -237,37 +353,45 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS, NBC))
             for (int h = 0; h < RS; ++h) asm volatile("" : "+v"(w[e][h]));
 #pragma unroll
         for (int e = 0; e < EM; ++e) {
-            if (e < n) {
+            if (e >= n) continue;
 #pragma unroll
-                for (int h = 0; h < RS; ++h) {
-                    const T v = w[e][h];
+            for (int h = 0; h < RS; ++h)
 #pragma unroll
-                    for (int t = 0; t < KP; ++t)
+                for (int t = 0; t < KP; ++t)
 #pragma unroll
-                        for (int q = 0; q < V; ++q) acc[h][t][q] += v * x[e][h][t][q];
-                }
-            }
+                    for (int q = 0; q < V; ++q) acc[h][t][q] += w[e][h] * x.v[e][h][t][q];
         }
         __builtin_amdgcn_wave_barrier();
+    };
+    auto clear_sums = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int h = 0; h < RS; ++h)
+#pragma unroll
+            for (int t = 0; t < KP; ++t)
+#pragma unroll
+                for (int q = 0; q < V; ++q) acc[h][t][q] = T(0);
     };
     auto pass_len = [](const ChainBlock &b) { return (b.info >> 3) & 15; };
     auto first_count = [&](const ChainBlock &b) { return min(pass_len(b), b.slots); };
 
+    uint32_t *cmax = reinterpret_cast<uint32_t *>(tf_smem + groups * (NBC * KS2 * 3 * 1024));
+    bool c_bad = false;      // (fp32) a column of C is outside of the bounds of the split
     // Start-up: the first gathers of the first block go out before C is put into LDS
     {
         const int total = groups * NBC * 16 * KS * 4;
         CPiece<T> tmp[kStageC];
-        auto first_issue = [&]() __attribute__((always_inline)) {
-            if (blk < end) {
-                put();
-                fetch(d.slots > pass_len(d) ? d.slot_base + pass_len(d) : dn.slot_base);
-                issue(first_count(d));
-            }
+        GatheredPieces<Vec, EM, RS, KP> x;
+        const int n = blk < end ? first_count(d) : 0;
+        auto first_gathers = [&]() __attribute__((always_inline)) {
+            if (blk >= end) return;
+            put();
+            fetch(d.slots > pass_len(d) ? d.slot_base + pass_len(d) : dn.slot_base);
+            send_first(n, x);
         };
         auto stage = [&](auto ct_c) __attribute__((always_inline)) {
             constexpr bool CT = decltype(ct_c)::value;
             load_c<T, KS, NBC, CT>(tmp, threadIdx.x, total, groups, col0, a);
-            first_issue();
+            first_gathers();
             write_c<T, NBC, CT>(Cl, tmp);
             for (int p0 = (int)threadIdx.x + kStageC * (int)blockDim.x; p0 < total;
                  p0 += kStageC * (int)blockDim.x) {
@@ -275,38 +399,61 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS, NBC))
                 write_c<T, NBC, CT>(Cl, tmp);
             }
         };
-        if (a.c_transposed) stage(std::true_type());
-        else stage(std::false_type());
+        if constexpr (SPLIT) {
+            auto stage_split = [&](auto ct_c) __attribute__((always_inline)) {
+                constexpr bool CT = decltype(ct_c)::value;
+                const int items = groups * NBC * KS2 * 16;
+                const SplitC from{static_cast<const float *>(a.C) + (CT ? (int64_t)col0 * a.bcol : col0), a.ccol, a.bcol, a.ccol - col0};
+                Word4 *const to = reinterpret_cast<Word4 *>(Cl);
+                floatx4 y[8];
+                load_split<KS2, CT>(y, from, threadIdx.x, items);
+                for (int i = threadIdx.x; i < groups * NBC * 16; i += (int)blockDim.x) cmax[i] = 0;
+                __syncthreads();
+                first_gathers();
+                write_split<KS2, NBC, CT>(to, cmax, y, threadIdx.x, items);
+                for (int p = (int)threadIdx.x + (int)blockDim.x; p < items; p += (int)blockDim.x) {
+                    load_split<KS2, CT>(y, from, p, items);
+                    write_split<KS2, NBC, CT>(to, cmax, y, p, items);
+                }
+            };
+            if (a.c_transposed) stage_split(std::true_type());
+            else stage_split(std::false_type());
+        } else {
+            if (a.c_transposed) stage(std::true_type());
+            else stage(std::false_type());
+        }
         __syncthreads();
         if (blk >= end) return;
         __builtin_amdgcn_s_waitcnt(0);
         asm volatile("" : : "v"(zeros_ahead));
+        if constexpr (SPLIT) {
+            for (int c = lane; c < groups * NBC * 16; c += 64) c_bad |= split_exceeds(__uint_as_float(cmax[c]), kSplitColMin);
+            c_bad = __builtin_amdgcn_ballot_w64(c_bad) != 0;
+        }
+        clear_sums();
+        add_first(n, x);
     }
 
-    for (;;) {
+    for (int s0 = pass_len(d);; s0 = 0) {
         const int next = block_after(blk);
         const bool has_next = next < end;
         const ChainBlock dnn = blocks[min(block_after(next), end - 1)];
-#pragma unroll
-        for (int h = 0; h < RS; ++h)
-#pragma unroll
-            for (int t = 0; t < KP; ++t)
-#pragma unroll
-                for (int q = 0; q < V; ++q) acc[h][t][q] = T(0);
-        const int len = pass_len(d);
-        consume(first_count(d));
-        for (int s0 = len; s0 < d.slots; s0 += len) {
+        for (const int len = pass_len(d); s0 < d.slots; s0 += len) {
+            if (s0) {
+                put();
+                fetch(s0 + len < d.slots ? d.slot_base + s0 + len : dn.slot_base);
+            }
             const int count = min(len, d.slots - s0);
-            put();
-            fetch(s0 + len < d.slots ? d.slot_base + s0 + len : dn.slot_base);
-            issue(count);
-            consume(count);
+            with_count(count, [&](auto n_c) __attribute__((always_inline)) {
+                GatheredPieces<Vec, decltype(n_c)::value, RS, KP> x;
+                gather(n_c, x);
+                add_up(n_c, x);
+            });
         }
-        // the gathers of the next block (the last block sends those of some block out, for nothing)
+        // the entries of the next block's first pass (the last block's wave takes those of some block, for nothing)
         put();
         row_n = row_id(dn);
         fetch(dn.slots > pass_len(dn) ? dn.slot_base + pass_len(dn) : dnn.slot_base);
-        issue(first_count(dn));
         __builtin_amdgcn_sched_barrier(0);
 
         // into the operand layout (a wave's LDS operations take effect in order)
@@ -366,44 +513,119 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS, NBC))
             er[r] = (r >> slog) < n_rows && (r & ((1 << slog) - 1)) == 0 ? (uint32_t)row * (uint32_t)a.ccol : ~0u;
         const bool empty = d.slots == 0;      // (empty rows are zeros whatever C holds)
         __builtin_amdgcn_s_setprio(0);
-        int grp = 0;
-        do {
-            const T *Cg = Cl + grp * (NBC * KS * V * 64) + lane;
-            typename Tr<T>::Acc o[NBC];
+        typedef typename Tr<T>::Acc Acc;
+        auto each_group = [&](auto multiply) __attribute__((always_inline)) {
+            int grp = 0;
+            do {
+                Acc o[NBC];
 #pragma unroll
-            for (int nb = 0; nb < NBC; ++nb) o[nb] = typename Tr<T>::Acc{0, 0, 0, 0};
+                for (int nb = 0; nb < NBC; ++nb) o[nb] = Acc{0, 0, 0, 0};
+                multiply(grp, o);
 #pragma unroll
-            for (int i = 0; i < KS * V; ++i)
+                for (int nb0 = 0; nb0 < NBC; nb0 += CB) {
 #pragma unroll
-                for (int nb = 0; nb < NBC; ++nb)
-                    o[nb] = mfma16(Cg[(i * NBC + nb) * 64], f[i / V][i % V], o[nb]);
+                    for (int nb = nb0; nb < nb0 + CB; ++nb)
 #pragma unroll
-            for (int nb0 = 0; nb0 < NBC; nb0 += CB) {
+                        for (int h = 0; h < 4 / V; ++h) {
+                            Vec16 y;
 #pragma unroll
-                for (int nb = nb0; nb < nb0 + CB; ++nb)
+                            for (int q = 0; q < V; ++q) y[q] = empty ? T(0) : o[nb][V * h + q];
+                            *reinterpret_cast<Vec16 *>(ex + r * PITCH + ((nb - nb0) * 16 / V + 4 * h + g) * 16) = y;
+                        }
+                    __builtin_amdgcn_wave_barrier();
 #pragma unroll
-                    for (int h = 0; h < 4 / V; ++h) {
-                        Vec16 y;
-#pragma unroll
-                        for (int q = 0; q < V; ++q) y[q] = empty ? T(0) : o[nb][V * h + q];
-                        *reinterpret_cast<Vec16 *>(ex + r * PITCH + ((nb - nb0) * 16 / V + 4 * h + g) * 16) = y;
+                    for (int i = 0; i < W / 4; ++i) {
+                        const int at = i * 64 + lane, sr = at / W, piece = at % W;
+                        const int col = col0 + 16 * (grp * NBC + nb0) + piece * V;
+                        const uint32_t row_off = er[sr];
+                        const Word4 y = *reinterpret_cast<const Word4 *>(ex + sr * PITCH + piece * 16);
+                        const uint32_t off = (row_off + (uint32_t)min(col, a.ccol - V)) * (uint32_t)sizeof(T);
+                        __builtin_amdgcn_raw_buffer_store_b128(y, Dr, row_off != ~0u && col < a.ccol ? off : ~0u,
+                                                               0, kNonTemporal);
                     }
-                __builtin_amdgcn_wave_barrier();
-#pragma unroll
-                for (int i = 0; i < W / 4; ++i) {
-                    const int at = i * 64 + lane, sr = at / W, piece = at % W;
-                    const int col = col0 + 16 * (grp * NBC + nb0) + piece * V;
-                    const uint32_t row_off = er[sr];
-                    const Word4 y = *reinterpret_cast<const Word4 *>(ex + sr * PITCH + piece * 16);
-                    const uint32_t off = (row_off + (uint32_t)min(col, a.ccol - V)) * (uint32_t)sizeof(T);
-                    __builtin_amdgcn_raw_buffer_store_b128(y, Dr, row_off != ~0u && col < a.ccol ? off : ~0u,
-                                                           0, kNonTemporal);
+                    __builtin_amdgcn_wave_barrier();
                 }
-                __builtin_amdgcn_wave_barrier();
+            } while (++grp < groups);
+        };
+        if constexpr (!SPLIT) {
+            each_group([&](int grp, Acc(&o)[NBC]) __attribute__((always_inline)) {
+                // (the operands of a step are read ahead of the multiplications of the one before: 2D stencil 301^2, fp32 50 ->
+                // 23, on the fp32 matrix cores 12.8 -> 12.3 us)
+                const T *Cg = Cl + grp * (NBC * KS * V * 64) + lane;
+                T c[2][NBC];
+#pragma unroll
+                for (int nb = 0; nb < NBC; ++nb) c[0][nb] = Cg[nb * 64];
+#pragma unroll
+                for (int i = 0; i < KS * V; ++i) {
+                    if (i + 1 < KS * V) {
+#pragma unroll
+                        for (int nb = 0; nb < NBC; ++nb) c[(i + 1) & 1][nb] = Cg[((i + 1) * NBC + nb) * 64];
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int nb = 0; nb < NBC; ++nb) o[nb] = mfma16(c[i & 1][nb], f[i / V][i % V], o[nb]);
+                }
+            });
+        } else if constexpr (SPLIT) {
+            float most = 0.0f;
+#pragma unroll
+            for (int s = 0; s < KS; ++s)
+#pragma unroll
+                for (int q = 0; q < V; q += 2) most = fmaxf(fmaxf(most, fabsf(f[s][q])), fabsf(f[s][q + 1]));
+            most = fmaxf(most, __shfl_xor(most, 16, 64));
+            most = fmaxf(most, __shfl_xor(most, 32, 64));
+            if (__builtin_amdgcn_ballot_w64(c_bad || split_exceeds(most, kSplitRowMin))) {
+                each_group([&](int grp, Acc(&o)[NBC]) __attribute__((always_inline)) {
+                    const float *C = static_cast<const float *>(a.C);
+                    int ldk = a.c_transposed ? 1 : a.ccol, bcol = a.bcol;
+                    const int ldc = a.c_transposed ? a.bcol : 1;
+                    asm volatile("" : "+s"(ldk), "+s"(bcol));      // (or addresses and tests are formed, and kept, outside of the loop over blocks)
+#pragma unroll
+                    for (int i = 0; i < KS * V; ++i) {
+                        const int k = KC * (i / V) + V * g + i % V;
+#pragma unroll
+                        for (int nb = 0; nb < NBC; ++nb) {
+                            const int col = min(col0 + 16 * (grp * NBC + nb) + (r & 12), a.ccol - 4) + (r & 3);
+                            const float c = C[k < bcol ? (int64_t)k * ldk + (int64_t)col * ldc : 0];
+                            o[nb] = mfma16(k < bcol ? c : 0.0f, f[i / V][i % V], o[nb]);
+                        }
+                    }
+                });
+            } else {
+                Word4 part[KS2][3];
+#pragma unroll
+                for (int s = 0; s < 2 * KS2; ++s)
+#pragma unroll
+                    for (int q = 0; q < V; q += 2)
+                        split_pair(part[s / 2], s % 2 * 2 + q / 2, s < KS ? f[s][q] : 0.0f, s < KS ? f[s][q + 1] : 0.0f);
+                each_group([&](int grp, Acc(&o)[NBC]) __attribute__((always_inline)) {
+                    const Word4 *Cg = reinterpret_cast<const Word4 *>(Cl) + grp * (NBC * KS2 * 3 * 64) + lane;
+#pragma unroll
+                    for (int s = 0; s < KS2; ++s) {
+                        // (two blocks at a time: a multiplication does not wait for the one before)
+#pragma unroll
+                        for (int nb = 0; nb < NBC; nb += 2) {
+                            constexpr int parts_of_c[] = {2, 0, 1, 1, 0, 0}, parts_of_b[] = {0, 2, 1, 0, 1, 0};
+                            Word4 c[2][3];
+#pragma unroll
+                            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                                for (int i = 0; i < 3; ++i)
+                                    if (nb + j < NBC) c[j][i] = Cg[((s * NBC + nb + j) * 3 + i) * 64];
+#pragma unroll
+                            for (int i = 0; i < 6; ++i)
+#pragma unroll
+                                for (int j = 0; j < 2; ++j)
+                                    if (nb + j < NBC)
+                                        o[nb + j < NBC ? nb + j : 0] = mfma16_bf16(c[j][parts_of_c[i]], part[s][parts_of_b[i]], o[nb + j < NBC ? nb + j : 0]);
+                        }
+                    }
+                });
             }
-        } while (++grp < groups);
+        }
         __builtin_amdgcn_s_setprio(3);
         if (!has_next) break;
+        clear_sums();
         d = dn;
         dn = dnn;
         row = row_n;
@@ -428,20 +650,24 @@ template <typename T, int KS, int NBC> int run_chain(ChainLaunch a, hipStream_t 
     // as chosen: bands of 17 entries, fp64 128 -> 128, n = 4096 34.3 / 21.4, 8192 40.7 / 27.5, 16384 40.9 /
     // 32.1; fp32 128 -> 128 20.1 / 11.8, 23.7 / 13.3, 23.8 / 18.9; with twice the waves 51.5 at n = 16384 in fp64,
     // 34.7 / 24.0 at 32768 in fp32; C of 32 KiB, fp64 32 -> 128, n = 16384, 12.0 / 11.1 with one group each).
-    const int64_t group_lds = (int64_t)NBC * KS * Tr<T>::V * 64 * (int64_t)sizeof(T);
-    const int64_t held = (int64_t)a.n_cu * (a.n_groups * group_lds <= 40 * 1024 ? 4 : 8);
+    // (by the size of C, whatever it takes in LDS)
+    const int64_t group_bytes = (int64_t)NBC * KS * Tr<T>::V * 64 * (int64_t)sizeof(T);
+    const int64_t group_lds = chain_group_lds(dtype_of<T>(), KS, NBC), wave_lds = chain_wave_lds(dtype_of<T>(), KS, NBC);
+    const int64_t held = (int64_t)a.n_cu * (a.n_groups * group_bytes <= 40 * 1024 ? 4 : 8);
     a.groups_per_wg = 1;
     while (a.n_blocks >= 2 * a.n_cu && a.groups_per_wg < a.n_groups &&
            (int64_t)a.n_blocks * ((a.n_groups + a.groups_per_wg - 1) / a.groups_per_wg) > held)
         ++a.groups_per_wg;
+    // (C in three parts may be more than the LDS holds, where C itself is not)
+    while (a.groups_per_wg > 1 && a.groups_per_wg * group_lds + kChainThreads / 64 * wave_lds > a.lds_limit) --a.groups_per_wg;
     const int n_y = (a.n_groups + a.groups_per_wg - 1) / a.groups_per_wg;
-    const int64_t lds_c = a.groups_per_wg * group_lds;
+    const int64_t lds_c = a.groups_per_wg * group_bytes;
     // Waves per workgroup: one copy of C per workgroup, so the more LDS it takes the more waves have
     // to share it; a launch with fewer blocks than the machine has room for is spread thin, as far
     // as a wave does not have to stage more than 8 KiB of C.
     int waves = lds_c <= 40 * 1024 ? 4 : 8;
     while (waves > 1 && (int64_t)a.n_blocks * n_y < (int64_t)a.n_cu * waves && waves * 4096 >= lds_c) waves /= 2;
-    const int64_t lds = lds_c + waves * chain_wave_lds(a.dtype, KS, NBC);
+    const int64_t lds = a.groups_per_wg * group_lds + waves * wave_lds;
     int wg_per_cu = 1;
     {
         std::lock_guard<std::mutex> lock(cs.m);

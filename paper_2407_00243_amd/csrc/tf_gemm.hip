@@ -1,4 +1,4 @@
-// D1 = B C in fp32 for rows of B of up to 128 columns, on the bf16 matrix cores.  Other products: k_gemm in tf_kernels.hip.
+// D1 = B C in fp32 on the bf16 matrix cores (gemm_splits; other products: k_gemm in tf_kernels.hip).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -24,13 +24,13 @@ namespace {
 //
 // Bound by memory.  us, on the fp32 matrix cores / here, and bytes moved: n = 2^20, 128 -> 128, with info words 300 / 218, 4.9
 // TB/s, which is what a copy reaches; n = 150000, 128 -> 41, 36 / 31, 3.7 TB/s; n = 131072, 64 -> 128, 38 / 29.5, 3.4 TB/s.  Of
-// these, lines of D1 and D written whole and not in halves by two instructions: 244 / 231, 31 / 30, 32 / 29.5.  B passes
-// through the L2 without staying there (and D rows that leave here): what the gather that follows reads does stay (128 ->
-// 128: 231 / 218, its gather 700 / 692; 128 -> 41: 30 / 32, 55 / 45; 64 -> 128: the next execution's gather 52 / 47).
+// these, lines of D1 and D written whole and not in halves by two instructions: 244 / 231, 31 / 30, 32 / 29.5.  PASS: B passes
+// through the L2 without staying there (run_split), as rows of D that leave here do: what the gather that follows reads does
+// stay (128 -> 128: 231 / 218, its gather 700 / 692; 128 -> 41: 30 / 32, 55 / 45).
 constexpr int kRowRor8 = 0x128;      // DPP: rotate sixteen lanes by eight
 __device__ __forceinline__ uint32_t other_half(uint32_t x) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, kRowRor8, 0xf, 0xf, false); }
 
-template <int KD, int NB>
+template <int KD, int NB, bool PASS>
 __global__ __launch_bounds__(kFusedThreads) void k_gemm_split(const GemmLaunch a) {
     typedef typename Piece16<float>::Vec Vec;
     const int slice = blockIdx.y;
@@ -57,9 +57,10 @@ __global__ __launch_bounds__(kFusedThreads) void k_gemm_split(const GemmLaunch a
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int h = 0; h < 2; ++h)
-                x[s][i][h] = __builtin_nontemporal_load(
-                    reinterpret_cast<const Vec *>(brow[i] + (s < KD - 1 ? 32 * s + 16 * h + 4 * g : last[h])));
+            for (int h = 0; h < 2; ++h) {
+                const Vec *p = reinterpret_cast<const Vec *>(brow[i] + (s < KD - 1 ? 32 * s + 16 * h + 4 * g : last[h]));
+                x[s][i][h] = PASS ? __builtin_nontemporal_load(p) : *p;
+            }
     };
 
     // C: the first pieces of it are on their way before the first rows of B, and split while these are
@@ -295,34 +296,38 @@ __global__ __launch_bounds__(kFusedThreads) void k_gemm_split(const GemmLaunch a
 
 // ------------------------------------------------------------------------------------------ host
 
-template <int KD, int NB> int run_split(const GemmLaunch &a, hipStream_t st) {
-    const int64_t lds = split_lds_bytes(KD, NB);
+template <int KD, int NB, bool PASS> int run_split2(const GemmLaunch &a, hipStream_t st) {
+    constexpr int64_t lds = split_lds_bytes(KD, NB);
     const int64_t nblk = (a.n + 31) / 32;
-    // as many workgroups as the machine holds at once; few blocks are spread thin (see run_gemm2)
-    int nwaves = kFusedThreads / 64;
-    while (nwaves > 1 && nblk * a.n_slices < (int64_t)a.n_cu * nwaves && nwaves * 2048 >= lds) nwaves /= 2;
+    constexpr int nwaves = kFusedThreads / 64;
     static std::mutex m;
-    static bool raised = false;
-    static int occ_waves = 0, occ = 1;
+    static int occ = 0;
     int wg_per_cu;
     {
         std::lock_guard<std::mutex> lock(m);
-        if (!raised) {
-            const int e = raise_lds_limit(k_gemm_split<KD, NB>, lds);
+        if (!occ) {
+            const int e = raise_lds_limit(k_gemm_split<KD, NB, PASS>, lds);
             if (e) return e;
-            raised = true;
-        }
-        if (nwaves != occ_waves) {
-            occ = resident_per_cu(k_gemm_split<KD, NB>, 64 * nwaves, lds, 16);
-            occ_waves = nwaves;
+            occ = resident_per_cu(k_gemm_split<KD, NB, PASS>, 64 * nwaves, lds, 16);
         }
         wg_per_cu = occ;
     }
+    // as many workgroups as the machine holds at once
     const int64_t most = std::max<int64_t>(1, (int64_t)a.n_cu * wg_per_cu / a.n_slices);
     const int64_t gx = std::min(most, (nblk + nwaves - 1) / nwaves);
     (void)hipGetLastError();
-    k_gemm_split<KD, NB><<<dim3((unsigned)gx, (unsigned)a.n_slices), dim3(64 * nwaves), lds, st>>>(a);
+    k_gemm_split<KD, NB, PASS><<<dim3((unsigned)gx, (unsigned)a.n_slices), dim3(64 * nwaves), lds, st>>>(a);
     return (int)hipGetLastError();
+}
+// Rows of B pass through the L2 without staying there where what is written is more than the L2s hold, which the launch that
+// follows gathers from, and rows of B are whole lines, or a line that a load takes a part of is gone when the next one comes
+// for the rest (whole executions on R-MAT graphs, us, staying / passing: 150000 rows, 128 -> 41 86.0 / 78.4, 64 -> 64 73.9 / 65.7,
+// 2^20 128 -> 128 930 / 910; 19 MB written, 150000 rows, 32 -> 32 35.2 / 38.1, 60000, 128 -> 41 35.9 / 40.3; rows of 400
+// bytes, 150000, 100 -> 100 141.7 / 152.2).
+template <int KD, int NB> int run_split(const GemmLaunch &a, hipStream_t st) {
+    const bool pass = a.bcol % 32 == 0 && a.n * a.d1_cols * 4 >= ((int64_t)32 << 20);
+    if (pass) return run_split2<KD, NB, true>(a, st);
+    return run_split2<KD, NB, false>(a, st);
 }
 
 template <int KD> int run_split_nb(const GemmLaunch &a, hipStream_t st) {

@@ -198,10 +198,15 @@ inline int64_t lds_sparse_b_bytes_per_row(int dtype) {
     return 2 * 8 + kSparseEntryCap * (4 + (int64_t)elem_size(dtype));    // extents of two tiles
 }
 
-// The fp32 product on the bf16 matrix cores (k_gemm_split): rows of B of kSplitMinDepth columns (a sixteen-byte piece) and
-// more, up to kSplitMaxDepth; blocks of sixteen columns that a slice of cs columns takes, and the LDS for C in three parts.
-constexpr int kSplitMinDepth = 4, kSplitMaxDepth = 128;
-inline bool gemm_splits(int dtype, int bcol) { return dtype == TF_F32 && bcol >= kSplitMinDepth && bcol <= kSplitMaxDepth; }
+// The fp32 product on the bf16 matrix cores (k_gemm_split): products of some size, rows of B of up to kSplitMaxDepth columns.
+// Below, the fp32 instructions of k_gemm: their C is laid out sooner and their blocks are half as many rows (whole executions on
+// R-MAT graphs, us, k_gemm / k_gemm_split: 20000 rows 64 -> 64 19.2 / 19.2, 128 -> 41 21.2 / 23.6, 128 -> 128 33.8 / 35.0; 60000
+// rows 8 -> 8 16.5 / 17.6, 64 -> 20 24.1 / 24.4, 16 -> 128 25.2 / 24.1, 32 -> 32 20.8 / 19.3, 128 -> 128 61.4 / 55.8).  Blocks of
+// sixteen columns that a slice of cs columns takes, and the LDS for C in three parts.
+constexpr int kSplitMinDepth = 16, kSplitMaxDepth = 128, kSplitMinCols = 32, kSplitMinRows = 32768;
+inline bool gemm_splits(int dtype, int64_t n, int bcol, int ccol) {
+    return dtype == TF_F32 && n >= kSplitMinRows && bcol >= kSplitMinDepth && bcol <= kSplitMaxDepth && ccol >= kSplitMinCols;
+}
 inline int split_col_blocks(int cs) {
     const int nb = (cs + 15) / 16;
     return nb == 5 ? 6 : nb == 7 ? 8 : nb;
@@ -389,8 +394,11 @@ constexpr int chain_ksteps_below(int dtype, int ks) {
     }
     return below;
 }
-// Entries per row whose gathers are in flight at once (about 24 pieces of 16 bytes per lane).
-constexpr int chain_entries(int ks) { return ks <= 2 ? 8 : ks == 3 ? 6 : ks == 4 ? 5 : ks <= 8 ? 3 : 2; }
+// Entries per row whose gathers are in flight at once (about 24 pieces of 16 bytes per lane; fp64 at depths 8 and 12, whose waves
+// have 256 registers, 40 and 36: bands, 64 -> 64 84 -> 80 us, 96 -> 96 134 -> 126).
+constexpr int chain_entries(int dtype, int ks) {
+    return ks <= 2 ? 8 : ks == 3 ? 6 : ks == 4 ? 5 : ks == 8 && dtype == TF_F64 ? 5 : ks <= 8 || (ks == 12 && dtype == TF_F64) ? 3 : 2;
+}
 // Waves per SIMD that the kernel is held to: where a third one costs no spilled registers (fp64 at depth 2 with
 // four blocks of columns: held to three it spills 12 bytes a lane; bands and 3D stencils, 16 -> 64, us
 // with three and two: 264964 rows of 5 32.9 / 30.9, 60^3 29.9 / 27.5, 439631 rows of 12, 8 -> 64, 63.7 / 61.3).
@@ -407,7 +415,7 @@ inline int chain_col_blocks(int ks, int64_t ccol) {
 }
 // LDS per wave (see k_gather_gemm): loads of 64 entries per pass, k steps per change of lanes, blocks of
 // sixteen columns that leave together, and what that comes to in bytes.
-constexpr int chain_entry_loads(int ks) { return (chain_entries(ks) + 3) / 4; }
+constexpr int chain_entry_loads(int dtype, int ks) { return (chain_entries(dtype, ks) + 3) / 4; }
 constexpr int chain_exchange(int ks) { return ks < 4 ? ks : ks < 16 ? 4 : 2; }
 constexpr int chain_store_blocks(int dtype, int ks, int nbc) {
     return dtype == TF_F32 ? nbc : ks < 16 && nbc % 2 == 0 ? 2 : 1;
@@ -418,9 +426,19 @@ constexpr int chain_exchange_bytes(int dtype, int ks, int nbc) {
     return in > out ? in : out;
 }
 constexpr int64_t chain_wave_lds(int dtype, int ks, int nbc) {
-    return chain_exchange_bytes(dtype, ks, nbc) + 64 + chain_entry_loads(ks) * 64 * (8 + (dtype == TF_F64 ? 8 : 4));
+    return chain_exchange_bytes(dtype, ks, nbc) + 64 + chain_entry_loads(dtype, ks) * 64 * (8 + (dtype == TF_F64 ? 8 : 4));
 }
-// LDS of the largest workgroup: C and the waves' own.
+// Whether the kernel multiplies on the bf16 matrix cores, by operands split in three: rows of B of more than 48 columns
+// (shorter ones: three parts of C take longer to lay out than is saved; us, fp32 instructions / split, 2D stencil 120^2: 8 -> 8
+// 5.1 / 6.1, 16 -> 64 5.7 / 7.0, 32 -> 32 5.5 / 6.6, 50 -> 23 6.4 / 6.1, 128 -> 32 8.8 / 7.8).
+constexpr bool chain_splits(int dtype, int ks) { return dtype == TF_F32 && ks >= 4; }
+// LDS of a group of blocks of columns of C: fp64 as the multiplications take it, fp32 in three parts of bf16 with the largest
+// number of each column.
+constexpr int64_t chain_group_lds(int dtype, int ks, int nbc) {
+    return chain_splits(dtype, ks) ? (int64_t)nbc * ((ks + 1) / 2 * 3 * 1024 + 64) : (int64_t)nbc * ks * 1024;
+}
+// What decides whether a plan may take the one pass: C and the LDS of the waves of the largest workgroup (C in three parts may
+// take more, it is then multiplied by in several workgroups).
 inline int64_t chain_lds_bytes(int dtype, int64_t bcol, int64_t ccol) {
     const int ks = chain_ksteps(dtype, bcol);
     const int64_t nb = (ccol + 15) / 16, nbc = chain_col_blocks(ks, ccol);
@@ -629,6 +647,7 @@ struct ChainLaunch {
     const void *zeros;                // kChainZeroRows x kChainRowBytes
     const void *B, *C;
     void *D;
+    int64_t lds_limit;                // of a workgroup
     int32_t whole_rounds;             // (set by the launcher) rounds of blocks in their order; the rest is dealt out
 };
 

@@ -4,7 +4,7 @@
 //   k_fused_gemm_spmm   first wavefront, dense B   (paper Section 3.2, fused GeMM-SpMM listing)
 //   k_fused_spmm_spmm   first wavefront, CSR B     (Section 3.2, fused SpMM-SpMM listing)
 //   k_gemm              D1 = B C for all rows: the GeMM of the unfused baseline, and the first
-//                       wavefront of a dense-B plan that needs no tile in LDS (fp32 rows of 4 to 128 columns:
+//                       wavefront of a dense-B plan that needs no tile in LDS (large fp32 products:
 //                       k_gemm_split in tf_gemm.hip)
 //
 // A fused workgroup owns one tile (a list of D1 rows) and one column slice.  It produces the
@@ -1389,7 +1389,7 @@ int launch_fused_spmm_spmm(const FusedLaunch &a, void *stream) {
 int launch_gemm(const GemmLaunch &a, void *stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (a.n == 0) return 0;
-    if (gemm_splits(a.dtype, a.bcol)) return launch_gemm_split(a, stream);
+    if (gemm_splits(a.dtype, a.n, a.bcol, a.ccol)) return launch_gemm_split(a, stream);
     // The depth: the smallest one that covers bCol where bCol is all of it, or where rows of B are not
     // aligned.  Aligned rows of other lengths take the loop over k, whose few registers leave room for
     // more waves (graph of 119367 rows, fp32 36 -> 128, whole chain: 146 us, 150 us with the covering
@@ -1402,12 +1402,8 @@ int launch_gemm(const GemmLaunch &a, void *stream) {
     const bool fast = exact || (!covered && a.bcol % v == 0);
     return dispatch_shape(a.dtype, a.cs, covered ? depth * kc : 1, true, [&](auto nb, auto ks) {
         constexpr int NB = decltype(nb)::value, KS = decltype(ks)::value;
-        if (a.dtype == TF_F32) {
-            // (the depths between are those of k_gemm_split)
-            if constexpr (KS == 0 || 16 * KS > kSplitMaxDepth)
-                return fast ? run_gemm<float, NB, KS, true>(a, st) : run_gemm<float, NB, KS, false>(a, st);
-            return (int)hipErrorInvalidValue;
-        }
+        if (a.dtype == TF_F32)
+            return fast ? run_gemm<float, NB, KS, true>(a, st) : run_gemm<float, NB, KS, false>(a, st);
         return fast ? run_gemm<double, NB, KS, true>(a, st) : run_gemm<double, NB, KS, false>(a, st);
     });
 }

@@ -1,4 +1,4 @@
-"""The fp32 product on the bf16 matrix cores (k_gemm_split): operands split in three."""
+"""fp32 products on the bf16 matrix cores (k_gemm_split, k_gather_gemm): operands split in three."""
 import numpy as np
 import pytest
 
@@ -7,35 +7,44 @@ import tf_inputs as ti
 pytestmark = pytest.mark.gpu
 
 
-def _products(B, C, streaming):
-    """B C through the unfused product (A = 1), or through a first wavefront that streams: rows of D that take one row of
-    D1 as it is, from the registers (the first half) or from the workspace (the others, which lie in another tile)."""
+def _products(B, C, how):
+    """B C through the unfused product (A = 1), through the one-pass chain (A = 1; C as it is or transposed), or through a
+    first wavefront that streams: rows of D that take one row of D1 as it is, from the registers (the first half) or
+    from the workspace (the others, which lie in another tile)."""
+    import paper_2407_00243_amd as tf
     from gpu_util import Case
     n = B.shape[0]
     cols = np.arange(n)
-    if streaming:
+    if how == "streaming":
         cols[n // 2:] = np.roll(cols[n // 2:], n // 4)
     A = ti.Csr(n, n, np.arange(n + 1, dtype=np.int32), cols.astype(np.int32), np.ones(n, np.float32))
-    c = Case(ti.Problem("product", "gemm_spmm", np.dtype(np.float32), A, B, C), **(dict(ct_size=16, p=1) if streaming else {}))
+    params = dict(streaming=dict(ct_size=16, p=1), transposed=dict(flags=tf.TF_FLAG_C_TRANSPOSED)).get(how, {})
+    c = Case(ti.Problem("product", "gemm_spmm", np.dtype(np.float32), A, B, C.T.copy() if how == "transposed" else C), **params)
     try:
-        if streaming:
-            assert c.plan.schedule()["first_wavefront_streams"]
-        return c.run(fused=streaming), cols
+        s = c.plan.schedule()
+        if how == "streaming":
+            assert s["first_wavefront_streams"]
+        if how in ("one_pass", "transposed"):
+            assert s["execution"] == tf.TF_EXECUTE_ONE_PASS
+        return c.run(fused=how != "unfused"), cols
     finally:
         c.close()
 
 
-@pytest.mark.parametrize("n,streaming", [(1, False), (16, False), (31, False), (33, False), (4097, False), (70001, False),
-                                         (4097, True), (70001, True)])
-@pytest.mark.parametrize("bcol,ccol", [(4, 1), (5, 4), (31, 16), (32, 17), (33, 41), (64, 96), (65, 33), (96, 50), (100, 100),
+@pytest.mark.parametrize("n,how", [(33, "unfused"), (32768, "unfused"), (32785, "unfused"), (70001, "unfused"),
+                                   (32767, "streaming"), (32799, "streaming"), (70001, "streaming"), (17, "one_pass"),
+                                   (4097, "one_pass"), (70001, "one_pass"), (4097, "transposed")])
+@pytest.mark.parametrize("bcol,ccol", [(4, 1), (15, 32), (16, 32), (17, 33), (31, 41), (32, 31), (33, 48), (64, 96), (65, 33), (96, 50), (100, 100),
                                        (127, 128), (128, 64), (128, 130)])
-def test_products_are_closer_than_sums_rounded_at_every_product(bcol, ccol, n, streaming):
+def test_products_are_closer_than_sums_rounded_at_every_product(bcol, ccol, n, how):
     """Against 64 bits.  The six products of the parts are exact and what is left out is below 2^-26 of a product; with a
     rounding of 2^-24 at each of bcol products the norm of the error stays within 2^-24 sqrt(bcol) of the norm of the
     terms, and so within that of the result (the terms are independent); no element errs by more than bcol of them."""
+    if how in ("one_pass", "transposed") and ccol < 4:
+        ccol = 4                                  # (narrower rows of D take two wavefronts)
     rng = np.random.default_rng(bcol + n)
     B, C = rng.standard_normal((n, bcol), dtype=np.float32), rng.standard_normal((bcol, ccol), dtype=np.float32)
-    got, cols = _products(B, C, streaming)
+    got, cols = _products(B, C, how)
     want = (B.astype(np.float64) @ C.astype(np.float64))[cols]
     W = (np.abs(B).astype(np.float64) @ np.abs(C).astype(np.float64))[cols]
     assert np.all(np.abs(got - want) <= bcol * 2.0 ** -24 * W)
@@ -43,14 +52,14 @@ def test_products_are_closer_than_sums_rounded_at_every_product(bcol, ccol, n, s
         assert np.linalg.norm(got - want) <= 2.0 ** -24 * np.sqrt(bcol) * np.linalg.norm(want)
 
 
-@pytest.mark.parametrize("streaming", [False, True])
-@pytest.mark.parametrize("bcol,ccol", [(6, 20), (32, 32), (50, 23), (128, 96)])
+@pytest.mark.parametrize("how", ["unfused", "streaming", "one_pass", "transposed"])
+@pytest.mark.parametrize("bcol,ccol", [(20, 32), (32, 40), (50, 33), (128, 96)])
 @pytest.mark.parametrize("where", ["B", "C"])
-def test_numbers_that_the_parts_do_not_hold(bcol, ccol, where, streaming):
+def test_numbers_that_the_parts_do_not_hold(bcol, ccol, where, how):
     """Rows of B, or columns of C, of infinities, NaN, numbers near the ends of the type's range and below it, and of these
     among ordinary ones: results as 64 bits give them, infinities and NaN where they belong, to the precision of
     above, and of the smallest normal number for each product."""
-    n = 4100
+    n = 40100 if how in ("unfused", "streaming") else 4100
     rng = np.random.default_rng(bcol)
     B, C = rng.standard_normal((n, bcol), dtype=np.float32), rng.standard_normal((bcol, ccol), dtype=np.float32)
     part = B[100:1100:7] if where == "B" else C.T
@@ -61,7 +70,7 @@ def test_numbers_that_the_parts_do_not_hold(bcol, ccol, where, streaming):
         else:
             part[k, k % bcol] = (np.inf, -np.inf, np.nan, 1e36, 1e-36, 1e-42, 0.0)[k // 2 % 7]
     part[1] = 0
-    got, cols = _products(B, C, streaming)
+    got, cols = _products(B, C, how)
     with np.errstate(invalid="ignore"):
         want = (B.astype(np.float64) @ C.astype(np.float64))[cols]
         W = (np.abs(B).astype(np.float64) @ np.abs(C).astype(np.float64))[cols]
