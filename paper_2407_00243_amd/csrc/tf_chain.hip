@@ -195,14 +195,15 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS, NBC))
     // behind C, per wave: the place where pieces change lanes -- sums into operands (TS x 16 rows x 64
     // bytes; the pieces of a row are swizzled so that the sixteen rows' pieces g sit in different
     // banks), results into rows of D (16 rows of CB blocks and 16 bytes) -- then the offsets of the
-    // rows of D and the entries of a pass (NE x 64 values, then addresses of rows of B)
+    // rows of D and the entries of a pass (ES values, then addresses of rows of B)
+    constexpr int ES = chain_entry_slots(dtype_of<T>(), KS);
     constexpr int NE = chain_entry_loads(dtype_of<T>(), KS), TS = chain_exchange(KS), CB = chain_store_blocks(dtype_of<T>(), KS, NBC);
     constexpr int W = CB * 16 / V, PITCH = W * 16 + 16;
     unsigned char *ex = tf_smem + a.groups_per_wg * (int)chain_group_lds(dtype_of<T>(), KS, NBC) +
                         wave * (int)chain_wave_lds(dtype_of<T>(), KS, NBC);
     uint32_t *er = reinterpret_cast<uint32_t *>(ex + chain_exchange_bytes(dtype_of<T>(), KS, NBC));
     T *ev = reinterpret_cast<T *>(er + 16);
-    uint64_t *ea = reinterpret_cast<uint64_t *>(ev + NE * 64);
+    uint64_t *ea = reinterpret_cast<uint64_t *>(ev + ES);
     const unsigned char *ex_r = ex + r * 64 + (g ^ (r >> 2)) * 16;
 
     // blocks of this wave: every XCD has a contiguous range, through which its waves move side by side
@@ -244,10 +245,11 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS, NBC))
             // (all ones for padding; kept from the compiler, which would make a branch of the choice)
             int32_t pad = ci[e] >> 31;
             asm("" : "+v"(pad));
-            ea[e * 64 + lane] = at ^ ((at ^ zeros) & (uint64_t)(int64_t)pad);
+            if (ES >= e * 64 + 64 || lane < ES - e * 64) ea[e * 64 + lane] = at ^ ((at ^ zeros) & (uint64_t)(int64_t)pad);
         }
 #pragma unroll
-        for (int e = 0; e < NE; ++e) ev[e * 64 + lane] = vi[e];
+        for (int e = 0; e < NE; ++e)
+            if (ES >= e * 64 + 64 || lane < ES - e * 64) ev[e * 64 + lane] = vi[e];
         __builtin_amdgcn_wave_barrier();
     };
     // row of D behind the lane's (virtual) row

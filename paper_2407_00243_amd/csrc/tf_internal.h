@@ -416,6 +416,11 @@ inline int chain_col_blocks(int ks, int64_t ccol) {
 // LDS per wave (see k_gather_gemm): loads of 64 entries per pass, k steps per change of lanes, blocks of
 // sixteen columns that leave together, and what that comes to in bytes.
 constexpr int chain_entry_loads(int dtype, int ks) { return (chain_entries(dtype, ks) + 3) / 4; }
+// (whole loads are put into LDS; fp64 at depth 8, whose C may leave no room for them, keeps to the entries of a pass: the test
+// for them costs 2 to 5 % where launches are small)
+constexpr int chain_entry_slots(int dtype, int ks) {
+    return dtype == TF_F64 && ks == 8 ? 16 * chain_entries(dtype, ks) : 64 * chain_entry_loads(dtype, ks);
+}
 constexpr int chain_exchange(int ks) { return ks < 4 ? ks : ks < 16 ? 4 : 2; }
 constexpr int chain_store_blocks(int dtype, int ks, int nbc) {
     return dtype == TF_F32 ? nbc : ks < 16 && nbc % 2 == 0 ? 2 : 1;
@@ -426,7 +431,7 @@ constexpr int chain_exchange_bytes(int dtype, int ks, int nbc) {
     return in > out ? in : out;
 }
 constexpr int64_t chain_wave_lds(int dtype, int ks, int nbc) {
-    return chain_exchange_bytes(dtype, ks, nbc) + 64 + chain_entry_loads(dtype, ks) * 64 * (8 + (dtype == TF_F64 ? 8 : 4));
+    return chain_exchange_bytes(dtype, ks, nbc) + 64 + chain_entry_slots(dtype, ks) * (8 + (dtype == TF_F64 ? 8 : 4));
 }
 // Whether the kernel multiplies on the bf16 matrix cores, by operands split in three: rows of B of more than 48 columns
 // (shorter ones: three parts of C take longer to lay out than is saved; us, fp32 instructions / split, 2D stencil 120^2: 8 -> 8
@@ -437,13 +442,14 @@ constexpr bool chain_splits(int dtype, int ks) { return dtype == TF_F32 && ks >=
 constexpr int64_t chain_group_lds(int dtype, int ks, int nbc) {
     return chain_splits(dtype, ks) ? (int64_t)nbc * ((ks + 1) / 2 * 3 * 1024 + 64) : (int64_t)nbc * ks * 1024;
 }
-// What decides whether a plan may take the one pass: C and the LDS of the waves of the largest workgroup (C in three parts may
-// take more, it is then multiplied by in several workgroups).
+// What decides whether a plan may take the one pass: C, and for each wave of the largest workgroup the exchange and 64 or 128
+// entries.  The kernel takes as much or, for entries of fp64 at depth 8, 256 bytes more a wave, for which there is room
+// (blocks of columns are 8 KiB there); C in three parts may take more, it is then multiplied by in several workgroups.
 inline int64_t chain_lds_bytes(int dtype, int64_t bcol, int64_t ccol) {
     const int ks = chain_ksteps(dtype, bcol);
     const int64_t nb = (ccol + 15) / 16, nbc = chain_col_blocks(ks, ccol);
     return (nb + nbc - 1) / nbc * nbc * 16 * ks * 4 * vec_elems(dtype) * elem_size(dtype) +
-           kChainThreads / 64 * chain_wave_lds(dtype, ks, (int)nbc);
+           kChainThreads / 64 * (chain_exchange_bytes(dtype, ks, (int)nbc) + 64 + (ks <= 4 ? 128 : 64) * (8 + elem_size(dtype)));
 }
 
 // Host-side schedule produced by the inspector.
