@@ -377,7 +377,8 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS, NBC))
     auto first_count = [&](const ChainBlock &b) { return min(pass_len(b), b.slots); };
 
     uint32_t *cmax = reinterpret_cast<uint32_t *>(tf_smem + groups * (NBC * KS2 * 3 * 1024));
-    bool c_bad = false;      // (fp32) a column of C is outside of the bounds of the split
+    bool c_bad = false;      // (fp32) a column of C is outside of the bounds of the split,
+    float row_least = 0.0f;  // what the largest element of a row may not be below
     // Start-up: the first gathers of the first block go out before C is put into LDS
     {
         const int total = groups * NBC * 16 * KS * 4;
@@ -429,8 +430,7 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS, NBC))
         __builtin_amdgcn_s_waitcnt(0);
         asm volatile("" : : "v"(zeros_ahead));
         if constexpr (SPLIT) {
-            for (int c = lane; c < groups * NBC * 16; c += 64) c_bad |= split_exceeds(__uint_as_float(cmax[c]), kSplitColMin);
-            c_bad = __builtin_amdgcn_ballot_w64(c_bad) != 0;
+            row_least = split_row_least(cmax, groups * NBC * 16, lane, c_bad);
         }
         clear_sums();
         add_first(n, x);
@@ -576,7 +576,7 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS, NBC))
                 for (int q = 0; q < V; q += 2) most = fmaxf(fmaxf(most, fabsf(f[s][q])), fabsf(f[s][q + 1]));
             most = fmaxf(most, __shfl_xor(most, 16, 64));
             most = fmaxf(most, __shfl_xor(most, 32, 64));
-            if (__builtin_amdgcn_ballot_w64(c_bad || split_exceeds(most, kSplitRowMin))) {
+            if (__builtin_amdgcn_ballot_w64(c_bad || split_exceeds(most, row_least))) {
                 each_group([&](int grp, Acc(&o)[NBC]) __attribute__((always_inline)) {
                     const float *C = static_cast<const float *>(a.C);
                     int ldk = a.c_transposed ? 1 : a.ccol, bcol = a.bcol;

@@ -116,11 +116,28 @@ __device__ __forceinline__ floatx4 mfma16_bf16(const Word4 &a, const Word4 &b, f
 }
 // The bf16 matrix cores take numbers below 2^-126 for zeros, and so would parts of small numbers be, or sums of their
 // products; infinities would meet zeros of the other operand's parts.  So a row of the first operand and a column of the
-// second are multiplied this way only if their largest element is 0 or lies within these bounds: what is flushed is then below
-// 2^-36 of the largest product, for 128 of them, and no sum reaches 2^127.
-constexpr float kSplitRowMin = 0x1p-64f, kSplitColMin = 0x1p-30f, kSplitMax = 0x1p60f;
+// second are multiplied this way only if their largest elements are 0 or lie between 2^-90 and 2^60, and so does their product
+// with 2^-94: an element that is flushed is then below 2^-36 of the largest of its row or column, a sum that is flushed below
+// 2^-32 of the largest product, and no sum of 128 products reaches 2^127.
+constexpr float kSplitMin = 0x1p-90f, kSplitMax = 0x1p60f, kSplitProduct = 0x1p-94f;
 __device__ __forceinline__ bool split_exceeds(float largest, float least) {
     return !(largest < kSplitMax) || (largest < least && largest != 0.0f);
+}
+// From the largest elements of the columns (bits): whether one is outside of the bounds, and the least that a row's may be.
+__device__ __forceinline__ float split_row_least(const uint32_t *cmax, int cols, int lane, bool &exceeds) {
+    float least = kSplitMax;
+    bool any = false;
+    for (int c = lane; c < cols; c += 64) {
+        const float m = __uint_as_float(cmax[c]);
+        any |= split_exceeds(m, kSplitMin);
+        if (m > 0.0f) least = fminf(least, m);
+    }
+    exceeds = __builtin_amdgcn_ballot_w64(any) != 0;
+    // (the exchange of the least takes 0.2 us, which small launches show)
+    constexpr float usual = 0x1p-30f;
+    if (__builtin_amdgcn_ballot_w64(least < usual) == 0) return kSplitProduct / usual;
+    for (int i = 1; i < 64; i <<= 1) least = fminf(least, __shfl_xor(least, i, 64));
+    return fmaxf(kSplitMin, kSplitProduct / fmaxf(least, kSplitMin));
 }
 
 // Stores the four columns a lane holds of accumulator block nb to `dst` (which points at the

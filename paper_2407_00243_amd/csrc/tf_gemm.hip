@@ -19,7 +19,7 @@ namespace {
 // (four lanes fetch 64 contiguous bytes); pieces of the last step that would reach past the row are moved back so that they
 // end with it and put right when they have arrived.
 //
-// A block with a row outside the bounds of the split (infinities, numbers that are all below 2^-64), or any block if a column
+// A block with a row outside the bounds of the split (infinities, numbers that are all very small), or any block if a column
 // of C is, is multiplied again by the fp32 instructions (slow_block), which read both operands from memory.
 //
 // Bound by memory.  us, on the fp32 matrix cores / here, and bytes moved: n = 2^20, 128 -> 128, with info words 300 / 218, 4.9
@@ -115,11 +115,8 @@ __global__ __launch_bounds__(kFusedThreads) void k_gemm_split(const GemmLaunch a
         put_c(e0);
     }
     __syncthreads();
-    bool c_bad = false;
-#pragma unroll
-    for (int c = 0; c < NB * 16; c += 64)
-        if (c + lane < NB * 16) c_bad |= split_exceeds(__uint_as_float(cmax[c + lane]), kSplitColMin);
-    c_bad = __builtin_amdgcn_ballot_w64(c_bad) != 0;
+    bool c_bad;
+    const float row_least = split_row_least(cmax, NB * 16, lane, c_bad);
 
     floatx4 acc[2][NB];
     auto slow_block = [&](uint32_t at) __attribute__((always_inline)) {
@@ -228,7 +225,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_gemm_split(const GemmLaunch a
             m = fmaxf(m, __shfl_xor(m, 32, 64));
             // (rows that are not stored may hold anything)
             const bool used = !a.row_info || (info[i] & (kInfoSpill | kInfoDirect));
-            bad |= used && split_exceeds(m, kSplitRowMin);
+            bad |= used && split_exceeds(m, row_least);
         }
         if (__builtin_amdgcn_ballot_w64(bad)) slow_block(lb);
         // Two blocks of columns leave together, eight rows at a time, so that an instruction writes whole lines of 128 bytes: a

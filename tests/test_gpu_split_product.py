@@ -63,7 +63,7 @@ def test_numbers_that_the_parts_do_not_hold(bcol, ccol, where, how):
     rng = np.random.default_rng(bcol)
     B, C = rng.standard_normal((n, bcol), dtype=np.float32), rng.standard_normal((bcol, ccol), dtype=np.float32)
     part = B[100:1100:7] if where == "B" else C.T
-    scales = [np.float32(x) for x in (1e-38, 1e-30, 1e-25, 1e-20, 1e-12, 1e-9, 1e17, 1e19, 1e30, 1e36)]
+    scales = [np.float32(x) for x in (1e-38, 1e-30, 1e-28, 1e-26, 1e-20, 1e-12, 1e17, 1e19, 1e30, 1e36)]
     for k in range(0, len(part), 2):
         if k % 3 == 0:
             part[k] *= scales[k // 2 % len(scales)]
@@ -79,3 +79,20 @@ def test_numbers_that_the_parts_do_not_hold(bcol, ccol, where, how):
     assert np.array_equal(got[inf], want[inf])
     ok = np.isfinite(want)
     assert ok.any() and np.all(np.abs(got[ok] - want[ok]) <= bcol * (2.0 ** -24 * W[ok] + 2.0 ** -126))
+
+
+@pytest.mark.parametrize("how", ["unfused", "one_pass"])
+@pytest.mark.parametrize("row_exp,col_exp", [(-90, 0), (-89, -4), (-47, -47), (-48, -47), (-4, -90), (0, -91), (-91, 0), (59, 59), (60, 0),
+                                             (0, 60)])
+def test_operands_at_the_bounds_of_the_split(row_exp, col_exp, how):
+    """Every row of B and column of C of one magnitude, at and on either side of where the parts cease to hold them."""
+    n, bcol, ccol = (40000, 64, 48) if how == "unfused" else (4100, 64, 48)
+    rng = np.random.default_rng(7)
+    B = (np.ldexp(rng.uniform(0.5, 1.99, (n, bcol)), row_exp) * rng.choice([-1, 1], (n, bcol))).astype(np.float32)
+    C = (np.ldexp(rng.uniform(0.5, 1.99, (bcol, ccol)), col_exp) * rng.choice([-1, 1], (bcol, ccol))).astype(np.float32)
+    got, _ = _products(B, C, how)
+    want = B.astype(np.float64) @ C.astype(np.float64)
+    W = np.abs(B).astype(np.float64) @ np.abs(C).astype(np.float64)
+    assert np.all(np.abs(got - want) <= bcol * (2.0 ** -24 * W + 2.0 ** -126))
+    if row_exp + col_exp > -100:
+        assert np.linalg.norm(got - want) <= 2.0 ** -24 * np.sqrt(bcol) * np.linalg.norm(want)
