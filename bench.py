@@ -305,7 +305,7 @@ def measure(cfg, args, steps, warmup, headline):
     elif not dom_is_wf0:
         kernel = "k_packed_spmm"
     elif sched["first_wavefront_streams"]:
-        kernel = "k_csr_spmm" if sparse else "k_gemm"
+        kernel = "k_csr_spmm" if sparse else "k_gemm_split" if es == 4 else "k_gemm"
     else:
         kernel = "k_fused_" + ("spmm_spmm" if sparse else "gemm_spmm")
     traffic = measured_traffic().get((f"cfg{cfg}", kernel))
