@@ -660,9 +660,14 @@ template <typename T, int KS, int NBC> int run_chain(ChainLaunch a, hipStream_t 
     while (a.n_blocks >= 2 * a.n_cu && a.groups_per_wg < a.n_groups &&
            (int64_t)a.n_blocks * ((a.n_groups + a.groups_per_wg - 1) / a.groups_per_wg) > held)
         ++a.groups_per_wg;
-    // (C in three parts may be more than the LDS holds, where C itself is not)
-    while (a.groups_per_wg > 1 && a.groups_per_wg * group_lds + kChainThreads / 64 * wave_lds > a.lds_limit) --a.groups_per_wg;
-    const int n_y = (a.n_groups + a.groups_per_wg - 1) / a.groups_per_wg;
+    // C in three parts may be more than the LDS holds, where C itself is not: then several workgroups take equal parts of the
+    // column groups
+    int n_y = (a.n_groups + a.groups_per_wg - 1) / a.groups_per_wg;
+    while (a.groups_per_wg > 1 && a.groups_per_wg * group_lds + kChainThreads / 64 * wave_lds > a.lds_limit) {
+        ++n_y;
+        a.groups_per_wg = (a.n_groups + n_y - 1) / n_y;
+    }
+    n_y = (a.n_groups + a.groups_per_wg - 1) / a.groups_per_wg;
     const int64_t lds_c = a.groups_per_wg * group_bytes;
     // Waves per workgroup: one copy of C per workgroup, so the more LDS it takes the more waves have
     // to share it; a launch with fewer blocks than the machine has room for is spread thin, as far

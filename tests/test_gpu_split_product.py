@@ -96,3 +96,14 @@ def test_operands_at_the_bounds_of_the_split(row_exp, col_exp, how):
     assert np.all(np.abs(got - want) <= bcol * (2.0 ** -24 * W + 2.0 ** -126))
     if row_exp + col_exp > -100:
         assert np.linalg.norm(got - want) <= 2.0 ** -24 * np.sqrt(bcol) * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("bcol,ccol", [(128, 144), (128, 160), (128, 200), (96, 250), (64, 400), (52, 447)])
+@pytest.mark.parametrize("n", [500, 30000])
+def test_wide_products_in_several_workgroups(bcol, ccol, n):
+    """The one-pass chain where C in three parts is more than the LDS of a workgroup holds, or nearly so."""
+    rng = np.random.default_rng(ccol)
+    B, C = rng.standard_normal((n, bcol), dtype=np.float32), rng.standard_normal((bcol, ccol), dtype=np.float32)
+    got, _ = _products(B, C, "one_pass")
+    W = np.abs(B).astype(np.float64) @ np.abs(C).astype(np.float64)
+    assert np.all(np.abs(got - B.astype(np.float64) @ C.astype(np.float64)) <= bcol * 2.0 ** -24 * W)
