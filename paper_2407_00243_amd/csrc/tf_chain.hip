@@ -166,7 +166,7 @@ template <typename Vec, int N, int R, int P> struct GatheredPieces {
 // bf16 instructions little more than the longer one).  us, before / with first gathers later and a piece of all entries
 // in turn / on the bf16 matrix cores: 2D stencil 512^2, 64 -> 64 42 / 40 / 34.5, 128 -> 128 108 / 108 / 89; band of 15204
 // rows of 41, 64 -> 64 15.8 / 14.0 / 12.5; 3D stencil 48^3, 64 -> 128 34.4 / 35.2 / 28.5.  Rows of B that are summed up
-// outside of the bounds of the split, or all if a column of C is, take the fp32 instructions, C from memory.
+// outside of the bound of the split, or all if a column of C is, take the fp32 instructions, C from memory.
 template <typename T, int KS, int NBC>
 __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS, NBC)) void k_gather_gemm(
     const ChainLaunch a, const ChainBlock *__restrict__ blocks, const int32_t *__restrict__ rows,
@@ -377,8 +377,7 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS, NBC))
     auto first_count = [&](const ChainBlock &b) { return min(pass_len(b), b.slots); };
 
     uint32_t *cmax = reinterpret_cast<uint32_t *>(tf_smem + groups * (NBC * KS2 * 3 * 1024));
-    bool c_bad = false;      // (fp32) a column of C is outside of the bounds of the split,
-    float row_least = 0.0f;  // what the largest element of a row may not be below
+    bool c_bad = false;      // (fp32) a column of C is outside of the bound of the split
     // Start-up: the first gathers of the first block go out before C is put into LDS
     {
         const int total = groups * NBC * 16 * KS * 4;
@@ -429,9 +428,7 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS, NBC))
         if (blk >= end) return;
         __builtin_amdgcn_s_waitcnt(0);
         asm volatile("" : : "v"(zeros_ahead));
-        if constexpr (SPLIT) {
-            row_least = split_row_least(cmax, groups * NBC * 16, lane, c_bad);
-        }
+        if constexpr (SPLIT) c_bad = split_columns_exceed(cmax, groups * NBC * 16, lane);
         clear_sums();
         add_first(n, x);
     }
@@ -576,7 +573,7 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS, NBC))
                 for (int q = 0; q < V; q += 2) most = fmaxf(fmaxf(most, fabsf(f[s][q])), fabsf(f[s][q + 1]));
             most = fmaxf(most, __shfl_xor(most, 16, 64));
             most = fmaxf(most, __shfl_xor(most, 32, 64));
-            if (__builtin_amdgcn_ballot_w64(c_bad || split_exceeds(most, row_least))) {
+            if (__builtin_amdgcn_ballot_w64(c_bad || split_exceeds(most))) {
                 each_group([&](int grp, Acc(&o)[NBC]) __attribute__((always_inline)) {
                     const float *C = static_cast<const float *>(a.C);
                     int ldk = a.c_transposed ? 1 : a.ccol, bcol = a.bcol;
@@ -622,6 +619,10 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS, NBC))
                                         o[nb + j < NBC ? nb + j : 0] = mfma16_bf16(c[j][parts_of_c[i]], part[s][parts_of_b[i]], o[nb + j < NBC ? nb + j : 0]);
                         }
                     }
+#pragma unroll
+                    for (int nb = 0; nb < NBC; ++nb)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) o[nb][v] *= kSplitUnscale;
                 });
             }
         }

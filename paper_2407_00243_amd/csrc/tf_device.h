@@ -97,8 +97,14 @@ typedef uint32_t Word4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
     return __builtin_bit_cast(uint32_t, Bf16x2{(__bf16)a, (__bf16)b});
 }
-// x[0], x[1] -> words `at` of the three parts
+// The bf16 matrix cores take numbers below 2^-126 for zeros.  Both operands are therefore multiplied by 2^24 first: the last bit
+// of the smallest fp32 number becomes 2^-125, so that no part of any number is lost, and what is lost of a product lies
+// below 2^-174 of the result, far under the spacing of the smallest numbers.  Sums come out 2^48 times too large.
+constexpr float kSplitScale = 0x1p24f, kSplitUnscale = 0x1p-48f;
+// 2^24 a, 2^24 b -> words `at` of the three parts
 __device__ __forceinline__ void split_pair(Word4 (&part)[3], int at, float a, float b) {
+    a *= kSplitScale;
+    b *= kSplitScale;
     const uint32_t h = bf16_pair(a, b);
     a -= __uint_as_float(h << 16);
     b -= __uint_as_float(h & 0xffff0000u);
@@ -114,30 +120,15 @@ __device__ __forceinline__ void split_pair(Word4 (&part)[3], int at, float a, fl
 __device__ __forceinline__ floatx4 mfma16_bf16(const Word4 &a, const Word4 &b, floatx4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(Bf16x8, a), __builtin_bit_cast(Bf16x8, b), c, 0, 0, 0);
 }
-// The bf16 matrix cores take numbers below 2^-126 for zeros, and so would parts of small numbers be, or sums of their
-// products; infinities would meet zeros of the other operand's parts.  So a row of the first operand and a column of the
-// second are multiplied this way only if their largest elements are 0 or lie between 2^-90 and 2^60, and so does their product
-// with 2^-94: an element that is flushed is then below 2^-36 of the largest of its row or column, a sum that is flushed below
-// 2^-32 of the largest product, and no sum of 128 products reaches 2^127.
-constexpr float kSplitMin = 0x1p-90f, kSplitMax = 0x1p60f, kSplitProduct = 0x1p-94f;
-__device__ __forceinline__ bool split_exceeds(float largest, float least) {
-    return !(largest < kSplitMax) || (largest < least && largest != 0.0f);
-}
-// From the largest elements of the columns (bits): whether one is outside of the bounds, and the least that a row's may be.
-__device__ __forceinline__ float split_row_least(const uint32_t *cmax, int cols, int lane, bool &exceeds) {
-    float least = kSplitMax;
+// A row of the first operand and a column of the second are multiplied this way if all their elements are below 2^36: no sum of
+// 128 products reaches 2^127 then.  Infinities, which would meet zeros of the other operand's parts, are beyond as well.
+constexpr float kSplitMax = 0x1p36f;
+__device__ __forceinline__ bool split_exceeds(float largest) { return !(largest < kSplitMax); }
+// From the largest elements of the columns (bits; a NaN counts as more than infinity): whether one is outside of the bound.
+__device__ __forceinline__ bool split_columns_exceed(const uint32_t *cmax, int cols, int lane) {
     bool any = false;
-    for (int c = lane; c < cols; c += 64) {
-        const float m = __uint_as_float(cmax[c]);
-        any |= split_exceeds(m, kSplitMin);
-        if (m > 0.0f) least = fminf(least, m);
-    }
-    exceeds = __builtin_amdgcn_ballot_w64(any) != 0;
-    // (the exchange of the least takes 0.2 us, which small launches show)
-    constexpr float usual = 0x1p-30f;
-    if (__builtin_amdgcn_ballot_w64(least < usual) == 0) return kSplitProduct / usual;
-    for (int i = 1; i < 64; i <<= 1) least = fminf(least, __shfl_xor(least, i, 64));
-    return fmaxf(kSplitMin, kSplitProduct / fmaxf(least, kSplitMin));
+    for (int c = lane; c < cols; c += 64) any |= split_exceeds(__uint_as_float(cmax[c]));
+    return __builtin_amdgcn_ballot_w64(any) != 0;
 }
 
 // Stores the four columns a lane holds of accumulator block nb to `dst` (which points at the

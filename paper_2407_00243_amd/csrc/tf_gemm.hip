@@ -19,8 +19,8 @@ namespace {
 // (four lanes fetch 64 contiguous bytes); pieces of the last step that would reach past the row are moved back so that they
 // end with it and put right when they have arrived.
 //
-// A block with a row outside the bounds of the split (infinities, numbers that are all very small), or any block if a column
-// of C is, is multiplied again by the fp32 instructions (slow_block), which read both operands from memory.
+// A block with a row outside the bound of the split (infinities, numbers from 2^36 on), or any block if a column of C is, is
+// multiplied again by the fp32 instructions (slow_block), which read both operands from memory.
 //
 // Bound by memory.  us, on the fp32 matrix cores / here, and bytes moved: n = 2^20, 128 -> 128, with info words 300 / 218, 4.9
 // TB/s, which is what a copy reaches; n = 150000, 128 -> 41, 36 / 31, 3.7 TB/s; n = 131072, 64 -> 128, 38 / 29.5, 3.4 TB/s.  Of
@@ -115,8 +115,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_gemm_split(const GemmLaunch a
         put_c(e0);
     }
     __syncthreads();
-    bool c_bad;
-    const float row_least = split_row_least(cmax, NB * 16, lane, c_bad);
+    const bool c_bad = split_columns_exceed(cmax, NB * 16, lane);
 
     floatx4 acc[2][NB];
     auto slow_block = [&](uint32_t at) __attribute__((always_inline)) {
@@ -225,9 +224,18 @@ __global__ __launch_bounds__(kFusedThreads) void k_gemm_split(const GemmLaunch a
             m = fmaxf(m, __shfl_xor(m, 32, 64));
             // (rows that are not stored may hold anything)
             const bool used = !a.row_info || (info[i] & (kInfoSpill | kInfoDirect));
-            bad |= used && split_exceeds(m, row_least);
+            bad |= used && split_exceeds(m);
         }
-        if (__builtin_amdgcn_ballot_w64(bad)) slow_block(lb);
+        if (__builtin_amdgcn_ballot_w64(bad)) {
+            slow_block(lb);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) acc[i][nb][v] *= kSplitUnscale;
+        }
         // Two blocks of columns leave together, eight rows at a time, so that an instruction writes whole lines of 128 bytes: a
         // lane changes places with the one eight rows on.
 #pragma unroll

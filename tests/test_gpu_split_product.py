@@ -83,7 +83,7 @@ def test_numbers_that_the_parts_do_not_hold(bcol, ccol, where, how):
 
 @pytest.mark.parametrize("how", ["unfused", "one_pass"])
 @pytest.mark.parametrize("row_exp,col_exp", [(-90, 0), (-89, -4), (-47, -47), (-48, -47), (-4, -90), (0, -91), (-91, 0), (59, 59), (60, 0),
-                                             (0, 60)])
+                                             (0, 60), (35, 35), (36, 0), (0, 36), (-126, 35), (35, -126)])
 def test_operands_at_the_bounds_of_the_split(row_exp, col_exp, how):
     """Every row of B and column of C of one magnitude, at and on either side of where the parts cease to hold them."""
     n, bcol, ccol = (40000, 64, 48) if how == "unfused" else (4100, 64, 48)
@@ -107,3 +107,23 @@ def test_wide_products_in_several_workgroups(bcol, ccol, n):
     got, _ = _products(B, C, "one_pass")
     W = np.abs(B).astype(np.float64) @ np.abs(C).astype(np.float64)
     assert np.all(np.abs(got - B.astype(np.float64) @ C.astype(np.float64)) <= bcol * 2.0 ** -24 * W)
+
+
+@pytest.mark.parametrize("how", ["unfused", "streaming", "one_pass", "transposed"])
+@pytest.mark.parametrize("bcol,ccol", [(32, 40), (64, 33), (128, 96)])
+@pytest.mark.parametrize("b_exp,c_exp", [(-112, 58), (-120, 50), (-60, -60), (-126, 35), (-140, 34), (-20, -105), (34, -140), (-47, -78), (-126, 100)])
+def test_small_elements_whose_row_and_column_have_large_ones_elsewhere(bcol, ccol, b_exp, c_exp, how):
+    """The largest element of a row of B meets a zero of C and the largest of a column of C a zero of B, so that a result is
+    one product of small elements: within 2^-23 for its last sum, which the matrix cores cut off, 2^-24 for what the six
+    products of parts leave out and 2^-28 for sums of small parts, to the spacing of the type's smallest numbers."""
+    n = 40100 if how in ("unfused", "streaming") else 4100
+    rng = np.random.default_rng(bcol)
+    B, C = np.zeros((n, bcol), np.float32), np.zeros((bcol, ccol), np.float32)
+    B[:, 1], C[3, :] = 1.0, 1.0
+    at = bcol - 1 - np.arange(n) % (bcol // 2)
+    small = np.ldexp(rng.uniform(1, 2, n), b_exp) * rng.choice([-1, 1], n)
+    B[np.arange(n), at] = small
+    C[bcol // 2:] = np.ldexp(rng.uniform(1, 2, (bcol - bcol // 2, ccol)), c_exp)
+    got, cols = _products(B, C, how)
+    want = (B[np.arange(n), at].astype(np.float64)[:, None] * C[at].astype(np.float64))[cols]
+    assert np.all(np.abs(got - want) <= (3 + 2.0 ** -4) * 2.0 ** -24 * np.abs(want) + 2.0 ** -149)
