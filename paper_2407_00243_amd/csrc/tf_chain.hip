@@ -146,6 +146,20 @@ __device__ __forceinline__ void write_split(Word4 *Cl, uint32_t *cmax, const flo
     }
 }
 
+// C as it is in the place of its parts (split_whole), all of it by one workgroup.
+template <int KS2, int NBC>
+__device__ __forceinline__ void write_whole(Word4 *Cl, const SplitC &c, bool transposed, int blocks) {
+#pragma unroll 1
+    for (int i = threadIdx.x; i < blocks * KS2 * 128; i += (int)blockDim.x) {
+        const int l = i & 63, half = i >> 6 & 1, s = (i >> 7) % KS2, nbt = (i >> 7) / KS2;
+        const int col = min(16 * nbt + (l & 12), c.cols - 4) + (l & 3), k0 = 32 * s + 16 * half + 4 * (l >> 4);
+        auto number = [&](int k) __attribute__((always_inline)) {
+            return k >= c.bcol ? 0u : __float_as_uint(c.C[transposed ? (int64_t)col * c.bcol + k : (int64_t)k * c.ld + col]);
+        };
+        Cl[(((nbt / NBC * KS2 + s) * NBC + nbt % NBC) * 3 + half) * 64 + l] = Word4{number(k0), number(k0 + 1), number(k0 + 2), number(k0 + 3)};
+    }
+}
+
 // What a pass gathers: N entries of R rows, P pieces each.
 template <typename Vec, int N, int R, int P> struct GatheredPieces {
     Vec v[N][R][P];
@@ -166,7 +180,8 @@ template <typename Vec, int N, int R, int P> struct GatheredPieces {
 // bf16 instructions little more than the longer one).  us, before / with first gathers later and a piece of all entries
 // in turn / on the bf16 matrix cores: 2D stencil 512^2, 64 -> 64 42 / 40 / 34.5, 128 -> 128 108 / 108 / 89; band of 15204
 // rows of 41, 64 -> 64 15.8 / 14.0 / 12.5; 3D stencil 48^3, 64 -> 128 34.4 / 35.2 / 28.5.  Rows of B that are summed up
-// outside of the bound of the split, or all if a column of C is, take the fp32 instructions, C from memory.
+// outside of the bound of the split take the fp32 instructions, and all do if a column of C is, which sits in LDS as it is then
+// (2D stencil 512^2, 128 -> 128: within 70, one column outside 104, every row 128; on the fp32 matrix cores alone 105).
 template <typename T, int KS, int NBC>
 __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS, NBC)) void k_gather_gemm(
     const ChainLaunch a, const ChainBlock *__restrict__ blocks, const int32_t *__restrict__ rows,
@@ -380,7 +395,8 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS, NBC))
     bool c_bad = false;      // (fp32) a column of C is outside of the bound of the split
     // Start-up: the first gathers of the first block go out before C is put into LDS
     {
-        const int total = groups * NBC * 16 * KS * 4;
+        const int total = groups * NBC * 16 * KS * 4, split_items = groups * NBC * KS2 * 16;
+        const SplitC split_from{static_cast<const float *>(a.C) + (a.c_transposed ? (int64_t)col0 * a.bcol : col0), a.ccol, a.bcol, a.ccol - col0};
         CPiece<T> tmp[kStageC];
         GatheredPieces<Vec, EM, RS, KP> x;
         const int n = blk < end ? first_count(d) : 0;
@@ -404,8 +420,8 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS, NBC))
         if constexpr (SPLIT) {
             auto stage_split = [&](auto ct_c) __attribute__((always_inline)) {
                 constexpr bool CT = decltype(ct_c)::value;
-                const int items = groups * NBC * KS2 * 16;
-                const SplitC from{static_cast<const float *>(a.C) + (CT ? (int64_t)col0 * a.bcol : col0), a.ccol, a.bcol, a.ccol - col0};
+                const int items = split_items;
+                const SplitC &from = split_from;
                 Word4 *const to = reinterpret_cast<Word4 *>(Cl);
                 floatx4 y[8];
                 load_split<KS2, CT>(y, from, threadIdx.x, items);
@@ -425,12 +441,20 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS, NBC))
             else stage(std::false_type());
         }
         __syncthreads();
-        if (blk >= end) return;
+        if constexpr (!SPLIT)
+            if (blk >= end) return;
         __builtin_amdgcn_s_waitcnt(0);
         asm volatile("" : : "v"(zeros_ahead));
-        if constexpr (SPLIT) c_bad = split_columns_exceed(cmax, groups * NBC * 16, lane);
         clear_sums();
         add_first(n, x);
+        if constexpr (SPLIT) {
+            c_bad = split_columns_exceed(cmax, groups * NBC * 16, lane);
+            if (c_bad) {      // (all waves of the workgroup; C as it is in the place of its parts)
+                write_whole<KS2, NBC>(reinterpret_cast<Word4 *>(Cl), split_from, a.c_transposed, groups * NBC);
+                __syncthreads();
+            }
+            if (blk >= end) return;
+        }
     }
 
     for (int s0 = pass_len(d);; s0 = 0) {
@@ -575,20 +599,17 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS, NBC))
             most = fmaxf(most, __shfl_xor(most, 32, 64));
             if (__builtin_amdgcn_ballot_w64(c_bad || split_exceeds(most))) {
                 each_group([&](int grp, Acc(&o)[NBC]) __attribute__((always_inline)) {
-                    const float *C = static_cast<const float *>(a.C);
-                    int ldk = a.c_transposed ? 1 : a.ccol, bcol = a.bcol;
-                    const int ldc = a.c_transposed ? a.bcol : 1;
-                    asm volatile("" : "+s"(ldk), "+s"(bcol));      // (or addresses and tests are formed, and kept, outside of the loop over blocks)
+                    const Word4 *Cg = reinterpret_cast<const Word4 *>(Cl) + grp * (NBC * KS2 * 3 * 64) + lane;
 #pragma unroll
-                    for (int i = 0; i < KS * V; ++i) {
-                        const int k = KC * (i / V) + V * g + i % V;
+                    for (int s = 0; s < KS2; ++s)
 #pragma unroll
                         for (int nb = 0; nb < NBC; ++nb) {
-                            const int col = min(col0 + 16 * (grp * NBC + nb) + (r & 12), a.ccol - 4) + (r & 3);
-                            const float c = C[k < bcol ? (int64_t)k * ldk + (int64_t)col * ldc : 0];
-                            o[nb] = mfma16(k < bcol ? c : 0.0f, f[i / V][i % V], o[nb]);
+                            float c[8];
+                            split_whole(c, Cg + (s * NBC + nb) * 3 * 64, c_bad);
+#pragma unroll
+                            for (int q = 0; q < 8; ++q)
+                                if (2 * s + q / 4 < KS) o[nb] = mfma16(c[q], f[2 * s + q / 4 < KS ? 2 * s + q / 4 : 0][q % 4], o[nb]);
                         }
-                    }
                 });
             } else {
                 Word4 part[KS2][3];

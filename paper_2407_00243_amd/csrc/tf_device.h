@@ -131,6 +131,27 @@ __device__ __forceinline__ bool split_columns_exceed(const uint32_t *cmax, int c
     return __builtin_amdgcn_ballot_w64(any) != 0;
 }
 
+// Eight numbers of an operand in LDS: put together again from their parts, which takes nothing from them, or as they are
+// (`whole`) in the place of the first two parts.
+__device__ __forceinline__ void split_whole(float (&x)[8], const Word4 *at, bool whole) {
+    const Word4 h = at[0], m = at[64];
+    if (whole) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            x[q] = __uint_as_float(h[q]);
+            x[4 + q] = __uint_as_float(m[q]);
+        }
+        return;
+    }
+    const Word4 l = at[128];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        x[2 * q] = (__uint_as_float(h[q] << 16) + (__uint_as_float(m[q] << 16) + __uint_as_float(l[q] << 16))) * (1.0f / kSplitScale);
+        x[2 * q + 1] = (__uint_as_float(h[q] & 0xffff0000u) + (__uint_as_float(m[q] & 0xffff0000u) + __uint_as_float(l[q] & 0xffff0000u))) *
+                       (1.0f / kSplitScale);
+    }
+}
+
 // Stores the four columns a lane holds of accumulator block nb to `dst` (which points at the
 // lane's first column, 16 nb + 4 g), keeping to columns below w: 16-byte pieces, at whatever element
 // they begin, and the columns of a block that w cuts one by one.

@@ -19,8 +19,10 @@ namespace {
 // (four lanes fetch 64 contiguous bytes); pieces of the last step that would reach past the row are moved back so that they
 // end with it and put right when they have arrived.
 //
-// A block with a row outside the bound of the split (infinities, numbers from 2^36 on), or any block if a column of C is, is
-// multiplied again by the fp32 instructions (slow_block), which read both operands from memory.
+// A block with a row outside the bound of the split (infinities, numbers from 2^36 on) is multiplied again by the fp32
+// instructions (fp32_block), which read B from memory and put C together from its parts.  Where a column of C is outside, C is put
+// into LDS as it is, and all blocks go there alone (whole executions, R-MAT graph of 2^20 rows, 128 -> 128, us: within the bound 905,
+// one column outside 1080, every row 1233, by k_gemm 990).
 //
 // Bound by memory.  us, on the fp32 matrix cores / here, and bytes moved: n = 2^20, 128 -> 128, with info words 300 / 218, 4.9
 // TB/s, which is what a copy reaches; n = 150000, 128 -> 41, 36 / 31, 3.7 TB/s; n = 131072, 64 -> 128, 38 / 29.5, 3.4 TB/s.  Of
@@ -80,6 +82,17 @@ __global__ __launch_bounds__(kFusedThreads) void k_gemm_split(const GemmLaunch a
             }
         }
     };
+    auto put_c_whole = [&](int e0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < NC; ++u) {
+            const int e = e0 + u * (int)blockDim.x;
+            if (e >= KD * NB * 64) break;
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+                Cl[((e >> 6) * 3 + p) * 64 + (e & 63)] = Word4{__float_as_uint(y[u][4 * p]), __float_as_uint(y[u][4 * p + 1]),
+                                                               __float_as_uint(y[u][4 * p + 2]), __float_as_uint(y[u][4 * p + 3])};
+        }
+    };
     auto put_c = [&](int e0) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < NC; ++u) {
@@ -116,27 +129,54 @@ __global__ __launch_bounds__(kFusedThreads) void k_gemm_split(const GemmLaunch a
     }
     __syncthreads();
     const bool c_bad = split_columns_exceed(cmax, NB * 16, lane);
+    if (c_bad) {      // (all waves of the workgroup; C as it is in the place of its parts)
+        for (int e0 = (int)threadIdx.x; e0 < KD * NB * 64; e0 += NC * (int)blockDim.x) {
+            load_c(e0);
+            put_c_whole(e0);
+        }
+        __syncthreads();
+    }
 
-    floatx4 acc[2][NB];
-    auto slow_block = [&](uint32_t at) __attribute__((always_inline)) {
-        int ws = w;      // (or the tests for every block of columns are made, and kept, outside of the loop)
-        asm volatile("" : "+s"(ws));
+    // pieces of the last step that were moved back
+    auto set_right = [&](Vec &x, int h) __attribute__((always_inline)) {
+        const int back = 32 * (KD - 1) + 16 * h + 4 * g - last[h];
+        Vec t;
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const float *brow = row_at(at, i);
+        for (int q = 0; q < 4; ++q) {
+            t[q] = 0.0f;
+#pragma unroll
+            for (int j = q; j < 4; ++j)
+                if (back == j - q) t[q] = x[j];
+        }
+        x = t;
+    };
+    floatx4 acc[2][NB];
+    auto fp32_block = [&](uint32_t at) __attribute__((always_inline)) {
+        const float *brow[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) brow[i] = row_at(at, i);
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) acc[i][nb] = floatx4{0, 0, 0, 0};
 #pragma unroll 1
-            for (int kq = 0; kq < KD * 32; ++kq) {
-                const int k = kq / 4 * 16 + 4 * g + kq % 4;
-                if (kq / 4 * 16 >= a.bcol) break;
-                const float b = k < a.bcol ? brow[k] : 0.0f;
+        for (int s = 0; s < KD; ++s) {
+            Vec b[2][2];
 #pragma unroll
-                for (int nb = 0; nb < NB; ++nb) {
-                    const bool in = k < a.bcol && 16 * nb + r < ws;
-                    const float c = C[in ? (int64_t)k * a.c_ldk + (int64_t)(c0 + 16 * nb + r) * a.c_ldc : 0];
-                    acc[i][nb] = mfma16(in ? c : 0.0f, b, acc[i][nb]);
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    b[i][h] = *reinterpret_cast<const Vec *>(brow[i] + (s < KD - 1 ? 32 * s + 16 * h + 4 * g : last[h]));
+                    if (s == KD - 1 && a.bcol != 32 * KD) set_right(b[i][h], h);
                 }
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) {
+                float c[8];
+                split_whole(c, Cl + (s * NB + nb) * 3 * 64 + lane, c_bad);
+#pragma unroll
+                for (int q = 0; q < 8; ++q)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) acc[i][nb] = mfma16(c[q], b[i][q / 4][q % 4], acc[i][nb]);
             }
         }
     };
@@ -162,23 +202,12 @@ __global__ __launch_bounds__(kFusedThreads) void k_gemm_split(const GemmLaunch a
             for (int nb = 0; nb < NB; ++nb) acc[i][nb] = floatx4{0, 0, 0, 0};
 #pragma unroll
         for (int s = 0; s < KD; ++s) {
+            if (c_bad) break;
             if (s == KD - 1 && a.bcol != 32 * KD) {
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const int back = 32 * s + 16 * h + 4 * g - last[h];
+                for (int h = 0; h < 2; ++h)
 #pragma unroll
-                    for (int i = 0; i < 2; ++i) {
-                        Vec t;
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            t[q] = 0.0f;
-#pragma unroll
-                            for (int j = q; j < 4; ++j)
-                                if (back == j - q) t[q] = x[s][i][h][j];
-                        }
-                        x[s][i][h] = t;
-                    }
-                }
+                    for (int i = 0; i < 2; ++i) set_right(x[s][i][h], h);
             }
             Word4 part[2][3];
 #pragma unroll
@@ -227,7 +256,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_gemm_split(const GemmLaunch a
             bad |= used && split_exceeds(m);
         }
         if (__builtin_amdgcn_ballot_w64(bad)) {
-            slow_block(lb);
+            fp32_block(lb);
         } else {
 #pragma unroll
             for (int i = 0; i < 2; ++i)
