@@ -620,12 +620,13 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS, NBC))
                         split_pair(part[s / 2], s % 2 * 2 + q / 2, s < KS ? f[s][q] : 0.0f, s < KS ? f[s][q + 1] : 0.0f);
                 each_group([&](int grp, Acc(&o)[NBC]) __attribute__((always_inline)) {
                     const Word4 *Cg = reinterpret_cast<const Word4 *>(Cl) + grp * (NBC * KS2 * 3 * 64) + lane;
+                    // (two blocks at a time: a multiplication does not wait for the one before)
 #pragma unroll
-                    for (int s = 0; s < KS2; ++s) {
-                        // (two blocks at a time: a multiplication does not wait for the one before)
+                    for (int nb = 0; nb < NBC; nb += 2) {
+                        constexpr int NP = 6, parts_of_c[NP] = {2, 0, 1, 1, 0, 0}, parts_of_b[NP] = {0, 2, 1, 0, 1, 0};
+                        Acc high[2] = {}, small[2] = {};
 #pragma unroll
-                        for (int nb = 0; nb < NBC; nb += 2) {
-                            constexpr int parts_of_c[] = {2, 0, 1, 1, 0, 0}, parts_of_b[] = {0, 2, 1, 0, 1, 0};
+                        for (int s = 0; s < KS2; ++s) {
                             Word4 c[2][3];
 #pragma unroll
                             for (int j = 0; j < 2; ++j)
@@ -633,17 +634,18 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS, NBC))
                                 for (int i = 0; i < 3; ++i)
                                     if (nb + j < NBC) c[j][i] = Cg[((s * NBC + nb + j) * 3 + i) * 64];
 #pragma unroll
-                            for (int i = 0; i < 6; ++i)
+                            for (int i = 0; i < NP; ++i)
 #pragma unroll
-                                for (int j = 0; j < 2; ++j)
-                                    if (nb + j < NBC)
-                                        o[nb + j < NBC ? nb + j : 0] = mfma16_bf16(c[j][parts_of_c[i]], part[s][parts_of_b[i]], o[nb + j < NBC ? nb + j : 0]);
+                                for (int j = 0; j < 2; ++j) {
+                                    if (nb + j >= NBC) continue;
+                                    Acc &sum = i == NP - 1 ? high[j] : small[j];
+                                    sum = mfma16_bf16(c[j][parts_of_c[i]], part[s][parts_of_b[i]], sum);
+                                }
                         }
+#pragma unroll
+                        for (int j = 0; j < 2; ++j)
+                            if (nb + j < NBC) o[nb + j < NBC ? nb + j : 0] = split_sum(high[j], small[j]);
                     }
-#pragma unroll
-                    for (int nb = 0; nb < NBC; ++nb)
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) o[nb][v] *= kSplitUnscale;
                 });
             }
         }

@@ -86,11 +86,13 @@ template <typename T, int N> __device__ __forceinline__ void store_any(T *p, con
 
 // fp32 products on the bf16 matrix cores (16 times the rate of the fp32 ones, and unlike these they run beside other vector
 // instructions of their SIMD).  x = h + m + l, each rounded to nearest even: 24 bits in three times eight, nothing is lost.
-// A product of two such sums is taken without m l, l m and l l, which lie below 2^-26 of it; all six others are exact, and
-// their sums are rounded once per 32 of them, the small ones before h h: against 64 bits the sums are closer than those of
-// the fp32 instructions, which round at every product (normal operands, relative error of 8192 x 16 sums of 8 / 16 / 32 / 64 /
-// 128 products: 3.4e-8 / 3.6e-8 / 3.8e-8 / 9.2e-8 / 1.5e-7, fp32 instructions 5.3e-8 / 7.3e-8 / 1.1e-7 / 1.4e-7 / 2.1e-7; all nine
-// products: the same).
+// All products of two parts are exact.  An instruction adds up the eight products that a lane supplies, and the accumulator if it
+// is the smaller one, cut off at 2^-24 of the largest (measured), and rounds their sum with the accumulator.  So the products h h,
+// of 16 bits, have accumulators of their own, in which little is cut off and one rounding in eight products is made, and
+// the small products others, whose errors are below 2^-31; both sums are joined by one rounded addition (split_sum).  With
+// both in one accumulator the small ones, or h h of the next step, were cut off: relative error of 40000 x 64 sums of 2 / 8 /
+// 16 / 64 products against 64 bits 4.4e-8 / 9.1e-8 / 1.2e-7 / 1.5e-7, by the fp32 instructions 3.1e-8 / 5.3e-8 / 7.4e-8 / 1.5e-7.
+// (Of the nine products of parts m l, l m and l l are left out, just under 2^-24 of the product at most.)
 typedef __bf16 Bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 Bf16x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t Word4 __attribute__((ext_vector_type(4)));
@@ -119,6 +121,13 @@ __device__ __forceinline__ void split_pair(Word4 (&part)[3], int at, float a, fl
 // results as for fp32 above.
 __device__ __forceinline__ floatx4 mfma16_bf16(const Word4 &a, const Word4 &b, floatx4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(Bf16x8, a), __builtin_bit_cast(Bf16x8, b), c, 0, 0, 0);
+}
+// Results from the sums of h h and those of the small products.
+__device__ __forceinline__ floatx4 split_sum(const floatx4 &high, const floatx4 &small) {
+    floatx4 y;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) y[v] = (high[v] + small[v]) * kSplitUnscale;
+    return y;
 }
 // A row of the first operand and a column of the second are multiplied this way if all their elements are below 2^36: no sum of
 // 128 products reaches 2^127 then.  Infinities, which would meet zeros of the other operand's parts, are beyond as well.

@@ -11,18 +11,18 @@ namespace {
 
 // A wave multiplies blocks of 32 rows of B (two blocks of sixteen, so that what is read of C from LDS is used twice: its
 // reads then take half of what the LDS delivers).  C sits in LDS in three parts (split_pair), in operand order: per step of
-// 32 k, per block of sixteen columns, per part sixteen bytes for each lane.  Rows of B are split as their step comes, and the
-// same step of the wave's next block is fetched into the registers that this frees: a block's loads are on their way for as
-// long as a block is multiplied, ahead of its stores, which they do not wait for.
+// 32 k, per block of sixteen columns, per part sixteen bytes for each lane.  Rows of B are split when all of them are there, and
+// the wave's next block is fetched into the registers that this frees: a block's loads are on their way for as long as a block
+// is multiplied, ahead of its stores, which they do not wait for.  The parts stay in registers, and blocks of columns are
+// multiplied and leave two at a time, so that few accumulators are needed.
 //
 // Lane group g = lane / 16 holds of step s the elements k = 32 s + 4 g + {0 .. 3} and 32 s + 16 + 4 g + {0 .. 3} of its rows
 // (four lanes fetch 64 contiguous bytes); pieces of the last step that would reach past the row are moved back so that they
 // end with it and put right when they have arrived.
 //
-// A block with a row outside the bound of the split (infinities, numbers from 2^36 on) is multiplied again by the fp32
-// instructions (fp32_block), which read B from memory and put C together from its parts.  Where a column of C is outside, C is put
-// into LDS as it is, and all blocks go there alone (whole executions, R-MAT graph of 2^20 rows, 128 -> 128, us: within the bound 905,
-// one column outside 1080, every row 1233, by k_gemm 990).
+// A block with a row outside the bound of the split (infinities, numbers from 2^36 on) takes the fp32 instructions, C put together
+// from its parts.  Where a column of C is outside, C is put into LDS as it is, and all blocks go there (whole executions,
+// R-MAT graph of 2^20 rows, 128 -> 128, us: within the bound 934, one column outside 1066, every row 1126, by k_gemm 985).
 //
 // Bound by memory.  us, on the fp32 matrix cores / here, and bytes moved: n = 2^20, 128 -> 128, with info words 300 / 218, 4.9
 // TB/s, which is what a copy reaches; n = 150000, 128 -> 41, 36 / 31, 3.7 TB/s; n = 131072, 64 -> 128, 38 / 29.5, 3.4 TB/s.  Of
@@ -150,45 +150,14 @@ __global__ __launch_bounds__(kFusedThreads) void k_gemm_split(const GemmLaunch a
         }
         x = t;
     };
-    floatx4 acc[2][NB];
-    auto fp32_block = [&](uint32_t at) __attribute__((always_inline)) {
-        const float *brow[2];
-#pragma unroll
-        for (int i = 0; i < 2; ++i) brow[i] = row_at(at, i);
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) acc[i][nb] = floatx4{0, 0, 0, 0};
-#pragma unroll 1
-        for (int s = 0; s < KD; ++s) {
-            Vec b[2][2];
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    b[i][h] = *reinterpret_cast<const Vec *>(brow[i] + (s < KD - 1 ? 32 * s + 16 * h + 4 * g : last[h]));
-                    if (s == KD - 1 && a.bcol != 32 * KD) set_right(b[i][h], h);
-                }
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) {
-                float c[8];
-                split_whole(c, Cl + (s * NB + nb) * 3 * 64 + lane, c_bad);
-#pragma unroll
-                for (int q = 0; q < 8; ++q)
-#pragma unroll
-                    for (int i = 0; i < 2; ++i) acc[i][nb] = mfma16(c[q], b[i][q / 4][q % 4], acc[i][nb]);
-            }
-        }
-    };
-
+    // (without info words any words are read: a load behind a branch is waited for there)
+    const uint32_t *infos = a.row_info ? a.row_info : static_cast<const uint32_t *>(a.B);
+    const float *scales = a.row_scale ? static_cast<const float *>(a.row_scale) : B;
     for (; lb < lb1; lb += nwaves) {
         // (the reads of C stay in the loop: in registers they would not fit)
-        if constexpr (KD * NB * 12 > 48) asm volatile("" ::: "memory");
-        // (without info words any words are read: a load behind a branch is waited for there)
-        const uint32_t *infos = a.row_info ? a.row_info : static_cast<const uint32_t *>(a.B);
-        const float *scales = a.row_scale ? static_cast<const float *>(a.row_scale) : B;
+        asm volatile("" ::: "memory");
         uint32_t info[2];
-        float scale[2], most[2] = {0.0f, 0.0f};
+        float scale[2];
         const float *brow[2];
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
@@ -196,119 +165,142 @@ __global__ __launch_bounds__(kFusedThreads) void k_gemm_split(const GemmLaunch a
             scale[i] = scales[row_of(lb, i)];
             brow[i] = row_at(lb + nwaves, i);
         }
+        if (a.bcol != 32 * KD) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+            for (int h = 0; h < 2; ++h)
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) acc[i][nb] = floatx4{0, 0, 0, 0};
+                for (int i = 0; i < 2; ++i) set_right(x[KD - 1][i][h], h);
+        }
+        Word4 part[KD][2][3];
+        float most[2] = {0.0f, 0.0f};
 #pragma unroll
-        for (int s = 0; s < KD; ++s) {
-            if (c_bad) break;
-            if (s == KD - 1 && a.bcol != 32 * KD) {
-#pragma unroll
-                for (int h = 0; h < 2; ++h)
-#pragma unroll
-                    for (int i = 0; i < 2; ++i) set_right(x[s][i][h], h);
-            }
-            Word4 part[2][3];
+        for (int s = 0; s < KD; ++s)
 #pragma unroll
             for (int i = 0; i < 2; ++i)
 #pragma unroll
                 for (int h = 0; h < 2; ++h)
 #pragma unroll
-                    for (int q = 0; q < 4; q += 2) {
-                        most[i] = fmaxf(fmaxf(most[i], fabsf(x[s][i][h][q])), fabsf(x[s][i][h][q + 1]));
-                        split_pair(part[i], 2 * h + q / 2, x[s][i][h][q], x[s][i][h][q + 1]);
-                    }
-            // (the next block's loads after the split, whose registers they take, and ahead of the multiplications)
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                asm volatile("" : "+v"(most[i]));
-#pragma unroll
-                for (int p = 0; p < 3; ++p) asm volatile("" : "+v"(part[i][p]));
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            load_step(s, brow);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) {
-                const Word4 *c = Cl + (s * NB + nb) * 3 * 64 + lane;
-                const Word4 ch = c[0], cm = c[64], cl = c[128];
-#define TF_MFMA(CP, BP)                                                                \
-    acc[0][nb] = mfma16_bf16(CP, part[0][BP], acc[0][nb]);                             \
-    acc[1][nb] = mfma16_bf16(CP, part[1][BP], acc[1][nb])
-                TF_MFMA(cl, 0);
-                TF_MFMA(ch, 2);
-                TF_MFMA(cm, 1);
-                TF_MFMA(cm, 0);
-                TF_MFMA(ch, 1);
-                TF_MFMA(ch, 0);
-#undef TF_MFMA
-            }
-        }
+                    for (int q = 0; q < 4; q += 2) most[i] = fmaxf(fmaxf(most[i], fabsf(x[s][i][h][q])), fabsf(x[s][i][h][q + 1]));
         bool bad = c_bad;
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-            asm volatile("" : "+v"(info[i]), "+v"(scale[i]));      // (here, not where they are fetched)
             float m = fmaxf(most[i], __shfl_xor(most[i], 16, 64));
             m = fmaxf(m, __shfl_xor(m, 32, 64));
             // (rows that are not stored may hold anything)
             const bool used = !a.row_info || (info[i] & (kInfoSpill | kInfoDirect));
             bad |= used && split_exceeds(m);
         }
-        if (__builtin_amdgcn_ballot_w64(bad)) {
-            fp32_block(lb);
-        } else {
+        const bool fp32 = __builtin_amdgcn_ballot_w64(bad) != 0;
+        if (!fp32) {
+#pragma unroll
+            for (int s = 0; s < KD; ++s) {
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+#pragma unroll
+                        for (int q = 0; q < 4; q += 2) split_pair(part[s][i], 2 * h + q / 2, x[s][i][h][q], x[s][i][h][q + 1]);
+                // (the next block's loads after the split, whose registers they take, and ahead of the multiplications)
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int p = 0; p < 3; ++p) asm volatile("" : "+v"(part[s][i][p]));
+                __builtin_amdgcn_sched_barrier(0);
+                load_step(s, brow);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+
+        // N blocks of columns from nb on: products and stores
+        auto columns = [&](auto n_c, int nb) __attribute__((always_inline)) {
+            constexpr int N = decltype(n_c)::value;
+            floatx4 acc[2][N];
 #pragma unroll
             for (int i = 0; i < 2; ++i)
 #pragma unroll
-                for (int nb = 0; nb < NB; ++nb)
+                for (int j = 0; j < N; ++j) acc[i][j] = floatx4{0, 0, 0, 0};
+            if (!fp32) {
+                floatx4 small[2][N];
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) acc[i][nb][v] *= kSplitUnscale;
-        }
-        // Two blocks of columns leave together, eight rows at a time, so that an instruction writes whole lines of 128 bytes: a
-        // lane changes places with the one eight rows on.
+                for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const uint32_t row0 = lb * 32 + 16 * i;
-            const uint32_t ri = row0 + r < n ? d1_info(a.row_info != nullptr, info[i]) : 0u, rx = other_half(ri);
-            const float scale_x = __uint_as_float(other_half(__float_as_uint(scale[i])));
-            // (to_d1: rows of the workspace, else of D)
-            auto store = [&](auto to_d1) __attribute__((always_inline)) {
-                constexpr bool TO_D1 = decltype(to_d1)::value;
-                constexpr uint32_t kinds = TO_D1 ? kInfoSpill : kInfoDirect | kInfoZero;
-                if (__builtin_amdgcn_ballot_w64((ri & kinds) != 0) == 0) return;
-                const int ws = TO_D1 ? w_d1 : w;
-                auto row_start = [&](uint32_t info, uint32_t row) __attribute__((always_inline)) {
-                    if constexpr (TO_D1) return D1 + d1_slot(a.row_info != nullptr, info, row) * a.d1_sw + 4 * g;
-                    else return D + (int64_t)row * a.ccol + c0 + 4 * g;
-                };
-                auto scaled = [&](floatx4 y, uint32_t info, float by) __attribute__((always_inline)) {
-                    if constexpr (!TO_D1)
+                    for (int j = 0; j < N; ++j) small[i][j] = floatx4{0, 0, 0, 0};
 #pragma unroll
-                        for (int v = 0; v < 4; ++v) y[v] = info & kInfoZero ? 0.0f : by * y[v];
-                    return y;
-                };
-                auto at_col = [&](int nb) __attribute__((always_inline)) {
-                    const int cb = c0 + 16 * nb;        // the workspace is cut into slices of d1_sw columns
-                    return TO_D1 ? (int64_t)(cb >> a.d1_sw_shift) * a.d1_slice_stride + (cb & a.d1_sw_mask) : 16 * nb;
-                };
-                const bool low = r < 8;
-                const uint32_t r0 = low ? ri : rx, r1 = low ? rx : ri;
-                const float s0 = low ? scale[i] : scale_x, s1 = low ? scale_x : scale[i];
-                float *own = row_start(ri, row0 + r), *dst0 = row_start(r0, row0 + (r & 7)) + (low ? 0 : 16),
-                      *dst1 = row_start(r1, row0 + 8 + (r & 7)) + (low ? 0 : 16);
+                for (int s = 0; s < KD; ++s) {
 #pragma unroll
-                for (int nb = 0; nb < NB; nb += 2) {
-                    const bool pair = nb + 1 < NB && 16 * nb + 32 <= ws && (!TO_D1 || ((c0 + 16 * nb) & a.d1_sw_mask) + 32 <= a.d1_sw);
+                    for (int j = 0; j < N; ++j) {
+                        Word4 c[3];
+#pragma unroll
+                        for (int p = 0; p < 3; ++p) c[p] = Cl[((s * NB + nb + j) * 3 + p) * 64 + lane];
+                        auto multiply = [&](floatx4(&sums)[2][N], int cp, int bp) __attribute__((always_inline)) {
+#pragma unroll
+                            for (int i = 0; i < 2; ++i) sums[i][j] = mfma16_bf16(c[cp], part[s][i][bp], sums[i][j]);
+                        };
+                        multiply(small, 2, 0);
+                        multiply(acc, 0, 0);
+                        multiply(small, 0, 2);
+                        multiply(small, 1, 1);
+                        multiply(small, 1, 0);
+                        multiply(small, 0, 1);
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int j = 0; j < N; ++j) acc[i][j] = split_sum(acc[i][j], small[i][j]);
+            } else {
+#pragma unroll
+                for (int s = 0; s < KD; ++s)
+#pragma unroll
+                    for (int j = 0; j < N; ++j) {
+                        float c[8];
+                        split_whole(c, Cl + (s * NB + nb + j) * 3 * 64 + lane, c_bad);
+#pragma unroll
+                        for (int q = 0; q < 8; ++q)
+#pragma unroll
+                            for (int i = 0; i < 2; ++i) acc[i][j] = mfma16(c[q], x[s][i][q / 4][q % 4], acc[i][j]);
+                    }
+            }
+            // Two blocks of columns leave together, eight rows at a time, so that an instruction writes whole lines of 128 bytes: a
+            // lane changes places with the one eight rows on.
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const uint32_t row0 = lb * 32 + 16 * i;
+                const uint32_t ri = row0 + r < n ? d1_info(a.row_info != nullptr, info[i]) : 0u, rx = other_half(ri);
+                const float scale_x = __uint_as_float(other_half(__float_as_uint(scale[i])));
+                // (to_d1: rows of the workspace, else of D)
+                auto store = [&](auto to_d1) __attribute__((always_inline)) {
+                    constexpr bool TO_D1 = decltype(to_d1)::value;
+                    constexpr uint32_t kinds = TO_D1 ? kInfoSpill : kInfoDirect | kInfoZero;
+                    if (__builtin_amdgcn_ballot_w64((ri & kinds) != 0) == 0) return;
+                    const int ws = TO_D1 ? w_d1 : w;
+                    auto row_start = [&](uint32_t info, uint32_t row) __attribute__((always_inline)) {
+                        if constexpr (TO_D1) return D1 + d1_slot(a.row_info != nullptr, info, row) * a.d1_sw + 4 * g;
+                        else return D + (int64_t)row * a.ccol + c0 + 4 * g;
+                    };
+                    auto scaled = [&](floatx4 y, uint32_t info, float by) __attribute__((always_inline)) {
+                        if constexpr (!TO_D1)
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) y[v] = info & kInfoZero ? 0.0f : by * y[v];
+                        return y;
+                    };
+                    auto at_col = [&](int nb) __attribute__((always_inline)) {
+                        const int cb = c0 + 16 * nb;        // the workspace is cut into slices of d1_sw columns
+                        return TO_D1 ? (int64_t)(cb >> a.d1_sw_shift) * a.d1_slice_stride + (cb & a.d1_sw_mask) : 16 * nb;
+                    };
+                    const bool low = r < 8;
+                    const uint32_t r0 = low ? ri : rx, r1 = low ? rx : ri;
+                    const float s0 = low ? scale[i] : scale_x, s1 = low ? scale_x : scale[i];
+                    const bool pair = N == 2 && 16 * nb + 32 <= ws && (!TO_D1 || ((c0 + 16 * nb) & a.d1_sw_mask) + 32 <= a.d1_sw);
                     if (pair) {
+                        float *dst0 = row_start(r0, row0 + (r & 7)) + (low ? 0 : 16), *dst1 = row_start(r1, row0 + 8 + (r & 7)) + (low ? 0 : 16);
                         floatx4 y0, y1;
 #pragma unroll
                         for (int v = 0; v < 4; ++v) {
-                            const int lo = __float_as_int(acc[i][nb][v]), hi = __float_as_int(acc[i][nb + 1 < NB ? nb + 1 : nb][v]);
+                            const int lo = __float_as_int(acc[i][0][v]), hi = __float_as_int(acc[i][N - 1][v]);
                             y0[v] = __int_as_float(__builtin_amdgcn_update_dpp(lo, hi, kRowRor8, 0xf, 0xc, false));
                             y1[v] = __int_as_float(__builtin_amdgcn_update_dpp(hi, lo, kRowRor8, 0xf, 0x3, false));
                         }
-                        typedef typename Piece16<float>::Vec Vec;
                         auto put = [&](float *to, const Vec &y) __attribute__((always_inline)) {
                             if constexpr (TO_D1) *reinterpret_cast<Vec *>(to) = y;
                             else __builtin_nontemporal_store(y, reinterpret_cast<Vec *>(to));
@@ -316,14 +308,21 @@ __global__ __launch_bounds__(kFusedThreads) void k_gemm_split(const GemmLaunch a
                         if (r0 & kinds) put(dst0 + at_col(nb), scaled(y0, r0, s0));
                         if (r1 & kinds) put(dst1 + at_col(nb), scaled(y1, r1, s1));
                     } else if (ri & kinds) {
-                        store_acc4<float>(own + at_col(nb), scaled(acc[i][nb], ri, scale[i]), nb, g, ws);
-                        if constexpr (NB > 1)
-                            if (nb + 1 < NB) store_acc4<float>(own + at_col(nb + 1), scaled(acc[i][nb + 1], ri, scale[i]), nb + 1, g, ws);
+                        float *own = row_start(ri, row0 + r);
+#pragma unroll
+                        for (int j = 0; j < N; ++j) store_acc4<float>(own + at_col(nb + j), scaled(acc[i][j], ri, scale[i]), nb + j, g, ws);
                     }
-                }
-            };
-            store(std::true_type());
-            store(std::false_type());
+                };
+                store(std::true_type());
+                store(std::false_type());
+            }
+        };
+#pragma unroll 1
+        for (int nb = 0; nb + 2 <= NB; nb += 2) columns(std::integral_constant<int, 2>(), nb);
+        if constexpr (NB % 2) columns(std::integral_constant<int, 1>(), NB - 1);
+        if (fp32) {
+#pragma unroll
+            for (int s = 0; s < KD; ++s) load_step(s, brow);
         }
     }
 }
