@@ -613,39 +613,36 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS, NBC))
                 });
             } else {
                 Word4 part[KS2][3];
-#pragma unroll
-                for (int s = 0; s < 2 * KS2; ++s)
-#pragma unroll
-                    for (int q = 0; q < V; q += 2)
-                        split_pair(part[s / 2], s % 2 * 2 + q / 2, s < KS ? f[s][q] : 0.0f, s < KS ? f[s][q + 1] : 0.0f);
                 each_group([&](int grp, Acc(&o)[NBC]) __attribute__((always_inline)) {
                     const Word4 *Cg = reinterpret_cast<const Word4 *>(Cl) + grp * (NBC * KS2 * 3 * 64) + lane;
-                    // (two blocks at a time: a multiplication does not wait for the one before)
+                    Acc small[NBC] = {};
 #pragma unroll
-                    for (int nb = 0; nb < NBC; nb += 2) {
-                        constexpr int NP = 6, parts_of_c[NP] = {2, 0, 1, 1, 0, 0}, parts_of_b[NP] = {0, 2, 1, 0, 1, 0};
-                        Acc high[2] = {}, small[2] = {};
+                    for (int s = 0; s < KS2; ++s) {
+                        if (grp == 0) {
 #pragma unroll
-                        for (int s = 0; s < KS2; ++s) {
-                            Word4 c[2][3];
+                            for (int h = 0; h < 2; ++h)
 #pragma unroll
-                            for (int j = 0; j < 2; ++j)
-#pragma unroll
-                                for (int i = 0; i < 3; ++i)
-                                    if (nb + j < NBC) c[j][i] = Cg[((s * NBC + nb + j) * 3 + i) * 64];
-#pragma unroll
-                            for (int i = 0; i < NP; ++i)
-#pragma unroll
-                                for (int j = 0; j < 2; ++j) {
-                                    if (nb + j >= NBC) continue;
-                                    Acc &sum = i == NP - 1 ? high[j] : small[j];
-                                    sum = mfma16_bf16(c[j][parts_of_c[i]], part[s][parts_of_b[i]], sum);
+                                for (int q = 0; q < V; q += 2) {
+                                    const int k = 2 * s + h;
+                                    split_pair(part[s], 2 * h + q / 2, k < KS ? f[k < KS ? k : 0][q] : 0.0f, k < KS ? f[k < KS ? k : 0][q + 1] : 0.0f);
                                 }
                         }
 #pragma unroll
-                        for (int j = 0; j < 2; ++j)
-                            if (nb + j < NBC) o[nb + j < NBC ? nb + j : 0] = split_sum(high[j], small[j]);
+                        for (int nb = 0; nb < NBC; ++nb) {
+                            const Word4 *at = Cg + (s * NBC + nb) * 3 * 64;
+                            const Word4 c[3] = {at[0], at[64], at[128]};
+                            small[nb] = mfma16_bf16(c[2], part[s][1], small[nb]);
+                            o[nb] = mfma16_bf16(c[0], part[s][0], o[nb]);
+                            small[nb] = mfma16_bf16(c[1], part[s][2], small[nb]);
+                            small[nb] = mfma16_bf16(c[2], part[s][0], small[nb]);
+                            small[nb] = mfma16_bf16(c[0], part[s][2], small[nb]);
+                            small[nb] = mfma16_bf16(c[1], part[s][1], small[nb]);
+                            small[nb] = mfma16_bf16(c[1], part[s][0], small[nb]);
+                            small[nb] = mfma16_bf16(c[0], part[s][1], small[nb]);
+                        }
                     }
+#pragma unroll
+                    for (int nb = 0; nb < NBC; ++nb) o[nb] = split_sum(o[nb], small[nb]);
                 });
             }
         }

@@ -92,7 +92,9 @@ template <typename T, int N> __device__ __forceinline__ void store_any(T *p, con
 // the small products others, whose errors are below 2^-31; both sums are joined by one rounded addition (split_sum).  With
 // both in one accumulator the small ones, or h h of the next step, were cut off: relative error of 40000 x 64 sums of 2 / 8 /
 // 16 / 64 products against 64 bits 4.4e-8 / 9.1e-8 / 1.2e-7 / 1.5e-7, by the fp32 instructions 3.1e-8 / 5.3e-8 / 7.4e-8 / 1.5e-7.
-// (Of the nine products of parts m l, l m and l l are left out, just under 2^-24 of the product at most.)
+// Of the nine products of parts only l l is left out, below 2^-33 of the product; m l and l m come to just under 2^-24 of it
+// (0x1.00ff8p0 squared), as much as its rounding (without them single products erred by up to twice that; 2D stencil 512^2, 64 ->
+// 64, 30.4 us, so 32.8, R-MAT graph of 2^20 rows, 128 -> 128, 930 us, so 958).
 typedef __bf16 Bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 Bf16x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t Word4 __attribute__((ext_vector_type(4)));

@@ -11,24 +11,28 @@ namespace {
 
 // A wave multiplies blocks of 32 rows of B (two blocks of sixteen, so that what is read of C from LDS is used twice: its
 // reads then take half of what the LDS delivers).  C sits in LDS in three parts (split_pair), in operand order: per step of
-// 32 k, per block of sixteen columns, per part sixteen bytes for each lane.  Rows of B are split when all of them are there, and
-// the wave's next block is fetched into the registers that this frees: a block's loads are on their way for as long as a block
-// is multiplied, ahead of its stores, which they do not wait for.  The parts stay in registers, and blocks of columns are
-// multiplied and leave two at a time, so that few accumulators are needed.
+// 32 k, per block of sixteen columns, per part sixteen bytes for each lane.  Rows of B are split as their step comes, and the
+// same step of the wave's next block is fetched into the registers that this frees: a block's loads are on their way for as
+// long as a block is multiplied, ahead of its stores, which they do not wait for.  More than four blocks of columns take two
+// turns, with the rows split twice: the two sums of all of them leave no registers for the rows on their way (parts of all steps
+// kept instead, two blocks of columns at a time, all loads together: n = 300000, 64 -> 64, the product alone 42.5 us, so 37.1;
+// 128 -> 64 38.8 / 32.0; 96 -> 96 70 / 71; n = 2^20, 128 -> 128 290 / 302).
 //
 // Lane group g = lane / 16 holds of step s the elements k = 32 s + 4 g + {0 .. 3} and 32 s + 16 + 4 g + {0 .. 3} of its rows
 // (four lanes fetch 64 contiguous bytes); pieces of the last step that would reach past the row are moved back so that they
 // end with it and put right when they have arrived.
 //
-// A block with a row outside the bound of the split (infinities, numbers from 2^36 on) takes the fp32 instructions, C put together
-// from its parts.  Where a column of C is outside, C is put into LDS as it is, and all blocks go there (whole executions,
-// R-MAT graph of 2^20 rows, 128 -> 128, us: within the bound 934, one column outside 1066, every row 1126, by k_gemm 985).
+// A block with a row outside the bound of the split (infinities, numbers from 2^36 on) is multiplied again by the fp32
+// instructions, which read B from memory and put C together from its parts.  Where a column of C is outside, C is put into
+// LDS as it is, and all blocks go there alone (whole executions, R-MAT graph of 2^20 rows, 128 -> 128, us: within the bound 973, one
+// column outside 1098, every row 1347, by k_gemm 1010; 2^17 rows, 64 -> 128, 69.5, 76.8, 90.5, 70.0).
 //
-// Bound by memory.  us, on the fp32 matrix cores / here, and bytes moved: n = 2^20, 128 -> 128, with info words 300 / 218, 4.9
-// TB/s, which is what a copy reaches; n = 150000, 128 -> 41, 36 / 31, 3.7 TB/s; n = 131072, 64 -> 128, 38 / 29.5, 3.4 TB/s.  Of
-// these, lines of D1 and D written whole and not in halves by two instructions: 244 / 231, 31 / 30, 32 / 29.5.  PASS: B passes
-// through the L2 without staying there (run_split), as rows of D that leave here do: what the gather that follows reads does
-// stay (128 -> 128: 231 / 218, its gather 700 / 692; 128 -> 41: 30 / 32, 55 / 45).
+// Bound by memory where columns are few; at 128 -> 128 the matrix cores are busy half of the time, behind loads, splits and
+// stores of two waves.  us, first wavefronts, on the fp32 matrix cores / here: n = 2^20, 128 -> 128, 356 / 302; n = 150000, 128 -> 64,
+// 37 / 32, 128 -> 41, 36 / 32; n = 300000, 96 -> 96, 87 / 71, 100 -> 50, 58 / 50; n = 40000, 64 -> 40, 12.1 / 9.2.  Lines of D1 and D
+// are written whole and not in halves by two instructions (with six products in one sum, n = 2^20, 128 -> 128, 244 / 231; n =
+// 131072, 64 -> 128, 32 / 29.5).  PASS: B passes through the L2 without staying there (run_split), as rows of D that leave here do: what
+// the gather that follows reads does stay.
 constexpr int kRowRor8 = 0x128;      // DPP: rotate sixteen lanes by eight
 __device__ __forceinline__ uint32_t other_half(uint32_t x) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, kRowRor8, 0xf, 0xf, false); }
 
@@ -165,79 +169,66 @@ __global__ __launch_bounds__(kFusedThreads) void k_gemm_split(const GemmLaunch a
             scale[i] = scales[row_of(lb, i)];
             brow[i] = row_at(lb + nwaves, i);
         }
-        if (a.bcol != 32 * KD) {
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-#pragma unroll
-                for (int i = 0; i < 2; ++i) set_right(x[KD - 1][i][h], h);
-        }
-        Word4 part[KD][2][3];
-        float most[2] = {0.0f, 0.0f};
-#pragma unroll
-        for (int s = 0; s < KD; ++s)
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int h = 0; h < 2; ++h)
-#pragma unroll
-                    for (int q = 0; q < 4; q += 2) most[i] = fmaxf(fmaxf(most[i], fabsf(x[s][i][h][q])), fabsf(x[s][i][h][q + 1]));
-        bool bad = c_bad;
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            float m = fmaxf(most[i], __shfl_xor(most[i], 16, 64));
-            m = fmaxf(m, __shfl_xor(m, 32, 64));
-            // (rows that are not stored may hold anything)
-            const bool used = !a.row_info || (info[i] & (kInfoSpill | kInfoDirect));
-            bad |= used && split_exceeds(m);
-        }
-        const bool fp32 = __builtin_amdgcn_ballot_w64(bad) != 0;
-        if (!fp32) {
-#pragma unroll
-            for (int s = 0; s < KD; ++s) {
-#pragma unroll
-                for (int i = 0; i < 2; ++i)
-#pragma unroll
-                    for (int h = 0; h < 2; ++h)
-#pragma unroll
-                        for (int q = 0; q < 4; q += 2) split_pair(part[s][i], 2 * h + q / 2, x[s][i][h][q], x[s][i][h][q + 1]);
-                // (the next block's loads after the split, whose registers they take, and ahead of the multiplications)
-#pragma unroll
-                for (int i = 0; i < 2; ++i)
-#pragma unroll
-                    for (int p = 0; p < 3; ++p) asm volatile("" : "+v"(part[s][i][p]));
-                __builtin_amdgcn_sched_barrier(0);
-                load_step(s, brow);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
-
-        // N blocks of columns from nb on: products and stores
-        auto columns = [&](auto n_c, int nb) __attribute__((always_inline)) {
-            constexpr int N = decltype(n_c)::value;
+        bool fp32 = c_bad;
+        // N blocks of columns from NB0 on: products and stores
+        auto columns = [&](auto n_c, auto nb0_c) __attribute__((always_inline)) {
+            constexpr int N = decltype(n_c)::value, NB0 = decltype(nb0_c)::value;
+            constexpr bool FIRST = NB0 == 0, LAST = NB0 + N == NB;
             floatx4 acc[2][N];
 #pragma unroll
             for (int i = 0; i < 2; ++i)
 #pragma unroll
                 for (int j = 0; j < N; ++j) acc[i][j] = floatx4{0, 0, 0, 0};
-            if (!fp32) {
+            if (!c_bad) {
                 floatx4 small[2][N];
+                float most[2] = {0.0f, 0.0f};
 #pragma unroll
                 for (int i = 0; i < 2; ++i)
 #pragma unroll
                     for (int j = 0; j < N; ++j) small[i][j] = floatx4{0, 0, 0, 0};
 #pragma unroll
                 for (int s = 0; s < KD; ++s) {
+                    if (FIRST && s == KD - 1 && a.bcol != 32 * KD) {
+#pragma unroll
+                        for (int h = 0; h < 2; ++h)
+#pragma unroll
+                            for (int i = 0; i < 2; ++i) set_right(x[s][i][h], h);
+                    }
+                    Word4 part[2][3];
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+#pragma unroll
+                        for (int h = 0; h < 2; ++h)
+#pragma unroll
+                            for (int q = 0; q < 4; q += 2) {
+                                if constexpr (FIRST) most[i] = fmaxf(fmaxf(most[i], fabsf(x[s][i][h][q])), fabsf(x[s][i][h][q + 1]));
+                                split_pair(part[i], 2 * h + q / 2, x[s][i][h][q], x[s][i][h][q + 1]);
+                            }
+                    // (the next block's loads after the last split, whose registers they take, and ahead of the multiplications)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        asm volatile("" : "+v"(most[i]));
+#pragma unroll
+                        for (int p = 0; p < 3; ++p) asm volatile("" : "+v"(part[i][p]));
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                    if constexpr (LAST) load_step(s, brow);
+                    __builtin_amdgcn_sched_barrier(0);
+                    // (one address a step: what lies past 64 KiB would have a register for every block, kept outside of the loop)
+                    int at_step = s * (NB * 3 * 64) + lane;
+                    if constexpr (KD * NB * 3 > 64) asm volatile("" : "+v"(at_step));
 #pragma unroll
                     for (int j = 0; j < N; ++j) {
-                        Word4 c[3];
-#pragma unroll
-                        for (int p = 0; p < 3; ++p) c[p] = Cl[((s * NB + nb + j) * 3 + p) * 64 + lane];
+                        const Word4 *at = Cl + (at_step + (NB0 + j) * 3 * 64);
+                        const Word4 c[3] = {at[0], at[64], at[128]};
                         auto multiply = [&](floatx4(&sums)[2][N], int cp, int bp) __attribute__((always_inline)) {
 #pragma unroll
-                            for (int i = 0; i < 2; ++i) sums[i][j] = mfma16_bf16(c[cp], part[s][i][bp], sums[i][j]);
+                            for (int i = 0; i < 2; ++i) sums[i][j] = mfma16_bf16(c[cp], part[i][bp], sums[i][j]);
                         };
-                        multiply(small, 2, 0);
+                        multiply(small, 2, 1);
                         multiply(acc, 0, 0);
+                        multiply(small, 1, 2);
+                        multiply(small, 2, 0);
                         multiply(small, 0, 2);
                         multiply(small, 1, 1);
                         multiply(small, 1, 0);
@@ -248,18 +239,48 @@ __global__ __launch_bounds__(kFusedThreads) void k_gemm_split(const GemmLaunch a
                 for (int i = 0; i < 2; ++i)
 #pragma unroll
                     for (int j = 0; j < N; ++j) acc[i][j] = split_sum(acc[i][j], small[i][j]);
-            } else {
+                if constexpr (FIRST) {
+                    bool bad = false;
 #pragma unroll
-                for (int s = 0; s < KD; ++s)
+                    for (int i = 0; i < 2; ++i) {
+                        asm volatile("" : "+v"(info[i]), "+v"(scale[i]));      // (here, not where they are fetched)
+                        float m = fmaxf(most[i], __shfl_xor(most[i], 16, 64));
+                        m = fmaxf(m, __shfl_xor(m, 32, 64));
+                        // (rows that are not stored may hold anything)
+                        const bool used = !a.row_info || (info[i] & (kInfoSpill | kInfoDirect));
+                        bad |= used && split_exceeds(m);
+                    }
+                    fp32 = __builtin_amdgcn_ballot_w64(bad) != 0;
+                }
+            }
+            if (fp32) {
+                const float *row[2];
+#pragma unroll
+                for (int i = 0; i < 2; ++i) row[i] = row_at(lb, i);
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int j = 0; j < N; ++j) acc[i][j] = floatx4{0, 0, 0, 0};
+#pragma unroll 1
+                for (int s = 0; s < KD; ++s) {
+                    Vec b[2][2];
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) {
+                            b[i][h] = *reinterpret_cast<const Vec *>(row[i] + (s < KD - 1 ? 32 * s + 16 * h + 4 * g : last[h]));
+                            if (s == KD - 1 && a.bcol != 32 * KD) set_right(b[i][h], h);
+                        }
 #pragma unroll
                     for (int j = 0; j < N; ++j) {
                         float c[8];
-                        split_whole(c, Cl + (s * NB + nb + j) * 3 * 64 + lane, c_bad);
+                        split_whole(c, Cl + (s * NB + NB0 + j) * 3 * 64 + lane, c_bad);
 #pragma unroll
                         for (int q = 0; q < 8; ++q)
 #pragma unroll
-                            for (int i = 0; i < 2; ++i) acc[i][j] = mfma16(c[q], x[s][i][q / 4][q % 4], acc[i][j]);
+                            for (int i = 0; i < 2; ++i) acc[i][j] = mfma16(c[q], b[i][q / 4][q % 4], acc[i][j]);
                     }
+                }
             }
             // Two blocks of columns leave together, eight rows at a time, so that an instruction writes whole lines of 128 bytes: a
             // lane changes places with the one eight rows on.
@@ -291,39 +312,41 @@ __global__ __launch_bounds__(kFusedThreads) void k_gemm_split(const GemmLaunch a
                     const bool low = r < 8;
                     const uint32_t r0 = low ? ri : rx, r1 = low ? rx : ri;
                     const float s0 = low ? scale[i] : scale_x, s1 = low ? scale_x : scale[i];
-                    const bool pair = N == 2 && 16 * nb + 32 <= ws && (!TO_D1 || ((c0 + 16 * nb) & a.d1_sw_mask) + 32 <= a.d1_sw);
-                    if (pair) {
-                        float *dst0 = row_start(r0, row0 + (r & 7)) + (low ? 0 : 16), *dst1 = row_start(r1, row0 + 8 + (r & 7)) + (low ? 0 : 16);
-                        floatx4 y0, y1;
+                    float *own = row_start(ri, row0 + r), *dst0 = row_start(r0, row0 + (r & 7)) + (low ? 0 : 16),
+                          *dst1 = row_start(r1, row0 + 8 + (r & 7)) + (low ? 0 : 16);
 #pragma unroll
-                        for (int v = 0; v < 4; ++v) {
-                            const int lo = __float_as_int(acc[i][0][v]), hi = __float_as_int(acc[i][N - 1][v]);
-                            y0[v] = __int_as_float(__builtin_amdgcn_update_dpp(lo, hi, kRowRor8, 0xf, 0xc, false));
-                            y1[v] = __int_as_float(__builtin_amdgcn_update_dpp(hi, lo, kRowRor8, 0xf, 0x3, false));
+                    for (int j = 0; j < N; j += 2) {
+                        const int nb = NB0 + j;
+                        const bool pair = j + 1 < N && 16 * nb + 32 <= ws && (!TO_D1 || ((c0 + 16 * nb) & a.d1_sw_mask) + 32 <= a.d1_sw);
+                        if (pair) {
+                            floatx4 y0, y1;
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) {
+                                const int lo = __float_as_int(acc[i][j][v]), hi = __float_as_int(acc[i][j + 1 < N ? j + 1 : j][v]);
+                                y0[v] = __int_as_float(__builtin_amdgcn_update_dpp(lo, hi, kRowRor8, 0xf, 0xc, false));
+                                y1[v] = __int_as_float(__builtin_amdgcn_update_dpp(hi, lo, kRowRor8, 0xf, 0x3, false));
+                            }
+                            typedef typename Piece16<float>::Vec Vec;
+                            auto put = [&](float *to, const Vec &y) __attribute__((always_inline)) {
+                                if constexpr (TO_D1) *reinterpret_cast<Vec *>(to) = y;
+                                else __builtin_nontemporal_store(y, reinterpret_cast<Vec *>(to));
+                            };
+                            if (r0 & kinds) put(dst0 + at_col(nb), scaled(y0, r0, s0));
+                            if (r1 & kinds) put(dst1 + at_col(nb), scaled(y1, r1, s1));
+                        } else if (ri & kinds) {
+                            store_acc4<float>(own + at_col(nb), scaled(acc[i][j], ri, scale[i]), nb, g, ws);
+                            if (j + 1 < N) store_acc4<float>(own + at_col(nb + 1), scaled(acc[i][j + 1 < N ? j + 1 : j], ri, scale[i]), nb + 1, g, ws);
                         }
-                        auto put = [&](float *to, const Vec &y) __attribute__((always_inline)) {
-                            if constexpr (TO_D1) *reinterpret_cast<Vec *>(to) = y;
-                            else __builtin_nontemporal_store(y, reinterpret_cast<Vec *>(to));
-                        };
-                        if (r0 & kinds) put(dst0 + at_col(nb), scaled(y0, r0, s0));
-                        if (r1 & kinds) put(dst1 + at_col(nb), scaled(y1, r1, s1));
-                    } else if (ri & kinds) {
-                        float *own = row_start(ri, row0 + r);
-#pragma unroll
-                        for (int j = 0; j < N; ++j) store_acc4<float>(own + at_col(nb + j), scaled(acc[i][j], ri, scale[i]), nb + j, g, ws);
                     }
                 };
                 store(std::true_type());
                 store(std::false_type());
             }
         };
-#pragma unroll 1
-        for (int nb = 0; nb + 2 <= NB; nb += 2) columns(std::integral_constant<int, 2>(), nb);
-        if constexpr (NB % 2) columns(std::integral_constant<int, 1>(), NB - 1);
-        if (fp32) {
-#pragma unroll
-            for (int s = 0; s < KD; ++s) load_step(s, brow);
-        }
+        // (four blocks at a time: registers for their two sums, rows of B and the next ones)
+        constexpr int N0 = NB < 4 ? NB : 4;
+        columns(std::integral_constant<int, N0>(), std::integral_constant<int, 0>());
+        if constexpr (NB > N0) columns(std::integral_constant<int, NB - N0>(), std::integral_constant<int, N0>());
     }
 }
 

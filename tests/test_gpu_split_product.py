@@ -137,7 +137,7 @@ def _products_rounded_at_every_one(B, C):
 @pytest.mark.parametrize("how", ["unfused", "one_pass"])
 @pytest.mark.parametrize("bcol,ccol", [(64, 48), (128, 64)])
 @pytest.mark.parametrize("positive", [False, True])
-@pytest.mark.parametrize("terms", [2, 3, 4, 8, 16, 32, 64])
+@pytest.mark.parametrize("terms", [1, 2, 3, 4, 8, 16, 32, 64])
 def test_no_further_off_than_sums_rounded_at_every_product(bcol, ccol, terms, positive, how):
     """Rows of B of few to 64 numbers that are not zeros, against 64 bits: the error of the split product in the
     2-norm is at most that of the fp32 instructions on the same operands (to 1 %: over 2 million results the norms' own
@@ -154,3 +154,20 @@ def test_no_further_off_than_sums_rounded_at_every_product(bcol, ccol, terms, po
     want = B.astype(np.float64) @ C.astype(np.float64)
     err, other = np.linalg.norm(got - want), np.linalg.norm(_products_rounded_at_every_one(B, C) - want)
     assert err <= 1.01 * other, f"{err / np.linalg.norm(want):.3e}, by the fp32 instructions {other / np.linalg.norm(want):.3e}"
+
+
+@pytest.mark.parametrize("how", ["unfused", "one_pass"])
+@pytest.mark.parametrize("bcol,ccol", [(64, 48), (128, 64)])
+def test_single_products_are_rounded_once(bcol, ccol, how):
+    """One product a result, among them 0x1.00ff8p0 squared, of which m l and l m make up 2^-24: within 2^-24 of it for its
+    rounding, and 2^-24 of that for sums of small parts that are cut off (112 of them at 2^-32 and less)."""
+    n = 40000
+    rng = np.random.default_rng(bcol)
+    B, C = np.zeros((n, bcol), np.float32), rng.uniform(1, 2, (bcol, ccol)).astype(np.float32)
+    at = np.arange(n) % bcol
+    B[np.arange(n), at] = rng.uniform(1, 2, n)
+    B[: n // 2, :][np.arange(n // 2), at[: n // 2]] = float.fromhex("0x1.00ff8p0")
+    C[:, ::2] = float.fromhex("0x1.00ff8p0")
+    got = _products(B, C, how)[0]
+    want = B[np.arange(n), at].astype(np.float64)[:, None] * C[at].astype(np.float64)
+    assert np.all(np.abs(got - want) <= 2.0 ** -24 * want * (1 + 112 * 2.0 ** -8))
