@@ -392,7 +392,8 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS, NBC))
     auto first_count = [&](const ChainBlock &b) { return min(pass_len(b), b.slots); };
 
     uint32_t *cmax = reinterpret_cast<uint32_t *>(tf_smem + groups * (NBC * KS2 * 3 * 1024));
-    bool c_bad = false;      // (fp32) a column of C is outside of the bound of the split
+    bool c_bad = false;      // (fp32) a column of C is outside of the bound of the split,
+    float row_bound = 0.0f;  // what the elements of a row must be below
     // Start-up: the first gathers of the first block go out before C is put into LDS
     {
         const int total = groups * NBC * 16 * KS * 4, split_items = groups * NBC * KS2 * 16;
@@ -448,7 +449,7 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS, NBC))
         clear_sums();
         add_first(n, x);
         if constexpr (SPLIT) {
-            c_bad = split_columns_exceed(cmax, groups * NBC * 16, lane);
+            row_bound = split_row_bound(cmax, groups * NBC * 16, lane, c_bad);
             if (c_bad) {      // (all waves of the workgroup; C as it is in the place of its parts)
                 write_whole<KS2, NBC>(reinterpret_cast<Word4 *>(Cl), split_from, a.c_transposed, groups * NBC);
                 __syncthreads();
@@ -597,7 +598,7 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS, NBC))
                 for (int q = 0; q < V; q += 2) most = fmaxf(fmaxf(most, fabsf(f[s][q])), fabsf(f[s][q + 1]));
             most = fmaxf(most, __shfl_xor(most, 16, 64));
             most = fmaxf(most, __shfl_xor(most, 32, 64));
-            if (__builtin_amdgcn_ballot_w64(c_bad || split_exceeds(most))) {
+            if (__builtin_amdgcn_ballot_w64(c_bad || split_exceeds(most, row_bound))) {
                 each_group([&](int grp, Acc(&o)[NBC]) __attribute__((always_inline)) {
                     const Word4 *Cg = reinterpret_cast<const Word4 *>(Cl) + grp * (NBC * KS2 * 3 * 64) + lane;
 #pragma unroll

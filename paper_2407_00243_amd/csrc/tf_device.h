@@ -131,17 +131,28 @@ __device__ __forceinline__ floatx4 split_sum(const floatx4 &high, const floatx4 
     for (int v = 0; v < 4; ++v) y[v] = (high[v] + small[v]) * kSplitUnscale;
     return y;
 }
-// A row of the first operand and a column of the second are multiplied this way if all their elements are below 2^36: no sum of
-// 128 products reaches 2^127 then.  Infinities, which would meet zeros of the other operand's parts, are beyond as well.
-constexpr float kSplitMax = 0x1p36f;
-__device__ __forceinline__ bool split_exceeds(float largest) { return !(largest < kSplitMax); }
-// From the largest elements of the columns (bits; a NaN counts as more than infinity): whether one is outside of the bound.
-__device__ __forceinline__ bool split_columns_exceed(const uint32_t *cmax, int cols, int lane) {
+// A row of the first operand and a column of the second are multiplied this way if their largest elements are below 2^60 and
+// the product of these is below 2^72: no sum of 128 products reaches 2^128 then, scaled by 2^48.  Infinities, which would meet
+// zeros of the other operand's parts, are beyond as well.
+constexpr float kSplitMax = 0x1p60f, kSplitProduct = 0x1p72f;
+__device__ __forceinline__ bool split_exceeds(float largest, float bound) { return !(largest < bound); }
+// From the largest elements of the columns (bits; a NaN counts as more than infinity): whether one is beyond, and what those
+// of a row must be below.
+__device__ __forceinline__ float split_row_bound(const uint32_t *cmax, int cols, int lane, bool &exceeds) {
+    float most = 0.0f;
     bool any = false;
-    for (int c = lane; c < cols; c += 64) any |= split_exceeds(__uint_as_float(cmax[c]));
-    return __builtin_amdgcn_ballot_w64(any) != 0;
+    for (int c = lane; c < cols; c += 64) {
+        const float m = __uint_as_float(cmax[c]);
+        any |= split_exceeds(m, kSplitMax);
+        most = fmaxf(most, m);
+    }
+    exceeds = __builtin_amdgcn_ballot_w64(any) != 0;
+    // (the exchange of the most takes 0.2 us, which small launches show)
+    constexpr float usual = kSplitProduct / kSplitMax;
+    if (__builtin_amdgcn_ballot_w64(most > usual) == 0) return kSplitMax;
+    for (int i = 1; i < 64; i <<= 1) most = fmaxf(most, __shfl_xor(most, i, 64));
+    return kSplitProduct / most;
 }
-
 // Eight numbers of an operand in LDS: put together again from their parts, which takes nothing from them, or as they are
 // (`whole`) in the place of the first two parts.
 __device__ __forceinline__ void split_whole(float (&x)[8], const Word4 *at, bool whole) {

@@ -22,10 +22,10 @@ namespace {
 // (four lanes fetch 64 contiguous bytes); pieces of the last step that would reach past the row are moved back so that they
 // end with it and put right when they have arrived.
 //
-// A block with a row outside the bound of the split (infinities, numbers from 2^36 on) is multiplied again by the fp32
+// A block with a row outside the bound of the split (infinities, very large numbers) is multiplied again by the fp32
 // instructions, which read B from memory and put C together from its parts.  Where a column of C is outside, C is put into
-// LDS as it is, and all blocks go there alone (whole executions, R-MAT graph of 2^20 rows, 128 -> 128, us: within the bound 973, one
-// column outside 1098, every row 1347, by k_gemm 1010; 2^17 rows, 64 -> 128, 69.5, 76.8, 90.5, 70.0).
+// LDS as it is, and all blocks go there alone (whole executions, R-MAT graph of 2^20 rows, 128 -> 128, us: within the bound 965, one
+// column outside 1090, every row 1347, by k_gemm 1013; 2^17 rows, 64 -> 128, 68, 76, 90, 69).
 //
 // Bound by memory where columns are few; at 128 -> 128 the matrix cores are busy half of the time, behind loads, splits and
 // stores of two waves.  us, first wavefronts, on the fp32 matrix cores / here: n = 2^20, 128 -> 128, 356 / 302; n = 150000, 128 -> 64,
@@ -132,7 +132,8 @@ __global__ __launch_bounds__(kFusedThreads) void k_gemm_split(const GemmLaunch a
         put_c(e0);
     }
     __syncthreads();
-    const bool c_bad = split_columns_exceed(cmax, NB * 16, lane);
+    bool c_bad;
+    const float row_bound = split_row_bound(cmax, NB * 16, lane, c_bad);
     if (c_bad) {      // (all waves of the workgroup; C as it is in the place of its parts)
         for (int e0 = (int)threadIdx.x; e0 < KD * NB * 64; e0 += NC * (int)blockDim.x) {
             load_c(e0);
@@ -248,7 +249,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_gemm_split(const GemmLaunch a
                         m = fmaxf(m, __shfl_xor(m, 32, 64));
                         // (rows that are not stored may hold anything)
                         const bool used = !a.row_info || (info[i] & (kInfoSpill | kInfoDirect));
-                        bad |= used && split_exceeds(m);
+                        bad |= used && split_exceeds(m, row_bound);
                     }
                     fp32 = __builtin_amdgcn_ballot_w64(bad) != 0;
                 }

@@ -83,7 +83,7 @@ def test_numbers_that_the_parts_do_not_hold(bcol, ccol, where, how):
 
 @pytest.mark.parametrize("how", ["unfused", "one_pass"])
 @pytest.mark.parametrize("row_exp,col_exp", [(-90, 0), (-89, -4), (-47, -47), (-48, -47), (-4, -90), (0, -91), (-91, 0), (59, 59), (60, 0),
-                                             (0, 60), (35, 35), (36, 0), (0, 36), (-126, 35), (35, -126)])
+                                             (0, 60), (36, 36), (35, 36), (59, 11), (59, 12), (59, 13), (11, 59), (13, 59), (-126, 59), (59, -126)])
 def test_operands_at_the_bounds_of_the_split(row_exp, col_exp, how):
     """Every row of B and column of C of one magnitude, at and on either side of where the parts cease to hold them."""
     n, bcol, ccol = (40000, 64, 48) if how == "unfused" else (4100, 64, 48)
