@@ -31,8 +31,8 @@ namespace {
 // stores of two waves.  us, first wavefronts, on the fp32 matrix cores / here: n = 2^20, 128 -> 128, 356 / 302; n = 150000, 128 -> 64,
 // 37 / 32, 128 -> 41, 36 / 32; n = 300000, 96 -> 96, 87 / 71, 100 -> 50, 58 / 50; n = 40000, 64 -> 40, 12.1 / 9.2.  Lines of D1 and D
 // are written whole and not in halves by two instructions (with six products in one sum, n = 2^20, 128 -> 128, 244 / 231; n =
-// 131072, 64 -> 128, 32 / 29.5).  PASS: B passes through the L2 without staying there (run_split), as rows of D that leave here do: what
-// the gather that follows reads does stay.
+// 131072, 64 -> 128, 32 / 29.5).  PASS: B passes through the caches without staying there (run_split), as rows of D that leave here do:
+// what the gather that follows reads does stay.
 constexpr int kRowRor8 = 0x128;      // DPP: rotate sixteen lanes by eight
 __device__ __forceinline__ uint32_t other_half(uint32_t x) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, kRowRor8, 0xf, 0xf, false); }
 
@@ -376,13 +376,15 @@ template <int KD, int NB, bool PASS> int run_split2(const GemmLaunch &a, hipStre
     k_gemm_split<KD, NB, PASS><<<dim3((unsigned)gx, (unsigned)a.n_slices), dim3(64 * nwaves), lds, st>>>(a);
     return (int)hipGetLastError();
 }
-// Rows of B pass through the L2 without staying there where what is written is more than the L2s hold, which the launch that
-// follows gathers from, and rows of B are whole lines, or a line that a load takes a part of is gone when the next one comes
-// for the rest (whole executions on R-MAT graphs, us, staying / passing: 150000 rows, 128 -> 41 86.0 / 78.4, 64 -> 64 73.9 / 65.7,
-// 2^20 128 -> 128 930 / 910; 19 MB written, 150000 rows, 32 -> 32 35.2 / 38.1, 60000, 128 -> 41 35.9 / 40.3; rows of 400
-// bytes, 150000, 100 -> 100 141.7 / 152.2).
+// Rows of B pass through the caches without staying there where B, D1 and D are more than the last-level cache holds (256 MB),
+// and rows of B are whole lines, or a line that a load takes a part of is gone when the next one comes for the rest (100 -> 100,
+// 150000 rows, 152 us passing, 142 staying).  Whole executions on R-MAT graphs, us, staying / passing, the same operands again and, in
+// brackets, others each time: 300000 rows, 128 -> 128 275 / 263 (277 / 265), 700000, 32 -> 32 168 / 163 (169 / 163), 10^6, 64 -> 32 261 / 256
+// (262 / 254); below, 150000, 128 -> 41 71 / 79 (77 / 78), 128 -> 64 72 / 77 (79 / 78), 300000, 64 -> 64 119 / 125 (127 / 126), 400000, 64 -> 32
+// 97 / 100 (100 / 100).  Not where the product is the second operation (D1 is D): what it reads was just written, and no launch
+// follows (staying / passing: 131072 rows, 64 -> 128 63.6 / 67.7, 300000, 32 -> 64 75.8 / 86.6, 10^6, 64 -> 128 663 / 683).
 template <int KD, int NB> int run_split(const GemmLaunch &a, hipStream_t st) {
-    const bool pass = a.bcol % 32 == 0 && a.n * a.d1_cols * 4 >= ((int64_t)32 << 20);
+    const bool pass = a.D1 != a.D && a.bcol % 32 == 0 && a.n * (a.bcol + a.d1_cols + a.ccol) * 4 >= ((int64_t)256 << 20);
     if (pass) return run_split2<KD, NB, true>(a, st);
     return run_split2<KD, NB, false>(a, st);
 }

@@ -52,6 +52,19 @@ def test_products_are_closer_than_sums_rounded_at_every_product(bcol, ccol, n, h
         assert np.linalg.norm(got - want) <= 2.0 ** -24 * np.sqrt(bcol) * np.linalg.norm(want)
 
 
+@pytest.mark.parametrize("n,bcol,ccol", [(699100, 32, 32), (381401, 64, 48), (300001, 96, 64), (214001, 128, 90)])
+@pytest.mark.parametrize("how", ["unfused", "streaming"])
+def test_rows_that_pass_through_the_cache(n, bcol, ccol, how):
+    """Products whose operands and results are more than 256 MiB read rows of B of whole lines past the caches; the bound of
+    above.  (On the host 1 in 16 rows.)"""
+    rng = np.random.default_rng(n)
+    B, C = rng.standard_normal((n, bcol), dtype=np.float32), rng.standard_normal((bcol, ccol), dtype=np.float32)
+    got, cols = _products(B, C, how)
+    got, B = got[5::16], B[cols[5::16]]
+    W = np.abs(B).astype(np.float64) @ np.abs(C).astype(np.float64)
+    assert np.all(np.abs(got - B.astype(np.float64) @ C.astype(np.float64)) <= bcol * 2.0 ** -24 * W)
+
+
 @pytest.mark.parametrize("how", ["unfused", "streaming", "one_pass", "transposed"])
 @pytest.mark.parametrize("bcol,ccol", [(20, 32), (32, 40), (50, 33), (128, 96)])
 @pytest.mark.parametrize("where", ["B", "C"])
