@@ -174,7 +174,8 @@ template <typename Vec, int N, int R, int P> struct GatheredPieces {
 // one time, so that what one wave fetches another finds in the L2 (2D stencil 512^2, fp64 128 -> 128: 357 MB fetched
 // past the L2; with the first pass on its way during the multiplications 597 MB, 195 us, so 190).
 //
-// fp32 from depth 4 on is multiplied on the bf16 matrix cores, operands split in three (tf_device.h; chain_splits).
+// fp32 from depth 4 on, more than sixteen columns, is multiplied on the bf16 matrix cores, operands split in three (tf_device.h;
+// chain_splits).
 // These leave the other waves of their SIMD to work; behind fp32 and fp64 matrix instructions every instruction of
 // theirs waits (loads, LDS reads or sums of four waves beside four that multiply take the sum of both times, beside
 // bf16 instructions little more than the longer one).  us, before / with first gathers later and a piece of all entries
@@ -201,7 +202,7 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS, NBC))
     // 64 / LR rows at a time, RS times; piece P = pp + LR t of the rows rr + 64 h / LR
     constexpr int LR = KS % 2 == 0 ? 8 : 4, RS = LR / 4, KP = KS / RS;
     const int pp = lane % LR, rr = lane / LR;
-    constexpr bool SPLIT = chain_splits(dtype_of<T>(), KS);     // (fp32 on the bf16 matrix cores)
+    constexpr bool SPLIT = chain_splits(dtype_of<T>(), KS, NBC);     // (fp32 on the bf16 matrix cores)
     constexpr int KS2 = (KS + 1) / 2;
     T *Cl = reinterpret_cast<T *>(tf_smem);
     // the column groups of this workgroup (all of them, unless the launch has few blocks of rows)

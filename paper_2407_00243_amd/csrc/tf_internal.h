@@ -433,14 +433,16 @@ constexpr int chain_exchange_bytes(int dtype, int ks, int nbc) {
 constexpr int64_t chain_wave_lds(int dtype, int ks, int nbc) {
     return chain_exchange_bytes(dtype, ks, nbc) + 64 + chain_entry_slots(dtype, ks) * (8 + (dtype == TF_F64 ? 8 : 4));
 }
-// Whether the kernel multiplies on the bf16 matrix cores, by operands split in three: rows of B of more than 48 columns
-// (shorter ones: three parts of C take longer to lay out than is saved; us, fp32 instructions / split, 2D stencil 120^2: 8 -> 8
-// 5.1 / 6.1, 16 -> 64 5.7 / 7.0, 32 -> 32 5.5 / 6.6, 50 -> 23 6.4 / 6.1, 128 -> 32 8.8 / 7.8).
-constexpr bool chain_splits(int dtype, int ks) { return dtype == TF_F32 && ks >= 4; }
+// Whether the kernel multiplies on the bf16 matrix cores, by operands split in three: rows of B of more than 48 columns and rows
+// of D of more than sixteen (shorter rows of B: three parts of C take longer to lay out than is saved; one block of columns:
+// splitting the rows does; us, fp32 instructions / split, 2D stencil 120^2: 8 -> 8 5.1 / 6.1, 16 -> 64 5.7 / 7.0, 32 -> 32 5.5 /
+// 6.6, 50 -> 23 6.4 / 6.1, 128 -> 32 8.8 / 7.8; 200^2: 56 -> 16 6.4 / 7.6, 128 -> 16 9.0 / 9.9, 128 -> 20 12.0 / 10.8; 353^2: 64 -> 16 11.6 /
+// 13.0, 64 -> 20 16.0 / 15.0).
+constexpr bool chain_splits(int dtype, int ks, int nbc) { return dtype == TF_F32 && ks >= 4 && nbc > 1; }
 // LDS of a group of blocks of columns of C: fp64 as the multiplications take it, fp32 in three parts of bf16 with the largest
 // number of each column.
 constexpr int64_t chain_group_lds(int dtype, int ks, int nbc) {
-    return chain_splits(dtype, ks) ? (int64_t)nbc * ((ks + 1) / 2 * 3 * 1024 + 64) : (int64_t)nbc * ks * 1024;
+    return chain_splits(dtype, ks, nbc) ? (int64_t)nbc * ((ks + 1) / 2 * 3 * 1024 + 64) : (int64_t)nbc * ks * 1024;
 }
 // What decides whether a plan may take the one pass: C, and for each wave of the largest workgroup the exchange and 64 or 128
 // entries.  The kernel takes as much or, for entries of fp64 at depth 8, 256 bytes more a wave, for which there is room

@@ -35,7 +35,7 @@ def _products(B, C, how):
                                    (32767, "streaming"), (32799, "streaming"), (70001, "streaming"), (17, "one_pass"),
                                    (4097, "one_pass"), (70001, "one_pass"), (4097, "transposed")])
 @pytest.mark.parametrize("bcol,ccol", [(4, 1), (15, 32), (16, 32), (17, 33), (31, 41), (32, 31), (33, 48), (64, 96), (65, 33), (96, 50), (100, 100),
-                                       (127, 128), (128, 64), (128, 130)])
+                                       (127, 128), (128, 64), (128, 130), (52, 16), (90, 7), (128, 17)])
 def test_products_are_closer_than_sums_rounded_at_every_product(bcol, ccol, n, how):
     """Against 64 bits.  The six products of the parts are exact and what is left out is below 2^-26 of a product; with a
     rounding of 2^-24 at each of bcol products the norm of the error stays within 2^-24 sqrt(bcol) of the norm of the
