@@ -575,20 +575,23 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS, NBC))
         if constexpr (!SPLIT) {
             each_group([&](int grp, Acc(&o)[NBC]) __attribute__((always_inline)) {
                 // (the operands of a step are read ahead of the multiplications of the one before: 2D stencil 301^2, fp32 50 ->
-                // 23, on the fp32 matrix cores 12.8 -> 12.3 us)
+                // 23, on the fp32 matrix cores 12.8 -> 12.3 us; further ahead where a step has few of them)
+                constexpr int AHEAD = NBC == 1 ? 4 : NBC == 2 ? 2 : 1;
                 const T *Cg = Cl + grp * (NBC * KS * V * 64) + lane;
-                T c[2][NBC];
+                T c[AHEAD + 1][NBC];
 #pragma unroll
-                for (int nb = 0; nb < NBC; ++nb) c[0][nb] = Cg[nb * 64];
+                for (int i = 0; i < AHEAD && i < KS * V; ++i)
+#pragma unroll
+                    for (int nb = 0; nb < NBC; ++nb) c[i][nb] = Cg[(i * NBC + nb) * 64];
 #pragma unroll
                 for (int i = 0; i < KS * V; ++i) {
-                    if (i + 1 < KS * V) {
+                    if (i + AHEAD < KS * V) {
 #pragma unroll
-                        for (int nb = 0; nb < NBC; ++nb) c[(i + 1) & 1][nb] = Cg[((i + 1) * NBC + nb) * 64];
+                        for (int nb = 0; nb < NBC; ++nb) c[(i + AHEAD) % (AHEAD + 1)][nb] = Cg[((i + AHEAD) * NBC + nb) * 64];
                     }
                     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                    for (int nb = 0; nb < NBC; ++nb) o[nb] = mfma16(c[i & 1][nb], f[i / V][i % V], o[nb]);
+                    for (int nb = 0; nb < NBC; ++nb) o[nb] = mfma16(c[i % (AHEAD + 1)][nb], f[i / V][i % V], o[nb]);
                 }
             });
         } else if constexpr (SPLIT) {
