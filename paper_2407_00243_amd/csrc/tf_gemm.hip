@@ -38,6 +38,7 @@ __device__ __forceinline__ uint32_t other_half(uint32_t x) { return (uint32_t)__
 
 template <int KD, int NB, bool PASS>
 __global__ __launch_bounds__(kFusedThreads) void k_gemm_split(const GemmLaunch a) {
+    static_assert(NB >= 2, "slices are of kSplitMinCols columns at least");
     typedef typename Piece16<float>::Vec Vec;
     const int slice = blockIdx.y;
     const int c0 = slice * a.cs;
@@ -391,7 +392,6 @@ template <int KD, int NB> int run_split(const GemmLaunch &a, hipStream_t st) {
 
 template <int KD> int run_split_nb(const GemmLaunch &a, hipStream_t st) {
     switch (split_col_blocks(a.cs)) {
-        case 1: return run_split<KD, 1>(a, st);
         case 2: return run_split<KD, 2>(a, st);
         case 3: return run_split<KD, 3>(a, st);
         case 4: return run_split<KD, 4>(a, st);

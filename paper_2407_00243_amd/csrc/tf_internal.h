@@ -204,8 +204,8 @@ inline int64_t lds_sparse_b_bytes_per_row(int dtype) {
 // rows 8 -> 8 16.5 / 17.6, 64 -> 20 24.1 / 24.4, 16 -> 128 25.2 / 24.1, 32 -> 32 20.8 / 19.3, 128 -> 128 61.4 / 55.8).  Blocks of
 // sixteen columns that a slice of cs columns takes, and the LDS for C in three parts.
 constexpr int kSplitMinDepth = 16, kSplitMaxDepth = 128, kSplitMinCols = 32, kSplitMinRows = 32768;
-inline bool gemm_splits(int dtype, int64_t n, int bcol, int ccol) {
-    return dtype == TF_F32 && n >= kSplitMinRows && bcol >= kSplitMinDepth && bcol <= kSplitMaxDepth && ccol >= kSplitMinCols;
+inline bool gemm_splits(int dtype, int64_t n, int bcol, int cs) {
+    return dtype == TF_F32 && n >= kSplitMinRows && bcol >= kSplitMinDepth && bcol <= kSplitMaxDepth && cs >= kSplitMinCols;
 }
 inline int split_col_blocks(int cs) {
     const int nb = (cs + 15) / 16;

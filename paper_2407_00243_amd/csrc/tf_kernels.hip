@@ -1389,7 +1389,7 @@ int launch_fused_spmm_spmm(const FusedLaunch &a, void *stream) {
 int launch_gemm(const GemmLaunch &a, void *stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (a.n == 0) return 0;
-    if (gemm_splits(a.dtype, a.n, a.bcol, a.ccol)) return launch_gemm_split(a, stream);
+    if (gemm_splits(a.dtype, a.n, a.bcol, a.cs)) return launch_gemm_split(a, stream);
     // The depth: the smallest one that covers bCol where bCol is all of it, or where rows of B are not
     // aligned.  Aligned rows of other lengths take the loop over k, whose few registers leave room for
     // more waves (graph of 119367 rows, fp32 36 -> 128, whole chain: 146 us, 150 us with the covering
