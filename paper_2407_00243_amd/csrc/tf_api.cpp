@@ -133,6 +133,7 @@ struct tf_plan {
     void *chain_blocks = nullptr, *chain_rows = nullptr, *chain_idx = nullptr, *chain_vals = nullptr;
     int32_t n_chain_blocks = 0;
     size_t chain_zeros = 0;                // bytes into chain_vals
+    bool chain_early = false;
     void *cut_counts = nullptr;
     DevBuf d1;                             // fused path: one slot per spilled D1 row; behind them the sums of cut rows
     size_t cut_sums_at = 0;
@@ -419,6 +420,7 @@ tf_status run_chain(const tf_plan *p, const void *B, const void *C, void *D, voi
     tf::ChainLaunch a{};
     a.dtype = p->dtype;
     a.n_blocks = p->n_chain_blocks;
+    a.early = p->chain_early;
     a.n = p->n;
     a.bcol = (int32_t)p->bcol;
     a.ccol = (int32_t)p->ccol;
@@ -633,6 +635,7 @@ tf_status tf_plan_create(const tf_csr *A, int64_t bCol, int64_t cCol, int32_t b_
         }
         if (!sc.chain.blocks.empty()) {
             p->n_chain_blocks = (int32_t)sc.chain.blocks.size();
+            p->chain_early = sc.chain.early;
             arena.add(sc.chain.blocks, p->chain_blocks);
             arena.add(sc.chain.rows, p->chain_rows);
             arena.add(sc.chain.idx, p->chain_idx);

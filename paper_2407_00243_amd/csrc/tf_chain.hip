@@ -171,8 +171,9 @@ template <typename Vec, int N, int R, int P> struct GatheredPieces {
 // A block's entries are gathered in passes of up to EM entries per row, with as many gathers on their way as the
 // registers hold.  A wave adds up all passes of a block, multiplies, stores, and only then sends out the next block's
 // first gathers: the other waves of its SIMD are at another step meanwhile, and the entries of a row are gathered at
-// one time, so that what one wave fetches another finds in the L2 (2D stencil 512^2, fp64 128 -> 128: 357 MB fetched
-// past the L2; with the first pass on its way during the multiplications 597 MB, 195 us, so 190).
+// one time, so that what one wave fetches another finds in the L2 (2D stencil 512^2, fp64 128 -> 128: 373 MB fetched
+// past the L2 and the matrix cores busy 62 % of the time; with the first pass on its way during the multiplications 657 MB,
+// 190 us, so 182).  EARLY (chain_early): the first pass of the next block is sent out before the multiplications all the same.
 //
 // fp32 from depth 4 on, more than sixteen columns, is multiplied on the bf16 matrix cores, operands split in three (tf_device.h;
 // chain_splits).
@@ -183,13 +184,13 @@ template <typename Vec, int N, int R, int P> struct GatheredPieces {
 // rows of 41, 64 -> 64 15.8 / 14.0 / 12.5; 3D stencil 48^3, 64 -> 128 34.4 / 35.2 / 28.5.  Rows of B that are summed up
 // outside of the bound of the split take the fp32 instructions, and all do if a column of C is, which sits in LDS as it is then
 // (2D stencil 512^2, 128 -> 128: within 70, one column outside 104, every row 128; on the fp32 matrix cores alone 105).
-template <typename T, int KS, int NBC>
+template <typename T, int KS, int NBC, bool EARLY>
 __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS, NBC)) void k_gather_gemm(
     const ChainLaunch a, const ChainBlock *__restrict__ blocks, const int32_t *__restrict__ rows,
     const int32_t *__restrict__ idx, const T *__restrict__ val, const char *__restrict__ B,
     void *D) {
     constexpr int V = Tr<T>::V, KC = 4 * V;
-    constexpr int EM = chain_entries(dtype_of<T>(), KS);
+    constexpr int EM = chain_entries(dtype_of<T>(), KS, EARLY);
     constexpr int K0 = chain_ksteps_below(dtype_of<T>(), KS);      // pieces that are whole for certain
     typedef typename Piece16<T>::Vec Vec;
     typedef T Vec16 __attribute__((ext_vector_type(V)));
@@ -212,11 +213,11 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS, NBC))
     // bytes; the pieces of a row are swizzled so that the sixteen rows' pieces g sit in different
     // banks), results into rows of D (16 rows of CB blocks and 16 bytes) -- then the offsets of the
     // rows of D and the entries of a pass (ES values, then addresses of rows of B)
-    constexpr int ES = chain_entry_slots(dtype_of<T>(), KS);
-    constexpr int NE = chain_entry_loads(dtype_of<T>(), KS), TS = chain_exchange(KS), CB = chain_store_blocks(dtype_of<T>(), KS, NBC);
+    constexpr int ES = chain_entry_slots(dtype_of<T>(), KS, EARLY);
+    constexpr int NE = chain_entry_loads(dtype_of<T>(), KS, EARLY), TS = chain_exchange(KS), CB = chain_store_blocks(dtype_of<T>(), KS, NBC);
     constexpr int W = CB * 16 / V, PITCH = W * 16 + 16;
     unsigned char *ex = tf_smem + a.groups_per_wg * (int)chain_group_lds(dtype_of<T>(), KS, NBC) +
-                        wave * (int)chain_wave_lds(dtype_of<T>(), KS, NBC);
+                        wave * (int)chain_wave_lds(dtype_of<T>(), KS, NBC, EARLY);
     uint32_t *er = reinterpret_cast<uint32_t *>(ex + chain_exchange_bytes(dtype_of<T>(), KS, NBC));
     T *ev = reinterpret_cast<T *>(er + 16);
     uint64_t *ea = reinterpret_cast<uint64_t *>(ev + ES);
@@ -345,7 +346,7 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS, NBC))
         };
         from(from, std::integral_constant<int, EM>());
     };
-    // The very first pass, whose sums are formed later: n entries per row (wave-uniform: a branch per entry).
+    // A pass whose sums are formed later: n entries per row (wave-uniform: a branch per entry).
     auto send_first = [&](int n, GatheredPieces<Vec, EM, RS, KP> &x) __attribute__((always_inline)) {
 #pragma unroll
         for (int e = 0; e < EM; ++e) {
@@ -395,18 +396,18 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS, NBC))
     uint32_t *cmax = reinterpret_cast<uint32_t *>(tf_smem + groups * (NBC * KS2 * 3 * 1024));
     bool c_bad = false;      // (fp32) a column of C is outside of the bound of the split,
     float row_bound = 0.0f;  // what the elements of a row must be below
+    GatheredPieces<Vec, EM, RS, KP> ahead;      // the first pass of the first block; EARLY: all passes
     // Start-up: the first gathers of the first block go out before C is put into LDS
     {
         const int total = groups * NBC * 16 * KS * 4, split_items = groups * NBC * KS2 * 16;
         const SplitC split_from{static_cast<const float *>(a.C) + (a.c_transposed ? (int64_t)col0 * a.bcol : col0), a.ccol, a.bcol, a.ccol - col0};
         CPiece<T> tmp[kStageC];
-        GatheredPieces<Vec, EM, RS, KP> x;
         const int n = blk < end ? first_count(d) : 0;
         auto first_gathers = [&]() __attribute__((always_inline)) {
             if (blk >= end) return;
             put();
             fetch(d.slots > pass_len(d) ? d.slot_base + pass_len(d) : dn.slot_base);
-            send_first(n, x);
+            send_first(n, ahead);
         };
         auto stage = [&](auto ct_c) __attribute__((always_inline)) {
             constexpr bool CT = decltype(ct_c)::value;
@@ -448,7 +449,7 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS, NBC))
         __builtin_amdgcn_s_waitcnt(0);
         asm volatile("" : : "v"(zeros_ahead));
         clear_sums();
-        add_first(n, x);
+        if constexpr (!EARLY) add_first(n, ahead);
         if constexpr (SPLIT) {
             row_bound = split_row_bound(cmax, groups * NBC * 16, lane, c_bad);
             if (c_bad) {      // (all waves of the workgroup; C as it is in the place of its parts)
@@ -459,26 +460,36 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS, NBC))
         }
     }
 
-    for (int s0 = pass_len(d);; s0 = 0) {
+    for (int s0 = pass_len(d);; s0 = EARLY ? pass_len(d) : 0) {
         const int next = block_after(blk);
         const bool has_next = next < end;
         const ChainBlock dnn = blocks[min(block_after(next), end - 1)];
+        if constexpr (EARLY) {
+            clear_sums();
+            add_first(first_count(d), ahead);
+        }
         for (const int len = pass_len(d); s0 < d.slots; s0 += len) {
             if (s0) {
                 put();
                 fetch(s0 + len < d.slots ? d.slot_base + s0 + len : dn.slot_base);
             }
             const int count = min(len, d.slots - s0);
-            with_count(count, [&](auto n_c) __attribute__((always_inline)) {
-                GatheredPieces<Vec, decltype(n_c)::value, RS, KP> x;
-                gather(n_c, x);
-                add_up(n_c, x);
-            });
+            if constexpr (EARLY) {
+                send_first(count, ahead);
+                add_first(count, ahead);
+            } else {
+                with_count(count, [&](auto n_c) __attribute__((always_inline)) {
+                    GatheredPieces<Vec, decltype(n_c)::value, RS, KP> x;
+                    gather(n_c, x);
+                    add_up(n_c, x);
+                });
+            }
         }
         // the entries of the next block's first pass (the last block's wave takes those of some block, for nothing)
         put();
         row_n = row_id(dn);
         fetch(dn.slots > pass_len(dn) ? dn.slot_base + pass_len(dn) : dnn.slot_base);
+        if constexpr (EARLY) send_first(first_count(dn), ahead);
         __builtin_amdgcn_sched_barrier(0);
 
         // into the operand layout (a wave's LDS operations take effect in order)
@@ -533,7 +544,10 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS, NBC))
         // Stores go through a buffer descriptor, and out-of-range lanes (virtual rows that are not the
         // first of their row, columns past cCol) name an offset beyond it, which the hardware drops:
         // without a branch around the stores the compiler knows how many are on their way, and its
-        // wait for the next block's gathers, which were sent out before, does not include them.
+        // wait for what was sent out before (the next pass's entries, EARLY the next block's gathers) does not
+        // include them.  Gathers that follow the stores do wait for these, while other waves of the SIMD go on.  (us, with a
+        // branch / without: 2D stencil 512^2, fp32 64 -> 64 32.2 / 31.6, 16 -> 16 9.40 / 9.29, fp64 128 -> 128 188.8 / 187.1, 32 -> 32
+        // 27.8 / 28.4, band of 20011 rows, fp32 64 -> 64, 8.93 / 8.78.)
         if (g == 0)
             er[r] = (r >> slog) < n_rows && (r & ((1 << slog) - 1)) == 0 ? (uint32_t)row * (uint32_t)a.ccol : ~0u;
         const bool empty = d.slots == 0;      // (empty rows are zeros whatever C holds)
@@ -576,7 +590,7 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS, NBC))
             each_group([&](int grp, Acc(&o)[NBC]) __attribute__((always_inline)) {
                 // (the operands of a step are read ahead of the multiplications of the one before: 2D stencil 301^2, fp32 50 ->
                 // 23, on the fp32 matrix cores 12.8 -> 12.3 us; further ahead where a step has few of them)
-                constexpr int AHEAD = NBC == 1 ? 4 : NBC == 2 ? 2 : 1;
+                constexpr int AHEAD = NBC == 1 ? 4 : NBC == 2 ? 2 : EARLY ? 0 : 1;
                 const T *Cg = Cl + grp * (NBC * KS * V * 64) + lane;
                 T c[AHEAD + 1][NBC];
 #pragma unroll
@@ -653,7 +667,7 @@ __global__ __launch_bounds__(kChainThreads, chain_waves(dtype_of<T>(), KS, NBC))
         }
         __builtin_amdgcn_s_setprio(3);
         if (!has_next) break;
-        clear_sums();
+        if constexpr (!EARLY) clear_sums();
         d = dn;
         dn = dnn;
         row = row_n;
@@ -669,9 +683,9 @@ struct ChainSetup {
     int occ_waves = 0, wg_per_cu = 1;
 };
 
-template <typename T, int KS, int NBC> int run_chain(ChainLaunch a, hipStream_t st) {
+template <typename T, int KS, int NBC, bool EARLY> int run_chain(ChainLaunch a, hipStream_t st) {
     static ChainSetup cs;
-    auto kernel = k_gather_gemm<T, KS, NBC>;
+    auto kernel = k_gather_gemm<T, KS, NBC, EARLY>;
     // A launch with few blocks of rows is spread over the machine by column groups too (the rows are then
     // gathered once per group, and a workgroup stages its part of C only): as far as the machine holds all
     // its waves at once, half of them where C is small and little is saved (us, all groups in one workgroup /
@@ -680,7 +694,7 @@ template <typename T, int KS, int NBC> int run_chain(ChainLaunch a, hipStream_t 
     // 34.7 / 24.0 at 32768 in fp32; C of 32 KiB, fp64 32 -> 128, n = 16384, 12.0 / 11.1 with one group each).
     // (by the size of C, whatever it takes in LDS)
     const int64_t group_bytes = (int64_t)NBC * KS * Tr<T>::V * 64 * (int64_t)sizeof(T);
-    const int64_t group_lds = chain_group_lds(dtype_of<T>(), KS, NBC), wave_lds = chain_wave_lds(dtype_of<T>(), KS, NBC);
+    const int64_t group_lds = chain_group_lds(dtype_of<T>(), KS, NBC), wave_lds = chain_wave_lds(dtype_of<T>(), KS, NBC, EARLY);
     const int64_t held = (int64_t)a.n_cu * (a.n_groups * group_bytes <= 40 * 1024 ? 4 : 8);
     a.groups_per_wg = 1;
     while (a.n_blocks >= 2 * a.n_cu && a.groups_per_wg < a.n_groups &&
@@ -733,14 +747,14 @@ template <typename T, int KS, int NBC> int run_chain(ChainLaunch a, hipStream_t 
     return (int)hipGetLastError();
 }
 
-template <typename T, int KS> int run_chain_nb(ChainLaunch a, hipStream_t st) {
+template <typename T, int KS, bool EARLY = false> int run_chain_nb(ChainLaunch a, hipStream_t st) {
     const int nb = (a.ccol + 15) / 16, nbc = chain_col_blocks(KS, a.ccol);
     a.n_groups = (nb + nbc - 1) / nbc;
     switch (nbc) {
-        case 1: return run_chain<T, KS, 1>(a, st);
-        case 2: return run_chain<T, KS, 2>(a, st);
+        case 1: return run_chain<T, KS, 1, EARLY>(a, st);
+        case 2: return run_chain<T, KS, 2, EARLY>(a, st);
     }
-    if constexpr (KS < 16) return nbc == 3 ? run_chain<T, KS, 3>(a, st) : run_chain<T, KS, 4>(a, st);
+    if constexpr (KS < 16) return nbc == 3 ? run_chain<T, KS, 3, EARLY>(a, st) : run_chain<T, KS, 4, EARLY>(a, st);
     return (int)hipErrorInvalidValue;
 }
 
@@ -764,7 +778,7 @@ int launch_chain(const ChainLaunch &a, void *stream) {
             case 2: return run_chain_nb<double, 2>(a, st);
             case 4: return run_chain_nb<double, 4>(a, st);
             case 6: return run_chain_nb<double, 6>(a, st);
-            case 8: return run_chain_nb<double, 8>(a, st);
+            case 8: return a.early ? run_chain_nb<double, 8, true>(a, st) : run_chain_nb<double, 8>(a, st);
             case 12: return run_chain_nb<double, 12>(a, st);
             case 16: return run_chain_nb<double, 16>(a, st);
         }

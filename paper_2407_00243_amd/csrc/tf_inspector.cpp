@@ -1178,7 +1178,7 @@ static double one_pass_us(const InspectorInput &in, double entries, double far =
 // others is no matter of row lengths, and in the fits of one_pass_us already (band of 50000 rows of 41, fp64 100 ->
 // 100, where it was charged here too: 169 us in two wavefronts, 121 in one pass).
 static double one_pass_tail_us(const InspectorInput &in, const ChainPack &c, int ks, int64_t per_block) {
-    const int em = chain_entries(in.dtype, ks);
+    const int em = chain_entries(in.dtype, ks, c.early);
     const int64_t nb = (int64_t)c.blocks.size(), per = (nb + kXcds - 1) / kXcds;
     const int per_simd = chain_waves(in.dtype, ks, chain_col_blocks(ks, in.ccol));
     const int64_t waves = std::max<int64_t>(1, std::min(per, (int64_t)in.n_cu / kXcds * 4 * per_simd));
@@ -1216,8 +1216,10 @@ void build_chain_pack(const InspectorInput &in, Schedule &s, bool entries) {
     const int64_t per_block = 16 >> slog;
     // A block far longer than the others holds one wave up while the rest of the machine is done: its
     // rows are cut further, until it has at most twice as many slots as a pass or a row of mean length.
-    const int64_t most_slots = 2 * std::max<int64_t>(chain_entries(in.dtype, ks), in.nnz / n >> slog);
     ChainPack &c = s.chain;
+    c.early = chain_early(in.dtype, ks, n, in.nnz, in.bcol, in.ccol);
+    const int em = chain_entries(in.dtype, ks, c.early);
+    const int64_t most_slots = 2 * std::max<int64_t>(em, in.nnz / n >> slog);
     // rows in their own order while that pads little, else sorted by length inside windows
     int64_t padded = 0;
     for (int64_t j0 = 0; j0 < n; j0 += per_block) {
@@ -1250,7 +1252,7 @@ void build_chain_pack(const InspectorInput &in, Schedule &s, bool entries) {
         }
         cb.slot_base = (uint32_t)slot;
         cb.row_begin = (int32_t)q0;
-        const int em = chain_entries(in.dtype, ks), passes = (cb.slots + em - 1) / em;
+        const int passes = (cb.slots + em - 1) / em;
         cb.info = cut | (passes ? (cb.slots + passes - 1) / passes : 0) << 3 | (int32_t)((q1 - q0) << 7);
         c.blocks.push_back(cb);
         slot += cb.slots;

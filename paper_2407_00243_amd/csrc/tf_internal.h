@@ -358,6 +358,7 @@ struct ChainPack {
     std::vector<int32_t> rows;           // row ids in block order
     RawVec<int32_t> idx;
     RawVec<unsigned char> vals;
+    bool early = false;                  // chain_early
 };
 constexpr int kChainThreads = 512;       // largest workgroup of the kernel
 constexpr int kChainMaxEntries = 8;      // most entries per row in flight
@@ -394,10 +395,24 @@ constexpr int chain_ksteps_below(int dtype, int ks) {
     }
     return below;
 }
+// Whether a wave sends out the next block's first gathers before it multiplies (k_gather_gemm, EARLY): fp64 at depth 8, whose rows
+// take two trips to memory with up to eight entries and have little to multiply meanwhile.  It pays where rows have few
+// entries and B does not fit the L2s, from 24 MiB at up to five entries a row, 36 MiB at up to seven; longer rows take more passes
+// of four than of five, and where B and D are more than the last-level cache holds, rows gathered twice come from memory twice.
+// us, all gathers after the stores / the first ones early: 2D stencils 200^2 64 -> 20 11.3 / 11.7, 225^2 64 -> 64 21.0 / 20.0, 512^2 64 ->
+// 20 47.5 / 43.9, 50 -> 23 47.1 / 42.1, 64 -> 64 64.8 / 63.4, 700^2 (329 MB) 64 -> 20 85.7 / 91.6, (500 MB) 64 -> 64 136 / 142; 3D 36^3 64 -> 20
+// 14.3 / 15.0, 40^3 57 -> 32 18.8 / 19.0, 48^3 64 -> 64 38.0 / 35.7, 64^3 64 -> 64 83.3 / 72.1; bands of 60000 rows, 64 -> 20, of 5 15.6 /
+// 14.8, of 7 16.4 / 17.0, of 9 18.2 / 19.0.  Before the gathers came after the stores at all, three entries a pass: 512^2 64 -> 20 45.2,
+// 50 -> 23 43.4, 64 -> 64 64.1, 64^3 64 -> 64 74.9.
+constexpr int64_t kChainEarlyMost = (int64_t)300 * 1000 * 1000;
+inline bool chain_early(int dtype, int ks, int64_t n, int64_t nnz, int64_t bcol, int64_t ccol) {
+    if (dtype != TF_F64 || ks != 8 || nnz > 7 * n) return false;
+    return n * bcol * 8 >= (int64_t)(nnz <= 5 * n ? 24 : 36) << 20 && n * (bcol + ccol) * 8 <= kChainEarlyMost;
+}
 // Entries per row whose gathers are in flight at once (about 24 pieces of 16 bytes per lane; fp64 at depths 8 and 12, whose waves
-// have 256 registers, 40 and 36: bands, 64 -> 64 84 -> 80 us, 96 -> 96 134 -> 126).
-constexpr int chain_entries(int dtype, int ks) {
-    return ks <= 2 ? 8 : ks == 3 ? 6 : ks == 4 ? 5 : ks == 8 && dtype == TF_F64 ? 5 : ks <= 8 || (ks == 12 && dtype == TF_F64) ? 3 : 2;
+// have 256 registers, 40 and 36, 32 early: bands, 64 -> 64 84 -> 80 us, 96 -> 96 134 -> 126).
+constexpr int chain_entries(int dtype, int ks, bool early) {
+    return early ? 4 : ks <= 2 ? 8 : ks == 3 ? 6 : ks == 4 ? 5 : ks == 8 && dtype == TF_F64 ? 5 : ks <= 8 || (ks == 12 && dtype == TF_F64) ? 3 : 2;
 }
 // Waves per SIMD that the kernel is held to: where a third one costs no spilled registers (fp64 at depth 2 with
 // four blocks of columns: held to three it spills 12 bytes a lane; bands and 3D stencils, 16 -> 64, us
@@ -415,11 +430,11 @@ inline int chain_col_blocks(int ks, int64_t ccol) {
 }
 // LDS per wave (see k_gather_gemm): loads of 64 entries per pass, k steps per change of lanes, blocks of
 // sixteen columns that leave together, and what that comes to in bytes.
-constexpr int chain_entry_loads(int dtype, int ks) { return (chain_entries(dtype, ks) + 3) / 4; }
+constexpr int chain_entry_loads(int dtype, int ks, bool early) { return (chain_entries(dtype, ks, early) + 3) / 4; }
 // (whole loads are put into LDS; fp64 at depth 8, whose C may leave no room for them, keeps to the entries of a pass: the test
 // for them costs 2 to 5 % where launches are small)
-constexpr int chain_entry_slots(int dtype, int ks) {
-    return dtype == TF_F64 && ks == 8 ? 16 * chain_entries(dtype, ks) : 64 * chain_entry_loads(dtype, ks);
+constexpr int chain_entry_slots(int dtype, int ks, bool early) {
+    return dtype == TF_F64 && ks == 8 ? 16 * chain_entries(dtype, ks, early) : 64 * chain_entry_loads(dtype, ks, early);
 }
 constexpr int chain_exchange(int ks) { return ks < 4 ? ks : ks < 16 ? 4 : 2; }
 constexpr int chain_store_blocks(int dtype, int ks, int nbc) {
@@ -430,8 +445,8 @@ constexpr int chain_exchange_bytes(int dtype, int ks, int nbc) {
     const int out = 16 * (chain_store_blocks(dtype, ks, nbc) * 16 * (dtype == TF_F64 ? 8 : 4) + 16);
     return in > out ? in : out;
 }
-constexpr int64_t chain_wave_lds(int dtype, int ks, int nbc) {
-    return chain_exchange_bytes(dtype, ks, nbc) + 64 + chain_entry_slots(dtype, ks) * (8 + (dtype == TF_F64 ? 8 : 4));
+constexpr int64_t chain_wave_lds(int dtype, int ks, int nbc, bool early) {
+    return chain_exchange_bytes(dtype, ks, nbc) + 64 + chain_entry_slots(dtype, ks, early) * (8 + (dtype == TF_F64 ? 8 : 4));
 }
 // Whether the kernel multiplies on the bf16 matrix cores, by operands split in three: rows of B of more than 48 columns and rows
 // of D of more than sixteen (shorter rows of B: three parts of C take longer to lay out than is saved; one block of columns:
@@ -656,6 +671,7 @@ struct ChainLaunch {
     const void *B, *C;
     void *D;
     int64_t lds_limit;                // of a workgroup
+    int32_t early;                    // chain_early
     int32_t whole_rounds;             // (set by the launcher) rounds of blocks in their order; the rest is dealt out
 };
 
