@@ -377,15 +377,17 @@ template <int KD, int NB, bool PASS> int run_split2(const GemmLaunch &a, hipStre
     k_gemm_split<KD, NB, PASS><<<dim3((unsigned)gx, (unsigned)a.n_slices), dim3(64 * nwaves), lds, st>>>(a);
     return (int)hipGetLastError();
 }
-// Rows of B pass through the caches without staying there where B, D1 and D are more than the last-level cache holds (256 MB),
-// and rows of B are whole lines, or a line that a load takes a part of is gone when the next one comes for the rest (100 -> 100,
-// 150000 rows, 152 us passing, 142 staying).  Whole executions on R-MAT graphs, us, staying / passing, the same operands again and, in
-// brackets, others each time: 300000 rows, 128 -> 128 275 / 263 (277 / 265), 700000, 32 -> 32 168 / 163 (169 / 163), 10^6, 64 -> 32 261 / 256
-// (262 / 254); below, 150000, 128 -> 41 71 / 79 (77 / 78), 128 -> 64 72 / 77 (79 / 78), 300000, 64 -> 64 119 / 125 (127 / 126), 400000, 64 -> 32
-// 97 / 100 (100 / 100).  Not where the product is the second operation (D1 is D): what it reads was just written, and no launch
-// follows (staying / passing: 131072 rows, 64 -> 128 63.6 / 67.7, 300000, 32 -> 64 75.8 / 86.6, 10^6, 64 -> 128 663 / 683).
+// Rows of B pass through the caches without staying there where what is written is more than the L2s hold, which the launch that
+// follows gathers from, and rows of B are whole lines, or a line that a load takes a part of is gone when the next one comes for the
+// rest (100 -> 100, 150000 rows, 152 us passing, 142 staying).  What decides below 256 MB of B, D1 and D is whether the program has used
+// the same operands just before, which only it knows; the rule takes those that come anew.  Whole executions on R-MAT graphs,
+// us, staying / passing, three sets of operands in turn and, in brackets, one set again and again: 150000 rows, 128 -> 41 83.3 / 75.4
+// (69.2 / 75.6), 128 -> 64 79.2 / 73.4 (68.2 / 73.1), 64 -> 64 69.5 / 63.7 (60.0 / 63.2), 96 -> 96 100.5 / 100.8 (90.5 / 98.0), 100000, 128 -> 128 99.5 /
+// 92.1 (87.5 / 91.1), 70000, 128 -> 128 70.5 / 68.8 (66.0 / 69.4), 300000, 64 -> 64 129 / 131 (119 / 119), 128 -> 128 277 / 265 (275 / 263), 10^6,
+// 64 -> 32 262 / 254 (261 / 256).  Not where the product is the second operation (D1 is D): what it reads was just written, and no
+// launch follows (131072 rows, 64 -> 128 63.6 / 67.7, 300000, 32 -> 64 75.8 / 86.6, 10^6, 64 -> 128 663 / 683).
 template <int KD, int NB> int run_split(const GemmLaunch &a, hipStream_t st) {
-    const bool pass = a.D1 != a.D && a.bcol % 32 == 0 && a.n * (a.bcol + a.d1_cols + a.ccol) * 4 >= ((int64_t)256 << 20);
+    const bool pass = a.D1 != a.D && a.bcol % 32 == 0 && a.n * a.d1_cols * 4 >= ((int64_t)32 << 20);
     if (pass) return run_split2<KD, NB, true>(a, st);
     return run_split2<KD, NB, false>(a, st);
 }

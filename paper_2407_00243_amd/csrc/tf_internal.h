@@ -370,8 +370,8 @@ constexpr int kChainSpareSlots = 2 * kChainMaxEntries;   // zero slots behind th
 constexpr int kChainZeroRows = 16;       // copies of a row of zeros, which padding reads, behind the values
 constexpr int kChainRowBytes = 1024;     // longest row of B
 // 16-byte pieces of a row of B per lane: ceil(bCol / (4 V)) rounded up to a depth the kernel is
-// instantiated for; 0 = none.  The depths end at 128 columns: there the kernel takes 242 of the 256 registers
-// of a wave in fp64, with two entries in flight per row, and 184 in fp32, with three; deeper instances were not
+// instantiated for; 0 = none.  The depths end at 128 columns: there the kernel takes 238 of the 256 registers
+// of a wave in fp64, with two entries in flight per row, and 234 in fp32, with three; deeper instances were not
 // built.  Wider rows of B take the two wavefronts (2D stencil 512^2, -> 64, us at 128, 132 and 129 columns: fp32
 // 61, 94, 133; fp64 at 128, 130 and 129: 133, 261, 288).
 constexpr int kChainDepths32[] = {1, 2, 3, 4, 6, 8}, kChainDepths64[] = {2, 4, 6, 8, 12, 16};
